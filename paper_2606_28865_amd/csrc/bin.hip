@@ -548,11 +548,11 @@ hipError_t dev_wave_fill(const double *tx, const double *ty, int64_t nout, int64
 // ---------------------------------------------------------------------------
 // History part: sources by spreading tile, per-tile lists, target tiles
 // ---------------------------------------------------------------------------
-// tile of a point, as the spreading kernels place it (32 x 32 grid points)
+// block of a point, as the spreading kernels place it (SPB x SPB grid points)
 __device__ inline int64_t tile_index(double x, double y, double ox, double oy, double h, int64_t ntile)
 {
-    int64_t ix = (int64_t)floor((x - ox) / h) / TILE;
-    int64_t iy = (int64_t)floor((y - oy) / h) / TILE;
+    int64_t ix = (int64_t)floor((x - ox) / h) / SPB;
+    int64_t iy = (int64_t)floor((y - oy) / h) / SPB;
     ix = min(ntile - 1, max((int64_t)0, ix));
     iy = min(ntile - 1, max((int64_t)0, iy));
     return iy * ntile + ix;
@@ -612,9 +612,9 @@ __global__ void __launch_bounds__(BT) k_source_gather(int64_t n, const int32_t *
     }
 }
 
-// Per tile (one wavefront each): the sorted sources whose window meets the
-// tile in both axes.  A window (W <= 16 < 32 points) reaches at most the
-// neighbouring tiles of its source's own tile, so the candidates are the
+// Per block (one wavefront each): the sorted sources whose window meets the
+// block in both axes.  A window (at most W/2 <= 8 < SPB points to either side)
+// reaches at most the neighbouring blocks of its source's own block, so the candidates are the
 // sources of the 3 x 3 neighbourhood, taken in increasing tile index, i.e.
 // in sorted order.
 template <bool FILL>
@@ -630,8 +630,8 @@ __global__ void __launch_bounds__(BT) k_tile_lists(const double *__restrict__ gx
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     auto span = [&](double g, int64_t &t0, int64_t &t1) {
         const int64_t m0 = (int64_t)ceil(g - 0.5 * W);
-        t0 = max((int64_t)0, (int64_t)floor((double)m0 / TILE));
-        t1 = min(ntile - 1, (int64_t)floor((double)(m0 + W - 1) / TILE));
+        t0 = max((int64_t)0, (int64_t)floor((double)m0 / SPB));
+        t1 = min(ntile - 1, (int64_t)floor((double)(m0 + W - 1) / SPB));
     };
     int64_t n = 0;
     const int64_t base = FILL ? ofs[t] : 0;
@@ -655,14 +655,35 @@ __global__ void __launch_bounds__(BT) k_tile_lists(const double *__restrict__ gx
     if (!FILL && lane == 0) cnt[t] = (int32_t)n;
 }
 
-// Sort the sources (x, y, w and, for the boundary, nx, ny) by tile and
-// count their tile lists: gx.. and idx get the sorted arrays, lofs the
-// list offsets (exclusive scan; lofs[nt2] = total, also in *total), tstart
-// the tile starts of the sorted sources (temporary, freed by the caller)
+// blocks that any window meets: flag per block, and their list in increasing
+// order (pos: exclusive scan of the flags)
+__global__ void __launch_bounds__(BT) k_block_flags(const int32_t *cnt, int64_t nt2, int32_t *on,
+                                                    uint8_t *__restrict__ flag)
+{
+    const int64_t t = (int64_t)blockIdx.x * BT + threadIdx.x;
+    if (t >= nt2) return;
+    on[t] = cnt[t] > 0 ? 1 : 0;
+    flag[t] = cnt[t] > 0 ? 1 : 0;
+}
+
+__global__ void __launch_bounds__(BT) k_block_list(const int32_t *__restrict__ pos, int64_t nt2,
+                                                   int32_t *__restrict__ active)
+{
+    const int64_t t = (int64_t)blockIdx.x * BT + threadIdx.x;
+    if (t < nt2 && pos[t + 1] != pos[t]) active[pos[t]] = (int32_t)t;
+}
+
+// Sort the sources (x, y, w and, for the boundary, nx, ny) by block and
+// count their block lists: gx.. and idx get the sorted arrays, lofs the
+// list offsets (exclusive scan; lofs[nt2] = total, also in *total), flag and
+// active (room for min(nt2, 4 n)) the blocks with a list, *nactive their
+// number, tstart the block starts of the sorted sources (temporary, freed by
+// the caller)
 hipError_t dev_sources_by_tile(const double *x, const double *y, const double *w, const double *nx, const double *ny,
                                int64_t n, double ox, double oy, double h, int64_t ntile, int W, double *gx, double *gy,
                                double *gw, double *gwx, double *gwy, int32_t *idx, int *sup, int32_t *lofs,
-                               int32_t **tstart_out, int64_t *total, hipStream_t st)
+                               uint8_t *flag, int32_t *active, int64_t *nactive, int32_t **tstart_out, int64_t *total,
+                               hipStream_t st)
 {
     const int64_t nt2 = ntile * ntile;
     uint32_t *key = nullptr;
@@ -690,6 +711,19 @@ hipError_t dev_sources_by_tile(const double *x, const double *y, const double *w
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = dev_scan(cnt, lofs, nt2, total, st);
+    int32_t *pos = nullptr;
+    if (e == hipSuccess) e = hipMallocAsync((void **)&pos, sizeof(int32_t) * (nt2 + 1), st);
+    if (e == hipSuccess) {
+        // the counts' array becomes the 0/1 flags
+        hipLaunchKernelGGL(k_block_flags, dim3(nblocks(nt2, BT)), dim3(BT), 0, st, cnt, nt2, cnt, flag);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = dev_scan(cnt, pos, nt2, nactive, st);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_block_list, dim3(nblocks(nt2, BT)), dim3(BT), 0, st, pos, nt2, active);
+        e = hipGetLastError();
+    }
+    if (pos) (void)hipFreeAsync(pos, st);
     if (key) (void)hipFreeAsync(key, st);
     if (cnt) (void)hipFreeAsync(cnt, st);
     if (e == hipSuccess) {

@@ -12,11 +12,10 @@
 //   FFT       rocFFT complex-to-real, in place;
 //   interp    u(x) = sum_m phi(x - x_m) U_m.
 //
-// Spreading: one workgroup owns one 32x32 tile of the fine grid and one
-// density of the batch; it adds the windows of the sources that meet the
-// tile (listed per tile at plan time) into LDS with LDS atomics and writes
-// the tile once: every grid value is written exactly once, with no global
-// atomics.
+// Spreading: one workgroup owns one 16x16 block of the fine grid and adds the
+// windows of the sources that meet it (listed per block at plan time) as
+// rank-4 updates on the FP64 matrix cores: every grid value is written
+// exactly once, with no atomics and in a fixed summation order.
 // Interpolation: one workgroup per non-empty target tile stages the tile plus
 // its window halo of the three result grids in LDS with coalesced row reads.
 #include "mhk_internal.h"
@@ -24,19 +23,22 @@
 namespace mhk {
 
 // threads per interpolation / spreading workgroup: a busy tile holds a few
-// hundred targets, one per thread; the tiles that hold volume sources hold
-// a couple of thousand (source, tile) pairs and are a small part of the
-// grid, so their workgroups take 512 threads (measured 4.42 against 4.57 ms
-// per bench step with 256; 1024 was slower)
+// hundred targets, one per thread; a spreading block's list is dealt to four
+// wavefronts in batches of 32
 constexpr int HB = 256;
-constexpr int SB = 512;
+constexpr int SB = 256;
+typedef double d4 __attribute__((ext_vector_type(4)));
+// doubles of LDS per spreading wavefront: 64 rows of W + 2 window values, the
+// strengths of 32 sources in NF fields, 64 window corners
+constexpr int SPREAD_LDS(int W, int NF) { return 64 * (W + 2) + NF * 32 + 32; }
 
 template <typename T>
 struct SpreadArgs {
     int64_t n, field, nb, nv;
-    int ntile, B;
-    int tbx0, tby0, ntbx;  // the launch covers tiles tbx0.. (ntbx per row) x tby0..: the box of the sources' windows
-    double beta;
+    int nblk, B;           // blocks per grid row
+    int64_t nvw;           // workgroups of the volume: (active block, group of NV densities)
+    int nvt, nbt;          // density groups of the volume and of the boundary (ND densities each)
+    const int32_t *vact, *bact;
     const double *bgx, *bgy, *bw, *bwx, *bwy;
     const int32_t *bidx, *blofs, *blist;
     const double *vgx, *vgy, *vw;
@@ -45,6 +47,21 @@ struct SpreadArgs {
     const T *wcoef;
     T *grid;               // [4][B][field]: S, V, Dx, Dy sources
 };
+
+// a b + c with c taken from scalar registers (the compiler copies a scalar
+// addend into vector registers first: two more instructions per FP64 step)
+__device__ inline double fma_s(double a, double b, double c)
+{
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
+    return r;
+}
+__device__ inline float fma_s(float a, float b, float c)
+{
+    float r;
+    asm("v_fma_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
+    return r;
+}
 
 // Window values phi(z_k), z_k = (m0 + k - g) 2/W, at the W grid points from
 // m0 = ceil(g - W/2), from the per-point polynomials in t = 2(m0 - g + W/2) - 1
@@ -80,14 +97,14 @@ __device__ inline void window_weights2(double gx, double gy, const T *__restrict
         T ex = c[2 * (NE - 1)], ey = ex;
 #pragma unroll
         for (int j = NE - 2; j >= 0; --j) {
-            ex = fma(ex, sx, c[2 * j]);
-            ey = fma(ey, sy, c[2 * j]);
+            ex = fma_s(ex, sx, c[2 * j]);
+            ey = fma_s(ey, sy, c[2 * j]);
         }
         T ox = c[2 * (NO - 1) + 1], oy = ox;
 #pragma unroll
         for (int j = NO - 2; j >= 0; --j) {
-            ox = fma(ox, sx, c[2 * j + 1]);
-            oy = fma(oy, sy, c[2 * j + 1]);
+            ox = fma_s(ox, sx, c[2 * j + 1]);
+            oy = fma_s(oy, sy, c[2 * j + 1]);
         }
         wx[k] = fma(tx, ox, ex);
         wy[k] = fma(ty, oy, ey);
@@ -98,80 +115,188 @@ __device__ inline void window_weights2(double gx, double gy, const T *__restrict
     }
 }
 
-// One workgroup per (tile, density), four passes over one LDS buffer: V from
-// the volume sources, then S, D_x, D_y from the boundary sources.  Each pass
-// takes the plan's list of the sources whose window meets the tile (one
-// source per thread, every lane busy) and adds the part of its w x w window
-// inside the tile (row and column tests; the column tests are formed once
-// per source).  The buffer has a margin of w - 1 points around the tile, so
-// that every address is the source's window corner plus an immediate
-// offset; the tile's interior is then written once, so every grid value is
-// written exactly once, with no global atomics.  (Adding whole windows into
-// the margin instead of testing costs more: at w = 12 a listed source lies
-// ~45% outside the tile.)  The accumulators are FP64 at both precisions: LDS atomic adds of
-// FP64 run at more than twice the rate of FP32 ones, and the sums lose
-// nothing before the single rounding on the way out.
+// Window values along one axis of one source, as above with one offset.
 template <int W, typename T>
+__device__ inline void window_weights1(double g, const T *__restrict__ cf, int &m0, T *w)
+{
+    constexpr int D = W + 3, NE = D / 2 + 1, NO = (D + 1) / 2;
+    typedef const __attribute__((address_space(4))) T *ConstPtr;   // scalar-loadable
+    ConstPtr cc = (ConstPtr)cf;
+    asm volatile("" : "+s"(cc));
+    m0 = (int)ceil(g - 0.5 * W);
+    const T t = (T)(2.0 * ((double)m0 - g + 0.5 * W) - 1.0), s = t * t;
+#pragma unroll
+    for (int k = 0; k < (W + 1) / 2; ++k) {
+        // two points' coefficients in flight
+        if (k > 1) asm volatile("" : "+s"(cc) : "v"(w[k - 2]));
+        ConstPtr c = cc + k * (D + 1);
+        T e = c[2 * (NE - 1)];
+#pragma unroll
+        for (int j = NE - 2; j >= 0; --j) e = fma_s(e, s, c[2 * j]);
+        T o = c[2 * (NO - 1) + 1];
+#pragma unroll
+        for (int j = NO - 2; j >= 0; --j) o = fma_s(o, s, c[2 * j + 1]);
+        w[k] = fma(t, o, e);
+        if (W - 1 - k != k) w[W - 1 - k] = fma(-t, o, e);
+    }
+}
+
+// LDS exchange among the lanes of one wavefront
+__device__ inline void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The list [e0, e1) of one block into NF fields: sum_s q_f(s) w_y(s) (x) w_x(s),
+// a product of a 16 x K matrix of y-window values, a diagonal of strengths and
+// a K x 16 matrix of x-window values, four sources at a time on
+// v_mfma_f64_16x16x4 (A: lane l holds row l % 16 of source l / 16, B: column
+// l % 16 of source l / 16, D: rows 4 v + l / 16, column l % 16).  Each of the
+// four wavefronts takes every fourth batch of 32 sources: lane l evaluates
+// the W window values of axis l / 32 of source l % 32 (half the lanes' work
+// of one thread per source, with scalar coefficients) into LDS rows of W + 2,
+// the first and last of them zero, so that a row clamped to [-1, W] reads
+// zero outside its window.  The windows of a list's sources cover 44% of the
+// block's rows and columns (W = 12); skipping the rest would cost more than
+// the matrix cores take.
+template <int W, typename T, int NF, bool VOL>
+__device__ inline void spread_block(const SpreadArgs<T> &A, int b0, int nf, int x0, int y0, int e0, int e1,
+                                    double *lds)
+{
+    constexpr int RW = W + 2;
+    const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
+    double *row = lds + wave * SPREAD_LDS(W, NF);
+    double *qs = row + 64 * RW;                       // [NF][32]
+    int *ms = reinterpret_cast<int *>(qs + NF * 32);  // [2][32]
+    d4 acc[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) acc[f] = d4{0.0, 0.0, 0.0, 0.0};
+    row[lane * RW] = 0.0;
+    row[lane * RW + W + 1] = 0.0;
+    const int axis = lane / 32, sl = lane % 32, i = lane % 16, k = lane / 16;
+    const double *__restrict__ gc = axis ? (VOL ? A.vgy : A.bgy) : (VOL ? A.vgx : A.bgx);
+    const int32_t *__restrict__ list = VOL ? A.vlist : A.blist, *__restrict__ idx = VOL ? A.vidx : A.bidx;
+    // the volume's densities alternate between the two halves of the
+    // wavefront; the lower half forms the boundary's strengths
+    constexpr int NQ = VOL ? (NF + 1) / 2 : NF;
+    const int step = 32 * (SB / 64);
+    struct Src {
+        double g, w[3], f[NQ];
+    };
+    // loads run ahead of their use: the coordinate and the densities of the
+    // next batch while this one is summed, the list entry one batch further
+    auto load = [&](int s, Src &r) {
+        const int id = idx[s];
+        r.g = gc[s];
+        if (VOL) {
+            r.w[0] = A.vw[s];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const int f = 2 * q + axis;
+                r.f[q] = f < nf ? (double)A.f_vol[(size_t)(b0 + f) * A.nv + id] : 0.0;
+            }
+        } else {
+            r.w[0] = A.bw[s];
+            r.w[1] = A.bwx[s];
+            r.w[2] = A.bwy[s];
+#pragma unroll
+            for (int d = 0; d < NF / 3; ++d) {
+                const size_t o = (size_t)(b0 + d) * A.nb + id;
+                r.f[3 * d] = A.sigma && 3 * d < nf ? (double)A.sigma[o] : 0.0;
+                r.f[3 * d + 1] = r.f[3 * d + 2] = A.mu && 3 * d < nf ? (double)A.mu[o] : 0.0;
+            }
+        }
+    };
+    int e = e0 + 32 * wave + sl;
+    Src cur{}, nxt{};
+    int s1 = 0;
+    if (e < e1) load(list[e], cur);
+    if (e + step < e1) s1 = list[e + step];
+    for (int base = e0 + 32 * wave; base < e1; base += step, e += step) {
+        int s2 = 0;
+        if (e + 2 * step < e1) s2 = list[e + 2 * step];
+        if (e + step < e1) load(s1, nxt);
+        int m = 1 << 20;                              // past the list's end: a window far outside, strength zero
+        if (e < e1) {
+            T w[W];
+            window_weights1<W, T>(cur.g, A.wcoef, m, w);
+            m -= axis ? y0 : x0;
+#pragma unroll
+            for (int q = 0; q < W; ++q) row[lane * RW + 1 + q] = (double)w[q];
+        }
+        const bool in = e < e1;
+        if (VOL) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+                if (2 * q + axis < NF) qs[(2 * q + axis) * 32 + sl] = in ? (double)(T)(cur.w[0] * cur.f[q]) : 0.0;
+        } else if (axis == 0) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) qs[q * 32 + sl] = in ? (double)(T)(cur.w[q % 3] * cur.f[q]) : 0.0;
+        }
+        ms[lane] = m;
+        // the wavefront's own LDS region: its lanes' writes are read below
+        wave_sync();
+#pragma unroll
+        for (int g = 0; g < 32; g += 4) {
+            const int src = g + k;
+            const int ix = min(max(i - ms[src], -1), W) + 1, iy = min(max(i - ms[32 + src], -1), W) + 1;
+            const double bx = row[src * RW + ix], ay = row[(32 + src) * RW + iy];
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+                acc[f] = __builtin_amdgcn_mfma_f64_16x16x4f64(ay, bx * qs[f * 32 + src], acc[f], 0, 0, 0);
+        }
+        wave_sync();
+        cur = nxt;
+        s1 = s2;
+    }
+    // the four wavefronts' sums, in order, one field at a time
+    const size_t fs = (size_t)A.B * A.field;
+    const size_t o = (size_t)(y0 + tid / 16) * (A.n + 2) + x0 + tid % 16;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        if (f >= nf) break;
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 4; ++v) lds[wave * 256 + (4 * v + k) * 16 + i] = acc[f][v];
+        __syncthreads();
+        const double sum = ((lds[tid] + lds[256 + tid]) + lds[512 + tid]) + lds[768 + tid];
+        if (VOL) {
+            A.grid[fs + (size_t)(b0 + f) * A.field + o] = (T)sum;
+        } else {
+            const int c = f % 3;                      // S in slot 0, D_x in 2, D_y in 3
+            if (c == 0 ? A.sigma != nullptr : A.mu != nullptr)
+                A.grid[(size_t)(c == 0 ? 0 : c + 1) * fs + (size_t)(b0 + f / 3) * A.field + o] = (T)sum;
+        }
+    }
+}
+
+// One workgroup per (active 16 x 16 block, group of densities): NV volume
+// densities or ND boundary densities (S, D_x and D_y each).  The accumulators
+// are FP64 at both precisions.  Bound by VALU issue: about 120 instructions of
+// window values and 90 of LDS addressing per batch of 32 sources (1000 cycles
+// a SIMD) beside 512 cycles of the matrix cores.  Measured alone, 1.04M volume
+// and 16384 boundary sources on 1920^2, W = 12: 126 us (LDS atomic adds over
+// 32 x 32 tiles: 312 us); 16 densities on 2880^2: 741 us (3013); 4.09M sources
+// on 3840^2, W = 8, FP32: 215 us (430).  Blocks that no window meets are not
+// launched: a workgroup each to write their zeros cost 50 us at 1920^2 and
+// 70 us at 3840^2; the row transforms skip them by their flags.
+template <int W, typename T, int NV, int ND>
 __global__ void __launch_bounds__(SB) k_spread(SpreadArgs<T> A)
 {
-    constexpr int PAD = W - 1, PT = TILE + 2 * PAD;
-    __shared__ double acc[PT * PT];
-    const int tile = (A.tby0 + (int)blockIdx.x / A.ntbx) * A.ntile + A.tbx0 + (int)blockIdx.x % A.ntbx;
-    const int b = blockIdx.y, tid = threadIdx.x;
-    const int x0 = (tile % A.ntile) * TILE, y0 = (tile / A.ntile) * TILE;
-    const size_t fs = (size_t)A.B * A.field;
-    T *gS = A.grid + (size_t)b * A.field, *gV = gS + fs, *gX = gV + fs, *gY = gX + fs;
-    for (int ph = 0; ph < 4; ++ph) {
-        T *out = ph == 0 ? gV : ph == 1 ? gS : ph == 2 ? gX : gY;
-        const bool vol = ph == 0;
-        const bool want = vol ? A.f_vol != nullptr : ph == 1 ? A.sigma != nullptr : A.mu != nullptr;
-        const int32_t *lofs = vol ? A.vlofs : A.blofs, *list = vol ? A.vlist : A.blist;
-        const int e0 = want ? lofs[tile] : 0, e1 = want ? lofs[tile + 1] : 0;
-        if (e0 == e1) {
-            for (int i = tid; i < TILE * TILE; i += SB)
-                out[(size_t)(y0 + i / TILE) * (A.n + 2) + x0 + (i % TILE)] = (T)0;
-            continue;
-        }
-        for (int i = tid; i < PT * PT; i += SB) acc[i] = 0.0;
-        __syncthreads();
-        for (int e = e0 + tid; e < e1; e += SB) {
-            const int s = list[e];
-            const double gx = vol ? A.vgx[s] : A.bgx[s], gy = vol ? A.vgy[s] : A.bgy[s];
-            int mx0, my0;
-            T wx[W], wy[W];
-            window_weights2<W, T>(gx, gy, A.wcoef, mx0, my0, wx, wy);
-            mx0 -= x0;
-            my0 -= y0;
-            // listed sources meet the tile; the test keeps every write inside
-            // the buffer whatever the list holds
-            if (mx0 <= -W || mx0 >= TILE || my0 <= -W || my0 >= TILE) continue;
-            T q;
-            if (vol) {
-                q = (T)(A.vw[s] * (double)A.f_vol[(size_t)b * A.nv + A.vidx[s]]);
-            } else {
-                const int i = A.bidx[s];
-                q = ph == 1 ? (T)(A.bw[s] * (double)A.sigma[(size_t)b * A.nb + i])
-                            : (T)((ph == 2 ? A.bwx[s] : A.bwy[s]) * (double)A.mu[(size_t)b * A.nb + i]);
-            }
-            double *base = acc + (my0 + PAD) * PT + (mx0 + PAD);
-            bool col[W];
-#pragma unroll
-            for (int kx = 0; kx < W; ++kx) col[kx] = (unsigned)(mx0 + kx) < (unsigned)TILE;
-#pragma unroll
-            for (int ky = 0; ky < W; ++ky) {
-                if ((unsigned)(my0 + ky) >= (unsigned)TILE) continue;
-                const T qy = q * wy[ky];
-#pragma unroll
-                for (int kx = 0; kx < W; ++kx)
-                    if (col[kx]) atomicAdd(base + ky * PT + kx, (double)(qy * wx[kx]));
-            }
-        }
-        __syncthreads();
-        for (int i = tid; i < TILE * TILE; i += SB)
-            out[(size_t)(y0 + i / TILE) * (A.n + 2) + x0 + (i % TILE)] =
-                (T)acc[(i / TILE + PAD) * PT + PAD + (i % TILE)];
-        __syncthreads();
-    }
+    constexpr int NM = NV > 3 * ND ? NV : 3 * ND;
+    constexpr int SZ = SPREAD_LDS(W, NM) * (SB / 64);
+    __shared__ double lds[SZ > 1024 ? SZ : 1024];
+    const bool vol = (int64_t)blockIdx.x < A.nvw;
+    const int id = (int)(blockIdx.x - (vol ? 0 : A.nvw)), nt = vol ? A.nvt : A.nbt;
+    const int blk = (vol ? A.vact : A.bact)[id / nt], b0 = id % nt * (vol ? NV : ND);
+    const int nd = min(vol ? NV : ND, A.B - b0);
+    const int x0 = blk % A.nblk * SPB, y0 = blk / A.nblk * SPB;
+    if (vol)
+        spread_block<W, T, NV, true>(A, b0, nd, x0, y0, A.vlofs[blk], A.vlofs[blk + 1], lds);
+    else
+        spread_block<W, T, 3 * ND, false>(A, b0, 3 * nd, x0, y0, A.blofs[blk], A.blofs[blk + 1], lds);
 }
 
 // Fourier multiplier on the half spectrum [n][n/2+1] of each field; the
@@ -439,8 +564,10 @@ template <typename T>
 struct RowArgs {
     int64_t n;
     int r0, nrow;                  // rows r0 .. r0 + nrow - 1 of every field of the launch
-    int m0, m1;                    // forward: complex points [m0, m1) of a row are read, the others are zero;
+    int m0, m1;                    // forward: complex points [m0, m1) of a row can be nonzero;
                                    // inverse: complex points [m0, m1) are written back
+    int B, nblk;                   // densities; blocks per grid row
+    const uint8_t *vflag, *bflag;  // forward: blocks holding volume / boundary sources; the others are zero, unwritten
     int ncol;                      // half-spectrum entries k < ncol can be nonzero after the multiplier
     int npass;
     int8_t radix[COL_MAXPASS];     // of n/2
@@ -459,10 +586,20 @@ __global__ void __launch_bounds__(RT) k_rows(RowArgs<T> A)
     T2 *c = reinterpret_cast<T2 *>(A.grid + (slot * (size_t)n + row) * (size_t)(n + 2));   // h + 1 complex
     const int tid = threadIdx.x;
     if (!INV) {
-        // the row is zero outside the sources' windows
+        // the row is zero outside the blocks of the sources' windows
         const T2 zero = c2<T2>((T)0, (T)0);
-        for (int m = tid; m < h; m += RT) buf[m] = m >= A.m0 && m < A.m1 ? c[m] : zero;
-        __syncthreads();
+        const uint8_t *__restrict__ flag =
+            (slot / A.B == 1 ? A.vflag : A.bflag) + (row / SPB) * (size_t)A.nblk;
+        int any = 0;
+        for (int m = tid; m < h; m += RT) {
+            const bool on = m >= A.m0 && m < A.m1 && flag[2 * m / SPB];
+            buf[m] = on ? c[m] : zero;
+            any |= on;
+        }
+        if (!__syncthreads_or(any)) {
+            for (int k = tid; k < A.ncol; k += RT) c[k] = zero;
+            return;
+        }
         lds_fft<false, RT, NMAX / 2>(buf, A.tw, 2, h, A.radix, A.npass);
         // only the columns that the multiplier keeps are read again
         for (int k = tid; k < A.ncol; k += RT) {
@@ -775,14 +912,23 @@ hipError_t launch_trunc_table(const double *tr, int lmax, const double *phi2inv,
 }
 
 template <int W, typename T>
-static hipError_t spread_w(mhk_plan *P, const SpreadArgs<T> &A)
+static hipError_t spread_w(mhk_plan *P, SpreadArgs<T> &A)
 {
     const History &G = P->hist;
-    // column path: only the tiles of the sources' windows (the transforms
-    // read nothing else); rocFFT's 2D transforms read the whole grid
-    const int nty = G.colpath ? (G.sy1 - 1) / TILE - A.tby0 + 1 : A.ntile;
-    dim3 grid((unsigned)(A.ntbx * nty), (unsigned)A.B);
-    hipLaunchKernelGGL((k_spread<W, T>), grid, dim3(SB), 0, P->stream, A);
+    // several densities share the window values of a workgroup: 8 accumulators
+    // of the volume or 6 of the boundary (4 doubles a lane each) stay in
+    // registers beside them
+    const bool one = A.B == 1;
+    const int nv = one ? 1 : 8, nd = one ? 1 : 2;
+    A.nvt = (A.B + nv - 1) / nv;
+    A.nbt = (A.B + nd - 1) / nd;
+    A.nvw = A.f_vol ? G.nvact * A.nvt : 0;
+    const int64_t wg = A.nvw + (A.sigma || A.mu ? G.nbact * A.nbt : 0);
+    if (wg == 0) return hipSuccess;
+    if (one)
+        hipLaunchKernelGGL((k_spread<W, T, 1, 1>), dim3((unsigned)wg), dim3(SB), 0, P->stream, A);
+    else
+        hipLaunchKernelGGL((k_spread<W, T, 8, 2>), dim3((unsigned)wg), dim3(SB), 0, P->stream, A);
     return hipGetLastError();
 }
 
@@ -822,12 +968,10 @@ static hipError_t spread_t(mhk_plan *P, const void *sigma, const void *mu, const
     A.field = G.field;
     A.nb = P->nb;
     A.nv = P->nv;
-    A.ntile = G.ntile;
+    A.nblk = (int)(G.n / SPB);
     A.B = P->bat;
-    A.tbx0 = G.colpath ? G.sx0 / TILE : 0;
-    A.tby0 = G.colpath ? G.sy0 / TILE : 0;
-    A.ntbx = G.colpath ? (G.sx1 - 1) / TILE - A.tbx0 + 1 : G.ntile;
-    A.beta = G.beta;
+    A.vact = G.vact;
+    A.bact = G.bact;
     A.bgx = G.bgx; A.bgy = G.bgy; A.bw = G.bw; A.bwx = G.bwx; A.bwy = G.bwy;
     A.bidx = G.bidx; A.blofs = G.blofs; A.blist = G.blist;
     A.vgx = G.vgx; A.vgy = G.vgy; A.vw = G.vw; A.vidx = G.vidx; A.vlofs = G.vlofs; A.vlist = G.vlist;
@@ -908,6 +1052,10 @@ static hipError_t rows_t(mhk_plan *P)
     A.nrow = INV ? G.ty1 - G.ty0 : G.sy1 - G.sy0;
     A.m0 = (INV ? G.tx0 : G.sx0) / 2;
     A.m1 = ((INV ? G.tx1 : G.sx1) + 1) / 2;
+    A.B = P->bat;
+    A.nblk = (int)(G.n / SPB);
+    A.vflag = G.vflag;
+    A.bflag = G.bflag;
     const size_t lds = sizeof(typename Vec2<T>::type) * (size_t)(G.n / 2);
     const int64_t rows = (INV ? 3 : 4) * (int64_t)P->bat * A.nrow;
     if (rows <= 0) return hipSuccess;

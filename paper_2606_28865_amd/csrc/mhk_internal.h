@@ -12,8 +12,8 @@
 //    densities, per-eval strengths q_S = w sigma, q_Dx = w nu_x mu,
 //    q_Dy = w nu_y mu in the same sorted order, and per target wavefront a
 //    flat list of the child nodes within R_j of its targets;
-//  * history: per-tile lists of the boundary and volume sources whose windows
-//    meet each 32x32 tile of the fine grid, the fine grids
+//  * history: per-block lists of the boundary and volume sources whose windows
+//    meet each 16x16 block of the fine grid, the fine grids
 //    [4][batch][n][n+2] (S, V, D_x, D_y sources, real, rows padded for
 //    in-place real-to-complex FFTs; only the rows and columns of the sources'
 //    and targets' windows are touched) and the 1D factors of the Fourier
@@ -41,6 +41,7 @@ namespace mhk {
 
 constexpr int NGL = 16;          // Gauss-Legendre nodes per panel (Section 3.2)
 constexpr int TILE = 32;         // fine-grid tile edge of spreading/interpolation
+constexpr int SPB = 16;          // fine-grid block edge of the spreading lists (TILE is a multiple)
 constexpr int MAXJ = 8;          // maximum number of dyadic levels
 constexpr int TAB_NC = 8;        // coefficients per table segment (degree 7)
 constexpr int TAB_NC64 = 5;      // FP64 path: c_0..c_4 stored as doubles, c_5..c_7 as floats
@@ -117,10 +118,15 @@ struct History {
     int32_t *bidx = nullptr;
     double *vgx = nullptr, *vgy = nullptr, *vw = nullptr;
     int32_t *vidx = nullptr;
-    // per tile, the sorted sources whose w x w window meets the tile (a
-    // source is listed in up to 4 tiles): lists [*lofs[t], *lofs[t + 1])
-    int32_t *blofs = nullptr, *blist = nullptr;   // boundary: [ntile*ntile + 1], entries
+    // per 16 x 16 block of the grid, the sorted sources whose w x w window
+    // meets it (a source is listed in up to 4 blocks): lists [*lofs[t], *lofs[t + 1])
+    int32_t *blofs = nullptr, *blist = nullptr;   // boundary: [(n/SPB)^2 + 1], entries
     int32_t *vlofs = nullptr, *vlist = nullptr;   // volume
+    // blocks with a list: flag per block, and their indices; the grid values
+    // of the others are zero and not written (column path)
+    uint8_t *bflag = nullptr, *vflag = nullptr;
+    int32_t *bact = nullptr, *vact = nullptr;
+    int64_t nbact = 0, nvact = 0;
     // targets by tile: list of non-empty tiles and their ranges in sorted order
     int n_ttiles = 0;
     int32_t *ttile_xy = nullptr;                  // [n_ttiles] tile index ty*ntile+tx
@@ -354,12 +360,14 @@ hipError_t dev_wave_fill(const double *tx, const double *ty, int64_t nout, int64
                          double ox, double oy, double cell, int64_t ncx, int64_t ncy, const int32_t *start,
                          const double *sx, const double *sy, const int32_t *ofs, int32_t *out, int32_t *order,
                          hipStream_t st);
-// History sources by spreading tile (sorted arrays, window bounds into
-// sup, list offsets into lofs) and their per-tile lists.
+// History sources by spreading block (SPB grid points; ntile blocks per row):
+// sorted arrays, window bounds into sup, list offsets into lofs, the blocks
+// with a list, and the lists.
 hipError_t dev_sources_by_tile(const double *x, const double *y, const double *w, const double *nx, const double *ny,
                                int64_t n, double ox, double oy, double h, int64_t ntile, int W, double *gx, double *gy,
                                double *gw, double *gwx, double *gwy, int32_t *idx, int *sup, int32_t *lofs,
-                               int32_t **tstart_out, int64_t *total, hipStream_t st);
+                               uint8_t *flag, int32_t *active, int64_t *nactive, int32_t **tstart_out, int64_t *total,
+                               hipStream_t st);
 hipError_t dev_tile_fill(const double *gx, const double *gy, const int32_t *tstart, int64_t ntile, int W,
                          const int32_t *lofs, int32_t *list, hipStream_t st);
 // Runs of equal tiles along the sorted targets, and their window bounds.

@@ -1253,9 +1253,9 @@ mhk_status build_history(mhk_plan *P, Host &H)
             if (fac[l] != 0.0) G.ncol = (int)l + 1;
     }
 
-    // Sources sorted by 32 x 32 tile of the grid, per-tile lists of the
+    // Sources sorted by 16 x 16 block of the grid, per-block lists of the
     // sorted sources whose window [m0, m0 + w) (m0 = ceil(g - w/2), as the
-    // spreading kernel forms it) meets the tile in both axes, and the grid
+    // spreading kernel forms it) meets the block in both axes, and the grid
     // rows and columns the windows use; targets (already sorted with tiles
     // contiguous) as runs of tiles, and the rows and columns of their
     // interpolation windows.  All on the device; the few totals and bounds
@@ -1264,14 +1264,14 @@ mhk_status build_history(mhk_plan *P, Host &H)
         const hipStream_t st = P->stream;
         StreamTmp tmp(st);
         const int64_t nb = H.b->n_panels * NGL, nv = H.v ? H.v->n : 0, nout = P->nout;
-        const int64_t nt2 = (int64_t)G.ntile * G.ntile;
+        const int64_t nsb = G.n / SPB, nt2 = nsb * nsb;      // spreading blocks
         const int n = (int)G.n;
         // window bounds [x0, x1) x [y0, y1): sources in bnd[0..3], targets in bnd[4..7]
         const int bnd0[8] = {n, 0, n, 0, n, 0, n, 0};
         int *bnd = nullptr;
-        int64_t *tots = nullptr;   // boundary list, volume list, target tile runs
+        int64_t *tots = nullptr;   // boundary list, volume list, target tile runs, active blocks of both lists
         TRY(tmp.upload(&bnd, bnd0, 8));
-        TRY(tmp.alloc(&tots, 3));
+        TRY(tmp.alloc(&tots, 5));
         G.nbs = nb;
         TRY(dalloc(P, &G.bgx, nb));
         TRY(dalloc(P, &G.bgy, nb));
@@ -1280,9 +1280,12 @@ mhk_status build_history(mhk_plan *P, Host &H)
         TRY(dalloc(P, &G.bwy, nb));
         TRY(dalloc(P, &G.bidx, nb));
         TRY(dalloc(P, &G.blofs, nt2 + 1));
+        TRY(dalloc(P, &G.bflag, nt2));
+        TRY(dalloc(P, &G.bact, std::min(nt2, 4 * nb)));
         int32_t *bstart = nullptr, *vstart = nullptr, *tflag = nullptr, *tpos = nullptr;
-        MHK_HIP(dev_sources_by_tile(P->bx, P->by, P->bw, P->bnx, P->bny, nb, G.ox, G.oy, G.h, G.ntile, G.w, G.bgx,
-                                    G.bgy, G.bw, G.bwx, G.bwy, G.bidx, bnd, G.blofs, &bstart, tots + 0, st));
+        MHK_HIP(dev_sources_by_tile(P->bx, P->by, P->bw, P->bnx, P->bny, nb, G.ox, G.oy, G.h, nsb, G.w, G.bgx,
+                                    G.bgy, G.bw, G.bwx, G.bwy, G.bidx, bnd, G.blofs, G.bflag, G.bact, tots + 3, &bstart,
+                                    tots + 0, st));
         tmp.ptrs.push_back(bstart);
         G.nvs = nv;
         double *vx = nullptr, *vy = nullptr, *vw = nullptr;
@@ -1294,26 +1297,31 @@ mhk_status build_history(mhk_plan *P, Host &H)
         TRY(dalloc(P, &G.vw, nv));
         TRY(dalloc(P, &G.vidx, nv));
         TRY(dalloc(P, &G.vlofs, nt2 + 1));
-        MHK_HIP(dev_sources_by_tile(vx, vy, vw, nullptr, nullptr, nv, G.ox, G.oy, G.h, G.ntile, G.w, G.vgx, G.vgy,
-                                    G.vw, nullptr, nullptr, G.vidx, bnd, G.vlofs, &vstart, tots + 1, st));
+        TRY(dalloc(P, &G.vflag, nt2));
+        TRY(dalloc(P, &G.vact, std::min(nt2, 4 * nv)));
+        MHK_HIP(dev_sources_by_tile(vx, vy, vw, nullptr, nullptr, nv, G.ox, G.oy, G.h, nsb, G.w, G.vgx, G.vgy,
+                                    G.vw, nullptr, nullptr, G.vidx, bnd, G.vlofs, G.vflag, G.vact, tots + 4, &vstart,
+                                    tots + 1, st));
         tmp.ptrs.push_back(vstart);
         MHK_HIP(dev_target_tiles_count(P->tx, P->ty, nout, G.ox, G.oy, G.h, G.ntile, G.w, bnd + 4, &tflag, &tpos,
                                        tots + 2, st));
         tmp.ptrs.push_back(tflag);
         tmp.ptrs.push_back(tpos);
-        int64_t tot[3];
+        int64_t tot[5];
         int bh[8];
         MHK_HIP(hipMemcpyAsync(tot, tots, sizeof tot, hipMemcpyDeviceToHost, st));
         TRY(tmp.fetch(bh, bnd, 8));
         if (tot[0] > (int64_t)INT32_MAX || tot[1] > (int64_t)INT32_MAX) {
-            set_error("spreading tile lists too large");
+            set_error("spreading lists too large");
             return MHK_EUNSUPPORTED;
         }
         TRY(dalloc(P, &G.blist, std::max<int64_t>(1, tot[0])));
         TRY(dalloc(P, &G.vlist, std::max<int64_t>(1, tot[1])));
-        MHK_HIP(dev_tile_fill(G.bgx, G.bgy, bstart, G.ntile, G.w, G.blofs, G.blist, st));
-        MHK_HIP(dev_tile_fill(G.vgx, G.vgy, vstart, G.ntile, G.w, G.vlofs, G.vlist, st));
+        MHK_HIP(dev_tile_fill(G.bgx, G.bgy, bstart, nsb, G.w, G.blofs, G.blist, st));
+        MHK_HIP(dev_tile_fill(G.vgx, G.vgy, vstart, nsb, G.w, G.vlofs, G.vlist, st));
         G.n_ttiles = (int)tot[2];
+        G.nbact = tot[3];
+        G.nvact = tot[4];
         TRY(dalloc(P, &G.ttile_xy, std::max<int64_t>(1, tot[2])));
         TRY(dalloc(P, &G.ttile_rng, tot[2] + 1));
         MHK_HIP(dev_target_tiles_fill(P->tx, P->ty, nout, G.ox, G.oy, G.h, G.ntile, tflag, tpos, G.ttile_xy,
@@ -1932,7 +1940,8 @@ mhk_status mhk_plan_footprint(const mhk_params *params, const mhk_boundary *b, c
         const int64_t es = p.prec == MHK_FP64 ? 8 : 4;
         s += 4 * B * g.n * (g.n + 2) * es * 2;   // grids + FFT work estimate
         s += (nb + nv) * (8 * 3 + 4);
-        s += (nb + nv) * 4 * 4 + 2 * (int64_t)(g.n / TILE) * (g.n / TILE) * 4;   // per-tile source lists
+        const int64_t nt2 = (g.n / SPB) * (g.n / SPB);   // per-block source lists
+        s += (nb + nv) * 4 * 4 + 2 * nt2 * 5 + 4 * (std::min(nt2, 4 * nb) + std::min(nt2, 4 * nv));
     }
     *bytes = s;
     return MHK_OK;
@@ -2109,6 +2118,8 @@ mhk_status enqueue(mhk_plan *P, int parts, const void *sigma, const void *mu, co
     // history part writes the accumulators (or zeros them)
     bool hist = (parts & MHK_PART_HISTORY) && P->hist.active;
     if (hist) {
+        // rocFFT's 2D transforms read every field and value of the grid
+        if (!P->hist.colpath) MHK_HIP(launch_fill(P, P->hist.grid, 4 * (int64_t)B * P->hist.field));
         MHK_HIP(launch_spread(P, ws ? sig_h : nullptr, wd ? mu_h : nullptr, wv ? fv_h : nullptr));
         if (P->timing) MHK_HIP(hipEventRecord(P->ev[1], st));
         void *buf[1] = {P->hist.grid};
