@@ -472,15 +472,31 @@ __global__ void __launch_bounds__(BT) k_wave_cands(const double *__restrict__ tx
     if (!FILL && lane == 0) cnt[wave] = (int32_t)min(n, (int64_t)INT32_MAX);
 }
 
-// key INT32_MAX - count: the stable ascending sort orders the wavefronts by
-// decreasing work, ties in wavefront order
-__global__ void __launch_bounds__(BT) k_wave_keys(const int32_t *__restrict__ ofs, int64_t nwave,
+// pieces of each wavefront's list
+__global__ void __launch_bounds__(BT) k_item_counts(const int32_t *__restrict__ ofs, int64_t nwave, int piece,
+                                                    int32_t *__restrict__ cnt)
+{
+    const int64_t w = (int64_t)blockIdx.x * BT + threadIdx.x;
+    if (w >= nwave) return;
+    cnt[w] = (int32_t)(((int64_t)ofs[w + 1] - ofs[w] + piece - 1) / piece);
+}
+
+// the items of each wavefront; key (batches of a full piece) - (batches of
+// the item): the stable ascending sort orders the items by decreasing length,
+// ties in item order
+__global__ void __launch_bounds__(BT) k_item_keys(const int32_t *__restrict__ ofs, const int32_t *__restrict__ item_ofs,
+                                                  int64_t nwave, int piece, int32_t *__restrict__ wave,
                                                   uint32_t *__restrict__ key, int32_t *__restrict__ val)
 {
     const int64_t w = (int64_t)blockIdx.x * BT + threadIdx.x;
     if (w >= nwave) return;
-    key[w] = (uint32_t)(INT32_MAX - (ofs[w + 1] - ofs[w]));
-    val[w] = (int32_t)w;
+    const int cnt = ofs[w + 1] - ofs[w], i0 = item_ofs[w], np = item_ofs[w + 1] - i0;
+    const int size = level_piece(cnt, np);
+    for (int p = 0; p < np; ++p) {
+        wave[i0 + p] = (int32_t)w;
+        key[i0 + p] = (uint32_t)(piece / 64 - (min(size, cnt - p * size) + 63) / 64);
+        val[i0 + p] = i0 + p;
+    }
 }
 
 hipError_t dev_child_nodes(int64_t n_src, int nch, const double *Tm, const double *bx, const double *by,
@@ -528,18 +544,32 @@ hipError_t dev_wave_counts(const double *tx, const double *ty, int64_t nout, int
 
 hipError_t dev_wave_fill(const double *tx, const double *ty, int64_t nout, int64_t nwave, double R, double R2,
                          double ox, double oy, double cell, int64_t ncx, int64_t ncy, const int32_t *start,
-                         const double *sx, const double *sy, const int32_t *ofs, int32_t *out, int32_t *order,
-                         hipStream_t st)
+                         const double *sx, const double *sy, const int32_t *ofs, int32_t *out, hipStream_t st)
 {
     hipLaunchKernelGGL(k_wave_cands<true>, dim3(nblocks(nwave * 64, BT)), dim3(BT), 0, st, tx, ty, nout, nwave, R, R2,
                        ox, oy, cell, ncx, ncy, start, sx, sy, (int32_t *)nullptr, ofs, out);
-    hipError_t e = hipGetLastError();
+    return hipGetLastError();
+}
+
+hipError_t dev_item_counts(const int32_t *ofs, int64_t nwave, int piece, int32_t *cnt, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_item_counts, dim3(nblocks(nwave, BT)), dim3(BT), 0, st, ofs, nwave, piece, cnt);
+    return hipGetLastError();
+}
+
+hipError_t dev_item_fill(const int32_t *ofs, const int32_t *item_ofs, int64_t nwave, int64_t n, int piece,
+                         int32_t *wave, int32_t *order, hipStream_t st)
+{
+    if (n <= 0) return hipSuccess;
     uint32_t *key = nullptr;
-    if (e == hipSuccess) e = hipMallocAsync((void **)&key, sizeof(uint32_t) * std::max<int64_t>(1, nwave), st);
+    hipError_t e = hipMallocAsync((void **)&key, sizeof(uint32_t) * n, st);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_wave_keys, dim3(nblocks(nwave, BT)), dim3(BT), 0, st, ofs, nwave, key, order);
+        hipLaunchKernelGGL(k_item_keys, dim3(nblocks(nwave, BT)), dim3(BT), 0, st, ofs, item_ofs, nwave, piece, wave,
+                           key, order);
         e = hipGetLastError();
-        if (e == hipSuccess) e = dev_sort_pairs(key, order, nwave, 31, st);
+        int bits = 1;
+        while (((int64_t)1 << bits) < piece / 64) ++bits;
+        if (e == hipSuccess) e = dev_sort_pairs(key, order, n, bits, st);
     }
     if (key) (void)hipFreeAsync(key, st);
     return e;

@@ -14,12 +14,19 @@
 // the double-layer sum is rescaled once per target.
 //
 // Work decomposition: a wavefront owns 64 consecutive targets of the Morton
-// order, one per lane, and a flat list (built at plan time) of the sources
-// within R_j of its targets' bounding box.  It reads the list 64 sources at
-// a time with vector loads (lane l holds source l) -- the next batch is
-// loaded while the current one is summed -- and hands each source to all
-// lanes with readlane; each lane keeps its target's sums in registers: no
-// atomics, no barriers in the loop, deterministic summation order.  Sources
+// order, one per lane, and one piece of the flat list (built at plan time) of
+// the sources within R_j of its targets' bounding box.  It reads the list 64
+// sources at a time with vector loads (lane l holds source l) -- the next
+// batch is loaded while the current one is summed -- and hands each source to
+// all lanes with readlane; each lane keeps its target's sums in registers: no
+// atomics, no barriers in the loop, deterministic summation order (the local
+// part adds the pieces in order).  The lists are cut because a whole one is a
+// serial chain: a few thousand wavefronts (or 72, for 4608 targets) with lists
+// of up to several thousand sources left the chip idle behind the longest
+// ones.  All levels go in one launch.  Measured with whole lists and a launch
+// per level against pieces of 128 to 1024 sources: 618 against 111 us at 4608
+// targets and 512 boundary nodes, 1895 against 930 us at 466 thousand targets
+// and 65536 boundary nodes (beside the history part).  Sources
 // are taken two at a time with no branch per lane, and a pair of sources out
 // of range of every lane is skipped as a whole.  The two polynomial
 // evaluations are independent, so their table reads and multiply-adds
@@ -42,32 +49,31 @@
 
 namespace mhk {
 
-// Child-node strengths of level j for the current densities: q_S = w sigma,
-// q_Dx = w nu_x mu, q_Dy = w nu_y mu, with sigma, mu at the child node
-// interpolated from the parent panel's 16 nodal values.
+// Child-node strengths of every level for the current densities: q_S = w
+// sigma, q_Dx = w nu_x mu, q_Dy = w nu_y mu, with sigma, mu at the child node
+// interpolated from the parent panel's 16 nodal values.  One launch for all
+// levels (workgroup ranges qblk0).
 template <typename T>
-__global__ void __launch_bounds__(256) k_level_q(int64_t n_src, int nch, int B, int64_t nb,
-                                                 const int32_t *__restrict__ code,
-                                                 const double *__restrict__ Tm,
-                                                 const double *__restrict__ sw,
-                                                 const double *__restrict__ swx,
-                                                 const double *__restrict__ swy,
-                                                 const T *__restrict__ sigma,
-                                                 const T *__restrict__ mu,
-                                                 T *__restrict__ q)
+__global__ void __launch_bounds__(256) k_level_q(const LevelDesc *__restrict__ desc, int J, int B, int64_t nb,
+                                                 const T *__restrict__ sigma, const T *__restrict__ mu)
 {
-    int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    int j = 0;
+    while (j + 1 < J && (int)blockIdx.x >= desc[j + 1].qblk0) ++j;
+    const LevelDesc &L = desc[j];
+    const int64_t n_src = L.n_src;
+    int64_t s = (int64_t)((int)blockIdx.x - L.qblk0) * blockDim.x + threadIdx.x;
     if (s >= n_src) return;
-    int c = code[s];
+    T *q = (T *)L.q;
+    int c = L.code[s];
     int k = c % NGL;
     int pc = c / NGL;
-    int child = pc % nch;
-    int64_t panel = pc / nch;
-    const double *row = Tm + ((size_t)child * NGL + k) * NGL;
+    int child = pc % L.nchild;
+    int64_t panel = pc / L.nchild;
+    const double *row = L.interp + ((size_t)child * NGL + k) * NGL;
     double r[NGL];
 #pragma unroll
     for (int i = 0; i < NGL; ++i) r[i] = row[i];
-    const double w = sw[s], wx = swx[s], wy = swy[s];
+    const double w = L.sw[s], wx = L.swx[s], wy = L.swy[s];
     for (int b = 0; b < B; ++b) {
         if (sigma) {
             const T *f = sigma + (size_t)b * nb + panel * NGL;
@@ -87,23 +93,15 @@ __global__ void __launch_bounds__(256) k_level_q(int64_t n_src, int nch, int B, 
     }
 }
 
-template <typename T>
 struct LevelArgs {
-    int64_t nout, n_src;
+    const LevelDesc *desc;
+    int lev0, nlev;       // levels [lev0, lev0 + nlev) of the launch
+    int64_t nout;
     const double *tx, *ty;
-    double inv4d, a_max, seg_inv, d_scale;
-    double pscale;        // sqrt(inv4d seg_inv): coordinates scaled by it give f = a seg_inv = |dx|^2
-    int nseg, B;
-    const int32_t *wave_ofs, *wave_src, *wave_order;
-    const double *sx, *sy;
-    const T *q, *tab;
-    T *acc_s, *acc_d;     // [B][nout] each (sorted order)
+    int B, ncomp;         // densities; components of an item's part (2: S and D, 1: S)
     int want_s, want_d;
-    int init;             // store (first level) instead of add
-    int64_t n_wave;       // wavefront lists (persistent launch: work items n_wave x density chunks)
     int *counter;         // persistent launch: next work item, zero at the launch
 };
-
 
 // Value of lane k (wave-uniform k) for the whole wave.
 __device__ inline double bcast(double v, int k)
@@ -159,20 +157,30 @@ __device__ inline PairGeo<T> pair_geo(double x, double y, double sxv, double syv
 
 // p(v) and p'(v) of a table segment by Horner's rule for two sources at
 // once (K_j^S and, up to the factor d_scale, K_j^D); the derivative's first
-// step is c_7.  FP32 table: eight floats.
+// step is c_7.  FP32 table: eight floats, read as two 16-byte LDS loads.
+struct Row32 {
+    float c[TABF_NC];
+};
+__device__ inline Row32 load_row(const PairGeo<float> &g)
+{
+    const float4 *r = reinterpret_cast<const float4 *>(g.c);
+    const float4 a = r[0], b = r[1];
+    return Row32{{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w}};
+}
 __device__ inline void horner2(const PairGeo<float> &g0, const PairGeo<float> &g1, float &ks0, float &kd0,
                                float &ks1, float &kd1)
 {
-    kd0 = g0.c[TAB_NC - 1];
-    kd1 = g1.c[TAB_NC - 1];
-    ks0 = fmaf(kd0, g0.v, g0.c[TAB_NC - 2]);
-    ks1 = fmaf(kd1, g1.v, g1.c[TAB_NC - 2]);
+    const Row32 w0 = load_row(g0), w1 = load_row(g1);
+    kd0 = w0.c[TABF_NC - 1];
+    kd1 = w1.c[TABF_NC - 1];
+    ks0 = fmaf(kd0, g0.v, w0.c[TABF_NC - 2]);
+    ks1 = fmaf(kd1, g1.v, w1.c[TABF_NC - 2]);
 #pragma unroll
-    for (int m = TAB_NC - 3; m >= 0; --m) {
+    for (int m = TABF_NC - 3; m >= 0; --m) {
         kd0 = fmaf(kd0, g0.v, ks0);
         kd1 = fmaf(kd1, g1.v, ks1);
-        ks0 = fmaf(ks0, g0.v, g0.c[m]);
-        ks1 = fmaf(ks1, g1.v, g1.c[m]);
+        ks0 = fmaf(ks0, g0.v, w0.c[m]);
+        ks1 = fmaf(ks1, g1.v, w1.c[m]);
     }
 }
 
@@ -229,12 +237,13 @@ __device__ inline void horner2(const PairGeo<double> &g0, const PairGeo<double> 
 }
 __device__ inline void horner1(const PairGeo<float> &g, float &ks, float &kd)
 {
-    kd = g.c[TAB_NC - 1];
-    ks = fmaf(kd, g.v, g.c[TAB_NC - 2]);
+    const Row32 w = load_row(g);
+    kd = w.c[TABF_NC - 1];
+    ks = fmaf(kd, g.v, w.c[TABF_NC - 2]);
 #pragma unroll
-    for (int m = TAB_NC - 3; m >= 0; --m) {
+    for (int m = TABF_NC - 3; m >= 0; --m) {
         kd = fmaf(kd, g.v, ks);
-        ks = fmaf(ks, g.v, g.c[m]);
+        ks = fmaf(ks, g.v, w.c[m]);
     }
 }
 __device__ inline void horner1(const PairGeo<double> &g, double &ks, double &kd)
@@ -251,21 +260,24 @@ __device__ inline void horner1(const PairGeo<double> &g, double &ks, double &kd)
     }
 }
 
-// One work item: the LV_WAVE targets of wavefront list `wave` against its
-// candidate sources, for the densities of chunk `chunk` (BCH of them).
+// One work item: the LV_WAVE targets of a wavefront against one piece of its
+// candidate list, for the densities of chunk `chunk` (BCH of them).
 template <int BCH, typename T, int STRIDE>
-__device__ inline void level_item(const LevelArgs<T> &A, const T *s_tab, const float *s_c7, int lane, int wave,
-                                  int chunk)
+__device__ inline void level_item(const LevelArgs &A, const LevelDesc &L, const T *s_tab, const float *s_c7, int lane,
+                                  int item, int chunk)
 {
+    const int wave = __builtin_amdgcn_readfirstlane(L.item_wave[item]);
     const int64_t t = (int64_t)wave * LV_WAVE + lane;
-    const double ps = A.pscale;
+    const double ps = L.pscale;
     double x = 0.0, y = 0.0;
     if (t < A.nout) {
         x = A.tx[t] * ps;
         y = A.ty[t] * ps;
     }
     const int b0 = chunk * BCH, nbh = min(BCH, A.B - b0);
-    const T f_max = (T)(A.a_max * A.seg_inv), f_zero = (T)A.nseg;
+    const T f_max = (T)L.f_max, f_zero = (T)L.nseg;
+    const double *__restrict__ sx = L.sx, *__restrict__ sy = L.sy;
+    const int32_t *__restrict__ wave_src = L.wave_src;
     T S[BCH], D[BCH];
     // FP32 path: the sums of each batch of 64 sources are added into FP64
     // totals (a volume level sums thousands of nodes per target, where one
@@ -274,18 +286,18 @@ __device__ inline void level_item(const LevelArgs<T> &A, const T *s_tab, const f
 #pragma unroll
     for (int b = 0; b < BCH; ++b) S[b] = D[b] = (T)0, S64[b] = D64[b] = 0.0;
     // strengths of density b0 + b: q[c][b0 + b][s] for c = S, D_x, D_y
-    const size_t fstride = (size_t)A.B * A.n_src;
-    const T *q0 = A.q + (size_t)b0 * A.n_src;
+    const size_t n_src = (size_t)L.n_src, fstride = (size_t)A.B * n_src;
+    const T *__restrict__ q0 = (const T *)L.q + (size_t)b0 * n_src;
     // lane l of a batch holds source l of the list; lanes past its end hold a
     // far-away source of zero strength
     auto load = [&](int pos, int end, SrcBatch<T, BCH> &sb) {
         if (pos < end) {
-            const int s = A.wave_src[pos];
-            sb.x = A.sx[s] * ps;
-            sb.y = A.sy[s] * ps;
+            const int s = wave_src[pos];
+            sb.x = sx[s] * ps;
+            sb.y = sy[s] * ps;
 #pragma unroll
             for (int b = 0; b < BCH; ++b) {
-                const T *qb = q0 + (size_t)min(b, nbh - 1) * A.n_src + s;
+                const T *qb = q0 + (size_t)min(b, nbh - 1) * n_src + s;
                 sb.qs[b] = A.want_s ? qb[0] : (T)0;
                 sb.qx[b] = A.want_d ? qb[fstride] : (T)0;
                 sb.qy[b] = A.want_d ? qb[2 * fstride] : (T)0;
@@ -304,7 +316,12 @@ __device__ inline void level_item(const LevelArgs<T> &A, const T *s_tab, const f
             D[b] = fma(fma(qxv, g.dx, qyv * g.dy), kd, D[b]);
         }
     };
-    const int c0 = A.wave_ofs[wave], c1 = A.wave_ofs[wave + 1];
+    // the item's piece of the list
+    const int l0 = L.wave_ofs[wave], l1 = L.wave_ofs[wave + 1];
+    const int i0 = L.item_ofs[wave], i1 = L.item_ofs[wave + 1];
+    const int size = level_piece(l1 - l0, i1 - i0);
+    const int c0 = __builtin_amdgcn_readfirstlane(l0 + (item - i0) * size);
+    const int c1 = __builtin_amdgcn_readfirstlane(min(l1, c0 + size));
     SrcBatch<T, BCH> cur, nxt;
     load(c0 + lane, c1, cur);
     for (int base = c0; base < c1; base += LV_WAVE) {
@@ -352,63 +369,68 @@ __device__ inline void level_item(const LevelArgs<T> &A, const T *s_tab, const f
 #pragma unroll
         for (int b = 0; b < BCH; ++b) {
             S[b] = (float)S64[b];
-            D[b] = (float)(D64[b] * A.d_scale);
+            D[b] = (float)(D64[b] * L.d_scale);
         }
     } else {
 #pragma unroll
-        for (int b = 0; b < BCH; ++b) D[b] *= A.d_scale;
+        for (int b = 0; b < BCH; ++b) D[b] *= L.d_scale;
     }
-    if (t < A.nout) {
+    T *part = (T *)L.part + (size_t)item * A.ncomp * A.B * LV_WAVE + lane;
 #pragma unroll
-        for (int b = 0; b < BCH; ++b) {
-            if (b < nbh) {
-                const size_t o = (size_t)(b0 + b) * A.nout + t;
-                const T s = S[b], d = D[b];
-                if (A.want_s) A.acc_s[o] = A.init ? s : A.acc_s[o] + s;
-                if (A.want_d) A.acc_d[o] = A.init ? d : A.acc_d[o] + d;
-            }
+    for (int b = 0; b < BCH; ++b) {
+        if (b < nbh) {
+            if (A.want_s) part[(size_t)(b0 + b) * LV_WAVE] = S[b];
+            if (A.want_d) part[(size_t)(A.B + b0 + b) * LV_WAVE] = D[b];
         }
     }
 }
 
-// The kernel table is loaded into LDS once per workgroup.  PERSIST = false:
-// one work item per wavefront (wave list from the launch position, density
-// chunk from blockIdx.y).  PERSIST = true: a grid sized to fill the device
-// once; every wavefront takes work items (list-major: the density chunks of
-// one list follow each other, so its candidates stay in cache) from a
-// counter in device memory, zeroed before the launch, until none is left --
-// the exit every wavefront reaches.
+// The level's kernel table is loaded into LDS once per workgroup.  PERSIST =
+// false: one launch over all levels, one work item per wavefront (the level
+// and the item from the launch position, density chunk from blockIdx.y), the
+// long items of a level first.  PERSIST = true: one launch per level, a grid
+// sized to fill the device once; every wavefront takes work items (item-major:
+// the density chunks of one item follow each other, so its candidates stay in
+// cache) from a counter in device memory, zeroed before the launch, until
+// none is left -- the exit every wavefront reaches.
 template <int BCH, typename T, int STRIDE, int NB, bool PERSIST>
-__global__ void __launch_bounds__(NB) k_level_sums(LevelArgs<T> A)
+__global__ void __launch_bounds__(NB) k_level_sums(LevelArgs A)
 {
     extern __shared__ double lds[];
+    int j = A.lev0;
+    if (!PERSIST)
+        while (j + 1 < A.lev0 + A.nlev && (int)blockIdx.x >= A.desc[j + 1].blk0) ++j;
+    const LevelDesc &L = A.desc[j];
     T *s_tab = reinterpret_cast<T *>(lds);                // [nseg + 1][STRIDE], the last segment zero
-    const int tid = threadIdx.x;
-    for (int i = tid; i < (A.nseg + 1) * STRIDE; i += NB) s_tab[i] = i < A.nseg * STRIDE ? A.tab[i] : (T)0;
+    const int tid = threadIdx.x, nseg = L.nseg;
+    const T *__restrict__ tab = (const T *)L.tab;
+    for (int i = tid; i < (nseg + 1) * STRIDE; i += NB) s_tab[i] = i < nseg * STRIDE ? tab[i] : (T)0;
     // FP64 table: c_7 of every segment (the zero segment's last) after the rows
     float *s_c7 = nullptr;
     if constexpr (std::is_same<T, double>::value) {
-        s_c7 = reinterpret_cast<float *>(s_tab + (A.nseg + 1) * STRIDE);
-        const float *g7 = reinterpret_cast<const float *>(A.tab + (size_t)A.nseg * STRIDE);
-        for (int i = tid; i <= A.nseg; i += NB) s_c7[i] = i < A.nseg ? g7[i] : 0.0f;
+        s_c7 = reinterpret_cast<float *>(s_tab + (nseg + 1) * STRIDE);
+        const float *g7 = reinterpret_cast<const float *>(tab + (size_t)nseg * STRIDE);
+        for (int i = tid; i <= nseg; i += NB) s_c7[i] = i < nseg ? g7[i] : 0.0f;
     }
     __syncthreads();
     const int lane = tid % LV_WAVE;
     if (!PERSIST) {
-        // the wave number is wave-uniform
-        const int wave = __builtin_amdgcn_readfirstlane(A.wave_order[blockIdx.x * (NB / LV_WAVE) + tid / LV_WAVE]);
-        level_item<BCH, T, STRIDE>(A, s_tab, s_c7, lane, wave, blockIdx.y);
+        // the item number is wave-uniform
+        const int64_t pos = (int64_t)((int)blockIdx.x - L.blk0) * (NB / LV_WAVE) + tid / LV_WAVE;
+        if (pos >= L.n_items) return;
+        const int item = __builtin_amdgcn_readfirstlane(L.item_order[pos]);
+        level_item<BCH, T, STRIDE>(A, L, s_tab, s_c7, lane, item, blockIdx.y);
         return;
     }
     const int nchunk = (A.B + BCH - 1) / BCH;
-    const int64_t nitems = A.n_wave * nchunk;
+    const int64_t nitems = L.n_items * nchunk;
     for (;;) {
-        int item = 0;
-        if (lane == 0) item = atomicAdd(A.counter, 1);
-        item = __builtin_amdgcn_readfirstlane(__shfl(item, 0));
-        if (item >= nitems) break;
-        const int wave = __builtin_amdgcn_readfirstlane(A.wave_order[item / nchunk]);
-        level_item<BCH, T, STRIDE>(A, s_tab, s_c7, lane, wave, item % nchunk);
+        int pos = 0;
+        if (lane == 0) pos = atomicAdd(A.counter, 1);
+        pos = __builtin_amdgcn_readfirstlane(__shfl(pos, 0));
+        if (pos >= nitems) break;
+        const int item = __builtin_amdgcn_readfirstlane(L.item_order[pos / nchunk]);
+        level_item<BCH, T, STRIDE>(A, L, s_tab, s_c7, lane, item, pos % nchunk);
     }
 }
 
@@ -423,173 +445,144 @@ static size_t level_lds(int nseg)
 }
 
 template <typename T>
-static hipError_t level_q(mhk_plan *P, hipStream_t st, int j, const void *sigma, const void *mu)
+static hipError_t level_q(mhk_plan *P, hipStream_t st, const void *sigma, const void *mu)
 {
-    Level &L = P->lev[j - 1];
-    const int64_t n = L.n_src;
-    dim3 grid((unsigned)((n + 255) / 256));
-    hipLaunchKernelGGL(k_level_q<T>, grid, dim3(256), 0, st, n, L.nchild, P->bat, P->nb, L.code,
-                       L.interp, L.sw, L.swx, L.swy, (const T *)sigma, (const T *)mu, (T *)L.q);
+    if (P->levq_grid == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_level_q<T>, dim3(P->levq_grid), dim3(256), 0, st, P->lev_desc, P->J, P->bat, P->nb,
+                       (const T *)sigma, (const T *)mu);
     return hipGetLastError();
 }
 
-hipError_t launch_level_densities(mhk_plan *P, hipStream_t st, int j, const void *sigma, const void *mu)
+hipError_t launch_level_densities(mhk_plan *P, hipStream_t st, const void *sigma, const void *mu)
 {
-    return P->p.prec == MHK_FP64 ? level_q<double>(P, st, j, sigma, mu) : level_q<float>(P, st, j, sigma, mu);
+    return P->p.prec == MHK_FP64 ? level_q<double>(P, st, sigma, mu) : level_q<float>(P, st, sigma, mu);
 }
 
-template <int BCH, typename T, int STRIDE, int NB, bool PERSIST>
-static void level_launch(const LevelArgs<T> &A, dim3 grid, size_t lds, hipStream_t st)
+mhk_status level_descs(mhk_plan *P, bool vol, std::vector<LevelDesc> &out)
 {
-    const void *fn = (const void *)k_level_sums<BCH, T, STRIDE, NB, PERSIST>;
-    if (lds > 64 * 1024) (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (PERSIST) {
-        // as many workgroups as are resident at once, at most one per item
-        int per_cu = 0, dev = 0, ncu = 0;
-        (void)hipGetDevice(&dev);
-        (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, NB, lds) != hipSuccess || per_cu < 1) per_cu = 1;
-        const int64_t items = A.n_wave * grid.y;
-        const int64_t wg = std::min<int64_t>((int64_t)per_cu * std::max(ncu, 1), (items + NB / LV_WAVE - 1) / (NB / LV_WAVE));
-        grid = dim3((unsigned)std::max<int64_t>(1, wg), 1u);
+    out.assign((size_t)P->J, LevelDesc{});
+    const bool f64 = P->p.prec == MHK_FP64;
+    const int per = P->p.lv_block / LV_WAVE;
+    int64_t blk = 0, qblk = 0;
+    for (int j = 0; j < P->J; ++j) {
+        const Level &L = P->lev[j];
+        LevelDesc &d = out[(size_t)j];
+        const LevelItems &I = vol ? P->vlev[j].items : L.items;
+        d.wave_ofs = vol ? P->vlev[j].wave_ofs : L.wave_ofs;
+        d.wave_src = vol ? P->vlev[j].wave_src : L.wave_src;
+        d.item_ofs = I.ofs;
+        d.item_wave = I.wave;
+        d.item_order = I.order;
+        d.part = I.part;
+        d.n_items = I.n;
+        d.sx = vol ? P->vlev[j].sx : L.sx;
+        d.sy = vol ? P->vlev[j].sy : L.sy;
+        d.q = vol ? P->vlev[j].q : L.q;
+        d.n_src = vol ? P->vlev[j].n_src : L.n_src;
+        d.tab = L.tab_dev;
+        d.nseg = L.nseg;
+        d.nchild = L.nchild;
+        d.code = L.code;
+        d.interp = L.interp;
+        d.sw = L.sw;
+        d.swx = L.swx;
+        d.swy = L.swy;
+        d.pscale = sqrt(L.inv4d * L.seg_inv);
+        d.d_scale = level_d_scale(L) / d.pscale;       // D is summed over scaled separations
+        d.f_max = L.a_max * L.seg_inv;
+        d.blk0 = (int)blk;
+        d.qblk0 = (int)qblk;
+        blk += (I.n + per - 1) / per;
+        qblk += (d.n_src + 255) / 256;
+        const size_t lds = f64 ? level_lds<double, TAB_STRIDE>(L.nseg) : level_lds<float, TABF_STRIDE>(L.nseg);
+        P->lev_lds = std::max(P->lev_lds, lds);
     }
-    hipLaunchKernelGGL((k_level_sums<BCH, T, STRIDE, NB, PERSIST>), grid, dim3(NB), lds, st, A);
+    if (P->lev_lds > 160 * 1024 || blk > INT32_MAX || qblk > INT32_MAX) {
+        set_error("level tables or work-item lists too large");
+        return MHK_EUNSUPPORTED;
+    }
+    if (vol) {
+        P->vlev_grid = (unsigned)blk;
+    } else {
+        P->lev_grid = (unsigned)blk;
+        P->levq_grid = (unsigned)qblk;
+    }
+    return MHK_OK;
+}
+
+template <int BCH, typename T, int STRIDE, int NB>
+static hipError_t level_launch(mhk_plan *P, LevelArgs A, bool vol, hipStream_t st)
+{
+    const size_t lds = P->lev_lds;
+    const unsigned nby = (unsigned)((A.B + BCH - 1) / BCH);
+    if (!P->p.lv_persist) {
+        const void *fn = (const void *)k_level_sums<BCH, T, STRIDE, NB, false>;
+        if (lds > 64 * 1024) (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        const unsigned grid = vol ? P->vlev_grid : P->lev_grid;
+        if (grid == 0) return hipSuccess;
+        A.lev0 = 0;
+        A.nlev = P->J;
+        hipLaunchKernelGGL((k_level_sums<BCH, T, STRIDE, NB, false>), dim3(grid, nby), dim3(NB), lds, st, A);
+        return hipGetLastError();
+    }
+    const void *fn = (const void *)k_level_sums<BCH, T, STRIDE, NB, true>;
+    if (lds > 64 * 1024) (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    // as many workgroups as are resident at once, at most one per item
+    int per_cu = 0, dev = 0, ncu = 0;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, NB, lds) != hipSuccess || per_cu < 1) per_cu = 1;
+    for (int j = 0; j < P->J; ++j) {
+        const int64_t items = (vol ? P->vlev[j].items.n : P->lev[j].items.n) * nby;
+        if (items == 0) continue;
+        const int64_t wg = std::min<int64_t>((int64_t)per_cu * std::max(ncu, 1), (items + NB / LV_WAVE - 1) / (NB / LV_WAVE));
+        hipError_t e = launch_fill_int(P->lv_counter, 1, st);
+        if (e != hipSuccess) return e;
+        A.lev0 = j;
+        A.nlev = 1;
+        hipLaunchKernelGGL((k_level_sums<BCH, T, STRIDE, NB, true>), dim3((unsigned)wg), dim3(NB), lds, st, A);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <int BCH, typename T, int STRIDE>
-static void level_launch_nb(int nb, bool persist, const LevelArgs<T> &A, int64_t nwave, size_t lds, hipStream_t st,
-                            int nbatch)
+static hipError_t level_launch_nb(mhk_plan *P, const LevelArgs &A, bool vol, hipStream_t st)
 {
-    // exactly nwave wavefronts (the lists are padded to whole workgroups of
-    // either shape), the batch in chunks of BCH along y
-    const dim3 grid((unsigned)(nwave / (nb / LV_WAVE)), (unsigned)nbatch);
-    if (nb == 512) {
-        if (persist) level_launch<BCH, T, STRIDE, 512, true>(A, grid, lds, st);
-        else level_launch<BCH, T, STRIDE, 512, false>(A, grid, lds, st);
-    } else {
-        if (persist) level_launch<BCH, T, STRIDE, 256, true>(A, grid, lds, st);
-        else level_launch<BCH, T, STRIDE, 256, false>(A, grid, lds, st);
-    }
+    return P->p.lv_block == 512 ? level_launch<BCH, T, STRIDE, 512>(P, A, vol, st)
+                                : level_launch<BCH, T, STRIDE, 256>(P, A, vol, st);
 }
 
+// vol: the volume potential's levels -- the same kernel tables, the volume
+// level nodes as sources (single-layer sums only)
 template <typename T, int STRIDE>
-static hipError_t level_sums(mhk_plan *P, hipStream_t st, int j, bool want_s, bool want_d, bool init)
+static hipError_t level_sums(mhk_plan *P, hipStream_t st, bool vol, bool want_s, bool want_d)
 {
-    Level &L = P->lev[j - 1];
-    const int B = P->bat;
-    LevelArgs<T> A;
+    LevelArgs A{};
+    A.desc = vol ? P->vlev_desc : P->lev_desc;
     A.nout = P->nout;
-    A.n_src = L.n_src;
     A.tx = P->tx;
     A.ty = P->ty;
-    A.inv4d = L.inv4d;
-    A.a_max = L.a_max;
-    A.seg_inv = L.seg_inv;
-    A.pscale = sqrt(L.inv4d * L.seg_inv);
-    A.d_scale = level_d_scale(L) / A.pscale;       // D was summed over scaled separations
-    A.nseg = L.nseg;
-    A.B = B;
-    A.wave_ofs = L.wave_ofs;
-    A.wave_src = L.wave_src;
-    A.wave_order = L.wave_order;
-    A.sx = L.sx;
-    A.sy = L.sy;
-    A.q = (const T *)L.q;
-    A.tab = (const T *)L.tab_dev;
-    A.acc_s = (T *)P->acc_lev;                              // component 0: S
-    A.acc_d = (T *)P->acc_lev + (size_t)B * P->nout;        // component 1: D
+    A.B = P->bat;
+    A.ncomp = vol ? 1 : 2;
     A.want_s = want_s;
     A.want_d = want_d;
-    A.init = init;
+    A.counter = P->lv_counter;
     // densities per pass: the plan's lv_bch, or fewer for a smaller batch
     // (rounded up to an instantiated size; missing densities of the last
     // pass are skipped)
-    const int want = std::min(B, P->p.lv_bch);
-    const int bch = want <= 1 ? 1 : want <= 2 ? 2 : want <= 4 ? 4 : 8;
-    const int nby = (B + bch - 1) / bch;
-    const size_t lds = level_lds<T, STRIDE>(L.nseg);
-    if (lds > 160 * 1024) return hipErrorInvalidValue;
-    const int nb = P->p.lv_block;
-    const bool pers = P->p.lv_persist != 0;
-    A.n_wave = L.n_wave;
-    A.counter = P->lv_counter;
-    if (pers) {
-        const hipError_t e = launch_fill_int(P->lv_counter, 1, st);
-        if (e != hipSuccess) return e;
-    }
-    switch (bch) {
-    case 1: level_launch_nb<1, T, STRIDE>(nb, pers, A, L.n_wave, lds, st, nby); break;
-    case 2: level_launch_nb<2, T, STRIDE>(nb, pers, A, L.n_wave, lds, st, nby); break;
-    case 4: level_launch_nb<4, T, STRIDE>(nb, pers, A, L.n_wave, lds, st, nby); break;
-    default: level_launch_nb<8, T, STRIDE>(nb, pers, A, L.n_wave, lds, st, nby); break;
-    }
-    return hipGetLastError();
+    const int want = std::min(A.B, P->p.lv_bch);
+    if (want <= 1) return level_launch_nb<1, T, STRIDE>(P, A, vol, st);
+    if (want <= 2) return level_launch_nb<2, T, STRIDE>(P, A, vol, st);
+    if (want <= 4) return level_launch_nb<4, T, STRIDE>(P, A, vol, st);
+    return level_launch_nb<8, T, STRIDE>(P, A, vol, st);
 }
 
-// the volume potential's level j: the same kernel table, the volume level
-// nodes as sources (single-layer sums only), into acc_vlev
-template <typename T, int STRIDE>
-static hipError_t level_sums_v(mhk_plan *P, hipStream_t st, int j, bool init)
+hipError_t launch_level_sums(mhk_plan *P, hipStream_t st, bool vol, bool want_s, bool want_d)
 {
-    Level &L = P->lev[j - 1];
-    VLevel &V = P->vlev[j - 1];
-    const int B = P->bat;
-    LevelArgs<T> A;
-    A.nout = P->nout;
-    A.n_src = V.n_src;
-    A.tx = P->tx;
-    A.ty = P->ty;
-    A.inv4d = L.inv4d;
-    A.a_max = L.a_max;
-    A.seg_inv = L.seg_inv;
-    A.pscale = sqrt(L.inv4d * L.seg_inv);
-    A.d_scale = level_d_scale(L) / A.pscale;       // D was summed over scaled separations
-    A.nseg = L.nseg;
-    A.B = B;
-    A.wave_ofs = V.wave_ofs;
-    A.wave_src = V.wave_src;
-    A.wave_order = V.wave_order;
-    A.sx = V.sx;
-    A.sy = V.sy;
-    A.q = (const T *)V.q;
-    A.tab = (const T *)L.tab_dev;
-    A.acc_s = (T *)P->acc_vlev;
-    A.acc_d = (T *)P->acc_vlev;            // not written (want_d = 0)
-    A.want_s = 1;
-    A.want_d = 0;
-    A.init = init;
-    const int want = std::min(B, P->p.lv_bch);
-    const int bch = want <= 1 ? 1 : want <= 2 ? 2 : want <= 4 ? 4 : 8;
-    const int nby = (B + bch - 1) / bch;
-    const size_t lds = level_lds<T, STRIDE>(L.nseg);
-    if (lds > 160 * 1024) return hipErrorInvalidValue;
-    const int nb = P->p.lv_block;
-    const bool pers = P->p.lv_persist != 0;
-    A.n_wave = V.n_wave;
-    A.counter = P->lv_counter;
-    if (pers) {
-        const hipError_t e = launch_fill_int(P->lv_counter, 1, st);
-        if (e != hipSuccess) return e;
-    }
-    switch (bch) {
-    case 1: level_launch_nb<1, T, STRIDE>(nb, pers, A, V.n_wave, lds, st, nby); break;
-    case 2: level_launch_nb<2, T, STRIDE>(nb, pers, A, V.n_wave, lds, st, nby); break;
-    case 4: level_launch_nb<4, T, STRIDE>(nb, pers, A, V.n_wave, lds, st, nby); break;
-    default: level_launch_nb<8, T, STRIDE>(nb, pers, A, V.n_wave, lds, st, nby); break;
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_level_sums_v(mhk_plan *P, hipStream_t st, int j, bool init)
-{
-    if (P->p.prec == MHK_FP64) return level_sums_v<double, TAB_STRIDE>(P, st, j, init);
-    return level_sums_v<float, TABF_STRIDE>(P, st, j, init);
-}
-
-hipError_t launch_level_sums(mhk_plan *P, hipStream_t st, int j, bool want_s, bool want_d, bool init)
-{
-    if (P->p.prec == MHK_FP64) return level_sums<double, TAB_STRIDE>(P, st, j, want_s, want_d, init);
-    return level_sums<float, TABF_STRIDE>(P, st, j, want_s, want_d, init);
+    if (P->p.prec == MHK_FP64) return level_sums<double, TAB_STRIDE>(P, st, vol, want_s, want_d);
+    return level_sums<float, TABF_STRIDE>(P, st, vol, want_s, want_d);
 }
 
 }  // namespace mhk

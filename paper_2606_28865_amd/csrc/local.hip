@@ -268,8 +268,9 @@ struct LocalArgs {
     double alpha, delta, dstar, band_s, band_v;
     int frows;             // rows of f_trg per density: 1 (f) or 6 (f and its gradient and Hessian)
     const T *acc;          // [3][B][nout]: S, D, V in sorted order (history part)
-    const T *lev;          // [2][B][nout]: S, D of the level sums, or null
-    const T *vlev;         // [B][nout]: the volume potential's level sums, or null
+    const LevelDesc *lev;  // [J]: the level sums' items (S and D parts), or null
+    const LevelDesc *vlev; // [J]: the volume potential's, or null
+    int J;
     T *out_s, *out_d, *out_v;
 };
 
@@ -592,6 +593,23 @@ __global__ void __launch_bounds__(256) k_local_geom(LocalArgs<double> A, double 
     flag[s] = (uint8_t)((near_s ? 1 : 0) | (ext ? 2 : 0));
 }
 
+// Sum of the level items' parts of sorted target s: component c of ncomp,
+// density b of B, levels and pieces in order (the wavefront's items are the
+// same for its 64 lanes, so the offsets are scalar loads)
+template <typename T>
+__device__ inline double level_parts(const LevelDesc *__restrict__ d, int J, int ncomp, int c, int B, int b, int64_t s)
+{
+    const int w = __builtin_amdgcn_readfirstlane((int)(s / LV_WAVE));
+    const int lane = threadIdx.x % LV_WAVE;
+    double v = 0.0;
+    for (int j = 0; j < J; ++j) {
+        const int i0 = d[j].item_ofs[w], i1 = d[j].item_ofs[w + 1];
+        const T *part = (const T *)d[j].part;
+        for (int i = i0; i < i1; ++i) v += (double)part[(((size_t)i * ncomp + c) * B + b) * LV_WAVE + lane];
+    }
+    return v;
+}
+
 // Local part of an evaluation from the per-plan geometry, added to the
 // accumulated history and level sums, and the scatter to the caller's order.
 template <typename T, typename TI, int ORDER>
@@ -660,7 +678,7 @@ __global__ void __launch_bounds__(256) k_local(LocalArgs<T, TI> A)
         const size_t ab = (size_t)b * A.nout + s;
         if (ws) {
             double v = (double)A.acc[(size_t)0 * A.B * A.nout + ab];
-            if (A.lev) v += (double)A.lev[ab];
+            if (A.lev) v += level_parts<T>(A.lev, A.J, 2, 0, A.B, b, s);
             if (do_local) {
                 if (on) {
                     const int64_t i = idx - A.nt;
@@ -685,7 +703,7 @@ __global__ void __launch_bounds__(256) k_local(LocalArgs<T, TI> A)
         }
         if (wd) {
             double v = (double)A.acc[(size_t)1 * A.B * A.nout + ab];
-            if (A.lev) v += (double)A.lev[(size_t)A.B * A.nout + ab];
+            if (A.lev) v += level_parts<T>(A.lev, A.J, 2, 1, A.B, b, s);
             if (do_local) {
                 if (on) {
                     const int64_t i = idx - A.nt;
@@ -719,7 +737,7 @@ __global__ void __launch_bounds__(256) k_local(LocalArgs<T, TI> A)
         }
         if (wv) {
             double v = (double)A.acc[(size_t)2 * A.B * A.nout + ab];
-            if (A.vlev) v += (double)A.vlev[ab];
+            if (A.vlev) v += level_parts<T>(A.vlev, A.J, 1, 0, A.B, b, s);
             if (do_local) {
                 // f (and with second order its gradient and Hessian) at the target
                 const TI *fr = A.f_trg + (size_t)b * A.frows * A.nout + idx;
@@ -865,8 +883,9 @@ static hipError_t local_t(mhk_plan *P, int parts, const void *sigma, const void 
 {
     LocalArgs<T, TI> A;
     fill_args(P, A);
-    A.lev = have_lev ? (const T *)P->acc_lev : nullptr;
-    A.vlev = have_vlev ? (const T *)P->acc_vlev : nullptr;
+    A.lev = have_lev ? P->lev_desc : nullptr;
+    A.vlev = have_vlev ? P->vlev_desc : nullptr;
+    A.J = P->J;
     A.parts = parts;
     A.sigma = (const TI *)sigma;
     A.mu = (const TI *)mu;

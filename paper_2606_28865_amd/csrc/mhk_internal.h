@@ -49,13 +49,15 @@ constexpr int TAB_STRIDE = 6;    // doubles per segment row: c_0..c_4 and c_5, c
                                  // c_7 (float) in an array of its own after the rows
                                  // (14 dwords: spreads segments over the banks)
 constexpr int TABF_NC = 8;       // FP32 path: coefficients per segment (degree 7)
-constexpr int TABF_STRIDE = 9;   // FP32 path: floats per segment
+constexpr int TABF_STRIDE = 12;  // FP32 path: floats per segment row (48 bytes: two aligned 16-byte loads, and
+                                 // neighbouring rows in different bank groups)
 constexpr int COL_NMAX = 8192;   // longest history-grid column transformed in LDS
 constexpr int COL_MAXPASS = 16;  // radix passes of a column transform
 constexpr int LV_CDIV = 4;       // level cells are R_j / LV_CDIV wide
 constexpr int MAXW = 16;         // maximum spreading window width
-constexpr int LV_BLOCK_MAX = 512;  // largest level-sum workgroup (targets); 256 or 512 per plan
 constexpr int LV_WAVE = 64;      // lanes per level-sum wavefront
+constexpr int LV_ITEMS = 16384;  // level-sum work items aimed at per level (four per wavefront slot of 256 CUs)
+constexpr int LV_PIECE_MIN = 128, LV_PIECE_MAX = 1024;   // sources per work item
 constexpr int LOCAL_GEO_N1 = 10; // doubles of local geometry per target, first-order plans
 constexpr int LOCAL_GEO_N2 = 27; // the same with the second-order terms (local_order = 2)
 
@@ -64,6 +66,46 @@ void set_error(const std::string &msg);
 template <typename T> struct Vec2;
 template <> struct Vec2<double> { typedef double2 type; };
 template <> struct Vec2<float> { typedef float2 type; };
+
+// Work items of the level sums: the candidate list of every target wavefront
+// cut into pieces of at most `piece` sources (whole batches of 64, of nearly
+// equal length), item_ofs[w] .. item_ofs[w + 1] those of wavefront w, in list
+// order; each item's sums go to its own part of `part`, [n][comp][batch][64],
+// and the local part adds them in item order.
+// length of a piece of a list of cnt sources cut into np: ceil(cnt / np)
+// rounded up to whole batches of 64 (never above the plan's piece, so that
+// no piece is empty)
+__host__ __device__ inline int level_piece(int cnt, int np)
+{
+    return np > 0 ? ((cnt + np - 1) / np + 63) / 64 * 64 : 0;
+}
+
+struct LevelItems {
+    int64_t n = 0;
+    int piece = 0;
+    int32_t *ofs = nullptr;                       // [n_wave + 1]
+    int32_t *wave = nullptr;                      // [n] the item's wavefront
+    int32_t *order = nullptr;                     // [n] items in decreasing length
+    void *part = nullptr;                         // per eval, plan precision
+};
+
+// What the level kernels need of one level, in device memory (one array per
+// plan for the layer levels, one for the volume levels).
+struct LevelDesc {
+    const int32_t *wave_ofs, *wave_src, *item_ofs, *item_wave, *item_order;
+    const double *sx, *sy;
+    const void *q, *tab;
+    void *part;
+    // child-node strengths (layer levels)
+    const int32_t *code;
+    const double *interp, *sw, *swx, *swy;
+    double pscale;        // sqrt(inv4d seg_inv): coordinates scaled by it give f = a seg_inv = |dx|^2
+    double d_scale;       // of the double-layer sums over scaled separations
+    double f_max;         // a_max seg_inv
+    int64_t n_src, n_items;
+    int nseg, nchild;
+    int blk0, qblk0;      // first workgroup of the level in the launch over all levels (sums, strengths)
+};
 
 struct Level {
     double delta_j = 0;          // delta / 4^(j-1): upper end of the level's time interval
@@ -86,10 +128,10 @@ struct Level {
     // of the wavefront's target bounding box, as one flat list of indices
     // (wave_src[wave_ofs[w] .. wave_ofs[w + 1]))
     int32_t *wave_ofs = nullptr;                  // [n_waves + 1]
-    int32_t *wave_order = nullptr;                // wavefronts in decreasing order of candidate work
     int32_t *wave_src = nullptr;                  // [n_cand]
     int64_t n_cand = 0;
-    int64_t n_wave = 0;                           // wavefronts of LV_WAVE targets (whole LV_BLOCK_MAX workgroups)
+    int64_t n_wave = 0;                           // wavefronts of LV_WAVE targets
+    LevelItems items;
     double *interp = nullptr;                     // [nchild][16][16] parent -> child values
     double *tab = nullptr;                        // [nseg][TAB_STRIDE]: K_j^S per segment (K_j^D from its derivative)
     float *tabf = nullptr;                        // FP32 path: [nseg][TABF_STRIDE]
@@ -226,8 +268,9 @@ struct VLevel {
     double *sx = nullptr, *sy = nullptr, *sw = nullptr;
     int32_t *tri = nullptr;
     int32_t *cell_start = nullptr;
-    int32_t *wave_ofs = nullptr, *wave_src = nullptr, *wave_order = nullptr;
+    int32_t *wave_ofs = nullptr, *wave_src = nullptr;
     int64_t n_wave = 0, n_cand = 0;
+    LevelItems items;
     void *q = nullptr;           // per eval: [batch][n_src], plan precision
 };
 }  // namespace mhk
@@ -258,7 +301,6 @@ struct mhk_plan {
     mhk::Local loc;
     mhk::FJets fj;
     mhk::VLevel vlev[mhk::MAXJ];                // volume levels (params.v_levels)
-    void *acc_vlev = nullptr;                    // [batch][n_out] their sums, sorted order
     double delta_v = 0;                          // time split of V's local part: delta, or delta* with volume levels
     std::vector<void *> allocs;                 // stream-ordered allocations on `stream`
     std::vector<std::vector<char>> stage;       // host bytes of uploads in flight during creation
@@ -269,11 +311,12 @@ struct mhk_plan {
     bool t_pending = false, t_levels = false, t_geom = false;   // stage events recorded, not read yet
     hipStream_t cap = nullptr;                  // capture stream of mhk_plan_capture
     // The level sums run on a second stream beside the history part (they
-    // share no data): they accumulate S and D into acc_lev, [2][batch][n_out],
-    // which the local part adds.
+    // share no data), into the items' parts, which the local part adds.
     hipStream_t side = nullptr;
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
-    void *acc_lev = nullptr;
+    mhk::LevelDesc *lev_desc = nullptr, *vlev_desc = nullptr;   // device, [J]
+    unsigned lev_grid = 0, vlev_grid = 0, levq_grid = 0;        // workgroups of the launches over all levels
+    size_t lev_lds = 0;                          // LDS bytes of the largest level table
     hipGraphExec_t gexec = nullptr;             // captured evaluation
 };
 
@@ -281,9 +324,12 @@ namespace mhk {
 
 // kernels launchers (defined in the .hip files); density and output pointers
 // are of the plan's precision
-hipError_t launch_level_densities(mhk_plan *P, hipStream_t st, int j, const void *sigma, const void *mu);
-// level j's sums into acc_lev on stream st: stored when init, else added
-hipError_t launch_level_sums(mhk_plan *P, hipStream_t st, int j, bool want_s, bool want_d, bool init);
+// child-node strengths of all levels, and the sums of all levels (vol: the
+// volume levels' single-layer sums), each into its items' parts
+hipError_t launch_level_densities(mhk_plan *P, hipStream_t st, const void *sigma, const void *mu);
+hipError_t launch_level_sums(mhk_plan *P, hipStream_t st, bool vol, bool want_s, bool want_d);
+// descriptors and launch shapes of the levels, once their buffers exist
+mhk_status level_descs(mhk_plan *P, bool vol, std::vector<LevelDesc> &d);
 hipError_t launch_panel_coeffs(mhk_plan *P, const void *sigma, const void *mu, const void *f_bnd);
 hipError_t launch_local_geom(mhk_plan *P, hipStream_t st);
 hipError_t launch_local(mhk_plan *P, int parts, const void *sigma, const void *mu,
@@ -304,8 +350,6 @@ hipError_t dev_vlevel_nodes(int64_t ntri, int j, const VRule &M, const double *v
                             double oy, double cell, int64_t ncx, int64_t ncy, double *sx, double *sy, double *sw,
                             int32_t *parent, int32_t *cell_start, hipStream_t st);
 hipError_t launch_vlevel_q(mhk_plan *P, hipStream_t st, int j, const void *f_vol);
-// level j's single-layer sums over the volume level nodes into acc_vlev
-hipError_t launch_level_sums_v(mhk_plan *P, hipStream_t st, int j, bool init);
 hipError_t dev_fj_setup(int64_t ntri, const double *vx, const double *vy, double *minv, double *tc, uint8_t *good,
                         hipStream_t st);
 hipError_t dev_fj_nearest(mhk_plan *P, const double *vx, const double *vy, const uint8_t *good, double ox,
@@ -352,14 +396,18 @@ hipError_t dev_child_nodes(int64_t n_src, int nch, const double *Tm, const doubl
                            double oy, double cell, int64_t ncx, int64_t ncy, double *sx, double *sy, double *sw,
                            double *swx, double *swy, int32_t *code, int32_t *cell_start, hipStream_t st);
 // Per-wavefront candidate lists of a level: counts, then (after the scan of
-// the counts into ofs) the lists and the wavefronts in decreasing work.
+// the counts into ofs) the lists.
 hipError_t dev_wave_counts(const double *tx, const double *ty, int64_t nout, int64_t nwave, double R, double R2,
                            double ox, double oy, double cell, int64_t ncx, int64_t ncy, const int32_t *start,
                            const double *sx, const double *sy, int32_t *cnt, hipStream_t st);
 hipError_t dev_wave_fill(const double *tx, const double *ty, int64_t nout, int64_t nwave, double R, double R2,
                          double ox, double oy, double cell, int64_t ncx, int64_t ncy, const int32_t *start,
-                         const double *sx, const double *sy, const int32_t *ofs, int32_t *out, int32_t *order,
-                         hipStream_t st);
+                         const double *sx, const double *sy, const int32_t *ofs, int32_t *out, hipStream_t st);
+// Work items of the lists: pieces per wavefront (then scanned into the item
+// offsets), and the items' wavefronts and order.
+hipError_t dev_item_counts(const int32_t *ofs, int64_t nwave, int piece, int32_t *cnt, hipStream_t st);
+hipError_t dev_item_fill(const int32_t *ofs, const int32_t *item_ofs, int64_t nwave, int64_t n, int piece,
+                         int32_t *wave, int32_t *order, hipStream_t st);
 // History sources by spreading block (SPB grid points; ntile blocks per row):
 // sorted arrays, window bounds into sup, list offsets into lofs, the blocks
 // with a list, and the lists.

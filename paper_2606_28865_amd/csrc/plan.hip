@@ -731,6 +731,37 @@ static mhk_status build_mask(mhk_plan *P, Host &H, StreamTmp &tmp, int8_t *rin)
 // the 16-point Gauss-Legendre nodes of each child interval, with geometry
 // interpolated by the parent's degree-15 polynomial, normals renormalised,
 // and weights w_GL,child * speed * 2^-j.
+// Pieces of a level's candidate lists (total sources in all lists).  A piece
+// is a whole number of 64-source batches, as long as the pieces of all levels
+// still fill the device several times over: about LV_ITEMS items per level
+// and density chunk, between LV_PIECE_MIN (a workgroup loads the level's
+// table once, some 30 loads per thread, which a piece should outweigh) and
+// LV_PIECE_MAX sources.
+static mhk_status build_items(mhk_plan *P, const int32_t *wave_ofs, int64_t nwave, int64_t total, int ncomp,
+                              LevelItems &I)
+{
+    const hipStream_t st = P->stream;
+    const int64_t chunks = (P->p.batch + P->p.lv_bch - 1) / P->p.lv_bch;
+    const int64_t want = (total * chunks / LV_ITEMS + 63) / 64 * 64;
+    I.piece = (int)std::min<int64_t>(LV_PIECE_MAX, std::max<int64_t>(LV_PIECE_MIN, want));
+    StreamTmp tmp(st);
+    int32_t *cnt = nullptr;
+    int64_t *tot = nullptr;
+    TRY(tmp.alloc(&cnt, nwave));
+    TRY(tmp.alloc(&tot, 1));
+    TRY(dalloc(P, &I.ofs, nwave + 1));
+    MHK_HIP(dev_item_counts(wave_ofs, nwave, I.piece, cnt, st));
+    MHK_HIP(dev_scan(cnt, I.ofs, nwave, tot, st));
+    TRY(tmp.fetch(&I.n, tot, 1));
+    TRY(dalloc(P, &I.wave, I.n));
+    TRY(dalloc(P, &I.order, I.n));
+    MHK_HIP(dev_item_fill(wave_ofs, I.ofs, nwave, I.n, I.piece, I.wave, I.order, st));
+    char *part = nullptr;
+    TRY(dalloc(P, &part, I.n * ncomp * (int64_t)P->p.batch * LV_WAVE * (int64_t)P->es));
+    I.part = part;
+    return MHK_OK;
+}
+
 mhk_status build_level(mhk_plan *P, Host &H, int j)
 {
     Level &L = P->lev[j - 1];
@@ -780,12 +811,10 @@ mhk_status build_level(mhk_plan *P, Host &H, int j)
                             ncx, ncy, L.sx, L.sy, L.sw, L.swx, L.swy, L.code, L.cell_start, st));
     // per wavefront of LV_WAVE targets: the sources within R_j of the
     // wavefront's target bounding box (flat lists, counted, scanned, then
-    // filled on the device); wavefronts past the last target get empty lists
+    // filled on the device)
     {
         const int64_t nout = P->nout;
-        // padded to whole workgroups of the larger tile shape, so that
-        // either one launches exactly nwave wavefronts
-        const int64_t nwave = ((nout + LV_BLOCK_MAX - 1) / LV_BLOCK_MAX) * (LV_BLOCK_MAX / LV_WAVE);
+        const int64_t nwave = (nout + LV_WAVE - 1) / LV_WAVE;
         L.n_wave = nwave;
         const double R = L.radius, R2 = R * R * (1.0 + 1e-9);
         int32_t *cnt = nullptr;
@@ -793,7 +822,6 @@ mhk_status build_level(mhk_plan *P, Host &H, int j)
         TRY(tmp.alloc(&cnt, nwave));
         TRY(tmp.alloc(&tot, 1));
         TRY(dalloc(P, &L.wave_ofs, nwave + 1));
-        TRY(dalloc(P, &L.wave_order, nwave));
         MHK_HIP(dev_wave_counts(P->tx, P->ty, nout, nwave, R, R2, L.ox, L.oy, L.cell, ncx, ncy, L.cell_start, L.sx,
                                 L.sy, cnt, st));
         MHK_HIP(dev_scan(cnt, L.wave_ofs, nwave, tot, st));
@@ -806,7 +834,8 @@ mhk_status build_level(mhk_plan *P, Host &H, int j)
         L.n_cand = total;
         TRY(dalloc(P, &L.wave_src, std::max<int64_t>(1, total)));
         MHK_HIP(dev_wave_fill(P->tx, P->ty, nout, nwave, R, R2, L.ox, L.oy, L.cell, ncx, ncy, L.cell_start, L.sx,
-                              L.sy, L.wave_ofs, L.wave_src, L.wave_order, st));
+                              L.sy, L.wave_ofs, L.wave_src, st));
+        TRY(build_items(P, L.wave_ofs, nwave, total, 2, L.items));
     }
     {
         char *q = nullptr;
@@ -1681,13 +1710,8 @@ mhk_status build_vlevels(mhk_plan *P, Host &H)
     double *vx = nullptr, *vy = nullptr;
     TRY(tmp.upload(&vx, v->x, nv));
     TRY(tmp.upload(&vy, v->y, nv));
-    {
-        char *a = nullptr;
-        TRY(dalloc(P, &a, (int64_t)P->p.batch * P->nout * (int64_t)P->es));
-        P->acc_vlev = a;
-    }
     const int64_t nout = P->nout;
-    const int64_t nwave = ((nout + LV_BLOCK_MAX - 1) / LV_BLOCK_MAX) * (LV_BLOCK_MAX / LV_WAVE);
+    const int64_t nwave = (nout + LV_WAVE - 1) / LV_WAVE;
     for (int j = 1; j <= P->J; ++j) {
         const Level &L = P->lev[j - 1];
         VLevel &V = P->vlev[j - 1];
@@ -1718,7 +1742,6 @@ mhk_status build_vlevels(mhk_plan *P, Host &H)
         TRY(tmp.alloc(&cnt, nwave));
         TRY(tmp.alloc(&tot, 1));
         TRY(dalloc(P, &V.wave_ofs, nwave + 1));
-        TRY(dalloc(P, &V.wave_order, nwave));
         MHK_HIP(dev_wave_counts(P->tx, P->ty, nout, nwave, R, R2, L.ox, L.oy, L.cell, L.ncx, L.ncy, V.cell_start,
                                 V.sx, V.sy, cnt, st));
         MHK_HIP(dev_scan(cnt, V.wave_ofs, nwave, tot, st));
@@ -1731,7 +1754,8 @@ mhk_status build_vlevels(mhk_plan *P, Host &H)
         V.n_cand = total;
         TRY(dalloc(P, &V.wave_src, std::max<int64_t>(1, total)));
         MHK_HIP(dev_wave_fill(P->tx, P->ty, nout, nwave, R, R2, L.ox, L.oy, L.cell, L.ncx, L.ncy, V.cell_start, V.sx,
-                              V.sy, V.wave_ofs, V.wave_src, V.wave_order, st));
+                              V.sy, V.wave_ofs, V.wave_src, st));
+        TRY(build_items(P, V.wave_ofs, nwave, total, 1, V.items));
     }
     MHK_HIP(hipStreamSynchronize(st));
     return MHK_OK;
@@ -1831,11 +1855,17 @@ mhk_status create(const mhk_params *params, const mhk_boundary *b, const mhk_vol
         char *a = nullptr;
         TRY(dalloc(P, &a, 3 * (int64_t)P->p.batch * P->nout * (int64_t)P->es));
         P->acc = a;
-        char *l = nullptr;
-        TRY(dalloc(P, &l, 2 * (int64_t)P->p.batch * P->nout * (int64_t)P->es));
-        P->acc_lev = l;
         if (P->p.in64) TRY(dalloc(P, &P->in32, (int64_t)P->p.batch * (2 * P->nb + P->nv)));
         TRY(dalloc(P, &P->lv_counter, 1));
+        std::vector<LevelDesc> d;
+        if (P->J > 0) {
+            TRY(level_descs(P, false, d));
+            TRY(upload(P, &P->lev_desc, d.data(), (int64_t)d.size()));
+        }
+        if (P->p.v_levels) {
+            TRY(level_descs(P, true, d));
+            TRY(upload(P, &P->vlev_desc, d.data(), (int64_t)d.size()));
+        }
     }
     for (auto &e : P->ev) MHK_HIP(hipEventCreate(&e));
     MHK_HIP(hipStreamCreateWithFlags(&P->side, hipStreamNonBlocking));
@@ -1916,10 +1946,10 @@ mhk_status mhk_plan_footprint(const mhk_params *params, const mhk_boundary *b, c
     int64_t s = 0;
     s += nb * 8 * 6;                          // boundary
     s += nout * (8 * 2 + 1 + 4);              // targets
-    s += 5 * B * nout * 8;                    // accumulators (history and levels)
-    for (int j = 1; j <= p.J; ++j) {          // levels
+    s += 3 * B * nout * 8;                    // history accumulators
+    for (int j = 1; j <= p.J; ++j) {          // levels: sources, and the items' parts (one item per wavefront)
         int64_t ns = nb << j;
-        s += ns * (8 * 5 + 4) + 3 * B * ns * 8;
+        s += ns * (8 * 5 + 4) + 3 * B * ns * 8 + 2 * B * nout * 8;
     }
     s += nb * (8 * 3 + 4) + 3 * B * nb * 8;   // local
     s += nout * ((p.local_order >= 2 ? LOCAL_GEO_N2 : LOCAL_GEO_N1) * 8 + 4 + 1);   // local geometry per target
@@ -2080,7 +2110,7 @@ mhk_status enqueue(mhk_plan *P, int parts, const void *sigma, const void *mu, co
     // The level sums share no data with the history part: they run on the
     // side stream, forked from and joined back into the plan's stream, so the
     // two overlap (the level sums are bound by LDS and FP64 issue, the FFTs by
-    // memory).  They write acc_lev; the local part adds it.
+    // memory).  They write the items' parts; the local part adds them.
     const bool levels = (parts & MHK_PART_LEVELS) && (ws || wd) && P->J > 0;
     // the volume potential's levels (v_levels) run there too
     const bool vlevels = (parts & MHK_PART_LEVELS) && wv && P->p.v_levels;
@@ -2102,16 +2132,14 @@ mhk_status enqueue(mhk_plan *P, int parts, const void *sigma, const void *mu, co
             MHK_HIP(launch_local_geom(P, P->side));
             if (P->timing) MHK_HIP(hipEventRecord(P->ev[9], P->side));
         }
-        if (levels)
-            for (int j = 1; j <= P->J; ++j) {
-                MHK_HIP(launch_level_densities(P, P->side, j, ws ? sig_h : nullptr, wd ? mu_h : nullptr));
-                MHK_HIP(launch_level_sums(P, P->side, j, ws, wd, j == 1));
-            }
-        if (vlevels)
-            for (int j = 1; j <= P->J; ++j) {
-                MHK_HIP(launch_vlevel_q(P, P->side, j, f_vol));
-                MHK_HIP(launch_level_sums_v(P, P->side, j, j == 1));
-            }
+        if (levels) {
+            MHK_HIP(launch_level_densities(P, P->side, ws ? sig_h : nullptr, wd ? mu_h : nullptr));
+            MHK_HIP(launch_level_sums(P, P->side, false, ws, wd));
+        }
+        if (vlevels) {
+            for (int j = 1; j <= P->J; ++j) MHK_HIP(launch_vlevel_q(P, P->side, j, f_vol));
+            MHK_HIP(launch_level_sums(P, P->side, true, true, false));
+        }
         if (P->timing) MHK_HIP(hipEventRecord(P->ev[6], P->side));
         MHK_HIP(hipEventRecord(P->join_ev, P->side));
     }
