@@ -6,7 +6,7 @@
 //    SoA x/y (FP64), inside flag and original output index;
 //  * boundary: the caller's panel-contiguous SoA arrays, plus per-panel
 //    Legendre coefficients of x, y and kappa for the closest-point search;
-//  * dyadic level j: the N_B 2^j child nodes of the bisected panels, sorted
+//  * dyadic level j: the child nodes of the bisected panels (at most N_B 2^j), sorted
 //    row-major by square cells of side R_j/4, as SoA x/y/w nx/w ny/w, with a
 //    code giving (panel, child, node) for the per-eval interpolation of the
 //    densities, per-eval strengths q_S = w sigma, q_Dx = w nu_x mu,
@@ -114,8 +114,8 @@ struct Level {
     double radius = 0;           // sqrt(4 delta_j a_max)
     double seg_inv = 0;          // segments per unit of a
     int nseg = 0;
-    int nchild = 0;              // 2^j
-    int64_t n_src = 0;           // N_B 2^j
+    int nchild = 0;              // child panels per panel, at most 2^j
+    int64_t n_src = 0;           // N_B nchild
     int ncx = 0, ncy = 0;
     double cell = 0, ox = 0, oy = 0;
     // device

@@ -475,6 +475,7 @@ struct Host {
     std::vector<double> gl_t, gl_w;
     std::vector<long double> bary;
     std::vector<int64_t> prev, next;
+    double panel_half = 0;             // largest half-length of a panel (speed in the panel parameter)
     double xmin, xmax, ymin, ymax;
     // all targets (off-surface then boundary), in output order
     std::vector<double> tx, ty;
@@ -568,6 +569,7 @@ void host_common(Host &H)
         H.bary[i] = 1 / pr;
     }
     const mhk_boundary *b = H.b;
+    for (int64_t i = 0; i < b->n_panels * NGL; ++i) H.panel_half = std::max(H.panel_half, b->w[i] / H.gl_w[i % NGL]);
     H.prev.assign(b->n_panels, 0);
     H.next.assign(b->n_panels, 0);
     for (int c = 0; c < b->n_curves; ++c) {
@@ -762,13 +764,35 @@ static mhk_status build_items(mhk_plan *P, const int32_t *wave_ofs, int64_t nwav
     return MHK_OK;
 }
 
+// Bisections of every panel at level j: at most j (Section 4.2), fewer where
+// the 16-node rule integrates level j's kernel on longer panels just as well.
+// The rule is exact to degree 31 and the densities are polynomials of degree
+// 15 on a panel, so the error is at most that of the best approximation of
+// the kernel by degree 16 along the panel, whatever the nodal values: with h
+// the panel's half-length in units of sqrt(delta_j), the Chebyshev tails
+// beyond degree 16 of K_j^S and of (x - y).nu K_j^D, largest over the target's
+// position, are 1.4e-12, 7.1e-12, 1.3e-10, 1.4e-9, 1.1e-8 and 2.9e-7 (D at
+// most 1.4 times as much) of the kernels' maxima at h = 0.9, 1, 1.2, 1.4, 1.6
+// and 2, below 1.5e-11 h^18 from h = 0.85 on; a child panel is as long as
+// keeps that below tol/100.  Half the nodes are half the work of a level: whole
+// evaluations of S and D with 65536 boundary nodes (h = 0.15 after j
+// bisections, tol 1e-8: j - 2 are taken) went from 1386 to 800 us, of 16
+// densities with 32768 (h = 0.26, tol 1e-10: j - 1) from 19.3 to 13.6 ms.
+static int level_bisections(const mhk_plan *P, const Host &H, int j)
+{
+    const double hmax = pow(P->p.tol * 1e-2 / 1.5e-11, 1.0 / 18.0) * sqrt(P->delta / pow(4.0, j - 1));
+    int m = j;
+    while (m > 0 && H.panel_half / (double)(1 << (m - 1)) <= hmax) --m;
+    return m;
+}
+
 mhk_status build_level(mhk_plan *P, Host &H, int j)
 {
     Level &L = P->lev[j - 1];
     const mhk_boundary *b = H.b;
     const int64_t npan = b->n_panels;
     const hipStream_t st = P->stream;
-    L.nchild = 1 << j;
+    L.nchild = 1 << level_bisections(P, H, j);
     L.n_src = npan * L.nchild * NGL;
     L.delta_j = P->delta / pow(4.0, j - 1);
     L.inv4d = 1.0 / (4.0 * L.delta_j);
