@@ -567,6 +567,7 @@ struct RowArgs {
     int m0, m1;                    // forward: complex points [m0, m1) of a row can be nonzero;
                                    // inverse: complex points [m0, m1) are written back
     int B, nblk;                   // densities; blocks per grid row
+    int8_t grp[4];                 // field groups of the launch: forward S, V, D_x, D_y sources, inverse S, V, D
     const uint8_t *vflag, *bflag;  // forward: blocks holding volume / boundary sources; the others are zero, unwritten
     int ncol;                      // half-spectrum entries k < ncol can be nonzero after the multiplier
     int npass;
@@ -582,14 +583,15 @@ __global__ void __launch_bounds__(RT) k_rows(RowArgs<T> A)
     extern __shared__ double lds_row[];
     T2 *buf = reinterpret_cast<T2 *>(lds_row);
     const int n = (int)A.n, h = n / 2;
-    const size_t slot = blockIdx.x / A.nrow, row = A.r0 + blockIdx.x % A.nrow;
+    const int gb = (int)(blockIdx.x / A.nrow), grp = A.grp[gb / A.B];
+    const size_t slot = (size_t)grp * A.B + gb % A.B, row = A.r0 + blockIdx.x % A.nrow;
     T2 *c = reinterpret_cast<T2 *>(A.grid + (slot * (size_t)n + row) * (size_t)(n + 2));   // h + 1 complex
     const int tid = threadIdx.x;
     if (!INV) {
         // the row is zero outside the blocks of the sources' windows
         const T2 zero = c2<T2>((T)0, (T)0);
         const uint8_t *__restrict__ flag =
-            (slot / A.B == 1 ? A.vflag : A.bflag) + (row / SPB) * (size_t)A.nblk;
+            (grp == 1 ? A.vflag : A.bflag) + (row / SPB) * (size_t)A.nblk;
         int any = 0;
         for (int m = tid; m < h; m += RT) {
             const bool on = m >= A.m0 && m < A.m1 && flag[2 * m / SPB];
@@ -633,6 +635,7 @@ template <typename T>
 struct ColArgs {
     int64_t n, field;
     int B, ncol, npass;
+    int8_t grp[3];         // outputs of the launch: 0 S, 1 V, 2 D
     int iy0, iy1;          // rows [iy0, iy1) of the input columns can be nonzero (the sources' windows)
     int oy0, oy1;          // rows [oy0, oy1) of the output columns are written (the targets' windows)
     int8_t radix[COL_MAXPASS];
@@ -660,7 +663,7 @@ __global__ void __launch_bounds__(CT) k_columns(ColArgs<T> A)
     const int per = (A.ncol + 7) / 8;
     const int lx = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
     if (lx >= A.ncol) return;
-    const int b = blockIdx.y, grp = blockIdx.z;
+    const int b = blockIdx.y, grp = A.grp[blockIdx.z];
     const size_t fs = (size_t)A.B * (A.field / 2);              // complex values per slot
     T2 *base = reinterpret_cast<T2 *>(A.grid) + (size_t)b * (A.field / 2) + lx;
     T2 *out = base + (size_t)grp * fs;
@@ -1000,10 +1003,16 @@ static hipError_t multiply_t(mhk_plan *P)
 }
 
 template <typename T>
-static hipError_t columns_t(mhk_plan *P)
+static hipError_t columns_t(mhk_plan *P, bool want_s, bool want_d, bool want_v)
 {
     const History &G = P->hist;
     ColArgs<T> A;
+    // the D spectra take two transforms: first, so that the long workgroups start first
+    int ng = 0;
+    if (want_d) A.grp[ng++] = 2;
+    if (want_s) A.grp[ng++] = 0;
+    if (want_v) A.grp[ng++] = 1;
+    if (ng == 0) return hipSuccess;
     A.n = G.n;
     A.field = G.field;
     A.B = P->bat;
@@ -1027,7 +1036,7 @@ static hipError_t columns_t(mhk_plan *P)
     const void *fn = G.n <= COL_NMAX / 2 ? (const void *)k_columns<T, COL_NMAX / 2> : (const void *)k_columns<T, COL_NMAX>;
     if (lds > 64 * 1024) (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (G.ncol == 0) return hipSuccess;     // the multiplier is zero everywhere
-    dim3 grid((unsigned)(((G.ncol + 7) / 8) * 8), (unsigned)P->bat, 3u);
+    dim3 grid((unsigned)(((G.ncol + 7) / 8) * 8), (unsigned)P->bat, (unsigned)ng);
     if (G.n <= COL_NMAX / 2)
         hipLaunchKernelGGL((k_columns<T, COL_NMAX / 2>), grid, dim3(CT), lds, P->stream, A);
     else
@@ -1036,10 +1045,15 @@ static hipError_t columns_t(mhk_plan *P)
 }
 
 template <bool INV, typename T>
-static hipError_t rows_t(mhk_plan *P)
+static hipError_t rows_t(mhk_plan *P, bool want_s, bool want_d, bool want_v)
 {
     const History &G = P->hist;
     RowArgs<T> A;
+    int ng = 0;
+    if (want_s) A.grp[ng++] = 0;
+    if (want_v) A.grp[ng++] = 1;
+    if (want_d) A.grp[ng++] = 2;
+    if (want_d && !INV) A.grp[ng++] = 3;
     A.n = G.n;
     A.ncol = G.ncol;
     A.npass = G.rnpass;
@@ -1057,7 +1071,7 @@ static hipError_t rows_t(mhk_plan *P)
     A.vflag = G.vflag;
     A.bflag = G.bflag;
     const size_t lds = sizeof(typename Vec2<T>::type) * (size_t)(G.n / 2);
-    const int64_t rows = (INV ? 3 : 4) * (int64_t)P->bat * A.nrow;
+    const int64_t rows = ng * (int64_t)P->bat * A.nrow;
     if (rows <= 0) return hipSuccess;
     if (G.n <= COL_NMAX / 2)
         hipLaunchKernelGGL((k_rows<INV, T, COL_NMAX / 2>), dim3((unsigned)rows), dim3(RT), lds, P->stream, A);
@@ -1066,15 +1080,17 @@ static hipError_t rows_t(mhk_plan *P)
     return hipGetLastError();
 }
 
-hipError_t launch_rows(mhk_plan *P, bool inverse)
+// only the fields of the densities given are transformed
+hipError_t launch_rows(mhk_plan *P, bool inverse, bool s, bool d, bool v)
 {
-    if (P->p.prec == MHK_FP64) return inverse ? rows_t<true, double>(P) : rows_t<false, double>(P);
-    return inverse ? rows_t<true, float>(P) : rows_t<false, float>(P);
+    if (P->p.prec == MHK_FP64)
+        return inverse ? rows_t<true, double>(P, s, d, v) : rows_t<false, double>(P, s, d, v);
+    return inverse ? rows_t<true, float>(P, s, d, v) : rows_t<false, float>(P, s, d, v);
 }
 
-hipError_t launch_columns(mhk_plan *P)
+hipError_t launch_columns(mhk_plan *P, bool s, bool d, bool v)
 {
-    return P->p.prec == MHK_FP64 ? columns_t<double>(P) : columns_t<float>(P);
+    return P->p.prec == MHK_FP64 ? columns_t<double>(P, s, d, v) : columns_t<float>(P, s, d, v);
 }
 
 hipError_t launch_multiply(mhk_plan *P)

@@ -337,8 +337,8 @@ hipError_t launch_local(mhk_plan *P, int parts, const void *sigma, const void *m
                         bool have_vlev);
 hipError_t launch_spread(mhk_plan *P, const void *sigma, const void *mu, const void *f_vol);
 hipError_t launch_multiply(mhk_plan *P);
-hipError_t launch_columns(mhk_plan *P);
-hipError_t launch_rows(mhk_plan *P, bool inverse);
+hipError_t launch_columns(mhk_plan *P, bool want_s, bool want_d, bool want_v);
+hipError_t launch_rows(mhk_plan *P, bool inverse, bool want_s, bool want_d, bool want_v);
 hipError_t launch_interp(mhk_plan *P, bool want_s, bool want_d, bool want_v);
 hipError_t launch_fill(mhk_plan *P, void *p, int64_t n);
 hipError_t launch_fill_int(int *p, int64_t n, hipStream_t st);   // zero n ints on st (a kernel, graph-safe)

@@ -2179,14 +2179,14 @@ mhk_status enqueue(mhk_plan *P, int parts, const void *sigma, const void *mu, co
         // multiplier, inverse row transforms; else rocFFT 2D transforms
         // around the multiplier
         if (P->hist.colpath)
-            MHK_HIP(launch_rows(P, false));
+            MHK_HIP(launch_rows(P, false, ws, wd, wv));
         else
             MHK_FFT(rocfft_execute(P->hist.fwd, buf, nullptr, P->hist.exec));
         if (P->timing) MHK_HIP(hipEventRecord(P->ev[2], st));
-        MHK_HIP(P->hist.colpath ? launch_columns(P) : launch_multiply(P));
+        MHK_HIP(P->hist.colpath ? launch_columns(P, ws, wd, wv) : launch_multiply(P));
         if (P->timing) MHK_HIP(hipEventRecord(P->ev[3], st));
         if (P->hist.colpath)
-            MHK_HIP(launch_rows(P, true));
+            MHK_HIP(launch_rows(P, true, ws, wd, wv));
         else
             MHK_FFT(rocfft_execute(P->hist.inv, buf, nullptr, P->hist.exec));
         if (P->timing) MHK_HIP(hipEventRecord(P->ev[4], st));
