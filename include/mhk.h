@@ -299,7 +299,8 @@ typedef struct mhk_nystrom mhk_nystrom;
 typedef struct {
     int64_t n;            /* N_B                                                    */
     double alpha;
-    int64_t device_bytes; /* K (8 N_B^2 bytes) plus GMRES and solve workspace      */
+    int64_t device_bytes; /* K (4 N_B^2 bytes: the triangle of its symmetric factor)
+                             plus GMRES and solve workspace                         */
     double ms_assemble;   /* time to build K on the device                         */
 } mhk_nys_info;
 
@@ -311,7 +312,8 @@ typedef struct {
 } mhk_solve_info;
 
 /* Assemble K on the device for the boundary (host arrays as for
- * mhk_plan_create; N_B <= 2^20, K needs 8 N_B^2 bytes of device memory).
+ * mhk_plan_create; N_B <= 2^20).  K_ij = S_ij w_j (x_i - x_j).nu_j with S
+ * symmetric, so S's lower triangle is kept: 4 N_B^2 bytes of device memory.
  * Later calls run on the given stream (NULL: default stream).  *out is NULL
  * on error (MHK_ENOMEM when K does not fit). */
 mhk_status mhk_nystrom_create(double alpha, const mhk_boundary *boundary, void *hip_stream, mhk_nystrom **out);

@@ -3,10 +3,13 @@
 // GMRES, and the Dirichlet and Neumann solves that combine them with the
 // potential evaluation of a plan.
 //
-// Layout: K is N_B x ld row-major FP64 (ld = N_B rounded up to even, the pad
-// column zero), 2 GiB at N_B = 16384 and 34 GiB at 65536, resident in HBM for
-// the life of the object.  The product y = (shift I + K) x streams K once per
-// call (HBM bound: 8 N_B^2 bytes); every other GMRES step is O(N_B m).
+// Layout: off the diagonal K_ij = S_ij w_j (x_i - x_j).nu_j with S_ij = alpha
+// K_1(alpha r)/(2 pi r) symmetric, so only S's lower triangle is kept, as FP64
+// tiles of 64 x 128 (1.1 GB at N_B = 16384, 17 GB at 65536), resident in HBM for
+// the life of the object, with the nodes' geometry and the diagonal of K.  The
+// product y = (shift I + K) x streams the tiles once per call, each element
+// serving rows i and j (HBM bound: 4 N_B^2 bytes); every other GMRES step is
+// O(N_B m).
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -15,11 +18,25 @@
 
 #include "mhk_internal.h"
 
+// partial sums of one product in flight: the object's own calls
+// (mhk_nystrom_apply), its solves and the allocation-free solves may run on
+// different streams, so each has its own
+struct NysPart {
+    double *cp = nullptr;       // [tiles][128] column sums
+    double *rp = nullptr;       // [items][64] row sums
+};
+
 struct mhk_nystrom {
-    int64_t n = 0, ld = 0;
+    int64_t n = 0, np = 0;      // nodes; padded to whole tile columns
     double alpha = 0;
     hipStream_t stream = nullptr;
-    double *K = nullptr;
+    double *S = nullptr;        // [tiles][64][128]
+    double *geo = nullptr;      // [6][np]: x, y, nu_x, nu_y, w, diagonal of K
+    int64_t nstrip = 0, ntile = 0, nitem = 0;
+    int run = 1;                // tiles per work item
+    int2 *item = nullptr;       // [nitem] strip and first tile column
+    int32_t *item_ofs = nullptr;  // [nstrip + 1] items of each strip
+    NysPart prod[3];            // NYS_APPLY, NYS_SOLVE, NYS_NOALLOC
     // GMRES workspace (grown on demand)
     int m_cap = 0;
     int nblk = 0;
@@ -35,7 +52,11 @@ struct mhk_nystrom {
     int64_t work_n = 0;
     int64_t ws_bytes = 0;       // GMRES workspace
     double ms_assemble = 0;
-    int64_t bytes() const { return (int64_t)sizeof(double) * (n * ld + 2 * work_n) + ws_bytes; }
+    int64_t bytes() const
+    {
+        return (int64_t)sizeof(double) * (ntile * 64 * 128 + 6 * np + 3 * (ntile * 128 + nitem * 64) + 2 * work_n) +
+               nitem * 8 + (nstrip + 1) * 4 + ws_bytes;
+    }
 };
 
 namespace mhk {
@@ -56,7 +77,11 @@ namespace mhk {
     } while (0)
 
 constexpr int BT = 256;         // threads per block of the vector kernels
-constexpr int GV_ROWS = 8;      // rows of K per block of the product
+constexpr int TR = 64, TC = 128;   // rows and columns of a tile
+enum { NYS_APPLY, NYS_SOLVE, NYS_NOALLOC };
+
+// tiles of the strips before strip I (strip k holds k/2 + 1 tile columns)
+__host__ __device__ inline int64_t tile_ofs(int64_t I) { return I > 0 ? I + (I - 1) * (I - 1) / 4 : 0; }
 
 // z e^z K_1(z) as a table of polynomials: eight segments of equal width per
 // binade of z from 2^-52 to 2^10 (below, the function is 1 to rounding; above,
@@ -141,33 +166,38 @@ __device__ inline double k1_scaled_dev(const double *tab, double z)
     return p;
 }
 
-// K_ij = w_j alpha/(2 pi) K_1(alpha r) (x_i - x_j).nu_j / r for i != j and
-// K_ii = -w_i kappa_i/(4 pi) (Section 3.2, with the diagonal limit of eq.
-// (dlp_diag_limit)).  NYS_ROWS rows per block, columns along threads.
-constexpr int NYS_ROWS = 16;
-__global__ void __launch_bounds__(BT) k_nys_assemble(int64_t n, int64_t ld, double alpha, const double *x,
-                                                     const double *y, const double *nx, const double *ny,
-                                                     const double *w, const double *kap, const double *tab, double *K)
+// The tiles of S_ij = alpha K_1(alpha r)/(2 pi r), i > j (zero elsewhere and in
+// the padding): K_ij = w_j S_ij (x_i - x_j).nu_j for i != j (Section 3.2; K_ii =
+// -w_i kappa_i/(4 pi), the diagonal limit of eq. (dlp_diag_limit), is kept
+// apart).  One workgroup per work item, a row per wavefront at a time, two
+// columns per lane.
+__global__ void __launch_bounds__(BT) k_nys_assemble(int64_t n, int64_t np, double alpha,
+                                                     const double *__restrict__ geo, const double *__restrict__ tab,
+                                                     const int2 *__restrict__ item, int run, double *__restrict__ S)
 {
     __shared__ double k1[K1_SEG * K1_NC];
     for (int t = threadIdx.x; t < K1_SEG * K1_NC; t += BT) k1[t] = tab[t];
     __syncthreads();
-    const int64_t j = (int64_t)blockIdx.y * BT + threadIdx.x;
-    if (j >= ld) return;
-    const bool col = j < n;
-    const double xj = col ? x[j] : 0.0, yj = col ? y[j] : 0.0, nxj = col ? nx[j] : 0.0, nyj = col ? ny[j] : 0.0;
-    const double wj = col ? w[j] / (2.0 * M_PI) : 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * NYS_ROWS; i < min(n, (int64_t)(blockIdx.x + 1) * NYS_ROWS); ++i) {
-        double v = 0.0;
-        if (col) {
-            if (j == i) {
-                v = -w[i] * kap[i] / (4.0 * M_PI);
-            } else {
-                const double dx = x[i] - xj, dy = y[i] - yj, r2 = dx * dx + dy * dy, z = alpha * sqrt(r2);
-                v = wj * (k1_scaled_dev(k1, z) * exp(-z)) * (dx * nxj + dy * nyj) / r2;
-            }
+    const int64_t I = item[blockIdx.x].x;
+    const int c0 = item[blockIdx.x].y, c1 = min(c0 + run, (int)(I / 2 + 1));
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+    const double *x = geo, *y = geo + np;
+    for (int c = c0; c < c1; ++c) {
+        const int64_t j = (int64_t)c * TC + 2 * lane;
+        const double2 xj = *reinterpret_cast<const double2 *>(x + j), yj = *reinterpret_cast<const double2 *>(y + j);
+        double *tile = S + (tile_ofs(I) + c) * (TR * TC) + 2 * lane;
+        for (int r = wave; r < TR; r += BT / 64) {
+            const int64_t i = I * TR + r;
+            auto elem = [&](double xv, double yv, int64_t jj) -> double {
+                if (jj >= i || i >= n) return 0.0;
+                const double dx = x[i] - xv, dy = y[i] - yv, r2 = dx * dx + dy * dy, z = alpha * sqrt(r2);
+                return k1_scaled_dev(k1, z) * exp(-z) / (2.0 * M_PI * r2);
+            };
+            double2 v;
+            v.x = elem(xj.x, yj.x, j);
+            v.y = elem(xj.y, yj.y, j + 1);
+            *reinterpret_cast<double2 *>(tile + r * TC) = v;
         }
-        K[i * ld + j] = v;
     }
 }
 
@@ -178,39 +208,142 @@ __device__ inline double wave_sum(double v)
     return v;
 }
 
-// y = shift x + K x; GV_ROWS rows per block, column pairs along the threads
-// (rows are 16-byte aligned since ld is even); fixed reduction order.
-__global__ void __launch_bounds__(BT) k_gemv(int64_t n, int64_t ld, const double *__restrict__ K, double shift,
-                                             const double *__restrict__ x, double *__restrict__ y)
+// Products of the tiles of one work item (a run of tile columns of one strip)
+// with x.  A wavefront takes 16 rows of the strip, two columns per lane: every
+// element adds to its row's sum (in registers over the run, reduced over the
+// lanes at its end) and to its column's sum (reduced over the four wavefronts
+// per tile).  Bound by HBM: 16384 nodes 0.206 ms (5.2 TB/s of tiles) against
+// 0.356 with the dense matrix (6.0 TB/s), 8192 nodes 57 against 102 us; the ten
+// FP64 instructions per element are a fifth of that.
+__global__ void __launch_bounds__(BT, 3) k_symv(int64_t n, int64_t np, const double *__restrict__ S,
+                                             const double *__restrict__ geo, const int2 *__restrict__ item, int run,
+                                             const double *__restrict__ x, double *__restrict__ cp,
+                                             double *__restrict__ rp)
 {
-    const int64_t r0 = (int64_t)blockIdx.x * GV_ROWS;
-    const int tid = threadIdx.x;
-    double acc[GV_ROWS];
-#pragma unroll
-    for (int r = 0; r < GV_ROWS; ++r) acc[r] = 0.0;
-    for (int64_t c = 2 * (int64_t)tid; c < n; c += 2 * BT) {
-        const double x0 = x[c], x1 = (c + 1 < n) ? x[c + 1] : 0.0;
-#pragma unroll
-        for (int r = 0; r < GV_ROWS; ++r) {
-            if (r0 + r < n) {
-                const double2 k = *reinterpret_cast<const double2 *>(K + (r0 + r) * ld + c);
-                acc[r] = fma(k.x, x0, acc[r]);
-                acc[r] = fma(k.y, x1, acc[r]);
-            }
-        }
-    }
-    __shared__ double red[GV_ROWS][BT / 64];
-#pragma unroll
-    for (int r = 0; r < GV_ROWS; ++r) {
-        const double s = wave_sum(acc[r]);
-        if ((tid & 63) == 0) red[r][tid >> 6] = s;
+    constexpr int RW = TR / (BT / 64);
+    __shared__ double col[2][BT / 64][TC];
+    __shared__ double row[TR][6];              // x, y, nu, w x of the strip's rows (broadcast reads)
+    const int64_t I = item[blockIdx.x].x;
+    const int c0 = item[blockIdx.x].y, c1 = min(c0 + run, (int)(I / 2 + 1));
+    const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const double *__restrict__ gx = geo, *__restrict__ gy = geo + np, *__restrict__ gnx = geo + 2 * np,
+                               *__restrict__ gny = geo + 3 * np, *__restrict__ gw = geo + 4 * np;
+    if (tid < TR) {
+        const int64_t i = I * TR + tid;
+        row[tid][0] = gx[i];
+        row[tid][1] = gy[i];
+        row[tid][2] = gnx[i];
+        row[tid][3] = gny[i];
+        row[tid][4] = i < n ? gw[i] * x[i] : 0.0;
     }
     __syncthreads();
-    if (tid < GV_ROWS && r0 + tid < n) {
-        double s = 0.0;
+    double acc[RW];
 #pragma unroll
-        for (int q = 0; q < BT / 64; ++q) s += red[tid][q];
-        y[r0 + tid] = fma(shift, x[r0 + tid], s);
+    for (int r = 0; r < RW; ++r) acc[r] = 0.0;
+    // loads run half a tile ahead: the second half of the wavefront's rows while
+    // the first is summed, the next tile's first half and columns while the
+    // second is
+    struct Cols {
+        double2 x, y, nx, ny, w;
+    };
+    auto cols = [&](int c, Cols &q) {
+        const int64_t j = (int64_t)c * TC + 2 * lane;
+        auto two = [&](const double *g) { return *reinterpret_cast<const double2 *>(g + j); };
+        q.x = two(gx);
+        q.y = two(gy);
+        q.nx = two(gnx);
+        q.ny = two(gny);
+        q.w = two(gw);
+        // nodes come in panels of 16, so a lane's two columns are both nodes or both padding
+        q.w.x *= j < n ? x[j] : 0.0;
+        q.w.y *= j < n ? x[j + 1] : 0.0;
+    };
+    const double *tile = S + (tile_ofs(I) + c0) * (TR * TC) + wave * RW * TC + 2 * lane;
+    auto half = [&](const double *p, double2 *s) {
+#pragma unroll
+        for (int r = 0; r < RW / 2; ++r) s[r] = *reinterpret_cast<const double2 *>(p + r * TC);
+    };
+    double2 s[RW / 2], s2[RW / 2];
+    Cols q;
+    half(tile, s);
+    cols(c0, q);
+    for (int c = c0; c < c1; ++c, tile += TR * TC) {
+        half(tile + RW / 2 * TC, s2);
+        double cs0 = 0.0, cs1 = 0.0;
+        auto one = [&](int r, double2 sv) {
+            const double *g = row[wave * RW + r];
+            const double2 p = *reinterpret_cast<const double2 *>(g), nu = *reinterpret_cast<const double2 *>(g + 2);
+            const double wi = g[4];
+            const double dx0 = p.x - q.x.x, dy0 = p.y - q.y.x, dx1 = p.x - q.x.y, dy1 = p.y - q.y.y;
+            acc[r] = fma(sv.x * fma(dx0, q.nx.x, dy0 * q.ny.x), q.w.x, acc[r]);
+            acc[r] = fma(sv.y * fma(dx1, q.nx.y, dy1 * q.ny.y), q.w.y, acc[r]);
+            cs0 = fma(sv.x * fma(dx0, nu.x, dy0 * nu.y), wi, cs0);
+            cs1 = fma(sv.y * fma(dx1, nu.x, dy1 * nu.y), wi, cs1);
+            // the sums are formed here: left to itself the compiler moves them
+            // past the barrier below, with their operands in scratch
+            asm volatile("" : "+v"(acc[r]), "+v"(cs0), "+v"(cs1));
+        };
+#pragma unroll
+        for (int r = 0; r < RW / 2; ++r) one(r, s[r]);
+        // (the last tile once more at the end of the run)
+        const int cn = min(c + 1, c1 - 1);
+        half(tile + (cn - c) * (TR * TC), s);
+#pragma unroll
+        for (int r = 0; r < RW / 2; ++r) one(RW / 2 + r, s2[r]);
+        cols(cn, q);
+        double(*cl)[TC] = col[c & 1];
+        cl[wave][2 * lane] = cs0;
+        cl[wave][2 * lane + 1] = cs1;
+        __syncthreads();
+        // the other buffer is written next: its readers passed the barrier above
+        if (tid < TC)
+            cp[(tile_ofs(I) + c) * TC + tid] = -(((cl[0][tid] + cl[1][tid]) + cl[2][tid]) + cl[3][tid]);
+    }
+    // the 16 rows' sums over the lanes, halving the rows a lane holds at each
+    // step: 17 exchanges instead of 96; the row is bits 5..2 of the lane
+    static_assert(RW == 16, "rows per wavefront");
+#pragma unroll
+    for (int h = RW / 2, m = 32; h >= 1; h /= 2, m /= 2) {
+        const bool up = (lane & m) != 0;
+#pragma unroll
+        for (int r = 0; r < h; ++r) {
+            const double keep = up ? acc[r + h] : acc[r], give = up ? acc[r] : acc[r + h];
+            acc[r] = keep + __shfl_xor(give, m, 64);
+        }
+    }
+    double v = acc[0] + __shfl_xor(acc[0], 2, 64);
+    v += __shfl_xor(v, 1, 64);
+    if ((lane & 3) == 0) rp[(int64_t)blockIdx.x * TR + wave * RW + lane / 4] = v;
+}
+
+// y_i = (shift + K_ii) x_i + the row sums of its strip's items + the column
+// sums of the tiles below it, in a fixed order: 128 outputs per workgroup, the
+// tiles dealt to eight groups of threads
+constexpr int SG = 8;
+__global__ void __launch_bounds__(TC * SG) k_symv_sum(int64_t n, int64_t np, int64_t nstrip,
+                                                      const double *__restrict__ geo,
+                                                      const int32_t *__restrict__ item_ofs,
+                                                      const double *__restrict__ cp, const double *__restrict__ rp,
+                                                      double shift, const double *__restrict__ x,
+                                                      double *__restrict__ y)
+{
+    __shared__ double sh[SG][TC];
+    const int cc = threadIdx.x % TC, g = threadIdx.x / TC;
+    const int64_t J = blockIdx.x, i = J * TC + cc;
+    double s = 0.0;
+#pragma unroll 4
+    for (int64_t I = 2 * J + g; I < nstrip; I += SG) s += cp[(tile_ofs(I) + J) * TC + cc];
+    const int64_t strip = i / TR;
+    if (strip < nstrip)
+        for (int it = item_ofs[strip] + g; it < item_ofs[strip + 1]; it += SG) s += rp[(int64_t)it * TR + i % TR];
+    sh[g][cc] = s;
+    __syncthreads();
+    if (g == 0 && i < n) {
+        double v = sh[0][cc];
+#pragma unroll
+        for (int q = 1; q < SG; ++q) v += sh[q][cc];
+        const double xi = x[i];
+        y[i] = fma(shift, xi, fma(geo[5 * np + i], xi, v));
     }
 }
 
@@ -345,6 +478,7 @@ static inline unsigned nb_of(int64_t n) { return (unsigned)((n + BT - 1) / BT); 
 // The object's own workspace (nys_workspace) or the fixed scratch array of
 // mhk_nystrom_solve_noalloc.
 struct GmresWs {
+    int set = NYS_SOLVE;        // partial sums of the products
     int nblk = 0;               // blocks of the two-stage dot products
     double *V = nullptr;        // [m + 1][n] Krylov basis
     double *wv = nullptr;       // [n]
@@ -443,10 +577,15 @@ static mhk_status nys_scratch(mhk_nystrom *N, int64_t nout)
     return MHK_OK;
 }
 
-static hipError_t gemv(const mhk_nystrom *N, double shift, const double *x, double *y, hipStream_t st)
+// y = (shift I + K) x with partial sums in set `set`
+static hipError_t product(const mhk_nystrom *N, int set, double shift, const double *x, double *y, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_gemv, dim3((unsigned)((N->n + GV_ROWS - 1) / GV_ROWS)), dim3(BT), 0, st, N->n, N->ld, N->K,
-                       shift, x, y);
+    const NysPart &p = N->prod[set];
+    hipLaunchKernelGGL(k_symv, dim3((unsigned)N->nitem), dim3(BT), 0, st, N->n, N->np, (const double *)N->S,
+                       (const double *)N->geo, (const int2 *)N->item, N->run, x, p.cp, p.rp);
+    hipLaunchKernelGGL(k_symv_sum, dim3((unsigned)(N->np / TC)), dim3(TC * SG), 0, st, N->n, N->np, N->nstrip,
+                       (const double *)N->geo, (const int32_t *)N->item_ofs, (const double *)p.cp,
+                       (const double *)p.rp, shift, x, y);
     return hipGetLastError();
 }
 
@@ -499,7 +638,7 @@ static mhk_status gmres(mhk_nystrom *N, const GmresWs &W, double shift, const do
         if (first) {
             BIE_HIP(hipMemcpyAsync(W.rv, b, sizeof(double) * n, hipMemcpyDeviceToDevice, st));
         } else {
-            BIE_HIP(gemv(N, shift, x, W.wv, st));
+            BIE_HIP(product(N, W.set, shift, x, W.wv, st));
             hipLaunchKernelGGL(k_axpby, dim3(nb_of(n)), dim3(BT), 0, st, n, 1.0, b, -1.0, (const double *)W.wv,
                                W.rv);
             BIE_HIP(hipGetLastError());
@@ -530,7 +669,7 @@ static mhk_status gmres(mhk_nystrom *N, const GmresWs &W, double shift, const do
         int jend = 0;
         for (int j = 0; j < m; ++j) {
             const double *vj = W.V + (int64_t)j * n;
-            BIE_HIP(gemv(N, shift, vj, W.wv, st));
+            BIE_HIP(product(N, W.set, shift, vj, W.wv, st));
             BIE_HIP(dots(N, W, W.V, j + 1, W.wv, h1, st));
             hipLaunchKernelGGL(k_orth, dim3(nb_of(n)), dim3(BT), 0, st, n, (const double *)W.V, j + 1,
                                (const double *)h1, W.wv);
@@ -677,31 +816,58 @@ mhk_status mhk_nystrom_create(double alpha, const mhk_boundary *b, void *hip_str
     }
     mhk_nystrom *N = new mhk_nystrom();
     N->n = n;
-    N->ld = (n + 1) / 2 * 2;
+    N->np = (n + TC - 1) / TC * TC;
     N->alpha = alpha;
     N->stream = (hipStream_t)hip_stream;
-    double *geo = nullptr;
-    mhk_status st = nys_alloc(N, &N->K, n * N->ld);
+    N->nstrip = (n + TR - 1) / TR;
+    N->ntile = tile_ofs(N->nstrip);
+    // tiles per work item: as many items as keep the device busy to the end
+    // (4096: four workgroups on each of 256 CUs, four times over)
+    N->run = (int)std::min<int64_t>(8, std::max<int64_t>(1, N->ntile / 4096));
+    std::vector<int2> item;
+    std::vector<int32_t> item_ofs((size_t)N->nstrip + 1, 0);
+    for (int64_t I = N->nstrip - 1; I >= 0; --I) item_ofs[(size_t)I + 1] = (int32_t)((I / 2 + N->run) / N->run);
+    for (int64_t I = 0; I < N->nstrip; ++I) {
+        item_ofs[(size_t)I + 1] += item_ofs[(size_t)I];
+        for (int64_t c = 0; c < I / 2 + 1; c += N->run) item.push_back(make_int2((int)I, (int)c));
+    }
+    N->nitem = (int64_t)item.size();
     const std::vector<double> &k1 = k1_table();
-    if (st == MHK_OK) st = nys_alloc(N, &geo, 6 * n + (int64_t)k1.size());
+    double *tab = nullptr, *ia = nullptr, *io = nullptr;
+    mhk_status st = nys_alloc(N, &N->S, N->ntile * TR * TC);
+    if (st == MHK_OK) st = nys_alloc(N, &N->geo, 6 * N->np);
+    if (st == MHK_OK) st = nys_alloc(N, &tab, (int64_t)k1.size());
+    if (st == MHK_OK) st = nys_alloc(N, &ia, N->nitem);
+    N->item = reinterpret_cast<int2 *>(ia);
+    if (st == MHK_OK) st = nys_alloc(N, &io, (N->nstrip + 2) / 2);
+    N->item_ofs = reinterpret_cast<int32_t *>(io);
+    for (NysPart &p : N->prod) {
+        if (st == MHK_OK) st = nys_alloc(N, &p.cp, N->ntile * TC);
+        if (st == MHK_OK) st = nys_alloc(N, &p.rp, N->nitem * TR);
+    }
     if (st != MHK_OK) {
+        nys_free(N, &tab);
         mhk_nystrom_destroy(N);
         return st;
     }
-    std::vector<double> h(6 * (size_t)n + k1.size());
-    memcpy(&h[6 * (size_t)n], k1.data(), sizeof(double) * k1.size());
-    const double *src[6] = {b->x, b->y, b->nx, b->ny, b->w, b->kappa};
-    for (int k = 0; k < 6; ++k) memcpy(&h[(size_t)k * n], src[k], sizeof(double) * n);
+    std::vector<double> h(6 * (size_t)N->np, 0.0);
+    const double *src[5] = {b->x, b->y, b->nx, b->ny, b->w};
+    for (int k = 0; k < 5; ++k) memcpy(&h[(size_t)(k * N->np)], src[k], sizeof(double) * n);
+    for (int64_t i = 0; i < n; ++i) h[(size_t)(5 * N->np + i)] = -b->w[i] * b->kappa[i] / (4.0 * M_PI);
     hipEvent_t e0 = nullptr, e1 = nullptr;
-    hipError_t e = hipMemcpyAsync(geo, h.data(), sizeof(double) * h.size(), hipMemcpyHostToDevice, N->stream);
+    auto up = [&](void *d, const void *s, size_t bytes) {
+        return hipMemcpyAsync(d, s, bytes, hipMemcpyHostToDevice, N->stream);
+    };
+    hipError_t e = up(N->geo, h.data(), sizeof(double) * h.size());
+    if (e == hipSuccess) e = up(tab, k1.data(), sizeof(double) * k1.size());
+    if (e == hipSuccess) e = up(N->item, item.data(), sizeof(int2) * item.size());
+    if (e == hipSuccess) e = up(N->item_ofs, item_ofs.data(), sizeof(int32_t) * item_ofs.size());
     if (e == hipSuccess) e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
     if (e == hipSuccess) e = hipEventRecord(e0, N->stream);
     if (e == hipSuccess) {
-        dim3 grid((unsigned)((n + NYS_ROWS - 1) / NYS_ROWS), (unsigned)((N->ld + BT - 1) / BT));
-        hipLaunchKernelGGL(k_nys_assemble, grid, dim3(BT), 0, N->stream, n, N->ld, alpha, (const double *)geo,
-                           (const double *)(geo + n), (const double *)(geo + 2 * n), (const double *)(geo + 3 * n),
-                           (const double *)(geo + 4 * n), (const double *)(geo + 5 * n), (const double *)(geo + 6 * n), N->K);
+        hipLaunchKernelGGL(k_nys_assemble, dim3((unsigned)N->nitem), dim3(BT), 0, N->stream, n, N->np, alpha,
+                           (const double *)N->geo, (const double *)tab, (const int2 *)N->item, N->run, N->S);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipEventRecord(e1, N->stream);
@@ -710,7 +876,7 @@ mhk_status mhk_nystrom_create(double alpha, const mhk_boundary *b, void *hip_str
     if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
-    nys_free(N, &geo);
+    nys_free(N, &tab);
     if (e != hipSuccess) {
         set_error(std::string("Nystrom assembly: ") + hipGetErrorString(e));
         mhk_nystrom_destroy(N);
@@ -740,7 +906,7 @@ mhk_status mhk_nystrom_apply(mhk_nystrom *N, double shift, const double *x, doub
         set_error("null Nystrom matrix or vector, or x aliases y");
         return MHK_EINVAL;
     }
-    BIE_HIP(gemv(N, shift, x, y, N->stream));
+    BIE_HIP(product(N, NYS_APPLY, shift, x, y, N->stream));
     return MHK_OK;
 }
 
@@ -802,6 +968,7 @@ mhk_status mhk_nystrom_solve_noalloc(mhk_nystrom *N, double shift, const double 
     double *base = nullptr;
     BIE_TRY(scratch_base(&base));
     GmresWs W;
+    W.set = NYS_NOALLOC;
     W.nblk = nblk;
     W.V = base;
     W.wv = W.V + nV;
@@ -951,8 +1118,13 @@ void mhk_nystrom_destroy(mhk_nystrom *N)
     if (!N) return;
     (void)hipStreamSynchronize(N->stream);
     nys_free_ws(N);
-    nys_free(N, &N->K);
-    nys_free(N, &N->work);
+    for (double **p : {&N->S, &N->geo, &N->work}) nys_free(N, p);
+    for (NysPart &p : N->prod) {
+        nys_free(N, &p.cp);
+        nys_free(N, &p.rp);
+    }
+    if (N->item) (void)hipFreeAsync(N->item, N->stream);
+    if (N->item_ofs) (void)hipFreeAsync(N->item_ofs, N->stream);
     (void)hipStreamSynchronize(N->stream);
     delete N;
 }
