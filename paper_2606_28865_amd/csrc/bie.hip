@@ -37,6 +37,7 @@ struct mhk_nystrom {
     int2 *item = nullptr;       // [nitem] strip and first tile column
     int32_t *item_ofs = nullptr;  // [nstrip + 1] items of each strip
     NysPart prod[3];            // NYS_APPLY, NYS_SOLVE, NYS_NOALLOC
+    double *na_part = nullptr;  // gpart of the allocation-free solves (restart <= NOALLOC_MAX_RESTART)
     // GMRES workspace (grown on demand)
     int m_cap = 0;
     int nblk = 0;
@@ -44,6 +45,7 @@ struct mhk_nystrom {
     double *wv = nullptr;       // [n]
     double *rv = nullptr;       // [n] residual / right-hand side
     double *part = nullptr;     // [(m_cap + 1) nblk] partial sums
+    double *gpart = nullptr;    // [2][m_cap + 1][np/TC] partial sums of the Gram-Schmidt passes
     double *hd = nullptr;       // [2 (m_cap + 1) + 1] h (two passes) and |w|^2
     double *yd = nullptr;       // [m_cap] least-squares solution
     double *hh = nullptr;       // pinned host mirror of hd / yd
@@ -54,7 +56,7 @@ struct mhk_nystrom {
     double ms_assemble = 0;
     int64_t bytes() const
     {
-        return (int64_t)sizeof(double) * (ntile * 64 * 128 + 6 * np + 3 * (ntile * 128 + nitem * 64) + 2 * work_n) +
+        return (int64_t)sizeof(double) * (ntile * 64 * 128 + 6 * np + 3 * (ntile * 128 + nitem * 64) + np + 2 * work_n) +
                nitem * 8 + (nstrip + 1) * 4 + ws_bytes;
     }
 };
@@ -318,14 +320,17 @@ __global__ void __launch_bounds__(BT, 3) k_symv(int64_t n, int64_t np, const dou
 
 // y_i = (shift + K_ii) x_i + the row sums of its strip's items + the column
 // sums of the tiles below it, in a fixed order: 128 outputs per workgroup, the
-// tiles dealt to eight groups of threads
+// tiles dealt to eight groups of threads.  With a basis V (count > 0) the
+// workgroup also leaves its share of the dot products V_k . y, part[k nblk +
+// block].
 constexpr int SG = 8;
 __global__ void __launch_bounds__(TC * SG) k_symv_sum(int64_t n, int64_t np, int64_t nstrip,
                                                       const double *__restrict__ geo,
                                                       const int32_t *__restrict__ item_ofs,
                                                       const double *__restrict__ cp, const double *__restrict__ rp,
                                                       double shift, const double *__restrict__ x,
-                                                      double *__restrict__ y)
+                                                      double *__restrict__ y, const double *__restrict__ V, int count,
+                                                      double *__restrict__ part)
 {
     __shared__ double sh[SG][TC];
     const int cc = threadIdx.x % TC, g = threadIdx.x / TC;
@@ -338,12 +343,29 @@ __global__ void __launch_bounds__(TC * SG) k_symv_sum(int64_t n, int64_t np, int
         for (int it = item_ofs[strip] + g; it < item_ofs[strip + 1]; it += SG) s += rp[(int64_t)it * TR + i % TR];
     sh[g][cc] = s;
     __syncthreads();
+    double yi = 0.0;
     if (g == 0 && i < n) {
         double v = sh[0][cc];
 #pragma unroll
         for (int q = 1; q < SG; ++q) v += sh[q][cc];
         const double xi = x[i];
-        y[i] = fma(shift, xi, fma(geo[5 * np + i], xi, v));
+        yi = fma(shift, xi, fma(geo[5 * np + i], xi, v));
+        y[i] = yi;
+    }
+    if (count == 0) return;
+    __syncthreads();
+    if (g == 0) sh[0][cc] = yi;
+    __syncthreads();
+    // one basis vector per wavefront at a time, two outputs per lane
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+    const double y0 = sh[0][lane], y1 = sh[0][64 + lane];
+    const int64_t i0 = J * TC + lane;
+    for (int k = wave; k < count; k += TC * SG / 64) {
+        const double *v = V + (int64_t)k * n;
+        double d = i0 < n ? v[i0] * y0 : 0.0;
+        if (i0 + 64 < n) d = fma(v[i0 + 64], y1, d);
+        d = wave_sum(d);
+        if (lane == 0) part[(int64_t)k * gridDim.x + J] = d;
     }
 }
 
@@ -385,25 +407,77 @@ __global__ void __launch_bounds__(BT) k_reduce(const double *__restrict__ part, 
     if (threadIdx.x == 0) out[i] = s;
 }
 
-// w -= sum_{i < count} h[i] V_i
-__global__ void __launch_bounds__(BT) k_orth(int64_t n, const double *__restrict__ V, int count,
-                                             const double *__restrict__ h, double *__restrict__ w)
+// One Gram-Schmidt pass of GMRES over 128 entries of w per workgroup, as the
+// products leave them: h = the sums of the partial dot products of the pass
+// before (every workgroup forms them, in the same order; the first one stores
+// them), w -= sum_k h_k V_k, then its share of the next pass's dot products
+// V_k . w, or (norm) of w . w.  A pass is one launch instead of the three of a
+// reduction, an update and a dot product, four launches an iteration with the
+// normalisation instead of ten: a solve of 24 iterations at 8192 nodes went
+// from 3.9 to 3.5 ms with the matrix, a heat step at 16384 nodes from 6.4 to 5.9.
+__global__ void __launch_bounds__(TC * SG) k_gs_pass(int64_t n, const double *__restrict__ V, int count,
+                                                     const double *__restrict__ pin, double *__restrict__ h,
+                                                     double *__restrict__ w, int norm, double *__restrict__ pout)
 {
-    const int64_t t = (int64_t)blockIdx.x * BT + threadIdx.x;
-    if (t >= n) return;
-    double s = w[t];
-    for (int i = 0; i < count; ++i) s = fma(-h[i], V[(int64_t)i * n + t], s);
-    w[t] = s;
+    extern __shared__ double hs[];                    // [count], then [SG][TC]
+    double(*sh)[TC] = reinterpret_cast<double(*)[TC]>(hs + count);
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64, nblk = gridDim.x;
+    for (int k = wave; k < count; k += TC * SG / 64) {
+        double d = 0.0;
+        for (int b = lane; b < nblk; b += 64) d += pin[(int64_t)k * nblk + b];
+        d = wave_sum(d);
+        if (lane == 0) {
+            hs[k] = d;
+            if (blockIdx.x == 0) h[k] = d;
+        }
+    }
+    __syncthreads();
+    const int cc = threadIdx.x % TC, g = threadIdx.x / TC;
+    const int64_t i = (int64_t)blockIdx.x * TC + cc;
+    double s = 0.0;
+    if (i < n)
+        for (int k = g; k < count; k += SG) s = fma(-hs[k], V[(int64_t)k * n + i], s);
+    sh[g][cc] = s;
+    __syncthreads();
+    if (g == 0) {
+        double v = i < n ? w[i] : 0.0;
+#pragma unroll
+        for (int q = 0; q < SG; ++q) v += sh[q][cc];
+        if (i < n) w[i] = v;
+        sh[0][cc] = i < n ? v : 0.0;
+    }
+    __syncthreads();
+    const double y0 = sh[0][lane], y1 = sh[0][64 + lane];
+    const int64_t i0 = (int64_t)blockIdx.x * TC + lane;
+    if (norm) {
+        if (wave == 0) {
+            const double d = wave_sum(fma(y0, y0, y1 * y1));
+            if (lane == 0) pout[blockIdx.x] = d;
+        }
+        return;
+    }
+    for (int k = wave; k < count; k += TC * SG / 64) {
+        const double *v = V + (int64_t)k * n;
+        double d = i0 < n ? v[i0] * y0 : 0.0;
+        if (i0 + 64 < n) d = fma(v[i0 + 64], y1, d);
+        d = wave_sum(d);
+        if (lane == 0) pout[(int64_t)k * nblk + blockIdx.x] = d;
+    }
 }
 
-// v = w / sqrt(nrm2) (zero when the norm vanishes: breakdown, v unused)
+// v = w / |w| with |w|^2 the sum of the partial sums (stored in *nrm2 by the
+// first workgroup); zero when the norm vanishes: breakdown, v unused
 __global__ void __launch_bounds__(BT) k_normalize(int64_t n, const double *__restrict__ w,
-                                                  const double *__restrict__ nrm2, double *__restrict__ v)
+                                                  const double *__restrict__ pin, int nblk, double *__restrict__ nrm2,
+                                                  double *__restrict__ v)
 {
+    __shared__ double sh[BT / 64];
+    double s = 0.0;
+    for (int b = threadIdx.x; b < nblk; b += BT) s += pin[b];
+    s = block_sum(s, sh);
     const int64_t t = (int64_t)blockIdx.x * BT + threadIdx.x;
-    if (t >= n) return;
-    const double s = *nrm2;
-    v[t] = s > 0.0 ? w[t] / sqrt(s) : 0.0;
+    if (t == 0) *nrm2 = s;
+    if (t < n) v[t] = s > 0.0 ? w[t] / sqrt(s) : 0.0;
 }
 
 // x += sum_{i < count} y[i] V_i
@@ -484,6 +558,7 @@ struct GmresWs {
     double *wv = nullptr;       // [n]
     double *rv = nullptr;       // [n] residual / right-hand side
     double *part = nullptr;     // [(m + 1) nblk] partial sums
+    double *gpart = nullptr;    // [2][m + 1][np/TC] partial sums of the Gram-Schmidt passes
     double *hd = nullptr;       // [2 (m + 1) + 1] h (two passes) and |w|^2
     double *yd = nullptr;       // [m] least-squares solution
     double *hh = nullptr;       // host, [2 (m + 1) + 1 + m]: mirror of hd, then y
@@ -519,7 +594,7 @@ static void nys_free(mhk_nystrom *N, double **p)
 
 static void nys_free_ws(mhk_nystrom *N)
 {
-    for (double **p : {&N->V, &N->wv, &N->rv, &N->part, &N->hd, &N->yd}) nys_free(N, p);
+    for (double **p : {&N->V, &N->wv, &N->rv, &N->part, &N->gpart, &N->hd, &N->yd}) nys_free(N, p);
     delete[] N->hh;
     N->hh = nullptr;
     N->ws_bytes = 0;
@@ -535,6 +610,7 @@ static mhk_status nys_workspace(mhk_nystrom *N, int m)
     BIE_TRY(nys_alloc(N, &N->wv, N->n));
     BIE_TRY(nys_alloc(N, &N->rv, N->n));
     BIE_TRY(nys_alloc(N, &N->part, (int64_t)(m + 1) * N->nblk));
+    BIE_TRY(nys_alloc(N, &N->gpart, 2 * (int64_t)(m + 1) * (N->np / TC)));
     BIE_TRY(nys_alloc(N, &N->hd, 2 * (m + 1) + 1));
     BIE_TRY(nys_alloc(N, &N->yd, m));
     // host mirror of the few Arnoldi values copied back per iteration
@@ -542,7 +618,7 @@ static mhk_status nys_workspace(mhk_nystrom *N, int m)
     // hipHostFree, which waits for the whole device)
     N->hh = new double[(size_t)(2 * (m + 1) + 1 + m)];
     N->m_cap = m;
-    N->ws_bytes = (int64_t)sizeof(double) * ((int64_t)(m + 3) * N->n + (int64_t)(m + 1) * N->nblk + 3 * (m + 1));
+    N->ws_bytes = (int64_t)sizeof(double) * ((int64_t)(m + 3) * N->n + (int64_t)(m + 1) * (N->nblk + 2 * (N->np / TC)) + 3 * (m + 1));
     return MHK_OK;
 }
 
@@ -562,7 +638,7 @@ static mhk_status own_workspace(mhk_nystrom *N, int m, OwnWs &o)
     o.yv.assign(m, 0.0);
     GmresWs &W = o.W;
     W.nblk = N->nblk;
-    W.V = N->V; W.wv = N->wv; W.rv = N->rv; W.part = N->part; W.hd = N->hd; W.yd = N->yd; W.hh = N->hh;
+    W.V = N->V; W.wv = N->wv; W.rv = N->rv; W.part = N->part; W.gpart = N->gpart; W.hd = N->hd; W.yd = N->yd; W.hh = N->hh;
     W.H = o.H.data(); W.cs = o.cs.data(); W.sn = o.sn.data(); W.g = o.g.data(); W.yv = o.yv.data();
     return MHK_OK;
 }
@@ -578,14 +654,16 @@ static mhk_status nys_scratch(mhk_nystrom *N, int64_t nout)
 }
 
 // y = (shift I + K) x with partial sums in set `set`
-static hipError_t product(const mhk_nystrom *N, int set, double shift, const double *x, double *y, hipStream_t st)
+// (and, with a basis, the partial dot products of y with its count vectors)
+static hipError_t product(const mhk_nystrom *N, int set, double shift, const double *x, double *y, hipStream_t st,
+                          const double *V = nullptr, int count = 0, double *part = nullptr)
 {
     const NysPart &p = N->prod[set];
     hipLaunchKernelGGL(k_symv, dim3((unsigned)N->nitem), dim3(BT), 0, st, N->n, N->np, (const double *)N->S,
                        (const double *)N->geo, (const int2 *)N->item, N->run, x, p.cp, p.rp);
     hipLaunchKernelGGL(k_symv_sum, dim3((unsigned)(N->np / TC)), dim3(TC * SG), 0, st, N->n, N->np, N->nstrip,
                        (const double *)N->geo, (const int32_t *)N->item_ofs, (const double *)p.cp,
-                       (const double *)p.rp, shift, x, y);
+                       (const double *)p.rp, shift, x, y, V, count, part);
     return hipGetLastError();
 }
 
@@ -630,6 +708,7 @@ static mhk_status gmres(mhk_nystrom *N, const GmresWs &W, double shift, const do
         set_error("right-hand side is not finite");
         return MHK_EINVAL;
     }
+    const int gblk = (int)(N->np / TC);               // workgroups of the Gram-Schmidt passes
     double *H = W.H, *cs = W.cs, *sn = W.sn, *g = W.g, *yv = W.yv;
     int total = 0;
     bool first = true;
@@ -661,24 +740,25 @@ static mhk_status gmres(mhk_nystrom *N, const GmresWs &W, double shift, const do
             info->converged = 0;
             break;
         }
+        // nrm holds |r|^2 (its own only partial sum here)
         hipLaunchKernelGGL(k_normalize, dim3(nb_of(n)), dim3(BT), 0, st, n, (const double *)W.rv,
-                           (const double *)nrm, W.V);
+                           (const double *)nrm, 1, W.part, W.V);
         BIE_HIP(hipGetLastError());
         std::fill(g, g + m + 1, 0.0);
         g[0] = beta;
         int jend = 0;
         for (int j = 0; j < m; ++j) {
             const double *vj = W.V + (int64_t)j * n;
-            BIE_HIP(product(N, W.set, shift, vj, W.wv, st));
-            BIE_HIP(dots(N, W, W.V, j + 1, W.wv, h1, st));
-            hipLaunchKernelGGL(k_orth, dim3(nb_of(n)), dim3(BT), 0, st, n, (const double *)W.V, j + 1,
-                               (const double *)h1, W.wv);
-            BIE_HIP(dots(N, W, W.V, j + 1, W.wv, h2, st));
-            hipLaunchKernelGGL(k_orth, dim3(nb_of(n)), dim3(BT), 0, st, n, (const double *)W.V, j + 1,
-                               (const double *)h2, W.wv);
-            BIE_HIP(dots(N, W, W.wv, 1, W.wv, nrm, st));
+            // the passes' partial sums alternate between the halves of `gpart`
+            double *p0 = W.gpart, *p1 = W.gpart + (int64_t)(m + 1) * gblk;
+            const size_t lds = sizeof(double) * (size_t)(j + 1 + SG * TC);
+            BIE_HIP(product(N, W.set, shift, vj, W.wv, st, W.V, j + 1, p0));
+            hipLaunchKernelGGL(k_gs_pass, dim3((unsigned)gblk), dim3(TC * SG), lds, st, n, (const double *)W.V, j + 1,
+                               (const double *)p0, h1, W.wv, 0, p1);
+            hipLaunchKernelGGL(k_gs_pass, dim3((unsigned)gblk), dim3(TC * SG), lds, st, n, (const double *)W.V, j + 1,
+                               (const double *)p1, h2, W.wv, 1, p0);
             hipLaunchKernelGGL(k_normalize, dim3(nb_of(n)), dim3(BT), 0, st, n, (const double *)W.wv,
-                               (const double *)nrm, W.V + (int64_t)(j + 1) * n);
+                               (const double *)p0, gblk, nrm, W.V + (int64_t)(j + 1) * n);
             BIE_HIP(hipGetLastError());
             BIE_TRY(fetch(N, W.hd, 2 * (m + 1) + 1, hh, st));
             double *col = &H[(size_t)j * (m + 1)];
@@ -836,6 +916,7 @@ mhk_status mhk_nystrom_create(double alpha, const mhk_boundary *b, void *hip_str
     double *tab = nullptr, *ia = nullptr, *io = nullptr;
     mhk_status st = nys_alloc(N, &N->S, N->ntile * TR * TC);
     if (st == MHK_OK) st = nys_alloc(N, &N->geo, 6 * N->np);
+    if (st == MHK_OK) st = nys_alloc(N, &N->na_part, 2 * (int64_t)(NOALLOC_MAX_RESTART + 1) * (N->np / TC));
     if (st == MHK_OK) st = nys_alloc(N, &tab, (int64_t)k1.size());
     if (st == MHK_OK) st = nys_alloc(N, &ia, N->nitem);
     N->item = reinterpret_cast<int2 *>(ia);
@@ -974,6 +1055,7 @@ mhk_status mhk_nystrom_solve_noalloc(mhk_nystrom *N, double shift, const double 
     W.wv = W.V + nV;
     W.rv = W.wv + nvec;
     W.part = W.rv + nvec;
+    W.gpart = N->na_part;
     W.hd = W.part + npart;
     W.yd = W.hd + nhd;
     // host side of the least-squares problem on the stack (restart <= 64)
@@ -1118,7 +1200,7 @@ void mhk_nystrom_destroy(mhk_nystrom *N)
     if (!N) return;
     (void)hipStreamSynchronize(N->stream);
     nys_free_ws(N);
-    for (double **p : {&N->S, &N->geo, &N->work}) nys_free(N, p);
+    for (double **p : {&N->S, &N->geo, &N->na_part, &N->work}) nys_free(N, p);
     for (NysPart &p : N->prod) {
         nys_free(N, &p.cp);
         nys_free(N, &p.rp);
