@@ -16,18 +16,20 @@
 // windows of the sources that meet it (listed per block at plan time) as
 // rank-4 updates on the FP64 matrix cores: every grid value is written
 // exactly once, with no atomics and in a fixed summation order.
-// Interpolation: one workgroup per non-empty target tile stages the tile plus
-// its window halo of the three result grids in LDS with coalesced row reads.
+// Interpolation: where the targets are dense on the grid, one wavefront per
+// non-empty block of grid cells on the matrix cores; else one workgroup per
+// non-empty target tile stages the tile plus its window halo of the three
+// result grids in LDS with coalesced row reads.
 #include "mhk_internal.h"
 
 namespace mhk {
 
 // threads per interpolation / spreading workgroup: a busy tile holds a few
-// hundred targets, one per thread; a spreading block's list is dealt to four
+// hundred targets, one per thread; a spreading block's list is dealt to NWV
 // wavefronts in batches of 32
 constexpr int HB = 256;
-constexpr int SB = 256;
 typedef double d4 __attribute__((ext_vector_type(4)));
+constexpr int INTERP_NB = 4;   // densities per interpolation wavefront, sharing its window values
 // doubles of LDS per spreading wavefront: 64 rows of W + 2 window values, the
 // strengths of 32 sources in NF fields, 64 window corners
 constexpr int SPREAD_LDS(int W, int NF) { return 64 * (W + 2) + NF * 32 + 32; }
@@ -154,14 +156,14 @@ __device__ inline void wave_sync()
 // a K x 16 matrix of x-window values, four sources at a time on
 // v_mfma_f64_16x16x4 (A: lane l holds row l % 16 of source l / 16, B: column
 // l % 16 of source l / 16, D: rows 4 v + l / 16, column l % 16).  Each of the
-// four wavefronts takes every fourth batch of 32 sources: lane l evaluates
+// NWV wavefronts takes every NWV-th batch of 32 sources: lane l evaluates
 // the W window values of axis l / 32 of source l % 32 (half the lanes' work
 // of one thread per source, with scalar coefficients) into LDS rows of W + 2,
 // the first and last of them zero, so that a row clamped to [-1, W] reads
 // zero outside its window.  The windows of a list's sources cover 44% of the
 // block's rows and columns (W = 12); skipping the rest would cost more than
 // the matrix cores take.
-template <int W, typename T, int NF, bool VOL>
+template <int W, typename T, int NF, bool VOL, int NWV>
 __device__ inline void spread_block(const SpreadArgs<T> &A, int b0, int nf, int x0, int y0, int e0, int e1,
                                     double *lds)
 {
@@ -181,7 +183,7 @@ __device__ inline void spread_block(const SpreadArgs<T> &A, int b0, int nf, int 
     // the volume's densities alternate between the two halves of the
     // wavefront; the lower half forms the boundary's strengths
     constexpr int NQ = VOL ? (NF + 1) / 2 : NF;
-    const int step = 32 * (SB / 64);
+    const int step = 32 * NWV;
     struct Src {
         double g, w[3], f[NQ];
     };
@@ -251,7 +253,7 @@ __device__ inline void spread_block(const SpreadArgs<T> &A, int b0, int nf, int 
         cur = nxt;
         s1 = s2;
     }
-    // the four wavefronts' sums, in order, one field at a time
+    // the wavefronts' sums, in order, one field at a time
     const size_t fs = (size_t)A.B * A.field;
     const size_t o = (size_t)(y0 + tid / 16) * (A.n + 2) + x0 + tid % 16;
 #pragma unroll
@@ -261,7 +263,10 @@ __device__ inline void spread_block(const SpreadArgs<T> &A, int b0, int nf, int 
 #pragma unroll
         for (int v = 0; v < 4; ++v) lds[wave * 256 + (4 * v + k) * 16 + i] = acc[f][v];
         __syncthreads();
-        const double sum = ((lds[tid] + lds[256 + tid]) + lds[512 + tid]) + lds[768 + tid];
+        if (tid >= 256) continue;
+        double sum = lds[tid];
+#pragma unroll
+        for (int q = 1; q < NWV; ++q) sum += lds[256 * q + tid];
         if (VOL) {
             A.grid[fs + (size_t)(b0 + f) * A.field + o] = (T)sum;
         } else {
@@ -282,21 +287,21 @@ __device__ inline void spread_block(const SpreadArgs<T> &A, int b0, int nf, int 
 // on 3840^2, W = 8, FP32: 215 us (430).  Blocks that no window meets are not
 // launched: a workgroup each to write their zeros cost 50 us at 1920^2 and
 // 70 us at 3840^2; the row transforms skip them by their flags.
-template <int W, typename T, int NV, int ND>
-__global__ void __launch_bounds__(SB) k_spread(SpreadArgs<T> A)
+template <int W, typename T, int NV, int ND, int NWV>
+__global__ void __launch_bounds__(64 * NWV) k_spread(SpreadArgs<T> A)
 {
     constexpr int NM = NV > 3 * ND ? NV : 3 * ND;
-    constexpr int SZ = SPREAD_LDS(W, NM) * (SB / 64);
-    __shared__ double lds[SZ > 1024 ? SZ : 1024];
+    constexpr int SZ = SPREAD_LDS(W, NM) * NWV;
+    __shared__ double lds[SZ > 256 * NWV ? SZ : 256 * NWV];
     const bool vol = (int64_t)blockIdx.x < A.nvw;
     const int id = (int)(blockIdx.x - (vol ? 0 : A.nvw)), nt = vol ? A.nvt : A.nbt;
     const int blk = (vol ? A.vact : A.bact)[id / nt], b0 = id % nt * (vol ? NV : ND);
     const int nd = min(vol ? NV : ND, A.B - b0);
     const int x0 = blk % A.nblk * SPB, y0 = blk / A.nblk * SPB;
     if (vol)
-        spread_block<W, T, NV, true>(A, b0, nd, x0, y0, A.vlofs[blk], A.vlofs[blk + 1], lds);
+        spread_block<W, T, NV, true, NWV>(A, b0, nd, x0, y0, A.vlofs[blk], A.vlofs[blk + 1], lds);
     else
-        spread_block<W, T, 3 * ND, false>(A, b0, 3 * nd, x0, y0, A.blofs[blk], A.blofs[blk + 1], lds);
+        spread_block<W, T, 3 * ND, false, NWV>(A, b0, 3 * nd, x0, y0, A.blofs[blk], A.blofs[blk + 1], lds);
 }
 
 // Fourier multiplier on the half spectrum [n][n/2+1] of each field; the
@@ -715,7 +720,9 @@ __global__ void __launch_bounds__(CT) k_columns(ColArgs<T> A)
 template <typename T>
 struct InterpArgs {
     int64_t n, field, nout;
-    int ntile, B;
+    int ntile, B;          // tiles (or blocks) per grid row
+    int nrun;              // non-empty tiles (or blocks)
+    int gx0, gx1, gy0, gy1;   // grid values [gx0, gx1) x [gy0, gy1) are set
     double beta, ox, oy, h;
     const int32_t *tile_xy, *tile_rng;
     const double *tx, *ty;
@@ -773,6 +780,155 @@ __global__ void __launch_bounds__(HB) k_interp(InterpArgs<T> A)
         if (A.want_s) A.acc[ob] = uS;
         if (A.want_d) A.acc[cs + ob] = uD;
         if (A.want_v) A.acc[2 * cs + ob] = uV;
+    }
+}
+
+// Interpolation on the matrix cores, for targets dense on the grid.  The windows
+// of the targets of an E x E block of grid cells (E + W <= 16) lie in one 16 x
+// 16 region U of each result grid, so u_j = sum_y w_y(j, y) sum_x U(y, x) w_x(j,
+// x) is, for 16 targets, a 16 x 16 x 16 product (four v_mfma_16x16x4 in the
+// plan's precision, A: U with lane l holding row l % 16 and columns 4 (l / 16) +
+// s of step s, B: the x-window values) and a dot product of each column with
+// the target's y-window values.  A wavefront owns a block: U stays in its
+// registers, the window values of 32 targets at a time go through LDS as in the
+// spreading.  One thread per target instead reads 3 W^2 values at addresses
+// that differ from lane to lane, bound by LDS bank conflicts.  Measured (three
+// results, W = 12, alone): 1.02M targets, 45 per block, 138 by tiles -> 71 us; 4608
+// targets, 23 per block, 45 -> 8 us; 16 densities, 1000 -> 846 us.
+template <typename T> struct Frag;
+template <> struct Frag<double> { typedef d4 type; };
+template <> struct Frag<float> { typedef float type __attribute__((ext_vector_type(4))); };
+__device__ inline d4 mma16(double a, double b, d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+__device__ inline Frag<float>::type mma16(float a, float b, Frag<float>::type c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+template <int W, typename T>
+__global__ void __launch_bounds__(HB) k_interp_mm(InterpArgs<T> A)
+{
+    typedef typename Frag<T>::type F;
+    constexpr int RW = W + 2, E = interp_edge(W);
+    __shared__ T rows[HB / 64][64 * RW];
+    __shared__ int corner[HB / 64][64];
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+    const int run = (int)blockIdx.x * (HB / 64) + wave;
+    if (run >= A.nrun) return;                        // wavefronts are independent: no workgroup barrier below
+    T *row = rows[wave];
+    int *ms = corner[wave];
+    const int blk = A.tile_xy[run], s0 = A.tile_rng[run], s1 = A.tile_rng[run + 1];
+    // the lowest window corner of the block's targets
+    const int x0 = blk % A.ntile * E - W / 2, y0 = blk / A.ntile * E - W / 2;
+    const int j = lane % 16, k = lane / 16, axis = lane / 32, sl = lane % 32;
+    const size_t fs = (size_t)A.B * A.field, cs = (size_t)A.B * A.nout;
+    const bool want[3] = {A.want_s != 0, A.want_v != 0, A.want_d != 0};
+    T u[3][4];
+    // values outside the set part of the grid are zero (their weights are, too)
+    auto region = [&](int b) {
+        const int gy = y0 + j, gx = x0 + 4 * k;
+        const bool iny = gy >= A.gy0 && gy < A.gy1;
+        const T *g = A.grid + (size_t)b * A.field + (size_t)gy * (A.n + 2) + gx;
+#pragma unroll
+        for (int f = 0; f < 3; ++f)
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                u[f][s] = want[f] && iny && gx + s >= A.gx0 && gx + s < A.gx1 ? g[f * fs + s] : (T)0;
+    };
+    row[lane * RW] = (T)0;
+    row[lane * RW + W + 1] = (T)0;
+    const int b0 = (int)blockIdx.y * INTERP_NB, b1 = min(A.B, b0 + INTERP_NB);
+    if (b1 - b0 == 1) region(b0);
+    for (int p = s0; p < s1; p += 32) {
+        const int s = p + sl;
+        int m = 1 << 20;                              // no target: a window far outside
+        if (s < s1) {
+            const double g = axis ? (A.ty[s] - A.oy) / A.h : (A.tx[s] - A.ox) / A.h;
+            T w[W];
+            window_weights1<W, T>(g, A.wcoef, m, w);
+            m -= axis ? y0 : x0;
+#pragma unroll
+            for (int q = 0; q < W; ++q) row[lane * RW + 1 + q] = w[q];
+        }
+        ms[lane] = m;
+        wave_sync();
+        const int cnt = min(32, s1 - p);
+        for (int b = b0; b < b1; ++b) {
+            if (b1 - b0 > 1) region(b);
+            for (int q0 = 0; q0 < cnt; q0 += 16) {
+                const int src = q0 + j, mx = ms[src], my = ms[32 + src];
+                T wx[4], wy[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    // D: row 4 v + k in FP64, 4 k + v in FP32
+                    const int y = sizeof(T) == 8 ? 4 * v + k : 4 * k + v;
+                    wx[v] = row[src * RW + min(max(4 * k + v - mx, -1), W) + 1];
+                    wy[v] = row[(32 + src) * RW + min(max(y - my, -1), W) + 1];
+                }
+                T r[3];
+#pragma unroll
+                for (int f = 0; f < 3; ++f) {
+                    F c = {(T)0, (T)0, (T)0, (T)0};
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) c = mma16(u[f][v], wx[v], c);
+                    r[f] = wy[0] * c[0];
+#pragma unroll
+                    for (int v = 1; v < 4; ++v) r[f] = fma(wy[v], c[v], r[f]);
+                    r[f] += __shfl_xor(r[f], 16, 64);
+                    r[f] += __shfl_xor(r[f], 32, 64);
+                }
+                if (lane < 16 && q0 + lane < cnt) {
+                    const size_t o = (size_t)b * A.nout + p + q0 + lane;
+                    if (want[0]) A.acc[o] = r[0];
+                    if (want[2]) A.acc[cs + o] = r[2];
+                    if (want[1]) A.acc[2 * cs + o] = r[1];
+                }
+            }
+        }
+        wave_sync();
+    }
+}
+
+// Interpolation of few targets far apart: sixteen lanes per target, one per
+// window column, read the W rows of the window straight from the grid (a tile
+// of 46 x 46 values staged for one or two targets took 65 us for 8065 targets
+// on 4858 tiles, one result; this takes 7 us).
+template <int W, typename T>
+__global__ void __launch_bounds__(HB) k_interp_few(InterpArgs<T> A)
+{
+    const int64_t s = ((int64_t)blockIdx.x * HB + threadIdx.x) / 16;
+    const int kx = threadIdx.x % 16, b = blockIdx.y;
+    if (s >= A.nout) return;                          // whole groups of sixteen lanes
+    const double gx = (A.tx[s] - A.ox) / A.h, gy = (A.ty[s] - A.oy) / A.h;
+    int mx0, my0;
+    T wx[W], wy[W];
+    window_weights2<W, T>(gx, gy, A.wcoef, mx0, my0, wx, wy);
+    T w = (T)0;
+#pragma unroll
+    for (int q = 0; q < W; ++q) w = kx == q ? wx[q] : w;
+    const size_t fs = (size_t)A.B * A.field, cs = (size_t)A.B * A.nout, o = (size_t)b * A.nout + s;
+    // windows lie inside the grid (its origin is W/2 + 3 points below the points)
+    const T *g = A.grid + (size_t)b * A.field + (size_t)my0 * (A.n + 2) + mx0 + kx;
+    auto one = [&](int f) {
+        T v = (T)0;
+        if (kx < W)
+#pragma unroll
+            for (int ky = 0; ky < W; ++ky) v = fma(wy[ky], g[f * fs + (size_t)ky * (A.n + 2)], v);
+        v *= w;
+#pragma unroll
+        for (int m = 8; m >= 1; m /= 2) v += __shfl_xor(v, m, 16);
+        return v;
+    };
+    if (A.want_s) {
+        const T v = one(0);
+        if (kx == 0) A.acc[o] = v;
+    }
+    if (A.want_v) {
+        const T v = one(1);
+        if (kx == 0) A.acc[2 * cs + o] = v;
+    }
+    if (A.want_d) {
+        const T v = one(2);
+        if (kx == 0) A.acc[cs + o] = v;
     }
 }
 
@@ -928,10 +1084,22 @@ static hipError_t spread_w(mhk_plan *P, SpreadArgs<T> &A)
     A.nvw = A.f_vol ? G.nvact * A.nvt : 0;
     const int64_t wg = A.nvw + (A.sigma || A.mu ? G.nbact * A.nbt : 0);
     if (wg == 0) return hipSuccess;
-    if (one)
-        hipLaunchKernelGGL((k_spread<W, T, 1, 1>), dim3((unsigned)wg), dim3(SB), 0, P->stream, A);
+    // wavefronts per block: few blocks leave the chip idle behind their long
+    // lists, so they take 16 (up to two workgroups per CU) or 8; many blocks
+    // fill it, and four shorter-lived wavefronts each finish more evenly.
+    // Measured with 4 / 8 / 16, alone: 40 workgroups 25 / 16 / 12 us, 476
+    // workgroups (FP32) 26 / 18 / 14 us, 2236 workgroups 126 / 107 / 122 us,
+    // 7149 workgroups (FP32) 219 / 234 / 287 us; 16 densities 750 / 843 us.  At
+    // 2236 the gain alone is lost beside the level sums, which the larger LDS
+    // share keeps out (whole evaluation 1288 / 1315 us).
+    if (!one)
+        hipLaunchKernelGGL((k_spread<W, T, 8, 2, 4>), dim3((unsigned)wg), dim3(256), 0, P->stream, A);
+    else if (wg <= 512)
+        hipLaunchKernelGGL((k_spread<W, T, 1, 1, 16>), dim3((unsigned)wg), dim3(1024), 0, P->stream, A);
+    else if (wg <= 1024)
+        hipLaunchKernelGGL((k_spread<W, T, 1, 1, 8>), dim3((unsigned)wg), dim3(512), 0, P->stream, A);
     else
-        hipLaunchKernelGGL((k_spread<W, T, 8, 2>), dim3((unsigned)wg), dim3(SB), 0, P->stream, A);
+        hipLaunchKernelGGL((k_spread<W, T, 1, 1, 4>), dim3((unsigned)wg), dim3(256), 0, P->stream, A);
     return hipGetLastError();
 }
 
@@ -939,6 +1107,18 @@ template <int W, typename T>
 static hipError_t interp_w(mhk_plan *P, const InterpArgs<T> &A)
 {
     if (P->hist.n_ttiles == 0) return hipSuccess;
+    if constexpr (interp_edge(W) > 0) {
+        if (P->hist.iedge > 0) {
+            dim3 grid((unsigned)((A.nrun + HB / 64 - 1) / (HB / 64)), (unsigned)((A.B + INTERP_NB - 1) / INTERP_NB));
+            hipLaunchKernelGGL((k_interp_mm<W, T>), grid, dim3(HB), 0, P->stream, A);
+            return hipGetLastError();
+        }
+    }
+    if (P->nout <= INTERP_FEW * (int64_t)P->hist.n_ttiles) {
+        dim3 grid((unsigned)((P->nout * 16 + HB - 1) / HB), (unsigned)A.B);
+        hipLaunchKernelGGL((k_interp_few<W, T>), grid, dim3(HB), 0, P->stream, A);
+        return hipGetLastError();
+    }
     dim3 grid((unsigned)P->hist.n_ttiles, (unsigned)A.B);
     hipLaunchKernelGGL((k_interp<W, T>), grid, dim3(HB), 0, P->stream, A);
     return hipGetLastError();
@@ -1106,7 +1286,12 @@ static hipError_t interp_t(mhk_plan *P, bool want_s, bool want_d, bool want_v)
     A.n = G.n;
     A.field = G.field;
     A.nout = P->nout;
-    A.ntile = G.ntile;
+    A.ntile = G.iedge > 0 ? (int)(G.n / G.iedge) : G.ntile;
+    A.nrun = G.n_ttiles;
+    A.gx0 = G.colpath ? G.tx0 : 0;
+    A.gx1 = G.colpath ? G.tx1 : (int)G.n;
+    A.gy0 = G.colpath ? G.ty0 : 0;
+    A.gy1 = G.colpath ? G.ty1 : (int)G.n;
     A.B = P->bat;
     A.beta = G.beta;
     A.ox = G.ox;

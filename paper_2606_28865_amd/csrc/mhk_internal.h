@@ -42,6 +42,18 @@ namespace mhk {
 constexpr int NGL = 16;          // Gauss-Legendre nodes per panel (Section 3.2)
 constexpr int TILE = 32;         // fine-grid tile edge of spreading/interpolation
 constexpr int SPB = 16;          // fine-grid block edge of the spreading lists (TILE is a multiple)
+// edge of the interpolation blocks (a power of two, so that a block's targets are
+// one run of the Morton order): windows of W points at edge + 1 corners lie in
+// 16 points; 0: none fits
+constexpr int interp_edge(int W) { return W <= 8 ? 8 : W <= 12 ? 4 : 0; }
+// Interpolation: by blocks (matrix cores) in FP64 with windows wider than 8
+// from INTERP_MIN targets per non-empty block on (1M targets, 45 per block: 71
+// against 138 us by tiles; a block costs about as much for one target as for
+// 32, so that by tiles is the better below a dozen), and for any window where
+// the tiles are too few to fill the chip (104 thousand FP32 targets on 32
+// tiles: 25 against 64 us; with 1481 tiles, W = 8, FP32, 121 against 88 us);
+// straight from the grid up to INTERP_FEW targets per tile; by tiles else.
+constexpr int64_t INTERP_MIN = 16, INTERP_MIN_TILES = 512, INTERP_FEW = 8;
 constexpr int MAXJ = 8;          // maximum number of dyadic levels
 constexpr int TAB_NC = 8;        // coefficients per table segment (degree 7)
 constexpr int TAB_NC64 = 5;      // FP64 path: c_0..c_4 stored as doubles, c_5..c_7 as floats
@@ -169,7 +181,9 @@ struct History {
     uint8_t *bflag = nullptr, *vflag = nullptr;
     int32_t *bact = nullptr, *vact = nullptr;
     int64_t nbact = 0, nvact = 0;
-    // targets by tile: list of non-empty tiles and their ranges in sorted order
+    // targets by tile (by block of edge iedge when iedge > 0): list of
+    // non-empty tiles and their ranges in sorted order
+    int iedge = 0;
     int n_ttiles = 0;
     int32_t *ttile_xy = nullptr;                  // [n_ttiles] tile index ty*ntile+tx
     int32_t *ttile_rng = nullptr;                 // [n_ttiles + 1]
@@ -418,12 +432,13 @@ hipError_t dev_sources_by_tile(const double *x, const double *y, const double *w
                                hipStream_t st);
 hipError_t dev_tile_fill(const double *gx, const double *gy, const int32_t *tstart, int64_t ntile, int W,
                          const int32_t *lofs, int32_t *list, hipStream_t st);
-// Runs of equal tiles along the sorted targets, and their window bounds.
+// Runs of equal tiles (edge x edge grid cells, ntile per grid row) along the
+// sorted targets, and their window bounds (win may be null).
 hipError_t dev_target_tiles_count(const double *tx, const double *ty, int64_t n, double ox, double oy, double h,
-                                  int64_t ntile, int W, int *win, int32_t **flag_out, int32_t **pos_out,
+                                  int64_t ntile, int edge, int W, int *win, int32_t **flag_out, int32_t **pos_out,
                                   int64_t *runs_dev, hipStream_t st);
 hipError_t dev_target_tiles_fill(const double *tx, const double *ty, int64_t n, double ox, double oy, double h,
-                                 int64_t ntile, const int32_t *flag, const int32_t *pos, int32_t *xy, int32_t *rng,
+                                 int64_t ntile, int edge, const int32_t *flag, const int32_t *pos, int32_t *xy, int32_t *rng,
                                  hipStream_t st);
 
 }  // namespace mhk

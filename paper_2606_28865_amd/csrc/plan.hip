@@ -1322,9 +1322,9 @@ mhk_status build_history(mhk_plan *P, Host &H)
         // window bounds [x0, x1) x [y0, y1): sources in bnd[0..3], targets in bnd[4..7]
         const int bnd0[8] = {n, 0, n, 0, n, 0, n, 0};
         int *bnd = nullptr;
-        int64_t *tots = nullptr;   // boundary list, volume list, target tile runs, active blocks of both lists
+        int64_t *tots = nullptr;   // boundary list, volume list, target tile runs, active blocks of both lists, target block runs
         TRY(tmp.upload(&bnd, bnd0, 8));
-        TRY(tmp.alloc(&tots, 5));
+        TRY(tmp.alloc(&tots, 6));
         G.nbs = nb;
         TRY(dalloc(P, &G.bgx, nb));
         TRY(dalloc(P, &G.bgy, nb));
@@ -1335,7 +1335,7 @@ mhk_status build_history(mhk_plan *P, Host &H)
         TRY(dalloc(P, &G.blofs, nt2 + 1));
         TRY(dalloc(P, &G.bflag, nt2));
         TRY(dalloc(P, &G.bact, std::min(nt2, 4 * nb)));
-        int32_t *bstart = nullptr, *vstart = nullptr, *tflag = nullptr, *tpos = nullptr;
+        int32_t *bstart = nullptr, *vstart = nullptr, *tflag = nullptr, *tpos = nullptr, *eflag = nullptr, *epos = nullptr;
         MHK_HIP(dev_sources_by_tile(P->bx, P->by, P->bw, P->bnx, P->bny, nb, G.ox, G.oy, G.h, nsb, G.w, G.bgx,
                                     G.bgy, G.bw, G.bwx, G.bwy, G.bidx, bnd, G.blofs, G.bflag, G.bact, tots + 3, &bstart,
                                     tots + 0, st));
@@ -1356,13 +1356,20 @@ mhk_status build_history(mhk_plan *P, Host &H)
                                     G.vw, nullptr, nullptr, G.vidx, bnd, G.vlofs, G.vflag, G.vact, tots + 4, &vstart,
                                     tots + 1, st));
         tmp.ptrs.push_back(vstart);
-        MHK_HIP(dev_target_tiles_count(P->tx, P->ty, nout, G.ox, G.oy, G.h, G.ntile, G.w, bnd + 4, &tflag, &tpos,
+        MHK_HIP(dev_target_tiles_count(P->tx, P->ty, nout, G.ox, G.oy, G.h, G.ntile, TILE, G.w, bnd + 4, &tflag, &tpos,
                                        tots + 2, st));
         tmp.ptrs.push_back(tflag);
         tmp.ptrs.push_back(tpos);
-        int64_t tot[5];
+        if (interp_edge(G.w) > 0) {
+            MHK_HIP(dev_target_tiles_count(P->tx, P->ty, nout, G.ox, G.oy, G.h, G.n / interp_edge(G.w),
+                                           interp_edge(G.w), G.w, nullptr, &eflag, &epos, tots + 5, st));
+            tmp.ptrs.push_back(eflag);
+            tmp.ptrs.push_back(epos);
+        }
+        int64_t tot[6] = {0};
+        const int edge = interp_edge(G.w);
         int bh[8];
-        MHK_HIP(hipMemcpyAsync(tot, tots, sizeof tot, hipMemcpyDeviceToHost, st));
+        MHK_HIP(hipMemcpyAsync(tot, tots, sizeof(int64_t) * (edge > 0 ? 6 : 5), hipMemcpyDeviceToHost, st));
         TRY(tmp.fetch(bh, bnd, 8));
         if (tot[0] > (int64_t)INT32_MAX || tot[1] > (int64_t)INT32_MAX) {
             set_error("spreading lists too large");
@@ -1372,13 +1379,19 @@ mhk_status build_history(mhk_plan *P, Host &H)
         TRY(dalloc(P, &G.vlist, std::max<int64_t>(1, tot[1])));
         MHK_HIP(dev_tile_fill(G.bgx, G.bgy, bstart, nsb, G.w, G.blofs, G.blist, st));
         MHK_HIP(dev_tile_fill(G.vgx, G.vgy, vstart, nsb, G.w, G.vlofs, G.vlist, st));
-        G.n_ttiles = (int)tot[2];
         G.nbact = tot[3];
         G.nvact = tot[4];
-        TRY(dalloc(P, &G.ttile_xy, std::max<int64_t>(1, tot[2])));
-        TRY(dalloc(P, &G.ttile_rng, tot[2] + 1));
-        MHK_HIP(dev_target_tiles_fill(P->tx, P->ty, nout, G.ox, G.oy, G.h, G.ntile, tflag, tpos, G.ttile_xy,
-                                      G.ttile_rng, st));
+        const bool few_tiles = tot[2] * P->p.batch < INTERP_MIN_TILES;
+        const bool blocks = few_tiles ? nout > INTERP_FEW * tot[2] && nout >= INTERP_MIN / 4 * tot[5]
+                                      : P->p.prec == MHK_FP64 && G.w > 8 && nout >= INTERP_MIN * tot[5];
+        G.iedge = edge > 0 && blocks ? edge : 0;
+        const int64_t runs = G.iedge ? tot[5] : tot[2];
+        G.n_ttiles = (int)runs;
+        TRY(dalloc(P, &G.ttile_xy, std::max<int64_t>(1, runs)));
+        TRY(dalloc(P, &G.ttile_rng, runs + 1));
+        MHK_HIP(dev_target_tiles_fill(P->tx, P->ty, nout, G.ox, G.oy, G.h, G.iedge ? G.n / G.iedge : G.ntile,
+                                      G.iedge ? G.iedge : TILE, G.iedge ? eflag : tflag, G.iedge ? epos : tpos,
+                                      G.ttile_xy, G.ttile_rng, st));
         G.sx0 = std::max(0, bh[0]);
         G.sx1 = std::min(n, bh[1]);
         G.sy0 = std::max(0, bh[2]);
