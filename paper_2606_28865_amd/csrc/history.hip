@@ -973,9 +973,13 @@ __global__ void __launch_bounds__(256) k_trunc_samples(double *buf, int64_t M, d
     const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (id >= M * M) return;
     const int64_t my = id / M, mx = id % M;
+    // the samples are symmetric in x and y: one of each pair is evaluated
+    if (my > mx) return;
     const double x = mx * h, y = my * h;
-    buf[id] = h * h * history_kernel(sqrt(x * x + y * y), alpha, delta, gt, gw) * 0.25 * erfc((x - rmid) * slope) *
-              erfc((y - rmid) * slope);
+    const double v = h * h * history_kernel(sqrt(x * x + y * y), alpha, delta, gt, gw) * 0.25 *
+                     erfc((x - rmid) * slope) * erfc((y - rmid) * slope);
+    buf[id] = v;
+    buf[mx * M + my] = v;
 }
 
 // One separable step of the cosine transform of the even samples:

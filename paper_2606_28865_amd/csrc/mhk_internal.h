@@ -317,6 +317,8 @@ struct mhk_plan {
     mhk::VLevel vlev[mhk::MAXJ];                // volume levels (params.v_levels)
     double delta_v = 0;                          // time split of V's local part: delta, or delta* with volume levels
     std::vector<void *> allocs;                 // stream-ordered allocations on `stream`
+    char *chunk = nullptr;                      // the rest of the last chunk of small buffers
+    size_t chunk_left = 0;
     std::vector<std::vector<char>> stage;       // host bytes of uploads in flight during creation
     int64_t bytes = 0;
     // stage timing: ev[0..7] history stages and local part on the plan's

@@ -174,6 +174,47 @@ struct TableEntry {
 static std::mutex g_table_mu;
 static std::map<std::array<uint64_t, 3>, TableEntry> g_tables;
 
+// e^{-2 pi i m / n}, m < n, as (re, im) pairs, rounded from long double; only
+// angles up to pi/4 are evaluated, the others are their reflections (n a
+// multiple of 8, as every grid size is; else all are)
+static std::vector<double> unit_roots(int64_t n)
+{
+    std::vector<double> r(2 * (size_t)n);
+    auto eval = [&](int64_t m, double &c, double &s) {
+        const long double a = 2.0L * M_PIl * (long double)m / (long double)n;
+        c = (double)cosl(a);
+        s = (double)sinl(a);
+    };
+    if (n % 8 != 0) {
+        for (int64_t m = 0; m < n; ++m) {
+            double c, s;
+            eval(m, c, s);
+            r[2 * m] = c;
+            r[2 * m + 1] = -s;
+        }
+        return r;
+    }
+    for (int64_t m = 0; m <= n / 8; ++m) {
+        double c, s;
+        eval(m, c, s);
+        // the eight reflections: angle a -> a, pi/2 - a, pi/2 + a, ...
+        auto put = [&](int64_t k, double x, double y) {
+            k %= n;
+            r[2 * k] = x;
+            r[2 * k + 1] = -y;
+        };
+        put(m, c, s);
+        put(n / 4 - m, s, c);
+        put(n / 4 + m, -s, c);
+        put(n / 2 - m, -c, s);
+        put(n / 2 + m, -c, -s);
+        put(3 * n / 4 - m, -s, -c);
+        put(3 * n / 4 + m, s, -c);
+        put(n - m, c, -s);
+    }
+    return r;
+}
+
 static int64_t good_fft_size(int64_t nmin)
 {
     int64_t m = (nmin + TILE - 1) / TILE;
@@ -355,6 +396,30 @@ static mhk_status dalloc(mhk_plan *P, T **ptr, int64_t count)
     *ptr = nullptr;
     if (count <= 0) count = 1;
     size_t bytes = sizeof(T) * (size_t)count;
+    // buffers are cut from chunks of a quarter of what the plan already holds,
+    // 1 to 64 MiB, up to a quarter of a chunk each: a plan has a hundred of
+    // them, and every call of the allocator costs 10 to 100 us at creation and
+    // again at destruction
+    const size_t mib = 1 << 20, need = (bytes + 255) / 256 * 256;
+    const size_t size = std::min<size_t>(64, std::max<size_t>(1, (size_t)P->bytes / (4 * mib))) * mib;
+    if (P->chunk_left >= need || need <= size / 4) {
+        if (P->chunk_left < need) {
+            char *c = nullptr;
+            if (hipMallocAsync((void **)&c, size, P->stream) != hipSuccess) {
+                (void)hipGetLastError();
+                set_error("device allocation of " + std::to_string(size) + " bytes failed");
+                return MHK_ENOMEM;
+            }
+            P->allocs.push_back(c);
+            P->chunk = c;
+            P->chunk_left = size;
+            P->bytes += (int64_t)size;
+        }
+        *ptr = (T *)P->chunk;
+        P->chunk += need;
+        P->chunk_left -= need;
+        return MHK_OK;
+    }
     hipError_t e = hipMallocAsync((void **)ptr, bytes, P->stream);
     if (e != hipSuccess) {
         (void)hipGetLastError();
@@ -739,8 +804,8 @@ static mhk_status build_mask(mhk_plan *P, Host &H, StreamTmp &tmp, int8_t *rin)
 // and density chunk, between LV_PIECE_MIN (a workgroup loads the level's
 // table once, some 30 loads per thread, which a piece should outweigh) and
 // LV_PIECE_MAX sources.
-static mhk_status build_items(mhk_plan *P, const int32_t *wave_ofs, int64_t nwave, int64_t total, int ncomp,
-                              LevelItems &I)
+static mhk_status count_items(mhk_plan *P, const int32_t *wave_ofs, int64_t nwave, int64_t total, LevelItems &I,
+                              int64_t *n_dev)
 {
     const hipStream_t st = P->stream;
     const int64_t chunks = (P->p.batch + P->p.lv_bch - 1) / P->p.lv_bch;
@@ -748,16 +813,19 @@ static mhk_status build_items(mhk_plan *P, const int32_t *wave_ofs, int64_t nwav
     I.piece = (int)std::min<int64_t>(LV_PIECE_MAX, std::max<int64_t>(LV_PIECE_MIN, want));
     StreamTmp tmp(st);
     int32_t *cnt = nullptr;
-    int64_t *tot = nullptr;
     TRY(tmp.alloc(&cnt, nwave));
-    TRY(tmp.alloc(&tot, 1));
     TRY(dalloc(P, &I.ofs, nwave + 1));
     MHK_HIP(dev_item_counts(wave_ofs, nwave, I.piece, cnt, st));
-    MHK_HIP(dev_scan(cnt, I.ofs, nwave, tot, st));
-    TRY(tmp.fetch(&I.n, tot, 1));
+    MHK_HIP(dev_scan(cnt, I.ofs, nwave, n_dev, st));
+    return MHK_OK;
+}
+
+// The items themselves, once their number I.n is known.
+static mhk_status fill_items(mhk_plan *P, const int32_t *wave_ofs, int64_t nwave, int ncomp, LevelItems &I)
+{
     TRY(dalloc(P, &I.wave, I.n));
     TRY(dalloc(P, &I.order, I.n));
-    MHK_HIP(dev_item_fill(wave_ofs, I.ofs, nwave, I.n, I.piece, I.wave, I.order, st));
+    MHK_HIP(dev_item_fill(wave_ofs, I.ofs, nwave, I.n, I.piece, I.wave, I.order, P->stream));
     char *part = nullptr;
     TRY(dalloc(P, &part, I.n * ncomp * (int64_t)P->p.batch * LV_WAVE * (int64_t)P->es));
     I.part = part;
@@ -786,7 +854,9 @@ static int level_bisections(const mhk_plan *P, const Host &H, int j)
     return m;
 }
 
-mhk_status build_level(mhk_plan *P, Host &H, int j)
+// Level j's child nodes and the counts of its candidate lists (the total into
+// *tot on the device).
+mhk_status level_nodes(mhk_plan *P, Host &H, int j, int64_t *tot)
 {
     Level &L = P->lev[j - 1];
     const mhk_boundary *b = H.b;
@@ -842,31 +912,41 @@ mhk_status build_level(mhk_plan *P, Host &H, int j)
         L.n_wave = nwave;
         const double R = L.radius, R2 = R * R * (1.0 + 1e-9);
         int32_t *cnt = nullptr;
-        int64_t *tot = nullptr;
         TRY(tmp.alloc(&cnt, nwave));
-        TRY(tmp.alloc(&tot, 1));
         TRY(dalloc(P, &L.wave_ofs, nwave + 1));
         MHK_HIP(dev_wave_counts(P->tx, P->ty, nout, nwave, R, R2, L.ox, L.oy, L.cell, ncx, ncy, L.cell_start, L.sx,
                                 L.sy, cnt, st));
         MHK_HIP(dev_scan(cnt, L.wave_ofs, nwave, tot, st));
-        int64_t total = 0;
-        TRY(tmp.fetch(&total, tot, 1));
-        if (total > (int64_t)INT32_MAX) {
-            set_error("level candidate lists too large");
-            return MHK_EUNSUPPORTED;
-        }
-        L.n_cand = total;
-        TRY(dalloc(P, &L.wave_src, std::max<int64_t>(1, total)));
-        MHK_HIP(dev_wave_fill(P->tx, P->ty, nout, nwave, R, R2, L.ox, L.oy, L.cell, ncx, ncy, L.cell_start, L.sx,
-                              L.sy, L.wave_ofs, L.wave_src, st));
-        TRY(build_items(P, L.wave_ofs, nwave, total, 2, L.items));
     }
     {
         char *q = nullptr;
         TRY(dalloc(P, &q, 3 * (int64_t)P->p.batch * L.n_src * (int64_t)P->es));
         L.q = q;
     }
+    return MHK_OK;
+}
 
+// Level j's candidate lists (total sources) and the number of its work items
+// (into *n_items on the device).
+mhk_status level_lists(mhk_plan *P, int j, int64_t total, int64_t *n_items)
+{
+    Level &L = P->lev[j - 1];
+    if (total > (int64_t)INT32_MAX) {
+        set_error("level candidate lists too large");
+        return MHK_EUNSUPPORTED;
+    }
+    L.n_cand = total;
+    TRY(dalloc(P, &L.wave_src, std::max<int64_t>(1, total)));
+    const double R = L.radius, R2 = R * R * (1.0 + 1e-9);
+    MHK_HIP(dev_wave_fill(P->tx, P->ty, P->nout, L.n_wave, R, R2, L.ox, L.oy, L.cell, L.ncx, L.ncy, L.cell_start,
+                          L.sx, L.sy, L.wave_ofs, L.wave_src, P->stream));
+    return count_items(P, L.wave_ofs, L.n_wave, total, L.items, n_items);
+}
+
+// Level j's kernel table.
+mhk_status level_table(mhk_plan *P, int j)
+{
+    Level &L = P->lev[j - 1];
     // Kernel table: piecewise polynomials in a = r^2/(4 delta_j), each in the
     // local variable v in [-1, 1] of its segment; coefficients from Chebyshev
     // interpolation converted to monomials in v.  Only K_j^S is tabulated:
@@ -1041,15 +1121,29 @@ mhk_status build_level(mhk_plan *P, Host &H, int j)
 // Exponential-of-semicircle window phi(z) = exp(beta (sqrt(1 - z^2) - 1)),
 // |z| < 1 (Barnett, Magland and af Klinteberg, SIAM J. Sci. Comput. 41 (2019)),
 // and its Fourier transform in physical units by Gauss-Legendre quadrature.
-double window_ft(double k, double half_width, double beta, const std::vector<double> &qt,
-                 const std::vector<double> &qw)
+// For l < count at k = 2 pi l / period; the window and the rule are even, so
+// half the nodes serve.
+static std::vector<double> window_fts(int64_t count, double period, double half_width, double beta)
 {
-    long double s = 0;
-    for (size_t i = 0; i < qt.size(); ++i) {
-        double z = qt[i];
-        s += qw[i] * exp(beta * (sqrt(1.0 - z * z) - 1.0)) * cos(k * half_width * z);
+    static const std::vector<std::vector<double>> rule = [] {
+        std::vector<std::vector<double>> r(2);
+        gauss_legendre(160, r[0], r[1]);
+        return r;
+    }();
+    std::vector<double> z, v;
+    for (size_t i = 0; i < rule[0].size(); ++i)
+        if (rule[0][i] > 0) {
+            z.push_back(half_width * rule[0][i]);
+            v.push_back(2.0 * rule[1][i] * exp(beta * (sqrt(1.0 - rule[0][i] * rule[0][i]) - 1.0)));
+        }
+    std::vector<double> out((size_t)count);
+    for (int64_t l = 0; l < count; ++l) {
+        const double k = 2 * M_PI * l / period;
+        long double s = 0;
+        for (size_t i = 0; i < z.size(); ++i) s += v[i] * cos(k * z[i]);
+        out[(size_t)l] = (double)(s * half_width);
     }
-    return (double)(s * half_width);
+    return out;
 }
 
 // Multiplier table of the smoothly truncated history kernel g_T(x, y) =
@@ -1063,7 +1157,7 @@ double window_ft(double k, double half_width, double beta, const std::vector<dou
 // samples vanish beyond M = ceil((D + trans)/h), so the two separable
 // cosine sums over the M x M quarter grid cost O(lmax M^2) multiply-adds
 // on the device (no FFT plan to build).
-mhk_status build_trunc_table(mhk_plan *P, const std::vector<double> &qt, const std::vector<double> &qw)
+mhk_status build_trunc_table(mhk_plan *P, const std::vector<double> &wft, const std::vector<double> &roots)
 {
     History &G = P->hist;
     const double rmid = G.trunc_d + 0.5 * G.trunc_w, slope = 11.8 / G.trunc_w;
@@ -1078,13 +1172,9 @@ mhk_status build_trunc_table(mhk_plan *P, const std::vector<double> &qt, const s
     std::vector<double> t16, w16;
     gauss_legendre(16, t16, w16);
     std::vector<double> phi2inv(L1);
-    for (int l = 0; l <= G.lmax; ++l) {
-        double k = 2 * M_PI * l / G.period;
-        double ph = window_ft(k, 0.5 * G.w * G.h, G.beta, qt, qw);
-        phi2inv[l] = 1.0 / (ph * ph);
-    }
+    for (int l = 0; l <= G.lmax; ++l) phi2inv[l] = 1.0 / (wft[(size_t)l] * wft[(size_t)l]);
     std::vector<double> costab(G.n);
-    for (int64_t m = 0; m < G.n; ++m) costab[m] = (double)cosl(2.0L * M_PIl * (long double)m / (long double)G.n);
+    for (int64_t m = 0; m < G.n; ++m) costab[m] = roots[2 * (size_t)m];
     const hipStream_t st = P->stream;
     StreamTmp tmp(st);
     double *samp = nullptr, *half = nullptr, *tr = nullptr, *gt = nullptr, *gw = nullptr, *phi = nullptr,
@@ -1229,15 +1319,24 @@ mhk_status build_history(mhk_plan *P, Host &H)
         auto phi = [&](long double z) -> long double {
             return fabsl(z) < 1 ? expl((long double)G.beta * (sqrtl(1 - z * z) - 1)) : 0.0L;
         };
-        for (int k = 0; k < W; ++k) {
-            std::vector<long double> f(nfit), ch(D + 1, 0);
-            for (int i = 0; i < nfit; ++i) {
-                long double t = cosl(M_PIl * (i + 0.5L) / nfit);
-                f[i] = phi(((t + 1) / 2 - W / 2.0L + k) * 2 / W);
+        std::vector<long double> basis((size_t)(D + 1) * nfit), node(nfit);   // cos(pi m (i + 1/2) / nfit)
+        for (int i = 0; i < nfit; ++i) {
+            node[i] = cosl(M_PIl * (i + 0.5L) / nfit);
+            long double c0 = 1, c1 = node[i];
+            for (int m = 0; m <= D; ++m) {
+                basis[(size_t)m * nfit + i] = c0;
+                const long double c2 = 2 * node[i] * c1 - c0;
+                c0 = c1;
+                c1 = c2;
             }
+        }
+        // the window is even: point W - 1 - k at t is point k at -t
+        for (int k = 0; k < (W + 1) / 2; ++k) {
+            std::vector<long double> f(nfit), ch(D + 1, 0);
+            for (int i = 0; i < nfit; ++i) f[i] = phi(((node[i] + 1) / 2 - W / 2.0L + k) * 2 / W);
             for (int m = 0; m <= D; ++m) {
                 long double acc = 0;
-                for (int i = 0; i < nfit; ++i) acc += f[i] * cosl(M_PIl * m * (i + 0.5L) / nfit);
+                for (int i = 0; i < nfit; ++i) acc += f[i] * basis[(size_t)m * nfit + i];
                 ch[m] = acc * (m == 0 ? 1.0L : 2.0L) / nfit;
             }
             std::vector<long double> mono(D + 1, 0), tp(D + 1, 0), tc(D + 1, 0), tn(D + 1, 0);
@@ -1254,7 +1353,11 @@ mhk_status build_history(mhk_plan *P, Host &H)
                 tp = tc;
                 tc = tn;
             }
-            for (int j = 0; j <= D; ++j) cf[(size_t)k * (D + 1) + j] = (double)mono[j];
+            for (int j = 0; j <= D; ++j) {
+                cf[(size_t)k * (D + 1) + j] = (double)mono[j];
+                if (W - 1 - k != k)
+                    cf[(size_t)(W - 1 - k) * (D + 1) + j] = j % 2 ? -(double)mono[j] : (double)mono[j];
+            }
             for (int i = 0; i <= 400; ++i) {
                 double t = -1.0 + 2.0 * i / 400.0;
                 double pv = 0;
@@ -1280,23 +1383,20 @@ mhk_status build_history(mhk_plan *P, Host &H)
             G.wcoef = d;
         }
     }
-    // multiplier factors
-    std::vector<double> qt, qw;
-    gauss_legendre(160, qt, qw);
+    // multiplier factors, on the modes up to the cut-off (and lmax of the
+    // truncated kernel, which the rounding of its floor may put one further)
     const int64_t nh = G.n / 2 + 1;
+    const int64_t nk = std::min<int64_t>(nh, (int64_t)floor(G.kcut * G.period / (2 * M_PI)) + 2);
+    const std::vector<double> wft = window_fts(nk, G.period, 0.5 * G.w * G.h, G.beta);
+    const std::vector<double> roots = unit_roots(G.n);
     std::vector<double> fac(nh);
     for (int64_t l = 0; l < nh; ++l) {
         double k = 2 * M_PI * l / G.period;
-        if (k > G.kcut) {
-            fac[l] = 0;
-            continue;
-        }
-        double ph = window_ft(k, 0.5 * G.w * G.h, G.beta, qt, qw);
-        fac[l] = exp(-delta * k * k) / (ph * ph);
+        fac[l] = k > G.kcut || l >= nk ? 0.0 : exp(-delta * k * k) / (wft[(size_t)l] * wft[(size_t)l]);
     }
     G.mult_c = pow(G.h, 4) / (G.period * G.period) * exp(-delta * alpha * alpha);
     TRY(upload(P, &G.fac, fac.data(), nh));
-    if (G.trunc) TRY(build_trunc_table(P, qt, qw));
+    if (G.trunc) TRY(build_trunc_table(P, wft, roots));
     // columns l_x that can hold a nonzero multiplier
     G.ncol = 0;
     if (G.trunc) {
@@ -1426,16 +1526,9 @@ mhk_status build_history(mhk_plan *P, Host &H)
     G.colpath = G.n <= COL_NMAX && G.n % 2 == 0 && factor(G.n, G.radix, G.npass) &&
                 factor(G.n / 2, G.rradix, G.rnpass);
     if (G.colpath) {
-        const size_t n1 = (size_t)G.n;
         // twiddles e^{-2 pi i m / n}
-        std::vector<double> tw(2 * n1);
-        for (size_t m = 0; m < n1; ++m) {
-            const long double a = -2.0L * M_PIl * (long double)m / (long double)n1;
-            tw[2 * m] = (double)cosl(a);
-            tw[2 * m + 1] = (double)sinl(a);
-        }
         double *d = nullptr;
-        TRY(upload(P, &d, tw.data(), (int64_t)tw.size()));
+        TRY(upload(P, &d, roots.data(), (int64_t)roots.size()));
         G.tw = d;
     } else {
         // rocFFT 2D transforms around k_multiply
@@ -1568,7 +1661,7 @@ mhk_status build_local(mhk_plan *P, Host &H)
                     if (ex * ex + ey * ey <= C.reach * C.reach) pairs.push_back({iy * ncx + ix, p});
                 }
         }
-        if (pairs.size() > ((size_t)1 << 31)) {
+        if (pairs.size() > (size_t)INT32_MAX) {
             set_error("closest-point cell lists too large");
             return MHK_EUNSUPPORTED;
         }
@@ -1580,24 +1673,26 @@ mhk_status build_local(mhk_plan *P, Host &H)
             const double ey = std::max(0.0, std::max(bb[2] - yc, yc - bb[3]));
             return ex * ex + ey * ey;
         };
-        // (the distance formed once per pair, not per comparison)
+        // counted into cells, then each cell's few panels sorted (the distance
+        // formed once per pair)
         struct Key {
-            int64_t cell;
             double d;
-            int64_t panel;
+            int32_t panel;
         };
         std::vector<Key> keys(pairs.size());
-        for (size_t k = 0; k < pairs.size(); ++k) keys[k] = {pairs[k][0], dist_c(pairs[k][0], pairs[k][1]), pairs[k][1]};
-        std::sort(keys.begin(), keys.end(), [](const Key &a, const Key &c) {
-            if (a.cell != c.cell) return a.cell < c.cell;
-            return a.d != c.d ? a.d < c.d : a.panel < c.panel;
-        });
-        cand.resize(std::max<size_t>(1, keys.size()));
-        for (size_t k = 0; k < keys.size(); ++k) {
-            start[keys[k].cell + 1]++;
-            cand[k] = (int32_t)keys[k].panel;
-        }
+        for (const auto &q : pairs) start[q[0] + 1]++;
         for (int64_t c = 0; c < ncx * ncy; ++c) start[c + 1] += start[c];
+        {
+            std::vector<int32_t> at(start.begin(), start.end() - 1);
+            for (const auto &q : pairs) keys[(size_t)at[q[0]]++] = {dist_c(q[0], q[1]), (int32_t)q[1]};
+        }
+        for (int64_t c = 0; c < ncx * ncy; ++c)
+            if (start[c + 1] - start[c] > 1)
+                std::sort(keys.begin() + start[c], keys.begin() + start[c + 1], [](const Key &a, const Key &e) {
+                    return a.d != e.d ? a.d < e.d : a.panel < e.panel;
+                });
+        cand.resize(std::max<size_t>(1, keys.size()));
+        for (size_t k = 0; k < keys.size(); ++k) cand[k] = keys[k].panel;
         TRY(upload(P, &C.cand, cand.data(), (int64_t)cand.size()));
         TRY(upload(P, &C.cell_start, start.data(), (int64_t)start.size()));
     }
@@ -1609,22 +1704,29 @@ mhk_status build_local(mhk_plan *P, Host &H)
         // panel whose box is farther than the best distance found cannot hold
         // the closest point
         std::vector<double> cbox(npan * 4);
-        const int ns = 129;
-        for (int64_t p = 0; p < npan; ++p) {
-            double x0 = 1e300, x1 = -1e300, y0 = 1e300, y1 = -1e300;
+        constexpr int ns = 129;
+        static const std::vector<double> pk = [] {       // P_k at the points, [NGL][ns]
+            std::vector<double> t(NGL * ns);
             for (int i = 0; i < ns; ++i) {
-                const double t = -cos(M_PI * i / (ns - 1));
-                double p0 = 1, p1 = t, xv = cx[p * NGL] + cx[p * NGL + 1] * t, yv = cy[p * NGL] + cy[p * NGL + 1] * t;
-                for (int k = 1; k + 1 < NGL; ++k) {
-                    const double p2 = ((2 * k + 1) * t * p1 - k * p0) / (k + 1);
-                    p0 = p1;
-                    p1 = p2;
-                    xv += cx[p * NGL + k + 1] * p2;
-                    yv += cy[p * NGL + k + 1] * p2;
-                }
-                x0 = std::min(x0, xv); x1 = std::max(x1, xv);
-                y0 = std::min(y0, yv); y1 = std::max(y1, yv);
+                const double x = -cos(M_PI * i / (ns - 1));
+                t[i] = 1;
+                t[ns + i] = x;
+                for (int k = 1; k + 1 < NGL; ++k)
+                    t[(k + 1) * ns + i] = ((2 * k + 1) * x * t[k * ns + i] - k * t[(k - 1) * ns + i]) / (k + 1);
             }
+            return t;
+        }();
+        for (int64_t p = 0; p < npan; ++p) {
+            double xv[ns] = {0}, yv[ns] = {0};
+            for (int k = 0; k < NGL; ++k) {
+                const double a = cx[p * NGL + k], c = cy[p * NGL + k], *q = &pk[(size_t)k * ns];
+                for (int i = 0; i < ns; ++i) {
+                    xv[i] += a * q[i];
+                    yv[i] += c * q[i];
+                }
+            }
+            const double x0 = *std::min_element(xv, xv + ns), x1 = *std::max_element(xv, xv + ns);
+            const double y0 = *std::min_element(yv, yv + ns), y1 = *std::max_element(yv, yv + ns);
             const double m = 0.01 * std::max(x1 - x0, y1 - y0) + 1e-12;
             cbox[p * 4 + 0] = x0 - m; cbox[p * 4 + 1] = x1 + m;
             cbox[p * 4 + 2] = y0 - m; cbox[p * 4 + 3] = y1 + m;
@@ -1792,7 +1894,9 @@ mhk_status build_vlevels(mhk_plan *P, Host &H)
         TRY(dalloc(P, &V.wave_src, std::max<int64_t>(1, total)));
         MHK_HIP(dev_wave_fill(P->tx, P->ty, nout, nwave, R, R2, L.ox, L.oy, L.cell, L.ncx, L.ncy, V.cell_start, V.sx,
                               V.sy, V.wave_ofs, V.wave_src, st));
-        TRY(build_items(P, V.wave_ofs, nwave, total, 1, V.items));
+        TRY(count_items(P, V.wave_ofs, nwave, total, V.items, tot));
+        TRY(tmp.fetch(&V.items.n, tot, 1));
+        TRY(fill_items(P, V.wave_ofs, nwave, 1, V.items));
     }
     MHK_HIP(hipStreamSynchronize(st));
     return MHK_OK;
@@ -1879,7 +1983,23 @@ mhk_status create(const mhk_params *params, const mhk_boundary *b, const mhk_vol
         MHK_HIP(dev_sort_targets(rx, ry, rin, nout, ox, oy, hh, P->tx, P->ty, P->tin, P->tidx, P->stream));
     }
     lap(1);
-    for (int j = 1; j <= P->J; ++j) TRY(build_level(P, H, j));
+    if (P->J > 0) {
+        // the levels' totals and item counts come back in one wait each; the
+        // tables are formed on the host while the device counts
+        StreamTmp tmp(P->stream);
+        int64_t *dev = nullptr, tot[MAXJ];
+        TRY(tmp.alloc(&dev, 2 * MAXJ));
+        for (int j = 1; j <= P->J; ++j) TRY(level_nodes(P, H, j, dev + j - 1));
+        for (int j = 1; j <= P->J; ++j) TRY(level_table(P, j));
+        TRY(tmp.fetch(tot, dev, P->J));
+        for (int j = 1; j <= P->J; ++j) TRY(level_lists(P, j, tot[j - 1], dev + MAXJ + j - 1));
+        TRY(tmp.fetch(tot, dev + MAXJ, P->J));
+        for (int j = 1; j <= P->J; ++j) {
+            Level &L = P->lev[j - 1];
+            L.items.n = tot[j - 1];
+            TRY(fill_items(P, L.wave_ofs, L.n_wave, 2, L.items));
+        }
+    }
     lap(2);
     TRY(build_history(P, H));
     MHK_HIP(hipStreamSynchronize(P->stream));
