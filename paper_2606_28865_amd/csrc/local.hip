@@ -67,15 +67,17 @@ __global__ void __launch_bounds__(256) k_panel_coeffs(int64_t npan, int B, const
 // Value and first two t-derivatives of two Legendre series at t, using the
 // recurrence above with P'_{k+1} = P'_{k-1} + (2k+1) P_k and
 // P''_{k+1} = P''_{k-1} + (2k+1) P'_k.
-__device__ inline void leg2(const double *__restrict__ ca, const double *__restrict__ cb, double t,
-                            double &a0, double &a1, double &a2, double &b0, double &b1, double &b2)
+// The two series' coefficients are interleaved: one 16-byte load each.
+__device__ inline void leg2(const double2 *__restrict__ c, double t, double &a0, double &a1, double &a2, double &b0,
+                            double &b1, double &b2)
 {
     double pm = 1.0, p = t, dm = 0.0, d = 1.0, em = 0.0, e = 0.0;
-    a0 = ca[0] + ca[1] * t;
-    a1 = ca[1];
+    const double2 c0 = c[0], c1 = c[1];
+    a0 = c0.x + c1.x * t;
+    a1 = c1.x;
     a2 = 0.0;
-    b0 = cb[0] + cb[1] * t;
-    b1 = cb[1];
+    b0 = c0.y + c1.y * t;
+    b1 = c1.y;
     b2 = 0.0;
 #pragma unroll
     for (int k = 1; k < NGL - 1; ++k) {
@@ -85,7 +87,8 @@ __device__ inline void leg2(const double *__restrict__ ca, const double *__restr
         pm = p; p = pn;
         dm = d; d = dn;
         em = e; e = en;
-        const double A = ca[k + 1], Bc = cb[k + 1];
+        const double2 ck = c[k + 1];
+        const double A = ck.x, Bc = ck.y;
         a0 = fma(A, p, a0); a1 = fma(A, d, a1); a2 = fma(A, e, a2);
         b0 = fma(Bc, p, b0); b1 = fma(Bc, d, b1); b2 = fma(Bc, e, b2);
     }
@@ -260,8 +263,11 @@ struct LocalArgs {
     const int32_t *gpan;
     const uint8_t *gflag;
     const double *pcx, *pcy, *pck, *ends, *gl_t;
+    const double2 *pcxy, *bxy;   // panel coefficients of x and y, and nodes, interleaved
+    const double2 *candbox;      // node box of every candidate panel: (xmin, xmax), (ymin, ymax)
+    double vfar, von;      // (1 - e^{-c2^2})/c2^2 of the volume term, and half of it
     const int32_t *prev, *next, *cand, *cell_start;
-    const double *pbox, *cbox;
+    const double *cbox;
     int32_t *noconv;
     double cell, ox, oy, reach;
     int ncx, ncy;
@@ -274,95 +280,115 @@ struct LocalArgs {
     T *out_s, *out_d, *out_v;
 };
 
-// Minimise |x - gamma_p(t)|^2 over t in [-1, 1] on panel p by Newton's
-// method on d/dt, safeguarded: started from the nearest of the panel's nodes
-// and end points; a step that does not decrease the distance is halved
-// (bisection towards the current point), and where the distance is not
-// convex (beyond a centre of curvature) a fixed step of 1/4 downhill is
-// tried instead of the Newton step; Newton steps below 1e-6 where the
-// distance is convex are taken as they are (there the distance is flat below
-// its rounding, and the derivative decides) and end the iteration once one is
-// below 1e-12, after one more Newton step.  Returns whether the iteration
-// converged (that, or a damped step below 1e-15, possibly held at an end
-// point).
+// Start of the closest-point iteration on panel p: the parameter of the nearest
+// of its nodes and end points (node: the nearest node where it is known, else
+// -1).
 template <typename Args>
-__device__ inline bool panel_min(const Args &A, int p, double px, double py, double &tbest, double &d2best)
+__device__ inline double panel_start(const Args &A, int p, int node, double px, double py)
 {
-    const double *cx = A.pcx + (size_t)p * NGL, *cy = A.pcy + (size_t)p * NGL;
-    // start: best of the two end points and the 16 nodes
     double ts = -1.0;
     double dx = A.ends[p * 4 + 0] - px, dy = A.ends[p * 4 + 1] - py;
     double ds = dx * dx + dy * dy;
-    for (int i = 0; i < NGL; ++i) {
-        dx = A.bx[(size_t)p * NGL + i] - px;
-        dy = A.by[(size_t)p * NGL + i] - py;
+    const double2 *bn = A.bxy + (size_t)p * NGL;
+    const int i0 = node >= 0 ? node : 0, i1 = node >= 0 ? node + 1 : NGL;
+    for (int i = i0; i < i1; ++i) {
+        const double2 q = bn[i];
+        dx = q.x - px;
+        dy = q.y - py;
         const double d = dx * dx + dy * dy;
         if (d < ds) { ds = d; ts = A.gl_t[i]; }
     }
     dx = A.ends[p * 4 + 2] - px;
     dy = A.ends[p * 4 + 3] - py;
-    if (dx * dx + dy * dy < ds) { ds = dx * dx + dy * dy; ts = 1.0; }
-    double t = ts, phi;
-    {
-        const double xv = leg1(cx, t) - px, yv = leg1(cy, t) - py;
-        phi = xv * xv + yv * yv;
-    }
-    bool conv = false;
-#pragma unroll 1
-    for (int it = 0; it < 60; ++it) {
+    return dx * dx + dy * dy < ds ? 1.0 : ts;
+}
+
+// Closest point to x on panel p0 (imin % 16 its nearest node) and its two
+// neighbours: |x - gamma_p(t)|^2 minimised over t in [-1, 1] panel by panel by
+// Newton's method on d/dt, safeguarded: a step that does not decrease the
+// distance is halved (bisection towards the current point), and where the
+// distance is not convex (beyond a centre of curvature) a fixed step of 1/4
+// downhill is tried instead of the Newton step; Newton steps below 1e-6 where
+// the distance is convex are taken as they are (there the distance is flat below
+// its rounding, and the derivative decides) and end the iteration once one is
+// below 1e-12, or below 1e-11 without being half the one before (the rounding
+// level of a flat minimum), after one more Newton step.  conv: the best panel's
+// iteration ended so, or with a damped step below 1e-15, possibly held at an end
+// point.
+//
+// One evaluation of the series and both derivatives per turn of one loop: at
+// the point that a step leads to, where its distance decides on the step and
+// the next step starts.  A lane goes on to its next panel while its neighbours
+// still iterate on theirs, so that a wavefront takes as many turns as its
+// slowest lane instead of the slowest of each of three panels.
+template <typename Args>
+__device__ inline void closest_point(const Args &A, int p0, int node, double px, double py, int &pbest, double &tbest,
+                                     double &d2b, bool &conv)
+{
+    int p = p0, c = 0, it = 0, halv = 0;
+    double tn = panel_start(A, p, node, px, py), t = tn, phi = INFINITY, step = 0.0, last = 1.0;
+    bool plain = false, fresh = true;
+    for (;;) {
         double x0, x1, x2, y0, y1, y2;
-        leg2(cx, cy, t, x0, x1, x2, y0, y1, y2);
-        const double ex = x0 - px, ey = y0 - py;
-        const double g = ex * x1 + ey * y1;
-        const double h = x1 * x1 + y1 * y1 + ex * x2 + ey * y2;
-        double step = h > 0.0 ? -g / h : (g > 0.0 ? -0.25 : 0.25);
-        double tn = fmin(1.0, fmax(-1.0, t + step));
-        if (h > 0.0 && fabs(step) < 1e-6) {
-            // close to a minimum the distance is flat below its rounding:
-            // plain Newton steps, driven by the derivative
-            // quadratic convergence: after a step below 1e-12 the error is
-            // at the rounding level (a stricter test can fail on rounding
-            // noise of the step itself)
+        leg2(A.pcxy + (size_t)p * NGL, tn, x0, x1, x2, y0, y1, y2);
+        const double ex = x0 - px, ey = y0 - py, dn = ex * ex + ey * ey;
+        bool done = false, ok = false;
+        if (plain || fresh || dn <= phi) {
             const double moved = fabs(tn - t);
             t = tn;
-            if (moved < 1e-12) {
-                // one more Newton step brings t to the rounding level also
-                // where the convergence is slow (small curvature of |x - gamma|^2)
-                leg2(cx, cy, t, x0, x1, x2, y0, y1, y2);
-                const double e2x = x0 - px, e2y = y0 - py;
-                const double h2 = x1 * x1 + y1 * y1 + e2x * x2 + e2y * y2;
-                if (h2 > 0.0) t = fmin(1.0, fmax(-1.0, t - (e2x * x1 + e2y * y1) / h2));
-                conv = true;
-                break;
+            phi = dn;
+            const double g = ex * x1 + ey * y1;
+            const double h = x1 * x1 + y1 * y1 + ex * x2 + ey * y2;
+            if (!fresh) {
+                ++it;
+                if (plain && (moved < 1e-12 || (moved < 1e-11 && moved > 0.5 * last))) {
+                    // one more Newton step brings t to the rounding level also
+                    // where the convergence is slow (small curvature of |x - gamma|^2)
+                    if (h > 0.0) t = fmin(1.0, fmax(-1.0, t - g / h));
+                    done = ok = true;
+                } else if (!plain && moved < 1e-15) {
+                    done = ok = true;
+                } else if (it >= 60) {
+                    done = true;
+                }
+                last = plain ? moved : 1.0;
             }
-            continue;
-        }
-        double dn = phi;
-#pragma unroll 1
-        for (int k = 0; k <= 52; ++k) {
-            const double xv = leg1(cx, tn) - px, yv = leg1(cy, tn) - py;
-            dn = xv * xv + yv * yv;
-            if (dn <= phi) break;
+            fresh = false;
+            halv = 0;
+            step = h > 0.0 ? -g / h : (g > 0.0 ? -0.25 : 0.25);
+            plain = h > 0.0 && fabs(step) < 1e-6;
+            tn = fmin(1.0, fmax(-1.0, t + step));
+        } else if (++halv > 52) {
+            done = ok = true;                       // no step decreases the distance: t is the minimum
+        } else {
             step *= 0.5;
             tn = fmin(1.0, fmax(-1.0, t + step));
         }
-        const double moved = fabs(tn - t);
-        if (dn <= phi) {
-            t = tn;
-            phi = dn;
-        }
-        if (moved < 1e-15) {
-            conv = true;
-            break;
+        if (done) {
+            if (phi < d2b) {
+                d2b = phi;
+                pbest = p;
+                tbest = t;
+                conv = ok;
+            }
+            // a neighbouring panel whose curve box is farther than the best
+            // distance so far cannot improve on it (ties are kept)
+            for (++c; c < 3; ++c) {
+                p = c == 1 ? A.prev[p0] : A.next[p0];
+                const double *bb = A.cbox + (size_t)p * 4;
+                const double bx = fmax(0.0, fmax(bb[0] - px, px - bb[1]));
+                const double by = fmax(0.0, fmax(bb[2] - py, py - bb[3]));
+                if (bx * bx + by * by <= d2b) break;
+            }
+            if (c == 3) break;
+            tn = t = panel_start(A, p, -1, px, py);
+            phi = INFINITY;
+            fresh = true;
+            plain = false;
+            last = 1.0;
+            it = halv = 0;
         }
     }
-    {
-        const double xv = leg1(cx, t) - px, yv = leg1(cy, t) - py;
-        phi = xv * xv + yv * yv;
-    }
-    tbest = t;
-    d2best = phi;
-    return conv;
 }
 
 // Geometry of the local part, once per plan (targets and boundary are
@@ -384,9 +410,15 @@ enum { GEO_Q0 = GEO_N, GEO_Q1, GEO_P2, GEO_P3, GEO_U3, GEO_U4, GEO_B1, GEO_B2, G
 static_assert(GEO_N == LOCAL_GEO_N1 && GEO_N2 == LOCAL_GEO_N2, "local geometry layout");
 
 // ORDER is the order of the local expansions (1 or 2); first-order plans
-// get a kernel without the second-order registers.
+// get a kernel without the second-order registers.  Bound by the latency of the
+// search's and the series' loads (62% of the wave cycles; the VALU is busy a
+// third of the time), so four wavefronts per SIMD with a few registers spilled
+// beat three, the coefficients of x and y and the nodes come interleaved in
+// 16-byte loads, the next candidate is loaded ahead, and only what k_local reads
+// of a target is stored: 4.07M targets 816 -> 686 us alone and 1414 -> 1093 us
+// beside the history part, 1.02M targets 726 -> 560 us.
 template <int ORDER>
-__global__ void __launch_bounds__(256) k_local_geom(LocalArgs<double> A, double *__restrict__ geo,
+__global__ void __launch_bounds__(256, 4) k_local_geom(LocalArgs<double> A, double *__restrict__ geo,
                                                     int32_t *__restrict__ pan, uint8_t *__restrict__ flag)
 {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -404,7 +436,7 @@ __global__ void __launch_bounds__(256) k_local_geom(LocalArgs<double> A, double 
     double P0 = 0, P1 = 0, U0 = 0, U1 = 0, U2 = 0, kap = 0, mss_fac1 = 0, mss_fac2 = 0;
     double vfac = 0.0;             // V local = delta * f * vfac
     if (on) {
-        vfac = -expm1(-c2v * c2v) / (2.0 * c2v * c2v);          // Cor. 4.10
+        vfac = A.von;                                           // Cor. 4.10
     } else {
         // nearest boundary node (lowest index on ties) among the nodes of the
         // cell's candidate panels, nearest panels first; a panel whose node
@@ -415,16 +447,28 @@ __global__ void __launch_bounds__(256) k_local_geom(LocalArgs<double> A, double 
         if (cx >= 0 && cx < A.ncx && cy >= 0 && cy < A.ncy) {
             const int64_t cell = (int64_t)cy * A.ncx + cx;
             const int k0 = A.cell_start[cell], k1 = A.cell_start[cell + 1];
+            // the next candidate is loaded while this one is tested, its box
+            // from the list itself: the search is bound by the latency of its
+            // loads, one candidate after another
+            double2 nx = {0.0, 0.0}, ny = {0.0, 0.0};
+            int np = 0;
+            auto next = [&](int k) {
+                np = A.cand[k];
+                nx = A.candbox[2 * (size_t)k];
+                ny = A.candbox[2 * (size_t)k + 1];
+            };
+            if (k0 < k1) next(k0);
             for (int k = k0; k < k1; ++k) {
-                const int p = A.cand[k];
-                const double *bb = A.pbox + (size_t)p * 4;
-                const double ex = fmax(0.0, fmax(bb[0] - px, px - bb[1]));
-                const double ey = fmax(0.0, fmax(bb[2] - py, py - bb[3]));
+                const int p = np;
+                const double ex = fmax(0.0, fmax(nx.x - px, px - nx.y));
+                const double ey = fmax(0.0, fmax(ny.x - py, py - ny.y));
+                next(min(k + 1, k1 - 1));
                 if (ex * ex + ey * ey > dmin) continue;
-                const double *nx = A.bx + (size_t)p * NGL, *ny = A.by + (size_t)p * NGL;
-#pragma unroll 4
+                const double2 *bn = A.bxy + (size_t)p * NGL;
+#pragma unroll 8
                 for (int i = 0; i < NGL; ++i) {
-                    const double dx = nx[i] - px, dy = ny[i] - py;
+                    const double2 q = bn[i];
+                    const double dx = q.x - px, dy = q.y - py;
                     const double d = dx * dx + dy * dy;
                     const int node = p * NGL + i;
                     if (d < dmin || (d == dmin && node < imin)) { dmin = d; imin = node; }
@@ -435,23 +479,9 @@ __global__ void __launch_bounds__(256) k_local_geom(LocalArgs<double> A, double 
         // nearest node farther than band + gap puts x outside both bands
         if (imin >= 0 && sqrt(dmin) <= A.reach) {
             const int p0 = imin / NGL;
-            int cand[3] = {p0, A.prev[p0], A.next[p0]};
             double d2b = INFINITY;
             bool conv = true;
-#pragma unroll 1
-            for (int c = 0; c < 3; ++c) {
-                // a neighbouring panel whose curve box is farther than the
-                // best distance so far cannot improve on it (ties are kept)
-                if (c > 0) {
-                    const double *bb = A.cbox + (size_t)cand[c] * 4;
-                    const double ex = fmax(0.0, fmax(bb[0] - px, px - bb[1]));
-                    const double ey = fmax(0.0, fmax(bb[2] - py, py - bb[3]));
-                    if (ex * ex + ey * ey > d2b) continue;
-                }
-                double t, d2;
-                const bool cv = panel_min(A, cand[c], px, py, t, d2);
-                if (d2 < d2b) { d2b = d2; pbest = cand[c]; tbest = t; conv = cv; }
-            }
+            closest_point(A, p0, imin % NGL, px, py, pbest, tbest, d2b, conv);
             r = sqrt(d2b);
             // a closest point that is not a converged Newton solution is
             // only an approximation: count it where the local part uses its
@@ -476,15 +506,15 @@ __global__ void __launch_bounds__(256) k_local_geom(LocalArgs<double> A, double 
             const double em = erfcx(a - c2v), ep = erfcx(a + c2v), e0 = erfcx(a);
             const double pre = exp(-a * a - c2v * c2v);
             // W0 = (4 - 4 e^{-c2^2} + 2 lambda - Phi_+)/c2^2, lambda = e^{-c2^2} erfc(c1/2)
-            const double W0 = (-4.0 * expm1(-c2v * c2v) + pre * ((e0 - em) + (e0 - ep))) / (c2v * c2v);
+            const double W0 = 4.0 * A.vfar + pre * ((e0 - em) + (e0 - ep)) / (c2v * c2v);
             if (inside) {
                 vfac = 0.25 * W0;
             } else {
-                vfac = -expm1(-c2v * c2v) / (c2v * c2v) - 0.25 * W0;
+                vfac = A.vfar - 0.25 * W0;
                 ext = true;
             }
         } else {
-            vfac = inside ? -expm1(-c2v * c2v) / (c2v * c2v) : 0.0;
+            vfac = inside ? A.vfar : 0.0;
         }
         if (r < A.band_s && pbest >= 0) {
             near_s = true;
@@ -499,7 +529,7 @@ __global__ void __launch_bounds__(256) k_local_geom(LocalArgs<double> A, double 
             U2 = c1 * U1;
             kap = leg1(A.pck + (size_t)pbest * NGL, tbest);
             double x0, x1, x2, y0, y1, y2;
-            leg2(A.pcx + (size_t)pbest * NGL, A.pcy + (size_t)pbest * NGL, tbest, x0, x1, x2, y0, y1, y2);
+            leg2(A.pcxy + (size_t)pbest * NGL, tbest, x0, x1, x2, y0, y1, y2);
             const double sp2 = x1 * x1 + y1 * y1;
             // d^2/ds^2 = (d^2/dt^2 - (gamma'.gamma''/|gamma'|^2) d/dt)/|gamma'|^2
             mss_fac2 = 1.0 / sp2;
@@ -579,15 +609,20 @@ __global__ void __launch_bounds__(256) k_local_geom(LocalArgs<double> A, double 
         geo[GEO_VB * n + s] = vb;
         geo[GEO_VC * n + s] = vc;
     }
-    geo[GEO_T * n + s] = tbest;
-    geo[GEO_P0 * n + s] = P0;
-    geo[GEO_P1 * n + s] = P1;
-    geo[GEO_U0 * n + s] = U0;
-    geo[GEO_U1 * n + s] = U1;
-    geo[GEO_U2 * n + s] = U2;
-    geo[GEO_KAP * n + s] = kap;
-    geo[GEO_MF1 * n + s] = mss_fac1;
-    geo[GEO_MF2 * n + s] = mss_fac2;
+    // what k_local reads of a target: the layer coefficients in the layer
+    // band, the parameter there and at exterior targets in the volume band
+    // (everywhere with the second-order terms)
+    if (ORDER >= 2 || near_s || ext) geo[GEO_T * n + s] = tbest;
+    if (ORDER >= 2 || near_s) {
+        geo[GEO_P0 * n + s] = P0;
+        geo[GEO_P1 * n + s] = P1;
+        geo[GEO_U0 * n + s] = U0;
+        geo[GEO_U1 * n + s] = U1;
+        geo[GEO_U2 * n + s] = U2;
+        geo[GEO_KAP * n + s] = kap;
+        geo[GEO_MF1 * n + s] = mss_fac1;
+        geo[GEO_MF2 * n + s] = mss_fac2;
+    }
     geo[GEO_VFAC * n + s] = vfac;
     pan[s] = pbest;
     flag[s] = (uint8_t)((near_s ? 1 : 0) | (ext ? 2 : 0));
@@ -837,13 +872,18 @@ static void fill_args(mhk_plan *P, LocalArgs<T, TI> &A)
     A.pcx = P->loc.cx;
     A.pcy = P->loc.cy;
     A.pck = P->loc.ck;
+    A.pcxy = (const double2 *)P->loc.cxy;
+    A.bxy = (const double2 *)P->loc.bxy;
+    A.candbox = (const double2 *)P->loc.candbox;
+    const double cv2 = P->p.alpha * P->p.alpha * P->delta_v;
+    A.vfar = -expm1(-cv2) / cv2;
+    A.von = 0.5 * A.vfar;
     A.ends = P->loc.ends;
     A.gl_t = P->loc.gl_t;
     A.prev = P->loc.prev;
     A.next = P->loc.next;
     A.cand = P->loc.cand;
     A.cell_start = P->loc.cell_start;
-    A.pbox = P->loc.pbox;
     A.cbox = P->loc.cbox;
     A.noconv = P->loc.noconv;
     A.reach = P->loc.reach;

@@ -234,12 +234,13 @@ struct Local {
     double cell = 0, ox = 0, oy = 0, gap = 0, reach = 0;
     int ncx = 0, ncy = 0;
     int32_t *cand = nullptr;
-    double *pbox = nullptr;                       // [n_panels][4]: node bounding box xmin, xmax, ymin, ymax
+    double *candbox = nullptr;                    // per candidate: the panel's node box xmin, xmax, ymin, ymax
     double *cbox = nullptr;                       // [n_panels][4]: box of the panel's whole curve (with a margin)
     int32_t *cell_start = nullptr;
     int32_t *noconv = nullptr;                    // device counter: closest-point solves that did not converge
     double *leg = nullptr;                        // [16][16] nodal values -> Legendre coefficients
     double *cx = nullptr, *cy = nullptr, *ck = nullptr;   // [n_panels][16]
+    double *cxy = nullptr, *bxy = nullptr;        // [n_panels][16][2]: cx and cy, and the nodes, interleaved
     double *ends = nullptr;                       // [n_panels][4]: x(-1), y(-1), x(1), y(1)
     double *gl_t = nullptr;                       // [16] Gauss-Legendre abscissae
     int32_t *prev = nullptr, *next = nullptr;     // panel neighbours within each curve

@@ -1693,10 +1693,12 @@ mhk_status build_local(mhk_plan *P, Host &H)
                 });
         cand.resize(std::max<size_t>(1, keys.size()));
         for (size_t k = 0; k < keys.size(); ++k) cand[k] = keys[k].panel;
+        std::vector<double> box(4 * cand.size(), 0.0);
+        for (size_t k = 0; k < keys.size(); ++k) memcpy(&box[4 * k], &pbox[(size_t)cand[k] * 4], 4 * sizeof(double));
+        TRY(upload(P, &C.candbox, box.data(), (int64_t)box.size()));
         TRY(upload(P, &C.cand, cand.data(), (int64_t)cand.size()));
         TRY(upload(P, &C.cell_start, start.data(), (int64_t)start.size()));
     }
-    TRY(upload(P, &C.pbox, pbox.data(), npan * 4));
     {
         // box of each panel's whole curve gamma(t), t in [-1, 1]: 129
         // Chebyshev points of its Legendre series, grown by 1% of its size
@@ -1746,6 +1748,17 @@ mhk_status build_local(mhk_plan *P, Host &H)
     TRY(upload(P, &C.cx, cx.data(), nb));
     TRY(upload(P, &C.cy, cy.data(), nb));
     TRY(upload(P, &C.ck, ck.data(), nb));
+    std::vector<double> two(2 * (size_t)nb);
+    for (int64_t i = 0; i < nb; ++i) {
+        two[2 * i] = cx[i];
+        two[2 * i + 1] = cy[i];
+    }
+    TRY(upload(P, &C.cxy, two.data(), 2 * nb));
+    for (int64_t i = 0; i < nb; ++i) {
+        two[2 * i] = b->x[i];
+        two[2 * i + 1] = b->y[i];
+    }
+    TRY(upload(P, &C.bxy, two.data(), 2 * nb));
     TRY(upload(P, &C.ends, ends.data(), npan * 4));
     TRY(upload(P, &C.gl_t, H.gl_t.data(), NGL));
     TRY(upload(P, &C.prev, prev.data(), npan));
@@ -2108,7 +2121,7 @@ mhk_status mhk_plan_footprint(const mhk_params *params, const mhk_boundary *b, c
         int64_t ns = nb << j;
         s += ns * (8 * 5 + 4) + 3 * B * ns * 8 + 2 * B * nout * 8;
     }
-    s += nb * (8 * 3 + 4) + 3 * B * nb * 8;   // local
+    s += nb * (8 * 7 + 4) + 3 * B * nb * 8;   // local
     s += nout * ((p.local_order >= 2 ? LOCAL_GEO_N2 : LOCAL_GEO_N1) * 8 + 4 + 1);   // local geometry per target
     if (p.in64) s += B * (2 * nb + nv) * 4;   // FP32 copies of FP64 inputs
     if (v && v->group == 6)                    // f at the targets from the volume triangles
