@@ -14,6 +14,7 @@
 #include <cmath>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "mhk_internal.h"
@@ -37,6 +38,7 @@ struct mhk_nystrom {
     int2 *item = nullptr;       // [nitem] strip and first tile column
     int32_t *item_ofs = nullptr;  // [nstrip + 1] items of each strip
     NysPart prod[3];            // NYS_APPLY, NYS_SOLVE, NYS_NOALLOC
+    std::mutex apply_mu;        // a product's two launches, which share prod[NYS_APPLY]
     double *na_part = nullptr;  // gpart of the allocation-free solves (restart <= NOALLOC_MAX_RESTART)
     // GMRES workspace (grown on demand)
     int m_cap = 0;
@@ -272,26 +274,45 @@ __global__ void __launch_bounds__(BT, 3) k_symv(int64_t n, int64_t np, const dou
     for (int c = c0; c < c1; ++c, tile += TR * TC) {
         half(tile + RW / 2 * TC, s2);
         double cs0 = 0.0, cs1 = 0.0;
-        auto one = [&](int r, double2 sv) {
+        // diag: the tile holds the diagonal, and its elements from there on, zero in
+        // S, are no part of the sums (nor is zero times an infinite x)
+        auto one = [&](auto diag, int r, double2 sv) {
             const double *g = row[wave * RW + r];
             const double2 p = *reinterpret_cast<const double2 *>(g), nu = *reinterpret_cast<const double2 *>(g + 2);
             const double wi = g[4];
             const double dx0 = p.x - q.x.x, dy0 = p.y - q.y.x, dx1 = p.x - q.x.y, dy1 = p.y - q.y.y;
-            acc[r] = fma(sv.x * fma(dx0, q.nx.x, dy0 * q.ny.x), q.w.x, acc[r]);
-            acc[r] = fma(sv.y * fma(dx1, q.nx.y, dy1 * q.ny.y), q.w.y, acc[r]);
-            cs0 = fma(sv.x * fma(dx0, nu.x, dy0 * nu.y), wi, cs0);
-            cs1 = fma(sv.y * fma(dx1, nu.x, dy1 * nu.y), wi, cs1);
+            // columns 2 lane and 2 lane + 1 of the tile, row wave RW + r of the strip's half
+            const int below = wave * RW + r + (int)(I % 2) * TR - 2 * lane;      // i - j of the first column
+            if (!diag || below > 0) {
+                acc[r] = fma(sv.x * fma(dx0, q.nx.x, dy0 * q.ny.x), q.w.x, acc[r]);
+                cs0 = fma(sv.x * fma(dx0, nu.x, dy0 * nu.y), wi, cs0);
+            }
+            if (!diag || below > 1) {
+                acc[r] = fma(sv.y * fma(dx1, q.nx.y, dy1 * q.ny.y), q.w.y, acc[r]);
+                cs1 = fma(sv.y * fma(dx1, nu.x, dy1 * nu.y), wi, cs1);
+            }
             // the sums are formed here: left to itself the compiler moves them
             // past the barrier below, with their operands in scratch
             asm volatile("" : "+v"(acc[r]), "+v"(cs0), "+v"(cs1));
         };
+        const bool dg = c == (int)(I / 2);
+        if (dg) {
 #pragma unroll
-        for (int r = 0; r < RW / 2; ++r) one(r, s[r]);
+            for (int r = 0; r < RW / 2; ++r) one(std::true_type(), r, s[r]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < RW / 2; ++r) one(std::false_type(), r, s[r]);
+        }
         // (the last tile once more at the end of the run)
         const int cn = min(c + 1, c1 - 1);
         half(tile + (cn - c) * (TR * TC), s);
+        if (dg) {
 #pragma unroll
-        for (int r = 0; r < RW / 2; ++r) one(RW / 2 + r, s2[r]);
+            for (int r = 0; r < RW / 2; ++r) one(std::true_type(), RW / 2 + r, s2[r]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < RW / 2; ++r) one(std::false_type(), RW / 2 + r, s2[r]);
+        }
         cols(cn, q);
         double(*cl)[TC] = col[c & 1];
         cl[wave][2 * lane] = cs0;
@@ -366,6 +387,60 @@ __global__ void __launch_bounds__(TC * SG) k_symv_sum(int64_t n, int64_t np, int
         if (i0 + 64 < n) d = fma(v[i0 + 64], y1, d);
         d = wave_sum(d);
         if (lane == 0) part[(int64_t)k * gridDim.x + J] = d;
+    }
+}
+
+// y = shift x + K x with nothing kept between launches, for products recorded
+// into a graph: its replays may run beside the object's other products, whose
+// partial sums k_symv keeps in the object.  One workgroup per 16 rows i (a
+// panel), four row groups of 64 lanes: the triangle's rows for j < i, then its
+// columns for j > i (16 neighbouring doubles of a row), so S is read twice.
+__global__ void __launch_bounds__(BT) k_nys_rows(int64_t n, int64_t np, const double *__restrict__ S,
+                                                 const double *__restrict__ geo, double shift,
+                                                 const double *__restrict__ x, double *__restrict__ y)
+{
+    constexpr int NR = 16;
+    const int64_t i0 = (int64_t)blockIdx.x * NR;
+    const double *__restrict__ gx = geo, *__restrict__ gy = geo + np, *__restrict__ gnx = geo + 2 * np,
+                               *__restrict__ gny = geo + 3 * np, *__restrict__ gw = geo + 4 * np;
+    __shared__ double sh[BT / NR][NR + 1];
+    const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
+    // w_j (x_i - x_j).nu_j x_j
+    auto term = [&](int64_t i, int64_t j) {
+        return fma(gx[i] - gx[j], gnx[j], (gy[i] - gy[j]) * gny[j]) * (gw[j] * x[j]);
+    };
+    // rows wave, wave + 4, ...: columns below the diagonal along the lanes
+    double low[NR / 4];
+#pragma unroll
+    for (int q = 0; q < NR / 4; ++q) {
+        const int64_t i = i0 + wave + 4 * q, I = i / TR;
+        double s = 0.0;
+        for (int64_t j = lane; j < i; j += 64)
+            s = fma(S[(tile_ofs(I) + j / TC) * (TR * TC) + i % TR * TC + j % TC], term(i, j), s);
+        low[q] = wave_sum(s);
+    }
+    // column i of the rows j > i: 16 columns by 16 rows at a time
+    const int c = tid % NR, g = tid / NR;
+    const int64_t i = i0 + c;
+    double s = 0.0;
+    for (int64_t j = i0 + g; j < n; j += BT / NR)
+        if (j > i) s = fma(S[(tile_ofs(j / TR) + i / TC) * (TR * TC) + j % TR * TC + i % TC], term(i, j), s);
+    sh[g][c] = s;
+    __syncthreads();
+    if (tid < NR) {
+        double v = 0.0;
+#pragma unroll
+        for (int q = 0; q < BT / NR; ++q) v += sh[q][tid];
+        sh[0][tid] = v;
+    }
+    __syncthreads();
+    if (lane == 0) {
+#pragma unroll
+        for (int q = 0; q < NR / 4; ++q) {
+            const int64_t r = i0 + wave + 4 * q;
+            const double xi = x[r];
+            y[r] = fma(shift, xi, fma(geo[5 * np + r], xi, low[q] + sh[0][wave + 4 * q]));
+        }
     }
 }
 
@@ -987,6 +1062,15 @@ mhk_status mhk_nystrom_apply(mhk_nystrom *N, double shift, const double *x, doub
         set_error("null Nystrom matrix or vector, or x aliases y");
         return MHK_EINVAL;
     }
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (N->stream) BIE_HIP(hipStreamIsCapturing(N->stream, &cap));
+    if (cap == hipStreamCaptureStatusActive) {
+        hipLaunchKernelGGL(k_nys_rows, dim3((unsigned)(N->n / NGL)), dim3(BT), 0, N->stream, N->n, N->np,
+                           (const double *)N->S, (const double *)N->geo, shift, x, y);
+        BIE_HIP(hipGetLastError());
+        return MHK_OK;
+    }
+    std::lock_guard<std::mutex> lock(N->apply_mu);
     BIE_HIP(product(N, NYS_APPLY, shift, x, y, N->stream));
     return MHK_OK;
 }

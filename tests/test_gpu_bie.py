@@ -160,3 +160,51 @@ def test_solve_rejects_bad_plans():
     for p in (p32, poff, pa):
         p.close()
     nys.close()
+
+
+def test_nystrom_apply_infinite_entry():
+    """One infinite entry of x: every product with a nonzero element of K is
+    infinite with the element's sign, none a NaN (but where shift x is infinite
+    with the other sign)."""
+    w = synth.config0()
+    M = _M()
+    print("case nystrom apply infinite entry", flush=True)
+    nys = M.Nystrom(1.0, w.boundary)
+    K = bie.nystrom_matrix(w.boundary, 1.0)
+    for k in (0, 63, 64, 127, 200, w.n_b - 1):
+        x = np.zeros(w.n_b)
+        x[k] = np.inf
+        y = nys.apply(_dev(x), shift=-0.5).cpu().numpy()
+        assert np.all(K[:, k] != 0)
+        with np.errstate(invalid="ignore"):
+            np.testing.assert_array_equal(y, -0.5 * np.where(x > 0, x, 0) + np.sign(K[:, k]) * np.inf)
+    nys.close()
+
+
+@pytest.mark.parametrize("panels", [1, 5, 48])
+def test_nystrom_apply_captured(panels):
+    """A captured product against the eager one (both sum in FP64 in a fixed
+    order), with other products of the object between the replays."""
+    M = _M()
+    bnd = synth.discretize([synth.Curve(r0=1.0, a=0.1, l1=3)], panels)
+    print(f"case nystrom apply captured panels={panels}", flush=True)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        nys = M.Nystrom(2.0, bnd)
+        g = torch.Generator(device="cuda").manual_seed(panels)
+        x = torch.randn(16 * panels, dtype=torch.float64, device="cuda", generator=g)
+        out, other = torch.empty_like(x), torch.empty_like(x)
+        st.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=st):
+            nys.apply(x, shift=0.5, out=out)
+        for _ in range(3):
+            x.normal_(generator=g)
+            out.fill_(float("nan"))
+            graph.replay()
+            nys.apply(-3.0 * x, shift=0.1, out=other)
+            ref = nys.apply(x, shift=0.5)
+            st.synchronize()
+            # sums of at most 768 terms in two orders, elements of a few ulp
+            assert rel_err(out.cpu().numpy(), ref.cpu().numpy()) < 1e-13
+    nys.close()
