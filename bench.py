@@ -286,13 +286,14 @@ def main():
 def roofline(stage, infos, w):
     """The dominant kernel, k_level_sums: algorithmic flops per launch over
     its measured HIP-event time per launch (the level stage of each plan,
-    on the stream the level sums are launched on, over its J launches)."""
+    on the stream the level sums are launched on: one launch over its J
+    levels)."""
     flops, pairs = 0.0, 0.0
     for info in infos:
         pr = level_pairs(w, info)
         pairs += pr
     flops = pairs * LEVEL_FLOPS_PER_PAIR
-    launches = sum(i["J"] for i in infos)
+    launches = sum(1 for i in infos if i["J"] > 0)
     ms = sum(stage["ms_levels"])
     ach = flops / (ms * 1e-3) / 1e12
     tr = level_sums_traffic()
@@ -393,8 +394,21 @@ def level_sums_traffic():
         return None
 
 
-def child_nodes(w, j):
-    """Positions of the level-j child nodes (every panel bisected j times, 16
+def level_bisections(w, info, j):
+    """Bisections of every panel at level j: j, or fewer where the 16-node
+    rule resolves the level's kernel to tol/100 on longer panels (the
+    library's rule, from the largest half-length of a panel)."""
+    import synth
+    _, wg = synth.gauss_legendre()
+    half = float(np.max(np.asarray(w.boundary["w"]).reshape(-1, 16) / wg))
+    hmax = (info["tol"] * 1e-2 / 1.5e-11) ** (1.0 / 18.0) * np.sqrt(info["delta"] / 4.0 ** (j - 1))
+    while j > 0 and half / (1 << (j - 1)) <= hmax:
+        j -= 1
+    return j
+
+
+def child_nodes(w, m):
+    """Positions of the child nodes of every panel bisected m times (16
     Gauss-Legendre nodes per child), from the analytic curves."""
     import synth
     tg, _ = synth.gauss_legendre()
@@ -403,7 +417,7 @@ def child_nodes(w, j):
     for c, cv in enumerate(w.curves):
         M = int(ofs[c + 1] - ofs[c])
         edges = np.linspace(0.0, 2 * np.pi, M + 1)
-        nch = 1 << j
+        nch = 1 << m
         h = (edges[1] - edges[0]) / nch
         t = (edges[:-1, None, None] + h * (np.arange(nch)[None, :, None] + 0.5 * (1 + tg[None, None, :]))).ravel()
         g, _, _ = cv.eval(t)
@@ -417,7 +431,7 @@ def level_pairs(w, info):
     tg = np.concatenate([np.stack([w.tx, w.ty], 1), np.stack([w.boundary["x"], w.boundary["y"]], 1)])
     pairs = 0.0
     for j in range(1, info["J"] + 1):
-        tree = cKDTree(child_nodes(w, j))
+        tree = cKDTree(child_nodes(w, level_bisections(w, info, j)))
         cnt = tree.query_ball_point(tg, info["level_radius"][j - 1], return_length=True, workers=-1)
         pairs += float(np.sum(cnt))
     return pairs
