@@ -20,6 +20,8 @@
 // non-empty block of grid cells on the matrix cores; else one workgroup per
 // non-empty target tile stages the tile plus its window halo of the three
 // result grids in LDS with coalesced row reads.
+#include <type_traits>
+
 #include "mhk_internal.h"
 
 namespace mhk {
@@ -363,8 +365,6 @@ __global__ void __launch_bounds__(256) k_multiply(int64_t n, int B, int64_t fiel
 // table (conjugated for the inverse); both directions are unnormalised, like
 // the rocFFT row transforms.
 // ---------------------------------------------------------------------------
-constexpr int CT = 512;            // threads per column workgroup
-
 template <typename T2>
 __device__ inline T2 c2(decltype(T2::x) x, decltype(T2::x) y)
 {
@@ -488,69 +488,86 @@ template <int R, bool INV, typename T2> __device__ inline void dft(T2 *x)
     }
 }
 
-// One radix-R pass of a length-N transform held in LDS by NT threads (N <=
-// NMAX); Ns = product of the radices of the passes before it.  The twiddle
-// table holds e^{-2 pi i m / (N ts)}, read at stride ts.
-template <int R, bool INV, int NT, int NMAX, typename T2>
-__device__ inline void fft_pass(T2 *buf, const double2 *__restrict__ tw, int ts, int N, int Ns)
+// Position of transform point i in LDS (lengths are multiples of 8): the low
+// bits of an aligned group of eight points turned by the group's number, so that
+// the first pass's writes, R points apart from lane to lane, spread over the
+// banks (radix 8 unturned: 128 bytes apart, four times the cycles).
+__device__ inline int lds_at(int i) { return i ^ (i >> 3 & 7); }
+
+// Twiddles of a radix-R butterfly: x_t times w^t, the powers by repeated
+// products in FP64 (R - 2 roundings of 1e-16), each rounded once to the
+// transform's precision.
+template <int R, typename T2> __device__ inline void twiddle(T2 *x, double2 w)
 {
     typedef decltype(T2::x) T;
+    double2 wt = w;
+#pragma unroll
+    for (int t = 1; t < R; ++t) {
+        x[t] = cmul(x[t], c2<T2>((T)wt.x, (T)wt.y));
+        if (t + 1 < R) wt = cmul(wt, w);
+    }
+}
+
+// j % Ns for j < 8192 (the quotient by FP32, at least 0.4/Ns from the next
+// whole number; an integer division takes some 20 instructions)
+__device__ inline int mod_small(int j, int Ns, float inv) { return j - Ns * (int)(((float)j + 0.5f) * inv); }
+
+// One radix-R pass of a length-N transform by NT threads (N <= NMAX); Ns =
+// product of the radices of the passes before it.  Input i comes from get(i),
+// output i goes to put(i, .): LDS, or on a transform's first and last pass global
+// memory.  PRE: every thread's inputs are read before any output is written;
+// POST: the outputs are visible to all at the end.  The twiddle table holds
+// e^{-2 pi i m / (N ts)}, read at stride ts.
+template <int R, bool INV, int NT, int NMAX, bool PRE, bool POST, typename T2, typename Get, typename Put>
+__device__ inline void fft_pass(Get get, Put put, const double2 *__restrict__ tw, int ts, int N, int Ns)
+{
     constexpr int MB = (NMAX / R + NT - 1) / NT;
     const int nb = N / R, step = N / (Ns * R) * ts;
+    const float inv = 1.0f / (float)Ns;
+    // formed anew in every pass: left to itself the compiler keeps the addresses
+    // of all the passes and radices in registers
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
     T2 v[MB][R];
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
-        const int j = threadIdx.x + i * NT;
+        const int j = tid + i * NT;
         if (j < nb) {
-            // one twiddle load per butterfly (issued before the LDS reads),
-            // w^t by repeated products in FP64 (R - 2 roundings of 1e-16),
-            // each rounded once to the transform's precision
+            // one twiddle load per butterfly, issued before the reads of LDS
             double2 w = make_double2(1.0, 0.0);
             if (Ns > 1) {
-                w = tw[(j % Ns) * step];
+                w = tw[mod_small(j, Ns, inv) * step];
                 if (INV) w.y = -w.y;
             }
 #pragma unroll
-            for (int t = 0; t < R; ++t) v[i][t] = buf[j + t * nb];
-            if (Ns > 1) {
-                double2 wt = w;
-#pragma unroll
-                for (int t = 1; t < R; ++t) {
-                    v[i][t] = cmul(v[i][t], c2<T2>((T)wt.x, (T)wt.y));
-                    if (t + 1 < R) wt = cmul(wt, w);
-                }
-            }
+            for (int t = 0; t < R; ++t) v[i][t] = get(j + t * nb);
+            if (Ns > 1) twiddle<R>(v[i], w);
         }
     }
-    __syncthreads();
+    if (PRE) __syncthreads();
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
-        const int j = threadIdx.x + i * NT;
+        const int j = tid + i * NT;
         if (j < nb) {
             dft<R, INV>(v[i]);
-            const int k = j % Ns, o = (j - k) * R + k;
+            const int k = mod_small(j, Ns, inv), o = (j - k) * R + k;
 #pragma unroll
-            for (int t = 0; t < R; ++t) buf[o + t * Ns] = v[i][t];
+            for (int t = 0; t < R; ++t) put(o + t * Ns, v[i][t]);
         }
     }
-    __syncthreads();
+    if (POST) __syncthreads();
 }
 
-template <bool INV, int NT, int NMAX, typename T2>
-__device__ inline void lds_fft(T2 *buf, const double2 *tw, int ts, int N, const int8_t *radix, int npass)
+template <bool INV, int NT, int NMAX, bool PRE, bool POST, typename T2, typename Get, typename Put>
+__device__ inline void fft_pass_any(int r, Get get, Put put, const double2 *__restrict__ tw, int ts, int N, int Ns)
 {
-    int Ns = 1;
-    for (int p = 0; p < npass; ++p) {
-        const int r = radix[p];
-        if (r == 8) fft_pass<8, INV, NT, NMAX>(buf, tw, ts, N, Ns);
-        else if (r == 9) fft_pass<9, INV, NT, NMAX>(buf, tw, ts, N, Ns);
-        else if (r == 6) fft_pass<6, INV, NT, NMAX>(buf, tw, ts, N, Ns);
-        else if (r == 4) fft_pass<4, INV, NT, NMAX>(buf, tw, ts, N, Ns);
-        else if (r == 2) fft_pass<2, INV, NT, NMAX>(buf, tw, ts, N, Ns);
-        else if (r == 3) fft_pass<3, INV, NT, NMAX>(buf, tw, ts, N, Ns);
-        else fft_pass<5, INV, NT, NMAX>(buf, tw, ts, N, Ns);
-        Ns *= r;
-    }
+    if (r == 8) fft_pass<8, INV, NT, NMAX, PRE, POST, T2>(get, put, tw, ts, N, Ns);
+    else if (r == 9) fft_pass<9, INV, NT, NMAX, PRE, POST, T2>(get, put, tw, ts, N, Ns);
+    else if (r == 6) fft_pass<6, INV, NT, NMAX, PRE, POST, T2>(get, put, tw, ts, N, Ns);
+    else if (r == 4) fft_pass<4, INV, NT, NMAX, PRE, POST, T2>(get, put, tw, ts, N, Ns);
+    else if (r == 2) fft_pass<2, INV, NT, NMAX, PRE, POST, T2>(get, put, tw, ts, N, Ns);
+    else if (r == 3) fft_pass<3, INV, NT, NMAX, PRE, POST, T2>(get, put, tw, ts, N, Ns);
+    else fft_pass<5, INV, NT, NMAX, PRE, POST, T2>(get, put, tw, ts, N, Ns);
 }
 
 // ---------------------------------------------------------------------------
@@ -563,8 +580,6 @@ __device__ inline void lds_fft(T2 *buf, const double2 *tw, int ts, int N, const 
 // (X_k - conj X_{n/2-k}) and transforms back (unnormalised, as the column
 // transforms).
 // ---------------------------------------------------------------------------
-constexpr int RT = 256;            // threads per row workgroup
-
 template <typename T>
 struct RowArgs {
     int64_t n;
@@ -581,12 +596,18 @@ struct RowArgs {
     const double2 *tw;             // e^{-2 pi i m / n}, FP64 at both precisions
 };
 
+// The first pass takes its inputs from global memory, tangled on the way for
+// the inverse, and the inverse's last pass writes there: a row's points go
+// through LDS once per two passes and once for the untangling.
 template <bool INV, typename T, int NMAX>
-__global__ void __launch_bounds__(RT) k_rows(RowArgs<T> A)
+__global__ void __launch_bounds__(NMAX / 16) k_rows(RowArgs<T> A)
 {
     typedef typename Vec2<T>::type T2;
+    constexpr int RT = NMAX / 16, HM = NMAX / 2;         // threads (one radix-8 butterfly each); longest transform
     extern __shared__ double lds_row[];
     T2 *buf = reinterpret_cast<T2 *>(lds_row);
+    auto get = [&](int i) { return buf[lds_at(i)]; };
+    auto put = [&](int i, T2 z) { buf[lds_at(i)] = z; };
     const int n = (int)A.n, h = n / 2;
     const int gb = (int)(blockIdx.x / A.nrow), grp = A.grp[gb / A.B];
     const size_t slot = (size_t)grp * A.B + gb % A.B, row = A.r0 + blockIdx.x % A.nrow;
@@ -597,20 +618,21 @@ __global__ void __launch_bounds__(RT) k_rows(RowArgs<T> A)
         const T2 zero = c2<T2>((T)0, (T)0);
         const uint8_t *__restrict__ flag =
             (grp == 1 ? A.vflag : A.bflag) + (row / SPB) * (size_t)A.nblk;
+        auto on = [&](int m) { return m >= A.m0 && m < A.m1 && flag[2 * m / SPB]; };
         int any = 0;
-        for (int m = tid; m < h; m += RT) {
-            const bool on = m >= A.m0 && m < A.m1 && flag[2 * m / SPB];
-            buf[m] = on ? c[m] : zero;
-            any |= on;
-        }
+        for (int m = tid * (SPB / 2); m < h; m += RT * (SPB / 2)) any |= flag[2 * m / SPB];
         if (!__syncthreads_or(any)) {
             for (int k = tid; k < A.ncol; k += RT) c[k] = zero;
             return;
         }
-        lds_fft<false, RT, NMAX / 2>(buf, A.tw, 2, h, A.radix, A.npass);
+        auto row_in = [&](int m) { return on(m) ? c[m] : zero; };
+        fft_pass_any<false, RT, HM, false, true, T2>(A.radix[0], row_in, put, A.tw, 2, h, 1);
+        int Ns = A.radix[0];
+        for (int p = 1; p < A.npass; Ns *= A.radix[p], ++p)
+            fft_pass_any<false, RT, HM, true, true, T2>(A.radix[p], get, put, A.tw, 2, h, Ns);
         // only the columns that the multiplier keeps are read again
         for (int k = tid; k < A.ncol; k += RT) {
-            const T2 zk = buf[k == h ? 0 : k], zc = buf[k == 0 ? 0 : h - k];
+            const T2 zk = get(k == h ? 0 : k), zc = get(k == 0 ? 0 : h - k);
             const double2 wd64 = A.tw[k];                                    // e^{-2 pi i k/n}
             const T2 w = c2<T2>((T)wd64.x, (T)wd64.y);
             const T2 sp = c2<T2>(zk.x + zc.x, zk.y - zc.y);                  // Z_k + conj Z_{h-k}
@@ -621,18 +643,24 @@ __global__ void __launch_bounds__(RT) k_rows(RowArgs<T> A)
     } else {
         // entries k >= ncol are zero (the column transforms leave them unwritten)
         const T2 zero = c2<T2>((T)0, (T)0);
-        for (int k = tid; k < h; k += RT) {
+        auto row_in = [&](int k) {
             const T2 a = k < A.ncol ? c[k] : zero, bb = h - k < A.ncol ? c[h - k] : zero;
             const T2 sp = c2<T2>(a.x + bb.x, a.y - bb.y);                    // X_k + conj X_{h-k}
             const T2 dm = c2<T2>(a.x - bb.x, a.y + bb.y);                    // X_k - conj X_{h-k}
             const double2 wd64 = A.tw[k];
             const T2 wd = cmul(c2<T2>((T)wd64.x, (T)-wd64.y), dm);           // e^{+2 pi i k/n} dm
-            buf[k] = c2<T2>(sp.x - wd.y, sp.y + wd.x);                       // sp + i wd
-        }
-        __syncthreads();
-        lds_fft<true, RT, NMAX / 2>(buf, A.tw, 2, h, A.radix, A.npass);
-        // only the points the interpolation windows use
-        for (int m = A.m0 + tid; m < A.m1; m += RT) c[m] = buf[m];
+            return c2<T2>(sp.x - wd.y, sp.y + wd.x);                         // sp + i wd
+        };
+        fft_pass_any<true, RT, HM, false, true, T2>(A.radix[0], row_in, put, A.tw, 2, h, 1);
+        int Ns = A.radix[0], p = 1;
+        for (; p + 1 < A.npass; Ns *= A.radix[p], ++p)
+            fft_pass_any<true, RT, HM, true, true, T2>(A.radix[p], get, put, A.tw, 2, h, Ns);
+        // only the points the interpolation windows use (the barrier above: every
+        // thread has read its points of the row)
+        auto row_out = [&](int m, T2 z) {
+            if (m >= A.m0 && m < A.m1) c[m] = z;
+        };
+        fft_pass_any<true, RT, HM, false, false, T2>(A.radix[p], get, row_out, A.tw, 2, h, Ns);
     }
 }
 
@@ -652,14 +680,22 @@ struct ColArgs {
 };
 
 // One workgroup per (column, density, output): 0 S, 1 V, 2 D (from the D_x
-// and D_y spectra: -i (k_x Gx + k_y Gy) M, as two transforms whose results
-// are added).
+// and D_y spectra: -i (k_x Gx + k_y Gy) M, two forward transforms and one
+// inverse).  The first forward pass reads global memory and the last inverse
+// one writes it; the last forward pass, the multiplier and the first inverse
+// pass, all on the same eight points of a thread, stay in registers: 2 (npass -
+// 1) exchanges through LDS per pair of transforms instead of 2 npass + 2, and three
+// transforms per D output instead of four.  Alone: D on 3840^2 217 -> 127 us, 16
+// densities on 2880^2 2.60 -> 1.81 ms.
 template <typename T, int NMAX>
-__global__ void __launch_bounds__(CT) k_columns(ColArgs<T> A)
+__global__ void __launch_bounds__(NMAX / 8, 4) k_columns(ColArgs<T> A)
 {
     typedef typename Vec2<T>::type T2;
+    constexpr int CT = NMAX / 8;       // threads: one radix-8 butterfly each
     extern __shared__ double lds_col[];
     T2 *buf = reinterpret_cast<T2 *>(lds_col);
+    auto get = [&](int i) { return buf[lds_at(i)]; };
+    auto put = [&](int i, T2 z) { buf[lds_at(i)] = z; };
     const int n = (int)A.n, nh = n / 2 + 1;
     // consecutive columns on one XCD (workgroups are dealt to the 8 XCDs in
     // turn), so that neighbouring columns share the XCD's L2 lines; only the
@@ -685,36 +721,58 @@ __global__ void __launch_bounds__(CT) k_columns(ColArgs<T> A)
         const double ky = A.dk * fy;
         return A.c * ax * ay / (A.alpha2 + kx * kx + ky * ky);
     };
-    const int nparts = grp == 2 ? 2 : 1;
+    const T2 zero = c2<T2>((T)0, (T)0);
+    const int nparts = grp == 2 ? 2 : 1, last = A.npass - 1, nb = n / 8;
+    // the spectrum's points j + t nb of thread j: outputs of the last forward
+    // pass (radix 8) and inputs of the first inverse one
+    int j = threadIdx.x;
+    T2 u[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) u[t] = zero;
     for (int part = 0; part < nparts; ++part) {
         const T2 *in = base + (size_t)(grp == 2 ? 2 + part : grp) * fs;
-        const T2 zero = c2<T2>((T)0, (T)0);
-        for (int y = threadIdx.x; y < n; y += CT) buf[y] = y >= A.iy0 && y < A.iy1 ? in[(size_t)y * nh] : zero;
-        __syncthreads();
-        lds_fft<false, CT, NMAX>(buf, A.tw, 1, n, A.radix, A.npass);
-        for (int ly = threadIdx.x; ly < n; ly += CT) {
-            const double M = mult(ly);
-            const T2 z = buf[ly];
-            if (grp < 2) {
-                buf[ly] = c2<T2>((T)(M * z.x), (T)(M * z.y));
-            } else {
-                // -i k M z with k = k_x (part 0) or k_y (part 1)
-                const int fy = ly <= n / 2 ? ly : ly - n;
-                const double kM = (part == 0 ? kx : A.dk * fy) * M;
-                buf[ly] = c2<T2>((T)(kM * z.y), (T)(-kM * z.x));
+        auto col_in = [&](int y) { return y >= A.iy0 && y < A.iy1 ? in[(size_t)y * nh] : zero; };
+        fft_pass_any<false, CT, NMAX, false, true, T2>(A.radix[0], col_in, put, A.tw, 1, n, 1);
+        int Ns = A.radix[0];
+        for (int p = 1; p < last; Ns *= A.radix[p], ++p)
+            fft_pass_any<false, CT, NMAX, true, true, T2>(A.radix[p], get, put, A.tw, 1, n, Ns);
+        asm volatile("" : "+v"(j));
+        if (j < nb) {
+            T2 z[8];
+            const double2 w = A.tw[j];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) z[t] = get(j + t * nb);
+            twiddle<8>(z, w);
+            dft<8, false>(z);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const int ly = j + t * nb;
+                const double M = mult(ly);
+                if (grp < 2) {
+                    u[t] = c2<T2>((T)(M * z[t].x), (T)(M * z[t].y));
+                } else {
+                    // -i k M z with k = k_x (part 0) or k_y (part 1)
+                    const int fy = ly <= n / 2 ? ly : ly - n;
+                    const double kM = (part == 0 ? kx : A.dk * fy) * M;
+                    u[t] = cadd(u[t], c2<T2>((T)(kM * z[t].y), (T)(-kM * z[t].x)));
+                }
             }
         }
         __syncthreads();
-        lds_fft<true, CT, NMAX>(buf, A.tw, 1, n, A.radix, A.npass);
-        // part 0 of D writes its column, part 1 adds to it (same thread, same
-        // rows: no other thread touches these values)
-        for (int y = A.oy0 + threadIdx.x; y < A.oy1; y += CT) {
-            T2 v = buf[y];
-            if (part == 1) v = cadd(out[(size_t)y * nh], v);
-            out[(size_t)y * nh] = v;
-        }
-        __syncthreads();
     }
+    if (j < nb) {
+        dft<8, true>(u);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) put(8 * j + t, u[t]);
+    }
+    __syncthreads();
+    int Ns = 8, p = last - 1;
+    for (; p > 0; Ns *= A.radix[p], --p)
+        fft_pass_any<true, CT, NMAX, true, true, T2>(A.radix[p], get, put, A.tw, 1, n, Ns);
+    auto col_out = [&](int y, T2 z) {
+        if (y >= A.oy0 && y < A.oy1) out[(size_t)y * nh] = z;
+    };
+    fft_pass_any<true, CT, NMAX, false, false, T2>(A.radix[0], get, col_out, A.tw, 1, n, Ns);
 }
 
 template <typename T>
@@ -1216,16 +1274,19 @@ static hipError_t columns_t(mhk_plan *P, bool want_s, bool want_d, bool want_v)
     A.oy0 = G.ty0;
     A.oy1 = G.ty1;
     const size_t lds = sizeof(typename Vec2<T>::type) * (size_t)G.n;
-    // register arrays sized for the longest column of the launch
-    const void *fn = G.n <= COL_NMAX / 2 ? (const void *)k_columns<T, COL_NMAX / 2> : (const void *)k_columns<T, COL_NMAX>;
-    if (lds > 64 * 1024) (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (G.ncol == 0) return hipSuccess;     // the multiplier is zero everywhere
     dim3 grid((unsigned)(((G.ncol + 7) / 8) * 8), (unsigned)P->bat, (unsigned)ng);
-    if (G.n <= COL_NMAX / 2)
-        hipLaunchKernelGGL((k_columns<T, COL_NMAX / 2>), grid, dim3(CT), lds, P->stream, A);
-    else
-        hipLaunchKernelGGL((k_columns<T, COL_NMAX>), grid, dim3(CT), lds, P->stream, A);
-    return hipGetLastError();
+    // threads and register arrays for the longest column of the variant
+    auto go = [&](auto nmax) {
+        constexpr int NMAX = decltype(nmax)::value;
+        const void *fn = (const void *)k_columns<T, NMAX>;
+        if (lds > 64 * 1024) (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipLaunchKernelGGL((k_columns<T, NMAX>), grid, dim3(NMAX / 8), lds, P->stream, A);
+        return hipGetLastError();
+    };
+    if (G.n <= COL_NMAX / 4) return go(std::integral_constant<int, COL_NMAX / 4>());
+    if (G.n <= COL_NMAX / 2) return go(std::integral_constant<int, COL_NMAX / 2>());
+    return go(std::integral_constant<int, COL_NMAX>());
 }
 
 template <bool INV, typename T>
@@ -1257,11 +1318,14 @@ static hipError_t rows_t(mhk_plan *P, bool want_s, bool want_d, bool want_v)
     const size_t lds = sizeof(typename Vec2<T>::type) * (size_t)(G.n / 2);
     const int64_t rows = ng * (int64_t)P->bat * A.nrow;
     if (rows <= 0) return hipSuccess;
-    if (G.n <= COL_NMAX / 2)
-        hipLaunchKernelGGL((k_rows<INV, T, COL_NMAX / 2>), dim3((unsigned)rows), dim3(RT), lds, P->stream, A);
-    else
-        hipLaunchKernelGGL((k_rows<INV, T, COL_NMAX>), dim3((unsigned)rows), dim3(RT), lds, P->stream, A);
-    return hipGetLastError();
+    auto go = [&](auto nmax) {
+        constexpr int NMAX = decltype(nmax)::value;
+        hipLaunchKernelGGL((k_rows<INV, T, NMAX>), dim3((unsigned)rows), dim3(NMAX / 16), lds, P->stream, A);
+        return hipGetLastError();
+    };
+    if (G.n <= COL_NMAX / 4) return go(std::integral_constant<int, COL_NMAX / 4>());
+    if (G.n <= COL_NMAX / 2) return go(std::integral_constant<int, COL_NMAX / 2>());
+    return go(std::integral_constant<int, COL_NMAX>());
 }
 
 // only the fields of the densities given are transformed

@@ -1523,8 +1523,11 @@ mhk_status build_history(mhk_plan *P, Host &H)
             while (m % f == 0 && np < COL_MAXPASS) { radix[np++] = (int8_t)f; m /= f; }
         return m == 1;
     };
-    G.colpath = G.n <= COL_NMAX && G.n % 2 == 0 && factor(G.n, G.radix, G.npass) &&
+    // columns: radix 8 last (grid sizes are multiples of 32, so that there are
+    // passes before it; the rows' half lengths have at least two)
+    G.colpath = G.n <= COL_NMAX && G.n % TILE == 0 && factor(G.n / 8, G.radix, G.npass) && G.npass < COL_MAXPASS &&
                 factor(G.n / 2, G.rradix, G.rnpass);
+    if (G.colpath) G.radix[G.npass++] = 8;
     if (G.colpath) {
         // twiddles e^{-2 pi i m / n}
         double *d = nullptr;
