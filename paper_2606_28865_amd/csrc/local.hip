@@ -266,6 +266,7 @@ struct LocalArgs {
     const double2 *pcxy, *bxy;   // panel coefficients of x and y, and nodes, interleaved
     const double2 *candbox;      // node box of every candidate panel: (xmin, xmax), (ymin, ymax)
     double vfar, von;      // (1 - e^{-c2^2})/c2^2 of the volume term, and half of it
+    double sq, con;        // sqrt(delta*), erf(c2)/(2 c2) with c2 = alpha sqrt(delta*) of the layer terms
     const int32_t *prev, *next, *cand, *cell_start;
     const double *cbox;
     int32_t *noconv;
@@ -628,27 +629,65 @@ __global__ void __launch_bounds__(256, 4) k_local_geom(LocalArgs<double> A, doub
     flag[s] = (uint8_t)((near_s ? 1 : 0) | (ext ? 2 : 0));
 }
 
-// Sum of the level items' parts of sorted target s: component c of ncomp,
-// density b of B, levels and pieces in order (the wavefront's items are the
-// same for its 64 lanes, so the offsets are scalar loads)
-template <typename T>
-__device__ inline double level_parts(const LevelDesc *__restrict__ d, int J, int ncomp, int c, int B, int b, int64_t s)
+// Sums of the level items' parts of sorted target s, added to v[c][q] for the
+// components c < NC wanted and NQ densities from b0 on (the last of B repeated):
+// levels and pieces in order.  The wavefront's items are the same for its 64
+// lanes, so the offsets are scalar loads, all levels' at once; the parts of all
+// components and densities are loaded together.
+template <int NC, int NQ, typename T>
+__device__ inline void level_parts(const LevelDesc *__restrict__ d, int J, int B, int b0, int64_t s, const bool *want,
+                                   double (*v)[NQ])
 {
     const int w = __builtin_amdgcn_readfirstlane((int)(s / LV_WAVE));
     const int lane = threadIdx.x % LV_WAVE;
-    double v = 0.0;
-    for (int j = 0; j < J; ++j) {
-        const int i0 = d[j].item_ofs[w], i1 = d[j].item_ofs[w + 1];
-        const T *part = (const T *)d[j].part;
-        for (int i = i0; i < i1; ++i) v += (double)part[(((size_t)i * ncomp + c) * B + b) * LV_WAVE + lane];
+    int i0[MAXJ], i1[MAXJ];
+#pragma unroll
+    for (int j = 0; j < MAXJ; ++j) {
+        i0[j] = i1[j] = 0;
+        if (j < J) {
+            i0[j] = d[j].item_ofs[w];
+            i1[j] = d[j].item_ofs[w + 1];
+        }
     }
-    return v;
+    double a[NC][NQ];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) a[c][q] = 0.0;
+#pragma unroll
+    for (int j = 0; j < MAXJ; ++j) {
+        if (j >= J) break;
+        const T *part = (const T *)d[j].part + lane;
+        for (int i = i0[j]; i < i1[j]; ++i) {
+            T x[NC][NQ];
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int q = 0; q < NQ; ++q)
+                    x[c][q] = want[c] ? part[(((size_t)i * NC + c) * B + min(b0 + q, B - 1)) * LV_WAVE] : (T)0;
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) a[c][q] += (double)x[c][q];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) v[c][q] += a[c][q];
 }
 
 // Local part of an evaluation from the per-plan geometry, added to the
 // accumulated history and level sums, and the scatter to the caller's order.
-template <typename T, typename TI, int ORDER>
-__global__ void __launch_bounds__(256) k_local(LocalArgs<T, TI> A)
+// Bound by the latency of its loads, so those of the sums of NQ densities (and of
+// S, D and V) are issued together; NQ densities per launch row (no loop over them:
+// the compiler keeps the constants of a loop's Legendre series in registers, 182
+// instead of 98), or with the second-order terms a loop over all.  Alone: 16
+// densities at 1.03M outputs 1.83 -> 1.25 ms, 8 FP32 densities at 366 thousand 330
+// -> 268 us, one at 1.02M 111 -> 91 us, one FP32 at 4.07M 373 -> 339 us; the
+// scattered 8-byte stores are most of what is left.
+template <typename T, typename TI, int ORDER, int NQ>
+__global__ void __launch_bounds__(256, ORDER >= 2 ? 1 : 4) k_local(LocalArgs<T, TI> A)
 {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= A.nout) return;
@@ -657,7 +696,7 @@ __global__ void __launch_bounds__(256) k_local(LocalArgs<T, TI> A)
     const bool on = idx >= A.nt;
     const bool do_local = (A.parts & MHK_PART_LOCAL) != 0;
     const bool ws = A.out_s != nullptr, wd = A.out_d != nullptr, wv = A.out_v != nullptr;
-    const double sq = sqrt(A.dstar), c2 = A.alpha * sq;
+    const double sq = A.sq;
     const double rho = inside ? 1.0 : -1.0;
     const int64_t n = A.nout;
     const uint8_t fl = A.gflag[s];
@@ -707,99 +746,116 @@ __global__ void __launch_bounds__(256) k_local(LocalArgs<T, TI> A)
     }
     const double d32 = A.dstar * sq, d2 = A.dstar * A.dstar;
 
+    const bool want_l[2] = {ws, wd}, want_v[1] = {true};
 #pragma unroll 1
-    for (int b = 0; b < A.B; ++b) {
-        const size_t ob = (size_t)b * A.nout + idx;
-        const size_t ab = (size_t)b * A.nout + s;
-        if (ws) {
-            double v = (double)A.acc[(size_t)0 * A.B * A.nout + ab];
-            if (A.lev) v += level_parts<T>(A.lev, A.J, 2, 0, A.B, b, s);
-            if (do_local) {
-                if (on) {
-                    const int64_t i = idx - A.nt;
-                    v += sq * (double)A.sigma[(size_t)b * A.nb + i] * erf(c2) / (2.0 * c2);        // Cor. 4.4
-                } else if (near_s) {
-                    const double sg = leg1(A.cs + ((size_t)b * A.npan + pbest) * NGL, tbest);
-                    v += sq * sg * P0 * 0.25 + A.dstar * rho * kap * sg * P1 * 0.125;     // Lemma 4.1
-                }
-                if (o2 && (on || near_s) && pp2 >= 0) {
-                    // delta*^{3/2} and delta*^2 terms of Lemma 4.1 (Cor. 4.4 on the boundary)
-                    double F[5], d[5];
-                    leg_taylor4(A.cs + ((size_t)b * A.npan + pp2) * NGL, tt2, F);
-                    xi_derivs(F, bb[0], bb[1], bb[2], bb[3], d);
-                    const double s0 = on ? (double)A.sigma[(size_t)b * A.nb + (idx - A.nt)] : d[0];
-                    const double k = kap2;
-                    v += d32 * (k * k * s0 / 32.0 * (q0 + 3.0 * p2) + d[2] / 8.0 * q0) +
-                         d2 * rho * (k * k * k * s0 / 64.0 * (-3.0 * q1 + 5.0 * p3) +
-                                     (3.0 * k * d[2] / 16.0 + d[1] * g3 / 8.0 + s0 * g4 / 32.0) * q1);
-                }
-            }
-            A.out_s[ob] = (T)v;
+    for (int p = 0; p < (ORDER >= 2 ? A.B : 1); ++p) {
+        const int b0 = (int)blockIdx.y * NQ + p;
+        // history and level sums, and f, of the densities b0 .. b0 + NQ - 1
+        double vl[2][NQ], vv[1][NQ], fv[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int b = min(b0 + q, A.B - 1);
+            const size_t ab = (size_t)b * A.nout + s;
+            vl[0][q] = ws ? (double)A.acc[ab] : 0.0;
+            vl[1][q] = wd ? (double)A.acc[(size_t)1 * A.B * A.nout + ab] : 0.0;
+            vv[0][q] = wv ? (double)A.acc[(size_t)2 * A.B * A.nout + ab] : 0.0;
+            fv[q] = do_local && wv && !ext ? (double)A.f_trg[(size_t)b * A.frows * A.nout + idx] : 0.0;
         }
-        if (wd) {
-            double v = (double)A.acc[(size_t)1 * A.B * A.nout + ab];
-            if (A.lev) v += level_parts<T>(A.lev, A.J, 2, 1, A.B, b, s);
-            if (do_local) {
-                if (on) {
-                    const int64_t i = idx - A.nt;
-                    v -= sq * A.bk[i] * (double)A.mu[(size_t)b * A.nb + i] * erf(c2) / (4.0 * c2);  // Cor. 4.7
-                } else if (near_s) {
-                    double m0, m1, m2;
-                    leg2s(A.cm + ((size_t)b * A.npan + pbest) * NGL, tbest, m0, m1, m2);
-                    const double mss = mss_fac2 * m2 + mss_fac1 * m1;
-                    v += -rho * m0 * U0 * 0.25 - sq * kap * m0 * (P0 + U1) * 0.125                // Lemma 4.5
-                         - A.dstar * (rho * mss * P1 * 0.125 + 3.0 * rho * kap * kap * m0 * (P1 + U2) / 32.0);
+        if (A.lev) level_parts<2, NQ, T>(A.lev, A.J, A.B, b0, s, want_l, vl);
+        if (A.vlev) level_parts<1, NQ, T>(A.vlev, A.J, A.B, b0, s, want_v, vv);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int b = b0 + q;
+            if (b >= A.B) break;
+            if (NQ > 1) asm volatile("" : "+v"(tbest) : : "memory");      // one density's series at a time
+            const size_t ob = (size_t)b * A.nout + idx;
+            if (ws) {
+                double v = vl[0][q];
+                if (do_local) {
+                    if (on) {
+                        const int64_t i = idx - A.nt;
+                        v += sq * (double)A.sigma[(size_t)b * A.nb + i] * A.con;        // Cor. 4.4
+                    } else if (near_s) {
+                        const double sg = leg1(A.cs + ((size_t)b * A.npan + pbest) * NGL, tbest);
+                        v += sq * sg * P0 * 0.25 + A.dstar * rho * kap * sg * P1 * 0.125;     // Lemma 4.1
+                    }
+                    if (o2 && (on || near_s) && pp2 >= 0) {
+                        // delta*^{3/2} and delta*^2 terms of Lemma 4.1 (Cor. 4.4 on the boundary)
+                        double F[5], d[5];
+                        leg_taylor4(A.cs + ((size_t)b * A.npan + pp2) * NGL, tt2, F);
+                        xi_derivs(F, bb[0], bb[1], bb[2], bb[3], d);
+                        const double s0 = on ? (double)A.sigma[(size_t)b * A.nb + (idx - A.nt)] : d[0];
+                        const double k = kap2;
+                        v += d32 * (k * k * s0 / 32.0 * (q0 + 3.0 * p2) + d[2] / 8.0 * q0) +
+                             d2 * rho * (k * k * k * s0 / 64.0 * (-3.0 * q1 + 5.0 * p3) +
+                                         (3.0 * k * d[2] / 16.0 + d[1] * g3 / 8.0 + s0 * g4 / 32.0) * q1);
+                    }
                 }
-                if (o2 && (on || near_s) && pp2 >= 0) {
-                    // delta*^{3/2} and delta*^2 terms of Lemma 4.5 (Cor. 4.7 on
-                    // the boundary); the gamma'''' term of the delta*^{3/2}
-                    // bracket multiplies (3 Q0 + P2) (the series of the local
-                    // integral; the kappa^3 term keeps (3 Q0 - U3))
-                    double F[5], d[5];
-                    leg_taylor4(A.cm + ((size_t)b * A.npan + pp2) * NGL, tt2, F);
-                    xi_derivs(F, bb[0], bb[1], bb[2], bb[3], d);
-                    const double m0 = on ? (double)A.mu[(size_t)b * A.nb + (idx - A.nt)] : d[0];
-                    const double k = kap2;
-                    v += d32 * (5.0 * k * k * k * m0 / 64.0 * (3.0 * q0 - u3) - m0 * g4 / 32.0 * (3.0 * q0 + p2) +
-                                3.0 * k * d[2] / 16.0 * (-q0 - p2) + d[1] * g3 / 8.0 * (-2.0 * q0 - p2)) +
-                         d2 * (35.0 * rho * k * k * k * k * m0 / 512.0 * (9.0 * q1 + 2.0 * p3 - u4) -
-                               rho * d[4] / 32.0 * q1 - 15.0 * rho * k * k * d[2] / 64.0 * (q1 + p3)) -
-                         d2 * (5.0 * rho * k * d[1] * g3 / 16.0 * (2.0 * q1 + p3) +
-                               (5.0 * rho * k * m0 * g4 / 64.0 + 5.0 * rho * m0 * g3 * g3 / 96.0) * (3.0 * q1 + p3));
-                }
+                A.out_s[ob] = (T)v;
             }
-            A.out_d[ob] = (T)v;
-        }
-        if (wv) {
-            double v = (double)A.acc[(size_t)2 * A.B * A.nout + ab];
-            if (A.vlev) v += level_parts<T>(A.vlev, A.J, 1, 0, A.B, b, s);
-            if (do_local) {
-                // f (and with second order its gradient and Hessian) at the target
-                const TI *fr = A.f_trg + (size_t)b * A.frows * A.nout + idx;
-                double f;
-                if (ext)
-                    f = A.cf ? leg1(A.cf + ((size_t)b * A.npan + pbest) * NGL, tbest) : NAN;
-                else
-                    f = (double)fr[0];
-                v += A.delta * f * vfac;
-                if (o2 && !ext) {
-                    // delta^{3/2} and delta^2 terms of Lemma 4.8 (Cor. 4.10 on the
-                    // boundary, Cor. 4.11 far from it): f's derivatives along
-                    // the inward normal N0 = (-t_y, t_x) and the tangent t
-                    const size_t nn = (size_t)A.nout;
-                    const double fx = (double)fr[nn], fy = (double)fr[2 * nn];
-                    const double fxx = (double)fr[3 * nn], fxy = (double)fr[4 * nn], fyy = (double)fr[5 * nn];
-                    const double nx = -tty, ny = ttx;
-                    const double fe = fx * nx + fy * ny;
-                    const double fee = fxx * nx * nx + 2.0 * fxy * nx * ny + fyy * ny * ny;
-                    const double fxi = fxx * ttx * ttx + 2.0 * fxy * ttx * tty + fyy * tty * tty;
-                    const double k = kap2;
-                    v += A.delta * sqrt(A.delta) * (2.0 * fe - f * k) / 8.0 * va +
-                         A.delta * A.delta * ((fe * k / 8.0 - 3.0 * f * k * k / 32.0 - fee / 8.0) * vb +
-                                              (fee + fxi) / 8.0 * vc);
+            if (wd) {
+                double v = vl[1][q];
+                if (do_local) {
+                    if (on) {
+                        const int64_t i = idx - A.nt;
+                        v -= sq * A.bk[i] * (double)A.mu[(size_t)b * A.nb + i] * (0.5 * A.con);  // Cor. 4.7
+                    } else if (near_s) {
+                        double m0, m1, m2;
+                        leg2s(A.cm + ((size_t)b * A.npan + pbest) * NGL, tbest, m0, m1, m2);
+                        const double mss = mss_fac2 * m2 + mss_fac1 * m1;
+                        v += -rho * m0 * U0 * 0.25 - sq * kap * m0 * (P0 + U1) * 0.125                // Lemma 4.5
+                             - A.dstar * (rho * mss * P1 * 0.125 + 3.0 * rho * kap * kap * m0 * (P1 + U2) / 32.0);
+                    }
+                    if (o2 && (on || near_s) && pp2 >= 0) {
+                        // delta*^{3/2} and delta*^2 terms of Lemma 4.5 (Cor. 4.7 on
+                        // the boundary); the gamma'''' term of the delta*^{3/2}
+                        // bracket multiplies (3 Q0 + P2) (the series of the local
+                        // integral; the kappa^3 term keeps (3 Q0 - U3))
+                        double F[5], d[5];
+                        leg_taylor4(A.cm + ((size_t)b * A.npan + pp2) * NGL, tt2, F);
+                        xi_derivs(F, bb[0], bb[1], bb[2], bb[3], d);
+                        const double m0 = on ? (double)A.mu[(size_t)b * A.nb + (idx - A.nt)] : d[0];
+                        const double k = kap2;
+                        v += d32 * (5.0 * k * k * k * m0 / 64.0 * (3.0 * q0 - u3) - m0 * g4 / 32.0 * (3.0 * q0 + p2) +
+                                    3.0 * k * d[2] / 16.0 * (-q0 - p2) + d[1] * g3 / 8.0 * (-2.0 * q0 - p2)) +
+                             d2 * (35.0 * rho * k * k * k * k * m0 / 512.0 * (9.0 * q1 + 2.0 * p3 - u4) -
+                                   rho * d[4] / 32.0 * q1 - 15.0 * rho * k * k * d[2] / 64.0 * (q1 + p3)) -
+                             d2 * (5.0 * rho * k * d[1] * g3 / 16.0 * (2.0 * q1 + p3) +
+                                   (5.0 * rho * k * m0 * g4 / 64.0 + 5.0 * rho * m0 * g3 * g3 / 96.0) * (3.0 * q1 + p3));
+                    }
                 }
+                A.out_d[ob] = (T)v;
             }
-            A.out_v[ob] = (T)v;
+            if (wv) {
+                double v = vv[0][q];
+                if (do_local) {
+                    // f (and with second order its gradient and Hessian) at the target
+                    const TI *fr = A.f_trg + (size_t)b * A.frows * A.nout + idx;
+                    double f;
+                    if (ext)
+                        f = A.cf ? leg1(A.cf + ((size_t)b * A.npan + pbest) * NGL, tbest) : NAN;
+                    else
+                        f = fv[q];
+                    v += A.delta * f * vfac;
+                    if (o2 && !ext) {
+                        // delta^{3/2} and delta^2 terms of Lemma 4.8 (Cor. 4.10 on the
+                        // boundary, Cor. 4.11 far from it): f's derivatives along
+                        // the inward normal N0 = (-t_y, t_x) and the tangent t
+                        const size_t nn = (size_t)A.nout;
+                        const double fx = (double)fr[nn], fy = (double)fr[2 * nn];
+                        const double fxx = (double)fr[3 * nn], fxy = (double)fr[4 * nn], fyy = (double)fr[5 * nn];
+                        const double nx = -tty, ny = ttx;
+                        const double fe = fx * nx + fy * ny;
+                        const double fee = fxx * nx * nx + 2.0 * fxy * nx * ny + fyy * ny * ny;
+                        const double fxi = fxx * ttx * ttx + 2.0 * fxy * ttx * tty + fyy * tty * tty;
+                        const double k = kap2;
+                        v += A.delta * sqrt(A.delta) * (2.0 * fe - f * k) / 8.0 * va +
+                             A.delta * A.delta * ((fe * k / 8.0 - 3.0 * f * k * k / 32.0 - fee / 8.0) * vb +
+                                                  (fee + fxi) / 8.0 * vc);
+                    }
+                }
+                A.out_v[ob] = (T)v;
+            }
         }
     }
 }
@@ -878,6 +934,8 @@ static void fill_args(mhk_plan *P, LocalArgs<T, TI> &A)
     const double cv2 = P->p.alpha * P->p.alpha * P->delta_v;
     A.vfar = -expm1(-cv2) / cv2;
     A.von = 0.5 * A.vfar;
+    A.sq = sqrt(P->dstar);
+    A.con = erf(P->p.alpha * A.sq) / (2.0 * P->p.alpha * A.sq);
     A.ends = P->loc.ends;
     A.gl_t = P->loc.gl_t;
     A.prev = P->loc.prev;
@@ -936,9 +994,11 @@ static hipError_t local_t(mhk_plan *P, int parts, const void *sigma, const void 
     A.out_v = (T *)out_v;
     const dim3 grid((unsigned)((P->nout + 255) / 256));
     if (P->p.local_order >= 2)
-        hipLaunchKernelGGL((k_local<T, TI, 2>), grid, dim3(256), 0, P->stream, A);
+        hipLaunchKernelGGL((k_local<T, TI, 2, 1>), grid, dim3(256), 0, P->stream, A);
+    else if (A.B == 1)
+        hipLaunchKernelGGL((k_local<T, TI, 1, 1>), grid, dim3(256), 0, P->stream, A);
     else
-        hipLaunchKernelGGL((k_local<T, TI, 1>), grid, dim3(256), 0, P->stream, A);
+        hipLaunchKernelGGL((k_local<T, TI, 1, 4>), dim3(grid.x, (unsigned)((A.B + 3) / 4)), dim3(256), 0, P->stream, A);
     return hipGetLastError();
 }
 
