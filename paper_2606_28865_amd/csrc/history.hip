@@ -990,104 +990,93 @@ __global__ void __launch_bounds__(HB) k_interp_few(InterpArgs<T> A)
     }
 }
 
-// History kernel G^H(r) = int_delta^inf H(t, r) dt (eq. (sl_sh)) by composite
-// 16-point Gauss-Legendre in u with t = delta e^{-u}, u in (-inf, 0]:
-//   G^H = (1/4pi) int exp(-a e^u - b e^{-u}) du,  a = r^2/(4 delta), b = alpha^2 delta,
-// truncated where the exponent is below -700; panels narrower than the
-// width 1/sqrt(2 sqrt(ab)) of the integrand's peak.
-__device__ double history_kernel(double r, double alpha, double delta, const double *__restrict__ gt,
-                                 const double *__restrict__ gw)
-{
-    const double a = r * r / (4.0 * delta), b = alpha * alpha * delta;
-    double lo = log(b / 700.0), hi = 0.0;
-    if (a > 0.0) hi = fmin(hi, log(700.0 / a));
-    if (!(hi > lo)) return 0.0;
-    const double width = 1.0 / sqrt(1.0 + 2.0 * sqrt(a * b));
-    int m = (int)ceil((hi - lo) / (0.5 * width));
-    m = max(1, min(m, 2000));
-    const double hp = (hi - lo) / m;
-    double s = 0.0;
-    for (int p = 0; p < m; ++p) {
-        const double c = lo + (p + 0.5) * hp;
-        double ps = 0.0;
-        for (int q = 0; q < 16; ++q) {
-            const double u = c + 0.5 * hp * gt[q];
-            ps = fma(gw[q], exp(-a * exp(u) - b * exp(-u)), ps);
-        }
-        s += ps;
-    }
-    return s * 0.5 * hp / (4.0 * M_PI);
-}
+// The smoothly truncated history kernel on the grid is a sum of products of one
+// factor per axis: G^H(r) = int_delta^inf H(t, r) dt (eq. (sl_sh)) with t = delta
+// e^{-u} is
+//   (1/4pi) int_{-inf}^0 exp(-a e^u - b e^{-u}) du,  a = r^2/(4 delta), b = alpha^2 delta,
+// and under a quadrature in u every node's exp(-a e^u) splits into its x and y
+// parts.  So do its cosine transforms: one transform per node instead of one per
+// row of the samples, and the spectrum is their sum of products.
 
-// Samples of the smoothly truncated history kernel on the quarter grid
-// x = mx h, y = my h, 0 <= mx, my < M (the kernel is even in x and y and
-// zero for |x| or |y| >= M h): h^2 G^H(r) chi(x) chi(y), chi(s) =
-// erfc((s - rmid) slope)/2, row-major [my][mx].
-__global__ void __launch_bounds__(256) k_trunc_samples(double *buf, int64_t M, double h, double alpha,
-                                                       double delta, double rmid, double slope,
-                                                       const double *__restrict__ gt,
-                                                       const double *__restrict__ gw)
+// Factor of every node q < Q at x = m h, m < M: exp(-x^2 su_q) chi(x), su_q =
+// e^{u_q}/(4 delta), chi(x) = erfc((x - rmid) slope)/2, row-major [q][m].
+__global__ void __launch_bounds__(256) k_trunc_factors(double *__restrict__ buf, int64_t M, int64_t Q, double h,
+                                                       double rmid, double slope, const double *__restrict__ su)
 {
     const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= M * M) return;
-    const int64_t my = id / M, mx = id % M;
-    // the samples are symmetric in x and y: one of each pair is evaluated
-    if (my > mx) return;
-    const double x = mx * h, y = my * h;
-    const double v = h * h * history_kernel(sqrt(x * x + y * y), alpha, delta, gt, gw) * 0.25 *
-                     erfc((x - rmid) * slope) * erfc((y - rmid) * slope);
-    buf[id] = v;
-    buf[mx * M + my] = v;
+    if (id >= M * Q) return;
+    const double x = (double)(id % M) * h;
+    buf[id] = exp(-x * x * su[id / M]) * 0.5 * erfc((x - rmid) * slope);
 }
 
-// One separable step of the cosine transform of the even samples:
-//   out[a][b] = sum_{k < K} c_k cos(2 pi a k / n) in[b][k],  c_0 = 1, c_k = 2,
-// for a < NA, b < NB (the +-k pairs of the even sequence folded into c_k).
-// Tiles of 64 x 64 outputs per 256-thread workgroup, 4 x 4 per thread, the
-// cosine factors (from a table of cos(2 pi m / n) at m = a k mod n) and the
-// input staged through LDS 32 values of k at a time.
-constexpr int CS_T = 64, CS_K = 32;
+// COS: the cosine transforms of even sequences,
+//   out[a][b] = sum_{k < K} c_k cos(2 pi a k / n) in[b][k],  c_0 = 1, c_k = 2
+// (the +-k pairs folded into c_k; the cosines from a table of cos(2 pi m / n) at m
+// = a k mod n); else the weighted products
+//   out[a][b] = sum_{k < K} w_k in[a][k] in[b][k],
+// for a < NA, b < NB.  Tiles of 32 x 32 outputs per 256-thread workgroup, 2 x 2
+// per thread (64 x 64 are too few tiles for the chip), both inputs staged through
+// LDS 32 values of k at a time.
+constexpr int CS_T = 32, CS_K = 32;
+template <bool COS>
 __global__ void __launch_bounds__(256) k_cos_step(const double *__restrict__ in, int64_t K, int64_t NA, int64_t NB,
-                                                  int n, const double *__restrict__ costab, double *__restrict__ out)
+                                                  int n, const double *__restrict__ tab, double *__restrict__ out)
 {
+    constexpr int E = CS_K * CS_T / 256, R = CS_T / 16;
     __shared__ double ca[CS_K][CS_T + 1];
     __shared__ double ib[CS_K][CS_T + 1];
     const int tid = threadIdx.x;
     const int64_t a0 = (int64_t)blockIdx.x * CS_T, b0 = (int64_t)blockIdx.y * CS_T;
     const int ta = tid / 16, tb = tid % 16;
-    double acc[4][4] = {};
+    // COS: table positions a k mod n of this thread's elements, and their steps
+    int pos[E], step[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+        const int e = tid + 256 * i;
+        const int64_t a = a0 + e % CS_T;
+        pos[i] = COS ? (int)(a * (e / CS_T) % n) : 0;
+        step[i] = COS ? (int)(a * CS_K % n) : 0;
+    }
+    double acc[R][R] = {};
     for (int64_t k0 = 0; k0 < K; k0 += CS_K) {
-        for (int e = tid; e < CS_K * CS_T; e += 256) {
-            const int kk = e / CS_T, aa = e % CS_T;
-            const int64_t k = k0 + kk, a = a0 + aa;
-            double v = 0.0;
-            if (k < K && a < NA) v = (k == 0 ? 1.0 : 2.0) * costab[(int)((a * k) % n)];
-            ca[kk][aa] = v;
-        }
-        for (int e = tid; e < CS_K * CS_T; e += 256) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            const int e = tid + 256 * i;
             const int bb = e / CS_K, kk = e % CS_K;
-            const int64_t k = k0 + kk, b = b0 + bb;
-            ib[kk][bb] = (k < K && b < NB) ? in[b * K + k] : 0.0;
+            const int64_t k = k0 + kk;
+            ib[kk][bb] = k < K && b0 + bb < NB ? in[(b0 + bb) * K + k] : 0.0;
+            if (!COS) ca[kk][bb] = k < K && a0 + bb < NA ? tab[k] * in[(a0 + bb) * K + k] : 0.0;
+        }
+        if (COS) {
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                const int e = tid + 256 * i;
+                const int64_t k = k0 + e / CS_T;
+                ca[e / CS_T][e % CS_T] = k < K && a0 + e % CS_T < NA ? (k == 0 ? 1.0 : 2.0) * tab[pos[i]] : 0.0;
+                pos[i] += step[i];
+                if (pos[i] >= n) pos[i] -= n;
+            }
         }
         __syncthreads();
+#pragma unroll 8
         for (int kk = 0; kk < CS_K; ++kk) {
-            double av[4], bv[4];
+            double av[R], bv[R];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < R; ++i) {
                 av[i] = ca[kk][ta + 16 * i];
                 bv[i] = ib[kk][tb + 16 * i];
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < R; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fma(av[i], bv[j], acc[i][j]);
+                for (int j = 0; j < R; ++j) acc[i][j] = fma(av[i], bv[j], acc[i][j]);
         }
         __syncthreads();
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < R; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < R; ++j) {
             const int64_t a = a0 + ta + 16 * i, b = b0 + tb + 16 * j;
             if (a < NA && b < NB) out[a * NB + b] = acc[i][j];
         }
@@ -1106,20 +1095,22 @@ __global__ void __launch_bounds__(256) k_trunc_table(const double *__restrict__ 
     mtab[id] = c * tr[ly * w + lx] * phi2inv[lx] * phi2inv[ly];
 }
 
-hipError_t launch_trunc_kernel_samples(double *buf, int64_t M, double h, double alpha, double delta, double rmid,
-                                       double slope, const double *gl_t, const double *gl_w, hipStream_t s)
+hipError_t launch_trunc_factors(double *buf, int64_t M, int64_t Q, double h, double rmid, double slope,
+                                const double *su, hipStream_t s)
 {
-    const int64_t tot = M * M;
-    hipLaunchKernelGGL(k_trunc_samples, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, buf, M, h, alpha,
-                       delta, rmid, slope, gl_t, gl_w);
+    hipLaunchKernelGGL(k_trunc_factors, dim3((unsigned)((M * Q + 255) / 256)), dim3(256), 0, s, buf, M, Q, h, rmid,
+                       slope, su);
     return hipGetLastError();
 }
 
-hipError_t launch_cos_step(const double *in, int64_t K, int64_t NA, int64_t NB, int n, const double *costab,
+hipError_t launch_cos_step(bool cosines, const double *in, int64_t K, int64_t NA, int64_t NB, int n, const double *tab,
                            double *out, hipStream_t s)
 {
-    dim3 grid((unsigned)((NA + CS_T - 1) / CS_T), (unsigned)((NB + CS_T - 1) / CS_T));
-    hipLaunchKernelGGL(k_cos_step, grid, dim3(256), 0, s, in, K, NA, NB, n, costab, out);
+    const dim3 grid((unsigned)((NA + CS_T - 1) / CS_T), (unsigned)((NB + CS_T - 1) / CS_T));
+    if (cosines)
+        hipLaunchKernelGGL(k_cos_step<true>, grid, dim3(256), 0, s, in, K, NA, NB, n, tab, out);
+    else
+        hipLaunchKernelGGL(k_cos_step<false>, grid, dim3(256), 0, s, in, K, NA, NB, n, tab, out);
     return hipGetLastError();
 }
 

@@ -371,9 +371,9 @@ hipError_t dev_fj_setup(int64_t ntri, const double *vx, const double *vy, double
                         hipStream_t st);
 hipError_t dev_fj_nearest(mhk_plan *P, const double *vx, const double *vy, const uint8_t *good, double ox,
                           double oy, double cell, int64_t ncx, int64_t ncy, int32_t *tri, hipStream_t st);
-hipError_t launch_trunc_kernel_samples(double *buf, int64_t M, double h, double alpha, double delta, double rmid,
-                                       double slope, const double *gl_t, const double *gl_w, hipStream_t s);
-hipError_t launch_cos_step(const double *in, int64_t K, int64_t NA, int64_t NB, int n, const double *costab,
+hipError_t launch_trunc_factors(double *buf, int64_t M, int64_t Q, double h, double rmid, double slope,
+                                const double *su, hipStream_t s);
+hipError_t launch_cos_step(bool cosines, const double *in, int64_t K, int64_t NA, int64_t NB, int n, const double *tab,
                            double *out, hipStream_t s);
 hipError_t launch_trunc_table(const double *tr, int lmax, const double *phi2inv, double c, double *mtab,
                               hipStream_t s);
