@@ -576,7 +576,7 @@ hipError_t dev_item_fill(const int32_t *ofs, const int32_t *item_ofs, int64_t nw
 }
 
 // ---------------------------------------------------------------------------
-// History part: sources by spreading tile, per-tile lists, target tiles
+// History part: sources by spreading block, per-block lists, target tiles
 // ---------------------------------------------------------------------------
 // block of a point, as the spreading kernels place it (SPB x SPB grid points)
 __device__ inline int64_t tile_index(double x, double y, double ox, double oy, double h, int64_t ntile)

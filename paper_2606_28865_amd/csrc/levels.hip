@@ -52,9 +52,11 @@ namespace mhk {
 // Child-node strengths of every level for the current densities: q_S = w
 // sigma, q_Dx = w nu_x mu, q_Dy = w nu_y mu, with sigma, mu at the child node
 // interpolated from the parent panel's 16 nodal values.  One launch for all
-// levels (workgroup ranges qblk0).
+// levels (workgroup ranges qblk0).  Layout [3][B][n_src], or for the sums on the
+// matrix cores (bp > 0) [3][n_src][bp], the densities of a node side by side and
+// zeros up to bp.
 template <typename T>
-__global__ void __launch_bounds__(256) k_level_q(const LevelDesc *__restrict__ desc, int J, int B, int64_t nb,
+__global__ void __launch_bounds__(256) k_level_q(const LevelDesc *__restrict__ desc, int J, int B, int bp, int64_t nb,
                                                  const T *__restrict__ sigma, const T *__restrict__ mu)
 {
     int j = 0;
@@ -74,22 +76,28 @@ __global__ void __launch_bounds__(256) k_level_q(const LevelDesc *__restrict__ d
 #pragma unroll
     for (int i = 0; i < NGL; ++i) r[i] = row[i];
     const double w = L.sw[s], wx = L.swx[s], wy = L.swy[s];
+    const size_t cs = (size_t)(bp > 0 ? bp : B) * n_src, bs = bp > 0 ? 1 : n_src;
+    q += bp > 0 ? (size_t)s * bp : (size_t)s;
     for (int b = 0; b < B; ++b) {
         if (sigma) {
             const T *f = sigma + (size_t)b * nb + panel * NGL;
             double v = 0;
 #pragma unroll
             for (int i = 0; i < NGL; ++i) v = fma(r[i], (double)f[i], v);
-            q[((size_t)0 * B + b) * n_src + s] = (T)(w * v);
+            q[b * bs] = (T)(w * v);
         }
         if (mu) {
             const T *f = mu + (size_t)b * nb + panel * NGL;
             double v = 0;
 #pragma unroll
             for (int i = 0; i < NGL; ++i) v = fma(r[i], (double)f[i], v);
-            q[((size_t)1 * B + b) * n_src + s] = (T)(wx * v);
-            q[((size_t)2 * B + b) * n_src + s] = (T)(wy * v);
+            q[cs + b * bs] = (T)(wx * v);
+            q[2 * cs + b * bs] = (T)(wy * v);
         }
+    }
+    for (int b = B; b < bp; ++b) {
+        if (sigma) q[b] = (T)0;
+        if (mu) q[cs + b] = q[2 * cs + b] = (T)0;
     }
 }
 
@@ -434,6 +442,120 @@ __global__ void __launch_bounds__(NB) k_level_sums(LevelArgs A)
     }
 }
 
+// The same sums for LV_MM_MIN or more FP64 densities, 16 of them per pass, as
+// products on the matrix cores: one kernel value per lane for 16 targets (lane %
+// 16) and 4 sources (lane / 16) is the 16 x 4 operand of v_mfma_f64_16x16x4, the
+// four sources' strengths the 4 x 16 one (D as K dx times q_Dx plus K dy times
+// q_Dy), and the sums of 16 targets by 16 densities the result (rows 4 v + lane /
+// 16, column lane % 16).  A table evaluation serves 16 densities instead of lv_bch,
+// no source is handed from lane to lane, and out-of-range pairs are skipped 16
+// targets by 4 sources at a time.  Per 64 pairs 192 cycles of the matrix cores
+// beside about 150 of the VALU, whatever the number of densities up to 16: whole
+// evaluations of S and D at 200 thousand targets, 16384 boundary nodes, with 16
+// densities 4.69 -> 3.64 ms, 8 2.42 -> 2.15, 5 1.87 -> 1.64; four take one table
+// evaluation of k_level_sums anyway (1.25 ms).  16 densities at 1.03M outputs,
+// 32768 boundary and 1M volume nodes: 11.8 -> 7.9 ms.
+typedef double d4 __attribute__((ext_vector_type(4)));
+__global__ void __launch_bounds__(256, 3) k_level_mm(LevelArgs A, int bp)
+{
+    extern __shared__ double lds[];
+    int j = 0;
+    while (j + 1 < A.nlev && (int)blockIdx.x >= A.desc[j + 1].mblk0) ++j;
+    const LevelDesc &L = A.desc[j];
+    const int tid = threadIdx.x, nseg = L.nseg;
+    const double *__restrict__ tab = (const double *)L.tab;
+    for (int i = tid; i < (nseg + 1) * TAB_STRIDE; i += 256) lds[i] = i < nseg * TAB_STRIDE ? tab[i] : 0.0;
+    float *s_c7 = reinterpret_cast<float *>(lds + (nseg + 1) * TAB_STRIDE);
+    const float *g7 = reinterpret_cast<const float *>(tab + (size_t)nseg * TAB_STRIDE);
+    for (int i = tid; i <= nseg; i += 256) s_c7[i] = i < nseg ? g7[i] : 0.0f;
+    __syncthreads();
+    const int64_t pos = (int64_t)((int)blockIdx.x - L.mblk0) * (256 / LV_WAVE) + tid / LV_WAVE;
+    if (pos >= L.n_items) return;
+    const int lane = tid % LV_WAVE, r = lane % 16, k = lane / 16;
+    const int item = __builtin_amdgcn_readfirstlane(L.item_order[pos]);
+    const int wave = __builtin_amdgcn_readfirstlane(L.item_wave[item]);
+    const double ps = L.pscale, f_max = L.f_max, f_zero = (double)nseg;
+    double tx[4], ty[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const int64_t t = (int64_t)wave * LV_WAVE + 16 * g + r;
+        tx[g] = t < A.nout ? A.tx[t] * ps : 0.0;
+        ty[g] = t < A.nout ? A.ty[t] * ps : 0.0;
+    }
+    // the item's piece of the list
+    const int l0 = L.wave_ofs[wave], l1 = L.wave_ofs[wave + 1];
+    const int i0 = L.item_ofs[wave], i1 = L.item_ofs[wave + 1];
+    const int size = level_piece(l1 - l0, i1 - i0);
+    const int c0 = __builtin_amdgcn_readfirstlane(l0 + (item - i0) * size);
+    const int c1 = __builtin_amdgcn_readfirstlane(min(l1, c0 + size));
+    const double *__restrict__ sx = L.sx, *__restrict__ sy = L.sy;
+    const int32_t *__restrict__ wave_src = L.wave_src;
+    const int b0 = (int)blockIdx.y * 16;
+    const size_t cs = (size_t)bp * L.n_src;
+    const double *__restrict__ q0 = (const double *)L.q + b0 + r;
+    // lane's source k of four (past the list's end a far one of zero strength),
+    // its strengths for density r; loaded one step ahead, the list entry two
+    struct Src {
+        double x, y, qs, qx, qy;
+    };
+    auto load = [&](int p, int id) {
+        Src v{1e100, 1e100, 0.0, 0.0, 0.0};
+        if (p < c1) {
+            v.x = sx[id] * ps;
+            v.y = sy[id] * ps;
+            const double *q = q0 + (size_t)id * bp;
+            if (A.want_s) v.qs = q[0];
+            if (A.want_d) {
+                v.qx = q[cs];
+                v.qy = q[2 * cs];
+            }
+        }
+        return v;
+    };
+    d4 S[4], D[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) S[g] = D[g] = d4{0.0, 0.0, 0.0, 0.0};
+    auto entry = [&](int p) { return p < c1 ? wave_src[p] : 0; };
+    Src cur = load(c0 + k, entry(c0 + k));
+    int id = entry(c0 + 4 + k);
+    for (int p = c0; p < c1; p += 4) {
+        const int id2 = entry(p + 8 + k);
+        const Src nxt = load(p + 4 + k, id);
+#pragma unroll
+        for (int g = 0; g < 4; g += 2) {
+            bool in0, in1;
+            const PairGeo<double> g0 =
+                pair_geo<double, TAB_STRIDE>(tx[g], ty[g], cur.x, cur.y, f_max, f_zero, lds, s_c7, in0);
+            const PairGeo<double> g1 =
+                pair_geo<double, TAB_STRIDE>(tx[g + 1], ty[g + 1], cur.x, cur.y, f_max, f_zero, lds, s_c7, in1);
+            if (!__any(in0 || in1)) continue;
+            double ks0, kd0, ks1, kd1;
+            horner2(g0, g1, ks0, kd0, ks1, kd1);
+            if (A.want_s) {
+                S[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(ks0, cur.qs, S[g], 0, 0, 0);
+                S[g + 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ks1, cur.qs, S[g + 1], 0, 0, 0);
+            }
+            if (A.want_d) {
+                D[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(kd0 * g0.dx, cur.qx, D[g], 0, 0, 0);
+                D[g + 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(kd1 * g1.dx, cur.qx, D[g + 1], 0, 0, 0);
+                D[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(kd0 * g0.dy, cur.qy, D[g], 0, 0, 0);
+                D[g + 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(kd1 * g1.dy, cur.qy, D[g + 1], 0, 0, 0);
+            }
+        }
+        cur = nxt;
+        id = id2;
+    }
+    if (b0 + r >= A.B) return;
+    double *part = (double *)L.part + ((size_t)item * A.ncomp * A.B + b0 + r) * LV_WAVE + k;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            if (A.want_s) part[16 * g + 4 * v] = S[g][v];
+            if (A.want_d) part[(size_t)A.B * LV_WAVE + 16 * g + 4 * v] = D[g][v] * L.d_scale;
+        }
+}
+
 // LDS bytes of a level's table: the rows of nseg + 1 segments (the last zero)
 // and, FP64, their c_7 as floats
 template <typename T, int STRIDE>
@@ -448,7 +570,8 @@ template <typename T>
 static hipError_t level_q(mhk_plan *P, hipStream_t st, const void *sigma, const void *mu)
 {
     if (P->levq_grid == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_level_q<T>, dim3(P->levq_grid), dim3(256), 0, st, P->lev_desc, P->J, P->bat, P->nb,
+    hipLaunchKernelGGL(k_level_q<T>, dim3(P->levq_grid), dim3(256), 0, st, P->lev_desc, P->J, P->bat,
+                       level_mm(P, P->bat) ? level_bp(P->bat) : 0, P->nb,
                        (const T *)sigma, (const T *)mu);
     return hipGetLastError();
 }
@@ -463,7 +586,7 @@ mhk_status level_descs(mhk_plan *P, bool vol, std::vector<LevelDesc> &out)
     out.assign((size_t)P->J, LevelDesc{});
     const bool f64 = P->p.prec == MHK_FP64;
     const int per = P->p.lv_block / LV_WAVE;
-    int64_t blk = 0, qblk = 0;
+    int64_t blk = 0, qblk = 0, mblk = 0;
     for (int j = 0; j < P->J; ++j) {
         const Level &L = P->lev[j];
         LevelDesc &d = out[(size_t)j];
@@ -492,12 +615,14 @@ mhk_status level_descs(mhk_plan *P, bool vol, std::vector<LevelDesc> &out)
         d.f_max = L.a_max * L.seg_inv;
         d.blk0 = (int)blk;
         d.qblk0 = (int)qblk;
+        d.mblk0 = (int)mblk;
         blk += (I.n + per - 1) / per;
+        mblk += (I.n + 256 / LV_WAVE - 1) / (256 / LV_WAVE);
         qblk += (d.n_src + 255) / 256;
         const size_t lds = f64 ? level_lds<double, TAB_STRIDE>(L.nseg) : level_lds<float, TABF_STRIDE>(L.nseg);
         P->lev_lds = std::max(P->lev_lds, lds);
     }
-    if (P->lev_lds > 160 * 1024 || blk > INT32_MAX || qblk > INT32_MAX) {
+    if (P->lev_lds > 160 * 1024 || mblk > INT32_MAX || qblk > INT32_MAX) {
         set_error("level tables or work-item lists too large");
         return MHK_EUNSUPPORTED;
     }
@@ -505,6 +630,7 @@ mhk_status level_descs(mhk_plan *P, bool vol, std::vector<LevelDesc> &out)
         P->vlev_grid = (unsigned)blk;
     } else {
         P->lev_grid = (unsigned)blk;
+        P->levm_grid = (unsigned)mblk;
         P->levq_grid = (unsigned)qblk;
     }
     return MHK_OK;
@@ -569,6 +695,17 @@ static hipError_t level_sums(mhk_plan *P, hipStream_t st, bool vol, bool want_s,
     A.want_s = want_s;
     A.want_d = want_d;
     A.counter = P->lv_counter;
+    if constexpr (std::is_same<T, double>::value)
+        if (!vol && level_mm(P, A.B)) {
+            if (P->levm_grid == 0) return hipSuccess;
+            A.nlev = P->J;
+            const void *fn = (const void *)k_level_mm;
+            if (P->lev_lds > 64 * 1024)
+                (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)P->lev_lds);
+            const int bp = level_bp(A.B);
+            hipLaunchKernelGGL(k_level_mm, dim3(P->levm_grid, (unsigned)(bp / 16)), dim3(256), P->lev_lds, st, A, bp);
+            return hipGetLastError();
+        }
     // densities per pass: the plan's lv_bch, or fewer for a smaller batch
     // (rounded up to an instantiated size; missing densities of the last
     // pass are skipped)

@@ -116,7 +116,8 @@ struct LevelDesc {
     double f_max;         // a_max seg_inv
     int64_t n_src, n_items;
     int nseg, nchild;
-    int blk0, qblk0;      // first workgroup of the level in the launch over all levels (sums, strengths)
+    int blk0, qblk0, mblk0;   // first workgroup of the level in the launch over all levels (sums, strengths,
+                              // sums on the matrix cores)
 };
 
 struct Level {
@@ -332,7 +333,7 @@ struct mhk_plan {
     hipStream_t side = nullptr;
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
     mhk::LevelDesc *lev_desc = nullptr, *vlev_desc = nullptr;   // device, [J]
-    unsigned lev_grid = 0, vlev_grid = 0, levq_grid = 0;        // workgroups of the launches over all levels
+    unsigned lev_grid = 0, vlev_grid = 0, levq_grid = 0, levm_grid = 0;   // workgroups of the launches over all levels
     size_t lev_lds = 0;                          // LDS bytes of the largest level table
     hipGraphExec_t gexec = nullptr;             // captured evaluation
 };
@@ -341,6 +342,17 @@ namespace mhk {
 
 // kernels launchers (defined in the .hip files); density and output pointers
 // are of the plan's precision
+// The layer levels' sums go through the matrix cores from LV_MM_MIN FP64
+// densities on (not in the persistent launch); the strengths are then padded to
+// whole groups of 16.  Five densities 1.87 -> 1.64 ms; four share one pass of the
+// other kernel (1.25 ms).
+constexpr int LV_MM_MIN = 5;
+inline bool level_mm(const mhk_plan *P, int batch)
+{
+    return P->p.prec == MHK_FP64 && batch >= LV_MM_MIN && !P->p.lv_persist;
+}
+constexpr int level_bp(int batch) { return (batch + 15) / 16 * 16; }
+
 // child-node strengths of all levels, and the sums of all levels (vol: the
 // volume levels' single-layer sums), each into its items' parts
 hipError_t launch_level_densities(mhk_plan *P, hipStream_t st, const void *sigma, const void *mu);

@@ -804,11 +804,12 @@ static mhk_status build_mask(mhk_plan *P, Host &H, StreamTmp &tmp, int8_t *rin)
 // and density chunk, between LV_PIECE_MIN (a workgroup loads the level's
 // table once, some 30 loads per thread, which a piece should outweigh) and
 // LV_PIECE_MAX sources.
-static mhk_status count_items(mhk_plan *P, const int32_t *wave_ofs, int64_t nwave, int64_t total, LevelItems &I,
-                              int64_t *n_dev)
+static mhk_status count_items(mhk_plan *P, bool vol, const int32_t *wave_ofs, int64_t nwave, int64_t total,
+                              LevelItems &I, int64_t *n_dev)
 {
     const hipStream_t st = P->stream;
-    const int64_t chunks = (P->p.batch + P->p.lv_bch - 1) / P->p.lv_bch;
+    const int per = !vol && level_mm(P, P->p.batch) ? 16 : P->p.lv_bch;      // densities per pass
+    const int64_t chunks = (P->p.batch + per - 1) / per;
     const int64_t want = (total * chunks / LV_ITEMS + 63) / 64 * 64;
     I.piece = (int)std::min<int64_t>(LV_PIECE_MAX, std::max<int64_t>(LV_PIECE_MIN, want));
     StreamTmp tmp(st);
@@ -920,7 +921,8 @@ mhk_status level_nodes(mhk_plan *P, Host &H, int j, int64_t *tot)
     }
     {
         char *q = nullptr;
-        TRY(dalloc(P, &q, 3 * (int64_t)P->p.batch * L.n_src * (int64_t)P->es));
+        const int64_t nq = level_mm(P, P->p.batch) ? level_bp(P->p.batch) : P->p.batch;
+        TRY(dalloc(P, &q, 3 * nq * L.n_src * (int64_t)P->es));
         L.q = q;
     }
     return MHK_OK;
@@ -940,7 +942,7 @@ mhk_status level_lists(mhk_plan *P, int j, int64_t total, int64_t *n_items)
     const double R = L.radius, R2 = R * R * (1.0 + 1e-9);
     MHK_HIP(dev_wave_fill(P->tx, P->ty, P->nout, L.n_wave, R, R2, L.ox, L.oy, L.cell, L.ncx, L.ncy, L.cell_start,
                           L.sx, L.sy, L.wave_ofs, L.wave_src, P->stream));
-    return count_items(P, L.wave_ofs, L.n_wave, total, L.items, n_items);
+    return count_items(P, false, L.wave_ofs, L.n_wave, total, L.items, n_items);
 }
 
 // Level j's kernel table.
@@ -1925,7 +1927,7 @@ mhk_status build_vlevels(mhk_plan *P, Host &H)
         TRY(dalloc(P, &V.wave_src, std::max<int64_t>(1, total)));
         MHK_HIP(dev_wave_fill(P->tx, P->ty, nout, nwave, R, R2, L.ox, L.oy, L.cell, L.ncx, L.ncy, V.cell_start, V.sx,
                               V.sy, V.wave_ofs, V.wave_src, st));
-        TRY(count_items(P, V.wave_ofs, nwave, total, V.items, tot));
+        TRY(count_items(P, true, V.wave_ofs, nwave, total, V.items, tot));
         TRY(tmp.fetch(&V.items.n, tot, 1));
         TRY(fill_items(P, V.wave_ofs, nwave, 1, V.items));
     }
@@ -2137,7 +2139,7 @@ mhk_status mhk_plan_footprint(const mhk_params *params, const mhk_boundary *b, c
     s += 3 * B * nout * 8;                    // history accumulators
     for (int j = 1; j <= p.J; ++j) {          // levels: sources, and the items' parts (one item per wavefront)
         int64_t ns = nb << j;
-        s += ns * (8 * 5 + 4) + 3 * B * ns * 8 + 2 * B * nout * 8;
+        s += ns * (8 * 5 + 4) + 3 * (B < LV_MM_MIN ? B : level_bp((int)B)) * ns * 8 + 2 * B * nout * 8;
     }
     s += nb * (8 * 7 + 4) + 3 * B * nb * 8;   // local
     s += nout * ((p.local_order >= 2 ? LOCAL_GEO_N2 : LOCAL_GEO_N1) * 8 + 4 + 1);   // local geometry per target
