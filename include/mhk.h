@@ -102,7 +102,7 @@ typedef struct {
                         256 or 512 (0: 256); the same sums in another order       */
     int lv_bch;      /* densities per pass of the level sums for batch > 1: 1, 2, 4
                         or 8 (0: 4); each kernel-table evaluation serves them all.
-                        FP64 sums of five or more densities take 16 at a time,
+                        Sums of five or more densities take 16 at a time,
                         whatever it says                                          */
     int lv_persist;  /* 1: the level sums run as one persistent launch per level (a
                         grid that fills the device once, wavefronts taking (target

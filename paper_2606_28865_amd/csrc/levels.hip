@@ -442,7 +442,7 @@ __global__ void __launch_bounds__(NB) k_level_sums(LevelArgs A)
     }
 }
 
-// The same sums for LV_MM_MIN or more FP64 densities, 16 of them per pass, as
+// The same sums for LV_MM_MIN or more densities, 16 of them per pass, as
 // products on the matrix cores: one kernel value per lane for 16 targets (lane %
 // 16) and 4 sources (lane / 16) is the 16 x 4 operand of v_mfma_f64_16x16x4, the
 // four sources' strengths the 4 x 16 one (D as K dx times q_Dx plus K dy times
@@ -455,7 +455,14 @@ __global__ void __launch_bounds__(NB) k_level_sums(LevelArgs A)
 // densities 4.69 -> 3.64 ms, 8 2.42 -> 2.15, 5 1.87 -> 1.64; four take one table
 // evaluation of k_level_sums anyway (1.25 ms).  16 densities at 1.03M outputs,
 // 32768 boundary and 1M volume nodes: 11.8 -> 7.9 ms.
+// FP32: 8 densities at 366 thousand outputs, 65536 boundary nodes 1.87 -> 1.78 ms;
+// at 200 thousand targets, 16384 boundary nodes 8 as before (1.02 against 1.01 ms),
+// 5 723 -> 712 us.
+// FP32 plans form the kernel values in FP32, as above, and their products and sums
+// in FP64 (the FP32 matrix instructions would need their sums moved to FP64 every
+// 64 sources).
 typedef double d4 __attribute__((ext_vector_type(4)));
+template <typename T, int STRIDE>
 __global__ void __launch_bounds__(256, 3) k_level_mm(LevelArgs A, int bp)
 {
     extern __shared__ double lds[];
@@ -463,18 +470,23 @@ __global__ void __launch_bounds__(256, 3) k_level_mm(LevelArgs A, int bp)
     while (j + 1 < A.nlev && (int)blockIdx.x >= A.desc[j + 1].mblk0) ++j;
     const LevelDesc &L = A.desc[j];
     const int tid = threadIdx.x, nseg = L.nseg;
-    const double *__restrict__ tab = (const double *)L.tab;
-    for (int i = tid; i < (nseg + 1) * TAB_STRIDE; i += 256) lds[i] = i < nseg * TAB_STRIDE ? tab[i] : 0.0;
-    float *s_c7 = reinterpret_cast<float *>(lds + (nseg + 1) * TAB_STRIDE);
-    const float *g7 = reinterpret_cast<const float *>(tab + (size_t)nseg * TAB_STRIDE);
-    for (int i = tid; i <= nseg; i += 256) s_c7[i] = i < nseg ? g7[i] : 0.0f;
+    T *s_tab = reinterpret_cast<T *>(lds);
+    const T *__restrict__ tab = (const T *)L.tab;
+    for (int i = tid; i < (nseg + 1) * STRIDE; i += 256) s_tab[i] = i < nseg * STRIDE ? tab[i] : (T)0;
+    float *s_c7 = nullptr;
+    if constexpr (std::is_same<T, double>::value) {
+        s_c7 = reinterpret_cast<float *>(s_tab + (nseg + 1) * STRIDE);
+        const float *g7 = reinterpret_cast<const float *>(tab + (size_t)nseg * STRIDE);
+        for (int i = tid; i <= nseg; i += 256) s_c7[i] = i < nseg ? g7[i] : 0.0f;
+    }
     __syncthreads();
     const int64_t pos = (int64_t)((int)blockIdx.x - L.mblk0) * (256 / LV_WAVE) + tid / LV_WAVE;
     if (pos >= L.n_items) return;
     const int lane = tid % LV_WAVE, r = lane % 16, k = lane / 16;
     const int item = __builtin_amdgcn_readfirstlane(L.item_order[pos]);
     const int wave = __builtin_amdgcn_readfirstlane(L.item_wave[item]);
-    const double ps = L.pscale, f_max = L.f_max, f_zero = (double)nseg;
+    const double ps = L.pscale;
+    const T f_max = (T)L.f_max, f_zero = (T)nseg;
     double tx[4], ty[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
@@ -492,18 +504,19 @@ __global__ void __launch_bounds__(256, 3) k_level_mm(LevelArgs A, int bp)
     const int32_t *__restrict__ wave_src = L.wave_src;
     const int b0 = (int)blockIdx.y * 16;
     const size_t cs = (size_t)bp * L.n_src;
-    const double *__restrict__ q0 = (const double *)L.q + b0 + r;
+    const T *__restrict__ q0 = (const T *)L.q + b0 + r;
     // lane's source k of four (past the list's end a far one of zero strength),
     // its strengths for density r; loaded one step ahead, the list entry two
     struct Src {
         double x, y, qs, qx, qy;
     };
+    constexpr double far = 1e15;
     auto load = [&](int p, int id) {
-        Src v{1e100, 1e100, 0.0, 0.0, 0.0};
+        Src v{far, far, 0.0, 0.0, 0.0};
         if (p < c1) {
             v.x = sx[id] * ps;
             v.y = sy[id] * ps;
-            const double *q = q0 + (size_t)id * bp;
+            const T *q = q0 + (size_t)id * bp;
             if (A.want_s) v.qs = q[0];
             if (A.want_d) {
                 v.qx = q[cs];
@@ -524,13 +537,13 @@ __global__ void __launch_bounds__(256, 3) k_level_mm(LevelArgs A, int bp)
 #pragma unroll
         for (int g = 0; g < 4; g += 2) {
             bool in0, in1;
-            const PairGeo<double> g0 =
-                pair_geo<double, TAB_STRIDE>(tx[g], ty[g], cur.x, cur.y, f_max, f_zero, lds, s_c7, in0);
-            const PairGeo<double> g1 =
-                pair_geo<double, TAB_STRIDE>(tx[g + 1], ty[g + 1], cur.x, cur.y, f_max, f_zero, lds, s_c7, in1);
+            const PairGeo<T> g0 = pair_geo<T, STRIDE>(tx[g], ty[g], cur.x, cur.y, f_max, f_zero, s_tab, s_c7, in0);
+            const PairGeo<T> g1 =
+                pair_geo<T, STRIDE>(tx[g + 1], ty[g + 1], cur.x, cur.y, f_max, f_zero, s_tab, s_c7, in1);
             if (!__any(in0 || in1)) continue;
-            double ks0, kd0, ks1, kd1;
-            horner2(g0, g1, ks0, kd0, ks1, kd1);
+            T s0, d0, s1, d1;
+            horner2(g0, g1, s0, d0, s1, d1);
+            const double ks0 = s0, kd0 = d0, ks1 = s1, kd1 = d1;
             if (A.want_s) {
                 S[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(ks0, cur.qs, S[g], 0, 0, 0);
                 S[g + 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ks1, cur.qs, S[g + 1], 0, 0, 0);
@@ -546,13 +559,13 @@ __global__ void __launch_bounds__(256, 3) k_level_mm(LevelArgs A, int bp)
         id = id2;
     }
     if (b0 + r >= A.B) return;
-    double *part = (double *)L.part + ((size_t)item * A.ncomp * A.B + b0 + r) * LV_WAVE + k;
+    T *part = (T *)L.part + ((size_t)item * A.ncomp * A.B + b0 + r) * LV_WAVE + k;
 #pragma unroll
     for (int g = 0; g < 4; ++g)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            if (A.want_s) part[16 * g + 4 * v] = S[g][v];
-            if (A.want_d) part[(size_t)A.B * LV_WAVE + 16 * g + 4 * v] = D[g][v] * L.d_scale;
+            if (A.want_s) part[16 * g + 4 * v] = (T)S[g][v];
+            if (A.want_d) part[(size_t)A.B * LV_WAVE + 16 * g + 4 * v] = (T)(D[g][v] * L.d_scale);
         }
 }
 
@@ -695,17 +708,17 @@ static hipError_t level_sums(mhk_plan *P, hipStream_t st, bool vol, bool want_s,
     A.want_s = want_s;
     A.want_d = want_d;
     A.counter = P->lv_counter;
-    if constexpr (std::is_same<T, double>::value)
-        if (!vol && level_mm(P, A.B)) {
-            if (P->levm_grid == 0) return hipSuccess;
-            A.nlev = P->J;
-            const void *fn = (const void *)k_level_mm;
-            if (P->lev_lds > 64 * 1024)
-                (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)P->lev_lds);
-            const int bp = level_bp(A.B);
-            hipLaunchKernelGGL(k_level_mm, dim3(P->levm_grid, (unsigned)(bp / 16)), dim3(256), P->lev_lds, st, A, bp);
-            return hipGetLastError();
-        }
+    if (!vol && level_mm(P, A.B)) {
+        if (P->levm_grid == 0) return hipSuccess;
+        A.nlev = P->J;
+        const void *fn = (const void *)k_level_mm<T, STRIDE>;
+        if (P->lev_lds > 64 * 1024)
+            (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)P->lev_lds);
+        const int bp = level_bp(A.B);
+        hipLaunchKernelGGL((k_level_mm<T, STRIDE>), dim3(P->levm_grid, (unsigned)(bp / 16)), dim3(256), P->lev_lds, st,
+                           A, bp);
+        return hipGetLastError();
+    }
     // densities per pass: the plan's lv_bch, or fewer for a smaller batch
     // (rounded up to an instantiated size; missing densities of the last
     // pass are skipped)

@@ -342,14 +342,14 @@ namespace mhk {
 
 // kernels launchers (defined in the .hip files); density and output pointers
 // are of the plan's precision
-// The layer levels' sums go through the matrix cores from LV_MM_MIN FP64
+// The layer levels' sums go through the matrix cores from LV_MM_MIN
 // densities on (not in the persistent launch); the strengths are then padded to
 // whole groups of 16.  Five densities 1.87 -> 1.64 ms; four share one pass of the
 // other kernel (1.25 ms).
 constexpr int LV_MM_MIN = 5;
 inline bool level_mm(const mhk_plan *P, int batch)
 {
-    return P->p.prec == MHK_FP64 && batch >= LV_MM_MIN && !P->p.lv_persist;
+    return batch >= LV_MM_MIN && !P->p.lv_persist;
 }
 constexpr int level_bp(int batch) { return (batch + 15) / 16 * 16; }
 
