@@ -394,15 +394,51 @@ def level_sums_traffic():
         return None
 
 
-def level_bisections(w, info, j):
+def panel_coefficients(boundary):
+    """Largest Legendre coefficients over the panels, per degree, of the
+    position, the speed and the normal (tails at rounding level dropped), and
+    the largest half-length of a panel."""
+    import synth
+    tg, wg = synth.gauss_legendre()
+    k = np.arange(16)
+    leg = (2 * k + 1) / 2 * wg[:, None] * np.polynomial.legendre.legvander(tg, 15)
+    x, y, nx, ny, w = (np.asarray(boundary[q]).reshape(-1, 16) for q in ("x", "y", "nx", "ny", "w"))
+    ext = max(np.abs(x).max(), np.abs(y).max())
+    x, y, sp = x - x[:, :1], y - y[:, :1], w / wg
+    g = np.hypot(x @ leg, y @ leg).max(0)
+    n = np.hypot(nx @ leg, ny @ leg).max(0)
+    s = np.abs(sp @ leg).max(0)
+    eps = 16 * 2.2e-16
+    g[(k > 1) & (g < eps * ext)] = 0.0
+    s[(k > 0) & (s < 16 * eps * s[0])] = 0.0
+    n[(k > 0) & (n < 16 * eps)] = 0.0
+    return g, s, n, float(sp.max())
+
+
+def rule_error(coef, m, delta_j):
+    """Bound of the 16-node rule's error on panels bisected m times (the
+    library's rule_error)."""
+    g, s, n, _ = coef
+    w, k, best = 0.5 ** m, np.arange(16), np.inf
+    rho = 1.5
+    while rho < 64.0:
+        a, b = 0.5 * (rho + 1 / rho), 0.5 * (rho - 1 / rho) * w
+        lr = np.arccosh(max(1 - w + w * a, np.sqrt(1 + b * b)))
+        c = np.cosh(k * lr)
+        e = (b * np.sum(g * k * np.sinh(k * lr)) / np.sinh(lr)) ** 2 / delta_j - 32 * np.log(rho)
+        if e < 600.0:
+            best = min(best, np.exp(e) * np.cosh(15 * lr) * np.sum(s * c) * np.sum(n * c))
+        rho *= 1.166
+    return best / (32 * s[0] * max(0.5, n[0]))
+
+
+def level_bisections(coef, info, j):
     """Bisections of every panel at level j: j, or fewer where the 16-node
     rule resolves the level's kernel to tol/100 on longer panels (the
-    library's rule, from the largest half-length of a panel)."""
-    import synth
-    _, wg = synth.gauss_legendre()
-    half = float(np.max(np.asarray(w.boundary["w"]).reshape(-1, 16) / wg))
-    hmax = (info["tol"] * 1e-2 / 1.5e-11) ** (1.0 / 18.0) * np.sqrt(info["delta"] / 4.0 ** (j - 1))
-    while j > 0 and half / (1 << (j - 1)) <= hmax:
+    library's rule)."""
+    delta_j, err = info["delta"] / 4.0 ** (j - 1), info["tol"] * 1e-2
+    hmax = (err / 1.5e-11) ** (1.0 / 18.0) * np.sqrt(delta_j)
+    while j > 0 and coef[3] / (1 << (j - 1)) <= hmax and rule_error(coef, j - 1, delta_j) <= err:
         j -= 1
     return j
 
@@ -429,9 +465,10 @@ def level_pairs(w, info):
     """Pairs (target, child node) with r < R_j summed over the levels."""
     from scipy.spatial import cKDTree
     tg = np.concatenate([np.stack([w.tx, w.ty], 1), np.stack([w.boundary["x"], w.boundary["y"]], 1)])
+    coef = panel_coefficients(w.boundary)
     pairs = 0.0
     for j in range(1, info["J"] + 1):
-        tree = cKDTree(child_nodes(w, level_bisections(w, info, j)))
+        tree = cKDTree(child_nodes(w, level_bisections(coef, info, j)))
         cnt = tree.query_ball_point(tg, info["level_radius"][j - 1], return_length=True, workers=-1)
         pairs += float(np.sum(cnt))
     return pairs

@@ -540,7 +540,11 @@ struct Host {
     std::vector<double> gl_t, gl_w;
     std::vector<long double> bary;
     std::vector<int64_t> prev, next;
+    std::vector<double> leg;           // [16][16] nodal values -> Legendre coefficients
     double panel_half = 0;             // largest half-length of a panel (speed in the panel parameter)
+    // largest |Legendre coefficient| over the panels, per degree: of the
+    // position (length of the vector), the speed and the normal
+    double cg[NGL] = {0}, cs[NGL] = {0}, cn[NGL] = {0};
     double xmin, xmax, ymin, ymax;
     // all targets (off-surface then boundary), in output order
     std::vector<double> tx, ty;
@@ -632,6 +636,21 @@ void host_common(Host &H)
         for (int k = 0; k < NGL; ++k)
             if (k != i) pr *= ((long double)H.gl_t[i] - H.gl_t[k]);
         H.bary[i] = 1 / pr;
+    }
+    // Legendre coefficients c_k = (2k+1)/2 sum_i w_i P_k(t_i) f_i
+    H.leg.assign(NGL * NGL, 0.0);
+    for (int i = 0; i < NGL; ++i) {
+        double t = H.gl_t[i], p0 = 1, p1 = t;
+        for (int k = 0; k < NGL; ++k) {
+            double pk = (k == 0) ? 1.0 : (k == 1 ? t : 0.0);
+            if (k >= 2) {
+                double p2 = ((2 * k - 1) * t * p1 - (k - 1) * p0) / k;
+                p0 = p1;
+                p1 = p2;
+                pk = p2;
+            }
+            H.leg[k * NGL + i] = (2 * k + 1) / 2.0 * H.gl_w[i] * pk;
+        }
     }
     const mhk_boundary *b = H.b;
     for (int64_t i = 0; i < b->n_panels * NGL; ++i) H.panel_half = std::max(H.panel_half, b->w[i] / H.gl_w[i % NGL]);
@@ -794,10 +813,12 @@ static mhk_status build_mask(mhk_plan *P, Host &H, StreamTmp &tmp, int8_t *rin)
     return MHK_OK;
 }
 
-// Dyadic level j (Section 4.2): every panel bisected j times; child nodes are
-// the 16-point Gauss-Legendre nodes of each child interval, with geometry
-// interpolated by the parent's degree-15 polynomial, normals renormalised,
-// and weights w_GL,child * speed * 2^-j.
+// Dyadic level j (Section 4.2): every panel bisected j times (or fewer times,
+// level_bisections); child nodes are the 16-point Gauss-Legendre nodes of each
+// child interval, with geometry interpolated by the parent's degree-15
+// polynomial, normals renormalised, and weights w_GL,child * speed * (child
+// length / panel length).
+//
 // Pieces of a level's candidate lists (total sources in all lists).  A piece
 // is a whole number of 64-source batches, as long as the pieces of all levels
 // still fill the device several times over: about LV_ITEMS items per level
@@ -833,25 +854,102 @@ static mhk_status fill_items(mhk_plan *P, const int32_t *wave_ofs, int64_t nwave
     return MHK_OK;
 }
 
+// Largest Legendre coefficients of the panels' geometry, per degree (H.cg, H.cs,
+// H.cn).
+static void panel_coefficients(Host &H)
+{
+    const mhk_boundary *b = H.b;
+    double lt[NGL][NGL];                               // [node][degree]
+    for (int i = 0; i < NGL; ++i)
+        for (int k = 0; k < NGL; ++k) lt[i][k] = H.leg[k * NGL + i];
+    double mg[NGL] = {0}, mn[NGL] = {0};
+    for (int64_t p = 0; p < b->n_panels; ++p) {
+        double x[NGL] = {0}, y[NGL] = {0}, nx[NGL] = {0}, ny[NGL] = {0}, s[NGL] = {0};
+        for (int i = 0; i < NGL; ++i) {
+            const int64_t q = p * NGL + i;
+            // (from the panel's first node: smaller numbers, less rounding)
+            const double xv = b->x[q] - b->x[p * NGL], yv = b->y[q] - b->y[p * NGL], sv = b->w[q] / H.gl_w[i];
+            for (int k = 0; k < NGL; ++k) {
+                x[k] += lt[i][k] * xv;
+                y[k] += lt[i][k] * yv;
+                nx[k] += lt[i][k] * b->nx[q];
+                ny[k] += lt[i][k] * b->ny[q];
+                s[k] += lt[i][k] * sv;
+            }
+        }
+        for (int k = 0; k < NGL; ++k) {
+            mg[k] = std::max(mg[k], x[k] * x[k] + y[k] * y[k]);
+            mn[k] = std::max(mn[k], nx[k] * nx[k] + ny[k] * ny[k]);
+            H.cs[k] = std::max(H.cs[k], fabs(s[k]));
+        }
+    }
+    // the rounding of the data is no content of the curve: it is the same for
+    // every number of bisections
+    const double eps = 16 * 2.2e-16, ext = std::max(std::max(fabs(H.xmin), fabs(H.xmax)), std::max(fabs(H.ymin), fabs(H.ymax)));
+    for (int k = 0; k < NGL; ++k) {
+        H.cg[k] = sqrt(mg[k]);
+        H.cn[k] = sqrt(mn[k]);
+        if (k > 1 && H.cg[k] < eps * ext) H.cg[k] = 0;
+        if (k > 0 && H.cs[k] < 16 * eps * H.cs[0]) H.cs[k] = 0;
+        if (k > 0 && H.cn[k] < 16 * eps) H.cn[k] = 0;
+    }
+}
+
+// Error of the 16-node rule on the children of panels bisected m times, for
+// level kernels of time delta_j, relative to the kernels' maxima and whatever the
+// nodal values.  What a child panel sums is density x speed x K_j^S(|x - gamma|), or
+// (x - gamma).nu K_j^D, all interpolated by the parent's polynomials, and a
+// Gauss rule errs by rho^-32 times the integrand's largest modulus on the child's
+// Bernstein ellipse of parameter rho (semi-axes a, b = (rho +- 1/rho)/2).  All
+// children's ellipses lie in the parent's ellipse of parameter R, where a Legendre
+// polynomial of degree k is at most cosh(k log R): the density is at most
+// cosh(15 log R), speed and normal grow by T and N, the curve moves by at most G
+// B off the real plane (B = b 2^-m, G its largest derivative), and a Gaussian of
+// time up to delta_j/4 grows by exp((G B)^2/delta_j).  The product, minimised over
+// rho, is an upper bound up to its constant, which is fitted: on 240 random curves
+// (starfish of 2 to 14 arms, uneven parameters and panels, ellipses of aspect up to
+// 8; 10 to 120 panels; 0, 1 and 2 bisections; half-lengths 0.15 to 2.2
+// sqrt(delta_j)) it was 1.9 times or more the largest error over all nodal values of
+// S or D, in the median 200 times without bisections and 3000 with one.
+static double rule_error(const Host &H, int m, double delta_j)
+{
+    const double w = ldexp(1.0, -m);
+    double best = 1e300;
+    for (double rho = 1.5; rho < 64.0; rho *= 1.166) {
+        const double a = 0.5 * (rho + 1.0 / rho), bb = 0.5 * (rho - 1.0 / rho) * w;
+        // the parent's ellipse through the end of the longer axis of the outermost child's
+        const double lr = acosh(std::max(1.0 - w + w * a, sqrt(1.0 + bb * bb))), sh = sinh(lr);
+        double G = 0, T = 0, N = 0;
+        for (int k = 0; k < NGL; ++k) {
+            const double c = cosh(k * lr);
+            G += H.cg[k] * k * sinh(k * lr) / sh;
+            T += H.cs[k] * c;
+            N += H.cn[k] * c;
+        }
+        const double g = G * bb;
+        best = std::min(best, exp(g * g / delta_j - 32.0 * log(rho)) * cosh(15.0 * lr) * T * N);
+    }
+    return best / (32.0 * H.cs[0] * std::max(0.5, H.cn[0]));
+}
+
 // Bisections of every panel at level j: at most j (Section 4.2), fewer where
 // the 16-node rule integrates level j's kernel on longer panels just as well.
-// The rule is exact to degree 31 and the densities are polynomials of degree
-// 15 on a panel, so the error is at most that of the best approximation of
-// the kernel by degree 16 along the panel, whatever the nodal values: with h
-// the panel's half-length in units of sqrt(delta_j), the Chebyshev tails
-// beyond degree 16 of K_j^S and of (x - y).nu K_j^D, largest over the target's
-// position, are 1.4e-12, 7.1e-12, 1.3e-10, 1.4e-9, 1.1e-8 and 2.9e-7 (D at
-// most 1.4 times as much) of the kernels' maxima at h = 0.9, 1, 1.2, 1.4, 1.6
-// and 2, below 1.5e-11 h^18 from h = 0.85 on; a child panel is as long as
-// keeps that below tol/100.  Half the nodes are half the work of a level: whole
-// evaluations of S and D with 65536 boundary nodes (h = 0.15 after j
-// bisections, tol 1e-8: j - 2 are taken) went from 1386 to 800 us, of 16
-// densities with 32768 (h = 0.26, tol 1e-10: j - 1) from 19.3 to 13.6 ms.
+// Two conditions keep the error below tol/100 on every child panel.  On a
+// straight one of half-length h sqrt(delta_j) it is the kernel's Chebyshev tail
+// beyond degree 16 (the density has degree 15, the rule degree 31), below 1.5e-11
+// h^18 from h = 0.85 on (1.4e-12, 1.3e-10, 1.1e-8 and 2.9e-7 at h = 0.9, 1.2, 1.6 and 2, D
+// at most 1.4 times as much).  Curved panels and uneven speeds add to the
+// integrand's degree: on the starfish with 32 panels (tol 1e-10, h = 0.86) D erred
+// by 1e-8 without bisections; rule_error bounds what they add.  Half the nodes
+// are half the work of a level: whole evaluations of S and D with 65536
+// boundary nodes (h = 0.15 after j bisections, tol 1e-8: j - 2 are taken) take 800
+// us against 1386 with j.
 static int level_bisections(const mhk_plan *P, const Host &H, int j)
 {
-    const double hmax = pow(P->p.tol * 1e-2 / 1.5e-11, 1.0 / 18.0) * sqrt(P->delta / pow(4.0, j - 1));
+    const double delta_j = P->delta / pow(4.0, j - 1), err = P->p.tol * 1e-2;
+    const double hmax = pow(err / 1.5e-11, 1.0 / 18.0) * sqrt(delta_j);
     int m = j;
-    while (m > 0 && H.panel_half / (double)(1 << (m - 1)) <= hmax) --m;
+    while (m > 0 && H.panel_half / (double)(1 << (m - 1)) <= hmax && rule_error(H, m - 1, delta_j) <= err) --m;
     return m;
 }
 
@@ -1589,21 +1687,7 @@ mhk_status build_local(mhk_plan *P, Host &H)
     Local &C = P->loc;
     const mhk_boundary *b = H.b;
     const int64_t npan = b->n_panels, nb = npan * NGL;
-    // Legendre coefficients c_k = (2k+1)/2 sum_i w_i P_k(t_i) f_i
-    std::vector<double> leg(NGL * NGL);
-    for (int i = 0; i < NGL; ++i) {
-        double t = H.gl_t[i], p0 = 1, p1 = t;
-        for (int k = 0; k < NGL; ++k) {
-            double pk = (k == 0) ? 1.0 : (k == 1 ? t : 0.0);
-            if (k >= 2) {
-                double p2 = ((2 * k - 1) * t * p1 - (k - 1) * p0) / k;
-                p0 = p1;
-                p1 = p2;
-                pk = p2;
-            }
-            leg[k * NGL + i] = (2 * k + 1) / 2.0 * H.gl_w[i] * pk;
-        }
-    }
+    const std::vector<double> &leg = H.leg;
     auto coeffs = [&](const double *f, std::vector<double> &out) {
         out.assign(nb, 0.0);
         for (int64_t p = 0; p < npan; ++p)
@@ -2022,6 +2106,7 @@ mhk_status create(const mhk_params *params, const mhk_boundary *b, const mhk_vol
         StreamTmp tmp(P->stream);
         int64_t *dev = nullptr, tot[MAXJ];
         TRY(tmp.alloc(&dev, 2 * MAXJ));
+        panel_coefficients(H);
         for (int j = 1; j <= P->J; ++j) TRY(level_nodes(P, H, j, dev + j - 1));
         for (int j = 1; j <= P->J; ++j) TRY(level_table(P, j));
         TRY(tmp.fetch(tot, dev, P->J));
