@@ -213,7 +213,9 @@ mhk_status mhk_plan_create(const mhk_params *params, const mhk_boundary *boundar
                            const mhk_volume *volume, const mhk_targets *targets,
                            void *hip_stream, mhk_plan **out);
 
-/* Device bytes a plan with these inputs would own, without allocating. */
+/* Device bytes a plan with these inputs would own, without allocating: an upper
+ * estimate (the work items of the level sums at their most; the candidate lists
+ * from the densities of the boundary and volume nodes). */
 mhk_status mhk_plan_footprint(const mhk_params *params, const mhk_boundary *boundary,
                               const mhk_volume *volume, const mhk_targets *targets,
                               int64_t *bytes);

@@ -824,15 +824,29 @@ static mhk_status build_mask(mhk_plan *P, Host &H, StreamTmp &tmp, int8_t *rin)
 // still fill the device several times over: about LV_ITEMS items per level
 // and density chunk, between LV_PIECE_MIN (a workgroup loads the level's
 // table once, some 30 loads per thread, which a piece should outweigh) and
-// LV_PIECE_MAX sources.
+// LV_PIECE_MAX sources; more than that where the lists would be cut into more
+// than LV_ITEMS plus two items per wavefront, so that the items' parts stay
+// within level_items_max.
+static int level_piece_size(int64_t total, int64_t chunks, int64_t nwave)
+{
+    auto piece = [&](int64_t items) { return ((total + items - 1) / items + 63) / 64 * 64; };
+    const int64_t most = std::max<int64_t>(LV_PIECE_MAX, piece(LV_ITEMS + 2 * nwave));
+    return (int)std::min(most, std::max<int64_t>(LV_PIECE_MIN, piece(std::max<int64_t>(1, LV_ITEMS / chunks))));
+}
+
+// Most items that a level's lists of n_src sources can be cut into.
+static int64_t level_items_max(int64_t nwave, int64_t n_src)
+{
+    return std::min(nwave * ((n_src + LV_PIECE_MIN - 1) / LV_PIECE_MIN), LV_ITEMS + 3 * nwave);
+}
+
 static mhk_status count_items(mhk_plan *P, bool vol, const int32_t *wave_ofs, int64_t nwave, int64_t total,
                               LevelItems &I, int64_t *n_dev)
 {
     const hipStream_t st = P->stream;
     const int per = !vol && level_mm(P, P->p.batch) ? 16 : P->p.lv_bch;      // densities per pass
     const int64_t chunks = (P->p.batch + per - 1) / per;
-    const int64_t want = (total * chunks / LV_ITEMS + 63) / 64 * 64;
-    I.piece = (int)std::min<int64_t>(LV_PIECE_MAX, std::max<int64_t>(LV_PIECE_MIN, want));
+    I.piece = level_piece_size(total, chunks, nwave);
     StreamTmp tmp(st);
     int32_t *cnt = nullptr;
     TRY(tmp.alloc(&cnt, nwave));
@@ -2222,33 +2236,66 @@ mhk_status mhk_plan_footprint(const mhk_params *params, const mhk_boundary *b, c
     s += nb * 8 * 6;                          // boundary
     s += nout * (8 * 2 + 1 + 4);              // targets
     s += 3 * B * nout * 8;                    // history accumulators
-    for (int j = 1; j <= p.J; ++j) {          // levels: sources, and the items' parts (one item per wavefront)
-        int64_t ns = nb << j;
-        s += ns * (8 * 5 + 4) + 3 * (B < LV_MM_MIN ? B : level_bp((int)B)) * ns * 8 + 2 * B * nout * 8;
+    double x0 = 1e300, x1 = -1e300, y0 = 1e300, y1 = -1e300;
+    auto acc = [&](double x, double y) {
+        x0 = std::min(x0, x); x1 = std::max(x1, x);
+        y0 = std::min(y0, y); y1 = std::max(y1, y);
+    };
+    for (int64_t i = 0; i < nb; ++i) acc(b->x[i], b->y[i]);
+    for (int64_t i = 0; i < nv; ++i) acc(v->x[i], v->y[i]);
+    for (int64_t i = 0; i < t->n; ++i) acc(t->x[i], t->y[i]);
+    const int64_t es = p.prec == MHK_FP64 ? 8 : 4;
+    double len = 0, area = 0;
+    for (int64_t i = 0; i < nb; ++i) len += fabs(b->w[i]);
+    for (int64_t i = 0; i < nv; ++i) area += fabs(v->w[i]);
+    for (int j = 1; j <= p.J; ++j) {          // levels: sources and cells
+        const int64_t ns = nb << j, nwave = (nout + LV_WAVE - 1) / LV_WAVE;
+        const double R = I.level_radius[j - 1];
+        const int64_t cells = (int64_t)std::min(ldexp(1.0, 26), ((x1 - x0) * LV_CDIV / R + 2) * ((y1 - y0) * LV_CDIV / R + 2));
+        s += ns * (8 * 5 + 4) + 3 * (B < LV_MM_MIN ? B : level_bp((int)B)) * ns * 8 + 4 * cells;
+        // candidate lists (about the sources of two curves within the level's
+        // radius per wavefront; of the area, with a margin), items, and their parts
+        auto lists = [&](int64_t n_src, double list, int ncomp) {
+            return nwave * 4 * (2 + std::min(n_src, (int64_t)(list * (double)n_src))) +
+                   level_items_max(nwave, n_src) * (8 + ncomp * B * LV_WAVE * es);
+        };
+        s += lists(ns, std::min(1.0, 4 * R / len), 2);
+        if (p.v_levels) {
+            const int64_t nvs = nv << (2 * j);
+            s += nvs * (8 * 3 + 4 + B * es) + 4 * cells + lists(nvs, std::min(1.0, 6 * R * R / area), 1);
+        }
     }
     s += nb * (8 * 7 + 4) + 3 * B * nb * 8;   // local
+    {                                         // closest-point cells: every panel in those within its reach
+        double gap = 0;
+        for (int64_t i = 0; i + 1 < nb; ++i)
+            if (i % NGL < NGL - 1) gap = std::max(gap, hypot(b->x[i + 1] - b->x[i], b->y[i + 1] - b->y[i]));
+        const double reach = std::max(I.band_layer, I.band_volume) + gap;
+        const double cell = std::max(0.5 * reach, std::max(x1 - x0, y1 - y0) / 2048.0);
+        const double nx = (x1 - x0) / cell + 2, ny = (y1 - y0) / cell + 2;
+        double pairs = 0;
+        for (int64_t q = 0; q < nb; q += NGL) {
+            const auto bx = std::minmax_element(b->x + q, b->x + q + NGL), by = std::minmax_element(b->y + q, b->y + q + NGL);
+            pairs += std::min(nx, (*bx.second - *bx.first + 2 * reach) / cell + 2) *
+                     std::min(ny, (*by.second - *by.first + 2 * reach) / cell + 2);
+        }
+        s += (int64_t)(4 * nx * ny + 36 * pairs);
+    }
     s += nout * ((p.local_order >= 2 ? LOCAL_GEO_N2 : LOCAL_GEO_N1) * 8 + 4 + 1);   // local geometry per target
     if (p.in64) s += B * (2 * nb + nv) * 4;   // FP32 copies of FP64 inputs
     if (v && v->group == 6)                    // f at the targets from the volume triangles
-        s += (nv / 6) * 39 * 8 + nout * 4 + B * (p.local_order >= 2 ? 6 : 1) * nout * 8;
+        s += (nv / 6) * (39 * 8 + 1) + nv * 8 + nout * 4 + B * (p.local_order >= 2 ? 6 : 1) * nout * 8;
     if (I.kmax > 0) {                         // history grid
-        double x0 = 1e300, x1 = -1e300, y0 = 1e300, y1 = -1e300;
-        auto acc = [&](double x, double y) {
-            x0 = std::min(x0, x); x1 = std::max(x1, x);
-            y0 = std::min(y0, y); y1 = std::max(y1, y);
-        };
-        for (int64_t i = 0; i < nb; ++i) acc(b->x[i], b->y[i]);
-        for (int64_t i = 0; i < nv; ++i) acc(v->x[i], v->y[i]);
-        for (int64_t i = 0; i < t->n; ++i) acc(t->x[i], t->y[i]);
         GridChoice g;
         TRY(choose_grid(p, I, x1 - x0, y1 - y0, g));
-        const int64_t es = p.prec == MHK_FP64 ? 8 : 4;
         s += 4 * B * g.n * (g.n + 2) * es * 2;   // grids + FFT work estimate
         s += (nb + nv) * (8 * 3 + 4);
         const int64_t nt2 = (g.n / SPB) * (g.n / SPB);   // per-block source lists
         s += (nb + nv) * 4 * 4 + 2 * nt2 * 5 + 4 * (std::min(nt2, 4 * nb) + std::min(nt2, 4 * nv));
     }
-    *bytes = s;
+    // small buffers are cut from chunks of up to a quarter of what the plan
+    // holds (dalloc), the last of them not filled
+    *bytes = s + std::min<int64_t>(s / 4, (int64_t)1 << 28) + ((int64_t)2 << 20);
     return MHK_OK;
 }
 
