@@ -305,8 +305,9 @@ typedef struct mhk_nystrom mhk_nystrom;
 typedef struct {
     int64_t n;            /* N_B                                                    */
     double alpha;
-    int64_t device_bytes; /* K (4 N_B^2 bytes: the triangle of its symmetric factor)
-                             plus GMRES and solve workspace                         */
+    int64_t device_bytes; /* K (4 N_B^2 bytes: the triangle of its symmetric factor;
+                             up to 5632 nodes 8 N_B^2 more, K itself) plus GMRES and
+                             solve workspace                                        */
     double ms_assemble;   /* time to build K on the device                         */
 } mhk_nys_info;
 
@@ -319,13 +320,15 @@ typedef struct {
 
 /* Assemble K on the device for the boundary (host arrays as for
  * mhk_plan_create; N_B <= 2^20).  K_ij = S_ij w_j (x_i - x_j).nu_j with S
- * symmetric, so S's lower triangle is kept: 4 N_B^2 bytes of device memory.
+ * symmetric, so S's lower triangle is kept: 4 N_B^2 bytes of device memory, and
+ * for N_B <= 5632 K itself beside it.
  * Later calls run on the given stream (NULL: default stream).  *out is NULL
  * on error (MHK_ENOMEM when K does not fit). */
 mhk_status mhk_nystrom_create(double alpha, const mhk_boundary *boundary, void *hip_stream, mhk_nystrom **out);
 
 /* y = shift x + K x, x and y device arrays of N_B doubles (y must not alias x);
- * asynchronous on the object's stream. */
+ * asynchronous on the object's stream.  Threads may call it at the same time, and
+ * it may be recorded into a graph whose replays run beside other products. */
 mhk_status mhk_nystrom_apply(mhk_nystrom *nys, double shift, const double *x, double *y);
 
 /* Solve (shift I + K) x = rhs by GMRES(restart), x = 0 initially, until the

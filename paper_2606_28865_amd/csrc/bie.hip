@@ -33,6 +33,7 @@ struct mhk_nystrom {
     hipStream_t stream = nullptr;
     double *S = nullptr;        // [tiles][64][128]
     double *geo = nullptr;      // [6][np]: x, y, nu_x, nu_y, w, diagonal of K
+    double *K = nullptr;        // [n][n], for products of few nodes only (n <= NYS_DENSE)
     int64_t nstrip = 0, ntile = 0, nitem = 0;
     int run = 1;                // tiles per work item
     int2 *item = nullptr;       // [nitem] strip and first tile column
@@ -58,7 +59,7 @@ struct mhk_nystrom {
     double ms_assemble = 0;
     int64_t bytes() const
     {
-        return (int64_t)sizeof(double) * (ntile * 64 * 128 + 6 * np + 3 * (ntile * 128 + nitem * 64) + np + 2 * work_n) +
+        return (int64_t)sizeof(double) * (ntile * 64 * 128 + 6 * np + 3 * (ntile * 128 + nitem * 64) + np + (K ? n * n : 0) + 2 * work_n) +
                nitem * 8 + (nstrip + 1) * 4 + ws_bytes;
     }
 };
@@ -82,6 +83,9 @@ namespace mhk {
 
 constexpr int BT = 256;         // threads per block of the vector kernels
 constexpr int TR = 64, TC = 128;   // rows and columns of a tile
+// nodes up to which K itself is kept beside its triangle, for products that keep
+// no partial sums (recorded ones), and up to which every product takes it
+constexpr int64_t NYS_DENSE = 5632, NYS_DENSE_ALL = 3072;
 enum { NYS_APPLY, NYS_SOLVE, NYS_NOALLOC };
 
 // tiles of the strips before strip I (strip k holds k/2 + 1 tile columns)
@@ -205,11 +209,62 @@ __global__ void __launch_bounds__(BT) k_nys_assemble(int64_t n, int64_t np, doub
     }
 }
 
+// K itself from the triangle of S, for the products of few nodes
+__global__ void __launch_bounds__(BT) k_nys_dense(int64_t n, int64_t np, const double *__restrict__ S,
+                                                  const double *__restrict__ geo, double *__restrict__ K)
+{
+    const int64_t i = blockIdx.x, j = (int64_t)blockIdx.y * BT + threadIdx.x;
+    if (j >= n) return;
+    const int64_t hi = max(i, j), lo = min(i, j);
+    const double s = S[(tile_ofs(hi / TR) + lo / TC) * (TR * TC) + hi % TR * TC + lo % TC];
+    const double *x = geo, *y = geo + np, *nx = geo + 2 * np, *ny = geo + 3 * np, *w = geo + 4 * np;
+    K[i * n + j] = i == j ? geo[5 * np + i] : w[j] * s * fma(x[i] - x[j], nx[j], (y[i] - y[j]) * ny[j]);
+}
+
 __device__ inline double wave_sum(double v)
 {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
+}
+
+// y = shift x + K x with K itself: GV_ROWS rows per workgroup, column pairs
+// along the threads (n is even); fixed reduction order.  One launch and no
+// partial sums, against the two of the triangle's product: 128, 2048, 3072 and
+// 3584 nodes 4.1, 5.4, 13.5 and 17.0 us against 7.6, 10.2, 13.9 and 17.6, and 27.8
+// against 21.0 at 4096, where the bytes decide; recorded, against k_nys_rows, 5.9 to
+// 11.9 us at 2048, 17.5 to 21.5 at 3584, 36 (at 5.7 TB/s) to 42 at 5632.
+constexpr int GV_ROWS = 8;
+__global__ void __launch_bounds__(BT) k_gemv(int64_t n, const double *__restrict__ K, double shift,
+                                             const double *__restrict__ x, double *__restrict__ y)
+{
+    const int64_t r0 = (int64_t)blockIdx.x * GV_ROWS;
+    const int tid = threadIdx.x;
+    double acc[GV_ROWS];
+#pragma unroll
+    for (int r = 0; r < GV_ROWS; ++r) acc[r] = 0.0;
+    for (int64_t c = 2 * (int64_t)tid; c < n; c += 2 * BT) {
+        const double x0 = x[c], x1 = x[c + 1];
+#pragma unroll
+        for (int r = 0; r < GV_ROWS; ++r) {
+            const double2 k = *reinterpret_cast<const double2 *>(K + (r0 + r) * n + c);
+            acc[r] = fma(k.x, x0, acc[r]);
+            acc[r] = fma(k.y, x1, acc[r]);
+        }
+    }
+    __shared__ double red[GV_ROWS][BT / 64];
+#pragma unroll
+    for (int r = 0; r < GV_ROWS; ++r) {
+        const double s = wave_sum(acc[r]);
+        if ((tid & 63) == 0) red[r][tid >> 6] = s;
+    }
+    __syncthreads();
+    if (tid < GV_ROWS) {
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < BT / 64; ++q) s += red[tid][q];
+        y[r0 + tid] = fma(shift, x[r0 + tid], s);
+    }
 }
 
 // Products of the tiles of one work item (a run of tile columns of one strip)
@@ -390,67 +445,138 @@ __global__ void __launch_bounds__(TC * SG) k_symv_sum(int64_t n, int64_t np, int
     }
 }
 
-// y = shift x + K x with nothing kept between launches, for products recorded
-// into a graph: its replays may run beside the object's other products, whose
-// partial sums k_symv keeps in the object.  One workgroup per 16 rows i (a
-// panel), four row groups of 64 lanes: the triangle's rows for j < i, then its
-// columns for j > i (16 neighbouring doubles of a row), so S is read twice:
-// 16384 nodes 0.81 ms against 0.21 (one load at a time per thread: 1.30).
-__global__ void __launch_bounds__(BT) k_nys_rows(int64_t n, int64_t np, const double *__restrict__ S,
-                                                 const double *__restrict__ geo, double shift,
-                                                 const double *__restrict__ x, double *__restrict__ y)
+// y = shift x + K x with nothing kept between launches, for products of more
+// than NYS_DENSE nodes recorded into a graph: its replays may run beside the
+// object's other products, whose partial sums k_symv keeps in the object.  One
+// workgroup per 8 QW rows i forms their whole sums: of the triangle's rows for j <
+// i and of its columns for j > i, so every element is read twice, by the
+// workgroups of its row and of its column.  At step t workgroups of the 128 rows
+// R take the elements of columns K = t - R (modulo the number of such groups), so
+// both read a tile at the same time and one of the reads can come from the
+// memory-side cache.  QW wavefronts a step (8 rows, or 128/QW rows of the columns,
+// each), G steps at a time.  Against the dense matrix (twice the bytes): 8192 nodes
+// 80 us (97), 10240 136 (140), 16384 318 (353), 32768 1375 (1439).
+template <int QW, int G>
+__global__ void __launch_bounds__(64 * QW * G) k_nys_rows(int64_t n, int64_t np, int64_t nstrip,
+                                                      const double *__restrict__ S, const double *__restrict__ geo,
+                                                      double shift, const double *__restrict__ x,
+                                                      double *__restrict__ y)
 {
-    constexpr int NR = 16;
+    constexpr int RW = 8, NR = RW * QW, JW = TC / QW, LR = NR / 2, JL = 64 / LR;
     const int64_t i0 = (int64_t)blockIdx.x * NR;
+    const int R = (int)(i0 / TC), NK = (int)(np / TC);
     const double *__restrict__ gx = geo, *__restrict__ gy = geo + np, *__restrict__ gnx = geo + 2 * np,
                                *__restrict__ gny = geo + 3 * np, *__restrict__ gw = geo + 4 * np;
-    __shared__ double sh[BT / NR][NR + 1];
-    const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
-    // rows wave, wave + 4, ...: columns below the diagonal along the lanes
-    constexpr int RQ = NR / 4;
-    double low[RQ] = {};
-    const double *rowp = S + tile_ofs(i0 / TR) * (TR * TC) + (i0 % TR + wave) * TC;
-#pragma unroll 2
-    for (int64_t j = lane; j < i0 + NR; j += 64) {
-        const double xj = gx[j], yj = gy[j], nx = gnx[j], ny = gny[j], wx = gw[j] * x[j];
-        const double *p = rowp + j / TC * (TR * TC) + j % TC;
+    __shared__ __align__(16) double jd[QW * G][JW][6];     // x, y, nu, w x of a wavefront's rows j
+    __shared__ double rs[QW * G][RW], cs[QW * G][NR];
+    const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64), qw = wave % QW;
+    // rows j < i: this wavefront's 8 rows, two columns per lane
+    const int64_t ir = i0 + RW * qw;
+    const double *rowp = S + tile_ofs(i0 / TR) * (TR * TC) + (ir % TR) * TC + 2 * lane;
+    double xr[RW], yr[RW], acc[RW];
 #pragma unroll
-        for (int q = 0; q < RQ; ++q) {
-            const int64_t i = i0 + wave + 4 * q;
-            const double t = fma(p[4 * q * TC] * fma(gx[i] - xj, nx, (gy[i] - yj) * ny), wx, low[q]);
-            low[q] = j < i ? t : low[q];
+    for (int r = 0; r < RW; ++r) {
+        xr[r] = gx[ir + r];
+        yr[r] = gy[ir + r];
+        acc[r] = 0.0;
+    }
+    // columns i of the rows j > i: two columns per lane, JL rows per load
+    const int c = 2 * (lane % LR), jr = lane / LR;
+    const double2 xc = *reinterpret_cast<const double2 *>(gx + i0 + c), yc = *reinterpret_cast<const double2 *>(gy + i0 + c);
+    double a0 = 0.0, a1 = 0.0;
+    // diag: the tile holds the diagonal; its other elements are no part of the
+    // sums (nor is zero times an infinite x)
+    auto rows = [&](auto diag, int K) {
+        const int64_t j = (int64_t)K * TC + 2 * lane;
+        const double *p = rowp + (int64_t)K * (TR * TC);
+        double2 s[RW];
+#pragma unroll
+        for (int r = 0; r < RW; ++r) s[r] = *reinterpret_cast<const double2 *>(p + r * TC);
+        auto two = [&](const double *g) { return *reinterpret_cast<const double2 *>(g + j); };
+        const double2 xj = two(gx), yj = two(gy), nx = two(gnx), ny = two(gny);
+        double2 w = two(gw);
+        w.x *= j < n ? x[j] : 0.0;
+        w.y *= j < n ? x[j + 1] : 0.0;
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            if (!diag || j < ir + r) acc[r] = fma(s[r].x * fma(xr[r] - xj.x, nx.x, (yr[r] - yj.x) * ny.x), w.x, acc[r]);
+            if (!diag || j + 1 < ir + r)
+                acc[r] = fma(s[r].y * fma(xr[r] - xj.y, nx.y, (yr[r] - yj.y) * ny.y), w.y, acc[r]);
+        }
+    };
+    auto cols = [&](auto diag, int K) {
+        const int64_t j0 = (int64_t)K * TC + JW * qw;
+        if (j0 / TR >= nstrip) return;
+        double2 s[JW / JL];
+#pragma unroll
+        for (int q = 0; q < JW / JL; ++q) {
+            // (a tile column's last strip may be missing)
+            const int64_t j = j0 + JL * q + jr, strip = j / TR;
+            s[q] = make_double2(0.0, 0.0);
+            if (JW <= TR || strip < nstrip)
+                s[q] = *reinterpret_cast<const double2 *>(S + (tile_ofs(strip) + R) * (TR * TC) + j % TR * TC + i0 % TC + c);
+        }
+        for (int k = lane; k < JW; k += 64) {
+            const int64_t j = j0 + k;
+            double *d = jd[wave][k];
+            d[0] = gx[j];
+            d[1] = gy[j];
+            d[2] = gnx[j];
+            d[3] = gny[j];
+            d[4] = j < n ? gw[j] * x[j] : 0.0;
+        }
+        // the wavefront's own rows: its lanes' writes are read below, and again
+        // overwritten at its next step
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int q = 0; q < JW / JL; ++q) {
+            const double *d = jd[wave][JL * q + jr];
+            const double2 g = *reinterpret_cast<const double2 *>(d), nu = *reinterpret_cast<const double2 *>(d + 2);
+            const double w = d[4];
+            const int64_t below = j0 + JL * q + jr - (i0 + c);      // j - i of the first column
+            if (!diag || below > 0) a0 = fma(s[q].x * fma(xc.x - g.x, nu.x, (yc.x - g.y) * nu.y), w, a0);
+            if (!diag || below > 1) a1 = fma(s[q].y * fma(xc.y - g.x, nu.x, (yc.y - g.y) * nu.y), w, a1);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    for (int t = wave / QW; t < NK; t += G) {
+        const int K = t >= R ? t - R : t - R + NK;
+        if (K < R) {
+            rows(std::false_type(), K);
+        } else if (K > R) {
+            cols(std::false_type(), K);
+        } else {
+            rows(std::true_type(), K);
+            cols(std::true_type(), K);
         }
     }
 #pragma unroll
-    for (int q = 0; q < RQ; ++q) low[q] = wave_sum(low[q]);
-    // column i of the rows j > i: 16 columns by 16 rows at a time
-    const int c = tid % NR, g = tid / NR;
-    const int64_t i = i0 + c;
-    const double xi = gx[i], yi = gy[i];
-    const double *colp = S + i / TC * (TR * TC) + i % TC;
-    double s = 0.0;
-#pragma unroll 4
-    for (int64_t j = i0 + g; j < n; j += BT / NR) {
-        const double e = colp[tile_ofs(j / TR) * (TR * TC) + j % TR * TC];
-        const double t = fma(e * fma(xi - gx[j], gnx[j], (yi - gy[j]) * gny[j]), gw[j] * x[j], s);
-        s = j > i ? t : s;
+    for (int r = 0; r < RW; ++r) {
+        const double v = wave_sum(acc[r]);
+        if (lane == 0) rs[wave][r] = v;
     }
-    sh[g][c] = s;
+#pragma unroll
+    for (int m = LR; m < 64; m *= 2) {
+        a0 += __shfl_xor(a0, m, 64);
+        a1 += __shfl_xor(a1, m, 64);
+    }
+    if (lane < LR) {
+        cs[wave][c] = a0;
+        cs[wave][c + 1] = a1;
+    }
     __syncthreads();
-    if (tid < NR) {
+    if (tid < NR && i0 + tid < n) {
         double v = 0.0;
 #pragma unroll
-        for (int q = 0; q < BT / NR; ++q) v += sh[q][tid];
-        sh[0][tid] = v;
-    }
-    __syncthreads();
-    if (lane == 0) {
+        for (int g = 0; g < G; ++g) v += rs[QW * g + tid / RW][tid % RW];
 #pragma unroll
-        for (int q = 0; q < NR / 4; ++q) {
-            const int64_t r = i0 + wave + 4 * q;
-            const double xr = x[r];
-            y[r] = fma(shift, xr, fma(geo[5 * np + r], xr, low[q] + sh[0][wave + 4 * q]));
-        }
+        for (int q = 0; q < QW * G; ++q) v += cs[q][tid];
+        const double xi = x[i0 + tid];
+        y[i0 + tid] = fma(shift, xi, fma(geo[5 * np + i0 + tid], xi, v));
     }
 }
 
@@ -1002,6 +1128,7 @@ mhk_status mhk_nystrom_create(double alpha, const mhk_boundary *b, void *hip_str
     mhk_status st = nys_alloc(N, &N->S, N->ntile * TR * TC);
     if (st == MHK_OK) st = nys_alloc(N, &N->geo, 6 * N->np);
     if (st == MHK_OK) st = nys_alloc(N, &N->na_part, 2 * (int64_t)(NOALLOC_MAX_RESTART + 1) * (N->np / TC));
+    if (st == MHK_OK && n <= NYS_DENSE) st = nys_alloc(N, &N->K, n * n);
     if (st == MHK_OK) st = nys_alloc(N, &tab, (int64_t)k1.size());
     if (st == MHK_OK) st = nys_alloc(N, &ia, N->nitem);
     N->item = reinterpret_cast<int2 *>(ia);
@@ -1034,6 +1161,11 @@ mhk_status mhk_nystrom_create(double alpha, const mhk_boundary *b, void *hip_str
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_nys_assemble, dim3((unsigned)N->nitem), dim3(BT), 0, N->stream, n, N->np, alpha,
                            (const double *)N->geo, (const double *)tab, (const int2 *)N->item, N->run, N->S);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess && N->K) {
+        hipLaunchKernelGGL(k_nys_dense, dim3((unsigned)n, (unsigned)((n + BT - 1) / BT)), dim3(BT), 0, N->stream, n,
+                           N->np, (const double *)N->S, (const double *)N->geo, N->K);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipEventRecord(e1, N->stream);
@@ -1072,11 +1204,36 @@ mhk_status mhk_nystrom_apply(mhk_nystrom *N, double shift, const double *x, doub
         set_error("null Nystrom matrix or vector, or x aliases y");
         return MHK_EINVAL;
     }
+    auto dense = [&]() -> mhk_status {
+        hipLaunchKernelGGL(k_gemv, dim3((unsigned)(N->n / GV_ROWS)), dim3(BT), 0, N->stream, N->n, (const double *)N->K,
+                           shift, x, y);
+        BIE_HIP(hipGetLastError());
+        return MHK_OK;
+    };
+    if (N->n <= NYS_DENSE_ALL) return dense();
+    // products that must keep no partial sums in the object: recorded ones
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (N->stream) BIE_HIP(hipStreamIsCapturing(N->stream, &cap));
-    if (cap == hipStreamCaptureStatusActive) {
-        hipLaunchKernelGGL(k_nys_rows, dim3((unsigned)(N->n / NGL)), dim3(BT), 0, N->stream, N->n, N->np,
-                           (const double *)N->S, (const double *)N->geo, shift, x, y);
+    const bool alone = cap == hipStreamCaptureStatusActive;
+    if (alone && N->K) return dense();
+    if (alone) {
+        auto rows = [&](auto qw, auto g) {
+            constexpr int QW = decltype(qw)::value, G = decltype(g)::value;
+            hipLaunchKernelGGL((k_nys_rows<QW, G>), dim3((unsigned)((N->n + 8 * QW - 1) / (8 * QW))), dim3(64 * QW * G),
+                               0, N->stream, N->n, N->np, N->nstrip, (const double *)N->S, (const double *)N->geo,
+                               shift, x, y);
+        };
+        // a workgroup per CU of as many wavefronts as fit (8192 nodes: 80 us, 81
+        // with <2, 2>); beyond 256 of them several small ones, which leave the CUs
+        // evenly loaded (10240: 136 against 170 us); and of 32 rows again once
+        // those are many too (14336: 249, 261 with <4, 3> and 280 with <2, 2>;
+        // 16384: 318, 324 and 353)
+        if (N->n <= 8192)
+            rows(std::integral_constant<int, 4>(), std::integral_constant<int, 3>());
+        else if (N->n <= 12288)
+            rows(std::integral_constant<int, 2>(), std::integral_constant<int, 2>());
+        else
+            rows(std::integral_constant<int, 4>(), std::integral_constant<int, 2>());
         BIE_HIP(hipGetLastError());
         return MHK_OK;
     }
@@ -1294,7 +1451,7 @@ void mhk_nystrom_destroy(mhk_nystrom *N)
     if (!N) return;
     (void)hipStreamSynchronize(N->stream);
     nys_free_ws(N);
-    for (double **p : {&N->S, &N->geo, &N->na_part, &N->work}) nys_free(N, p);
+    for (double **p : {&N->S, &N->geo, &N->K, &N->na_part, &N->work}) nys_free(N, p);
     for (NysPart &p : N->prod) {
         nys_free(N, &p.cp);
         nys_free(N, &p.rp);

@@ -1,0 +1,53 @@
+"""Nystrom products that keep no partial sums in their object: recorded into a
+graph at sizes around the edges of its kernels (the dense matrix kept up to 5632
+nodes; then whole rows from the triangle, with remainders of 16 to 112 nodes in
+the last tile column).  Compared with the eager products of the triangle, which other tests
+compare with the dense matrix of the oracle."""
+import numpy as np
+import pytest
+
+import synth
+from helpers import rel_err
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# sums of at most 12352 terms in another order, 12352 eps = 1.4e-12 of their
+# absolute sums at worst; random signs leave about the root of that
+TOL = 1e-12
+
+
+def _boundary(panels):
+    return synth.discretize([synth.Curve(r0=1.0, a=0.3, l1=5)], panels)
+
+
+@pytest.mark.parametrize("panels", [192, 193, 352, 353, 356, 359, 512, 513, 768, 772])
+def test_captured(panels):
+    import paper_2606_28865_amd as M
+    n = 16 * panels
+    print(f"case captured product n={n}", flush=True)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        nys = M.Nystrom(3.0, _boundary(panels))
+        g = torch.Generator(device="cuda").manual_seed(panels)
+        x = torch.randn(n, dtype=torch.float64, device="cuda", generator=g)
+        out = torch.empty_like(x)
+        st.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=st):
+            nys.apply(x, shift=0.5, out=out)
+        for k in (None, 0, 63, 64, 127, 128, n - 1):
+            x.normal_(generator=g)
+            if k is not None:
+                x[k] = np.inf                    # its column alone is infinite, and nothing a NaN beside row k
+            out.fill_(float("nan"))
+            graph.replay()
+            ref = nys.apply(x, shift=0.5)
+            st.synchronize()
+            a, b = out.cpu().numpy(), ref.cpu().numpy()
+            if k is None:
+                assert rel_err(a, b) < TOL
+            else:
+                np.testing.assert_array_equal(a, b)
+                assert np.isinf(np.delete(a, k)).all()
+    nys.close()
