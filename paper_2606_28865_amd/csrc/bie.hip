@@ -84,7 +84,8 @@ namespace mhk {
 constexpr int BT = 256;         // threads per block of the vector kernels
 constexpr int TR = 64, TC = 128;   // rows and columns of a tile
 // nodes up to which K itself is kept beside its triangle, for products that keep
-// no partial sums (recorded ones), and up to which every product takes it
+// no partial sums (recorded ones, and those of the per-thread stream), and up to
+// which every product takes it
 constexpr int64_t NYS_DENSE = 5632, NYS_DENSE_ALL = 3072;
 enum { NYS_APPLY, NYS_SOLVE, NYS_NOALLOC };
 
@@ -1211,10 +1212,11 @@ mhk_status mhk_nystrom_apply(mhk_nystrom *N, double shift, const double *x, doub
         return MHK_OK;
     };
     if (N->n <= NYS_DENSE_ALL) return dense();
-    // products that must keep no partial sums in the object: recorded ones
+    // products that must keep no partial sums in the object: recorded ones, and
+    // those of threads that each have a stream of their own under this handle
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (N->stream) BIE_HIP(hipStreamIsCapturing(N->stream, &cap));
-    const bool alone = cap == hipStreamCaptureStatusActive;
+    const bool alone = cap == hipStreamCaptureStatusActive || N->stream == hipStreamPerThread;
     if (alone && N->K) return dense();
     if (alone) {
         auto rows = [&](auto qw, auto g) {

@@ -1,8 +1,11 @@
 """Nystrom products that keep no partial sums in their object: recorded into a
 graph at sizes around the edges of its kernels (the dense matrix kept up to 5632
 nodes; then whole rows from the triangle, with remainders of 16 to 112 nodes in
-the last tile column).  Compared with the eager products of the triangle, which other tests
+the last tile column), and of two threads that share the per-thread stream's
+handle.  Compared with the eager products of the triangle, which other tests
 compare with the dense matrix of the oracle."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -51,3 +54,31 @@ def test_captured(panels):
                 np.testing.assert_array_equal(a, b)
                 assert np.isinf(np.delete(a, k)).all()
     nys.close()
+
+
+@pytest.mark.parametrize("panels", [256, 353])
+def test_per_thread_stream(panels):
+    import paper_2606_28865_amd as M
+    n = 16 * panels
+    print(f"case per-thread stream n={n}", flush=True)
+    nys = M.Nystrom(3.0, _boundary(panels), stream=torch.cuda.ExternalStream(2))
+    ref = M.Nystrom(3.0, _boundary(panels))
+    x = torch.randn((2, 40, n), dtype=torch.float64, device="cuda")
+    out = torch.empty_like(x)
+    want = torch.stack([torch.stack([ref.apply(x[k, i], shift=-0.5) for i in range(40)]) for k in range(2)])
+    torch.cuda.synchronize()
+
+    def run(k):
+        torch.cuda.set_device(0)
+        for i in range(40):
+            nys.apply(x[k, i], shift=-0.5, out=out[k, i])
+        nys.stream.synchronize()                 # this thread's stream
+
+    th = [threading.Thread(target=run, args=(k,)) for k in range(2)]
+    for t in th:
+        t.start()
+    for t in th:
+        t.join()
+    assert rel_err(out.cpu().numpy(), want.cpu().numpy()) < TOL
+    nys.close()
+    ref.close()
