@@ -312,10 +312,8 @@ __device__ inline double panel_start(const Args &A, int p, int node, double px, 
 // downhill is tried instead of the Newton step; Newton steps below 1e-6 where
 // the distance is convex are taken as they are (there the distance is flat below
 // its rounding, and the derivative decides) and end the iteration once one is
-// below 1e-12, or below 1e-11 without being half the one before (the rounding
-// level of a flat minimum), after one more Newton step.  conv: the best panel's
-// iteration ended so, or with a damped step below 1e-15, possibly held at an end
-// point.
+// below 1e-12, after one more Newton step.  conv: the best panel's iteration
+// ended so, or with a damped step below 1e-15, possibly held at an end point.
 //
 // One evaluation of the series and both derivatives per turn of one loop: at
 // the point that a step leads to, where its distance decides on the step and
@@ -327,7 +325,7 @@ __device__ inline void closest_point(const Args &A, int p0, int node, double px,
                                      double &d2b, bool &conv)
 {
     int p = p0, c = 0, it = 0, halv = 0;
-    double tn = panel_start(A, p, node, px, py), t = tn, phi = INFINITY, step = 0.0, last = 1.0;
+    double tn = panel_start(A, p, node, px, py), t = tn, phi = INFINITY, step = 0.0;
     bool plain = false, fresh = true;
     for (;;) {
         double x0, x1, x2, y0, y1, y2;
@@ -342,7 +340,7 @@ __device__ inline void closest_point(const Args &A, int p0, int node, double px,
             const double h = x1 * x1 + y1 * y1 + ex * x2 + ey * y2;
             if (!fresh) {
                 ++it;
-                if (plain && (moved < 1e-12 || (moved < 1e-11 && moved > 0.5 * last))) {
+                if (plain && moved < 1e-12) {
                     // one more Newton step brings t to the rounding level also
                     // where the convergence is slow (small curvature of |x - gamma|^2)
                     if (h > 0.0) t = fmin(1.0, fmax(-1.0, t - g / h));
@@ -352,7 +350,6 @@ __device__ inline void closest_point(const Args &A, int p0, int node, double px,
                 } else if (it >= 60) {
                     done = true;
                 }
-                last = plain ? moved : 1.0;
             }
             fresh = false;
             halv = 0;
@@ -360,7 +357,11 @@ __device__ inline void closest_point(const Args &A, int p0, int node, double px,
             plain = h > 0.0 && fabs(step) < 1e-6;
             tn = fmin(1.0, fmax(-1.0, t + step));
         } else if (++halv > 52) {
-            done = ok = true;                       // no step decreases the distance: t is the minimum
+            // no step decreases the distance: t is the minimum, unless a Newton
+            // step so long (the distance almost flat) was halved to no less
+            // than the rounding of t
+            done = true;
+            ok = 0.5 * fabs(tn - t) < 1e-15;
         } else {
             step *= 0.5;
             tn = fmin(1.0, fmax(-1.0, t + step));
@@ -386,7 +387,6 @@ __device__ inline void closest_point(const Args &A, int p0, int node, double px,
             phi = INFINITY;
             fresh = true;
             plain = false;
-            last = 1.0;
             it = halv = 0;
         }
     }
