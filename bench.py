@@ -395,9 +395,8 @@ def level_sums_traffic():
 
 
 def panel_coefficients(boundary):
-    """Largest Legendre coefficients over the panels, per degree, of the
-    position, the speed and the normal (tails at rounding level dropped), and
-    the largest half-length of a panel."""
+    """Legendre coefficients of every panel's position, speed and normal
+    (tails at rounding level dropped), and the largest half-length of a panel."""
     import synth
     tg, wg = synth.gauss_legendre()
     k = np.arange(16)
@@ -405,40 +404,43 @@ def panel_coefficients(boundary):
     x, y, nx, ny, w = (np.asarray(boundary[q]).reshape(-1, 16) for q in ("x", "y", "nx", "ny", "w"))
     ext = max(np.abs(x).max(), np.abs(y).max())
     x, y, sp = x - x[:, :1], y - y[:, :1], w / wg
-    g = np.hypot(x @ leg, y @ leg).max(0)
-    n = np.hypot(nx @ leg, ny @ leg).max(0)
-    s = np.abs(sp @ leg).max(0)
+    g, s, n = np.hypot(x @ leg, y @ leg), np.abs(sp @ leg), np.hypot(nx @ leg, ny @ leg)
     eps = 16 * 2.2e-16
     g[(k > 1) & (g < eps * ext)] = 0.0
-    s[(k > 0) & (s < 16 * eps * s[0])] = 0.0
+    s[(k > 0) & (s < 16 * eps * s[:, :1])] = 0.0
     n[(k > 0) & (n < 16 * eps)] = 0.0
     return g, s, n, float(sp.max())
 
 
-def rule_error(coef, m, delta_j):
-    """Bound of the 16-node rule's error on panels bisected m times (the
-    library's rule_error)."""
+def rule_error_below(coef, m, delta_j, limit):
+    """Whether the 16-node rule's error on panels bisected m times is bounded
+    by limit (the library's rule_error_below)."""
     g, s, n, _ = coef
-    w, k, best = 0.5 ** m, np.arange(16), np.inf
-    rho = 1.5
-    while rho < 64.0:
+    w, k = 0.5 ** m, np.arange(16)
+    scale = 32 * s[:, 0].max() * max(0.5, n[:, 0].max())
+
+    def bound(rho, g, s, n):
         a, b = 0.5 * (rho + 1 / rho), 0.5 * (rho - 1 / rho) * w
         lr = np.arccosh(max(1 - w + w * a, np.sqrt(1 + b * b)))
         c = np.cosh(k * lr)
-        e = (b * np.sum(g * k * np.sinh(k * lr)) / np.sinh(lr)) ** 2 / delta_j - 32 * np.log(rho)
-        if e < 600.0:
-            best = min(best, np.exp(e) * np.cosh(15 * lr) * np.sum(s * c) * np.sum(n * c))
-        rho *= 1.166
-    return best / (32 * s[0] * max(0.5, n[0]))
+        h = (g @ (k * np.sinh(k * lr))) * (b / np.sinh(lr))
+        return h * h / delta_j + np.log((s @ c) * (n @ c) * c[15] / scale) - 32 * np.log(rho)
+
+    top = [v.max(0) for v in (g, s, n)]
+    rhos = 1.5 * 1.166 ** np.arange(25)
+    least = [bound(r, *top) for r in rhos]
+    i, lim = int(np.argmin(least)), np.log(limit)
+    if least[i] <= lim:
+        return True
+    return bool(least[i] <= lim + np.log(1e3) and bound(rhos[i], g, s, n).max() <= lim)
 
 
 def level_bisections(coef, info, j):
     """Bisections of every panel at level j: j, or fewer where the 16-node
-    rule resolves the level's kernel to tol/100 on longer panels (the
-    library's rule)."""
-    delta_j, err = info["delta"] / 4.0 ** (j - 1), info["tol"] * 1e-2
-    hmax = (err / 1.5e-11) ** (1.0 / 18.0) * np.sqrt(delta_j)
-    while j > 0 and coef[3] / (1 << (j - 1)) <= hmax and rule_error(coef, j - 1, delta_j) <= err:
+    rule resolves the level's kernel on longer panels (the library's rule)."""
+    delta_j, tol = info["delta"] / 4.0 ** (j - 1), info["tol"]
+    hmax = (tol * 1e-2 / 1.5e-11) ** (1.0 / 18.0) * np.sqrt(delta_j)
+    while j > 0 and coef[3] / (1 << (j - 1)) <= hmax and rule_error_below(coef, j - 1, delta_j, 0.1 * tol):
         j -= 1
     return j
 

@@ -11,9 +11,9 @@
  * delta/4^(j-1)], j = 1..J, are the dyadic difference-kernel levels of the
  * layer potentials, summed over locally bisected panels (Section 4.2, eqs.
  * (diffker_s), (diffker_dlp); at level j every panel is bisected j times, or
- * fewer times where the panels' geometry keeps the error of the 16-node rule
- * on longer children below tol/100 for any densities); t < delta* = delta/4^J (delta for V) is the
- * local asymptotic part (Lemmas 4.1, 4.5, 4.8 and Corollaries 4.4, 4.7,
+ * fewer times where a bound of the 16-node rule's error on longer children,
+ * for any densities, stays below tol/10); t < delta* = delta/4^J (delta for V)
+ * is the local asymptotic part (Lemmas 4.1, 4.5, 4.8 and Corollaries 4.4, 4.7,
  * 4.10, 4.11, kept to first order as stated in Section 4.1).
  *
  * Conventions common to every call

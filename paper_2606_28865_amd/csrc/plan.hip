@@ -542,9 +542,9 @@ struct Host {
     std::vector<int64_t> prev, next;
     std::vector<double> leg;           // [16][16] nodal values -> Legendre coefficients
     double panel_half = 0;             // largest half-length of a panel (speed in the panel parameter)
-    // largest |Legendre coefficient| over the panels, per degree: of the
-    // position (length of the vector), the speed and the normal
-    double cg[NGL] = {0}, cs[NGL] = {0}, cn[NGL] = {0};
+    // |Legendre coefficients| of every panel's position (length of the vector),
+    // speed and normal, [n_panels][3][16], then the largest over the panels
+    std::vector<double> coef;
     double xmin, xmax, ymin, ymax;
     // all targets (off-surface then boundary), in output order
     std::vector<double> tx, ty;
@@ -868,44 +868,55 @@ static mhk_status fill_items(mhk_plan *P, const int32_t *wave_ofs, int64_t nwave
     return MHK_OK;
 }
 
-// Largest Legendre coefficients of the panels' geometry, per degree (H.cg, H.cs,
-// H.cn).
+// Legendre coefficients of the panels' geometry (H.coef).
 static void panel_coefficients(Host &H)
 {
     const mhk_boundary *b = H.b;
-    double lt[NGL][NGL];                               // [node][degree]
-    for (int i = 0; i < NGL; ++i)
-        for (int k = 0; k < NGL; ++k) lt[i][k] = H.leg[k * NGL + i];
-    double mg[NGL] = {0}, mn[NGL] = {0};
-    for (int64_t p = 0; p < b->n_panels; ++p) {
-        double x[NGL] = {0}, y[NGL] = {0}, nx[NGL] = {0}, ny[NGL] = {0}, s[NGL] = {0};
-        for (int i = 0; i < NGL; ++i) {
-            const int64_t q = p * NGL + i;
-            // (from the panel's first node: smaller numbers, less rounding)
-            const double xv = b->x[q] - b->x[p * NGL], yv = b->y[q] - b->y[p * NGL], sv = b->w[q] / H.gl_w[i];
-            for (int k = 0; k < NGL; ++k) {
-                x[k] += lt[i][k] * xv;
-                y[k] += lt[i][k] * yv;
-                nx[k] += lt[i][k] * b->nx[q];
-                ny[k] += lt[i][k] * b->ny[q];
-                s[k] += lt[i][k] * sv;
+    constexpr int HF = NGL / 2, NC = 3 * NGL;
+    double even[HF][HF], odd[HF][HF];                  // [node][degree / 2]; the nodes are symmetric
+    for (int i = 0; i < HF; ++i)
+        for (int k = 0; k < HF; ++k) {
+            even[i][k] = H.leg[2 * k * NGL + i];
+            odd[i][k] = H.leg[(2 * k + 1) * NGL + i];
+        }
+    auto coeffs = [&](const double *f, double f0, double *c) {
+        double e[HF] = {0}, o[HF] = {0};
+        for (int i = 0; i < HF; ++i) {
+            const double u = f[i] - f0, v = f[NGL - 1 - i] - f0;
+            for (int k = 0; k < HF; ++k) {
+                e[k] += even[i][k] * (u + v);
+                o[k] += odd[i][k] * (u - v);
             }
         }
-        for (int k = 0; k < NGL; ++k) {
-            mg[k] = std::max(mg[k], x[k] * x[k] + y[k] * y[k]);
-            mn[k] = std::max(mn[k], nx[k] * nx[k] + ny[k] * ny[k]);
-            H.cs[k] = std::max(H.cs[k], fabs(s[k]));
+        for (int k = 0; k < HF; ++k) {
+            c[2 * k] = e[k];
+            c[2 * k + 1] = o[k];
         }
-    }
+    };
     // the rounding of the data is no content of the curve: it is the same for
     // every number of bisections
     const double eps = 16 * 2.2e-16, ext = std::max(std::max(fabs(H.xmin), fabs(H.xmax)), std::max(fabs(H.ymin), fabs(H.ymax)));
-    for (int k = 0; k < NGL; ++k) {
-        H.cg[k] = sqrt(mg[k]);
-        H.cn[k] = sqrt(mn[k]);
-        if (k > 1 && H.cg[k] < eps * ext) H.cg[k] = 0;
-        if (k > 0 && H.cs[k] < 16 * eps * H.cs[0]) H.cs[k] = 0;
-        if (k > 0 && H.cn[k] < 16 * eps) H.cn[k] = 0;
+    H.coef.assign((size_t)(b->n_panels + 1) * NC, 0.0);
+    double *top = &H.coef[(size_t)b->n_panels * NC];
+    for (int64_t p = 0; p < b->n_panels; ++p) {
+        const int64_t q = p * NGL;
+        double x[NGL], y[NGL], nx[NGL], ny[NGL], sp[NGL], *c = &H.coef[(size_t)p * NC];
+        for (int i = 0; i < NGL; ++i) sp[i] = b->w[q + i] / H.gl_w[i];
+        // (positions from the panel's first node: smaller numbers, less rounding)
+        coeffs(b->x + q, b->x[q], x);
+        coeffs(b->y + q, b->y[q], y);
+        coeffs(b->nx + q, 0.0, nx);
+        coeffs(b->ny + q, 0.0, ny);
+        coeffs(sp, 0.0, c + NGL);
+        for (int k = 0; k < NGL; ++k) {
+            c[k] = sqrt(x[k] * x[k] + y[k] * y[k]);
+            c[NGL + k] = fabs(c[NGL + k]);
+            c[2 * NGL + k] = sqrt(nx[k] * nx[k] + ny[k] * ny[k]);
+            if (k > 1 && c[k] < eps * ext) c[k] = 0.0;
+            if (k > 0 && c[NGL + k] < 16 * eps * c[NGL]) c[NGL + k] = 0.0;
+            if (k > 0 && c[2 * NGL + k] < 16 * eps) c[2 * NGL + k] = 0.0;
+        }
+        for (int k = 0; k < NC; ++k) top[k] = std::max(top[k], c[k]);
     }
 }
 
@@ -920,50 +931,81 @@ static void panel_coefficients(Host &H)
 // cosh(15 log R), speed and normal grow by T and N, the curve moves by at most G
 // B off the real plane (B = b 2^-m, G its largest derivative), and a Gaussian of
 // time up to delta_j/4 grows by exp((G B)^2/delta_j).  The product, minimised over
-// rho, is an upper bound up to its constant, which is fitted: on 240 random curves
+// rho, is an upper bound up to its constant, which is fitted: on 360 random curves
 // (starfish of 2 to 14 arms, uneven parameters and panels, ellipses of aspect up to
-// 8; 10 to 120 panels; 0, 1 and 2 bisections; half-lengths 0.15 to 2.2
-// sqrt(delta_j)) it was 1.9 times or more the largest error over all nodal values of
-// S or D, in the median 200 times without bisections and 3000 with one.
-static double rule_error(const Host &H, int m, double delta_j)
+// 8; 10 to 120 panels; 0 and 1 bisections; half-lengths 0.2 to 1.6 sqrt(delta_j)) it
+// was 1.6 times or more the largest error over all nodal values of S or D (of those
+// above 5e-14), in the median 60 times without bisections and 900 with one.
+// First for the largest coefficients of all panels (never below the largest of
+// the panels' own bounds), and where that is up to a thousand times too much
+// panel by panel, with the rho found.
+static bool rule_error_below(const Host &H, int m, double delta_j, double limit)
 {
-    const double w = ldexp(1.0, -m);
-    double best = 1e300;
-    for (double rho = 1.5; rho < 64.0; rho *= 1.166) {
+    constexpr int NC = 3 * NGL;
+    const int64_t npan = H.b->n_panels;
+    const double w = ldexp(1.0, -m), *top = &H.coef[(size_t)npan * NC];
+    const double scale = 32.0 * top[NGL] * std::max(0.5, top[2 * NGL]);
+    if (!(scale > 0.0)) return false;
+    struct Ellipse {
+        double c[NGL], d[NGL], rest;   // cosh(k log R), k sinh(k log R)/sinh(log R) B/sqrt(delta_j)
+    };
+    auto ellipse = [&](double rho, Ellipse &E) {
         const double a = 0.5 * (rho + 1.0 / rho), bb = 0.5 * (rho - 1.0 / rho) * w;
         // the parent's ellipse through the end of the longer axis of the outermost child's
-        const double lr = acosh(std::max(1.0 - w + w * a, sqrt(1.0 + bb * bb))), sh = sinh(lr);
-        double G = 0, T = 0, N = 0;
+        const double lr = acosh(std::max(1.0 - w + w * a, sqrt(1.0 + bb * bb))), f = bb / sinh(lr) / sqrt(delta_j);
         for (int k = 0; k < NGL; ++k) {
-            const double c = cosh(k * lr);
-            G += H.cg[k] * k * sinh(k * lr) / sh;
-            T += H.cs[k] * c;
-            N += H.cn[k] * c;
+            E.c[k] = cosh(k * lr);
+            E.d[k] = k * sinh(k * lr) * f;
         }
-        const double g = G * bb;
-        best = std::min(best, exp(g * g / delta_j - 32.0 * log(rho)) * cosh(15.0 * lr) * T * N);
+        E.rest = log(E.c[NGL - 1] / scale) - 32.0 * log(rho);
+    };
+    // logarithm of the bound
+    auto bound = [&](const Ellipse &E, const double *c) {
+        double g = 0, t = 0, n = 0;
+        for (int k = 0; k < NGL; ++k) {
+            g += c[k] * E.d[k];
+            t += c[NGL + k] * E.c[k];
+            n += c[2 * NGL + k] * E.c[k];
+        }
+        return g * g + log(t * n) + E.rest;
+    };
+    Ellipse E, best;
+    double least = INFINITY;
+    for (double rho = 1.5; rho < 64.0; rho *= 1.166) {
+        ellipse(rho, E);
+        const double v = bound(E, top);
+        if (v < least) {
+            least = v;
+            best = E;
+        }
     }
-    return best / (32.0 * H.cs[0] * std::max(0.5, H.cn[0]));
+    const double lim = log(limit);
+    if (!(least <= lim + log(1e3))) return false;
+    for (int64_t p = 0; least > lim && p < npan; ++p)
+        if (!(bound(best, &H.coef[(size_t)p * NC]) <= lim)) return false;
+    return true;
 }
 
 // Bisections of every panel at level j: at most j (Section 4.2), fewer where
 // the 16-node rule integrates level j's kernel on longer panels just as well.
-// Two conditions keep the error below tol/100 on every child panel.  On a
-// straight one of half-length h sqrt(delta_j) it is the kernel's Chebyshev tail
-// beyond degree 16 (the density has degree 15, the rule degree 31), below 1.5e-11
-// h^18 from h = 0.85 on (1.4e-12, 1.3e-10, 1.1e-8 and 2.9e-7 at h = 0.9, 1.2, 1.6 and 2, D
-// at most 1.4 times as much).  Curved panels and uneven speeds add to the
-// integrand's degree: on the starfish with 32 panels (tol 1e-10, h = 0.86) D erred
-// by 1e-8 without bisections; rule_error bounds what they add.  Half the nodes
-// are half the work of a level: whole evaluations of S and D with 65536
+// Two conditions.  On a straight panel of half-length h sqrt(delta_j) the error is
+// the kernel's Chebyshev tail beyond degree 16 (the density has degree 15, the
+// rule degree 31), kept below tol/100 of the kernel: it is below 1.5e-11 h^18 from
+// h = 0.85 on (1.4e-12, 1.3e-10, 1.1e-8 and 2.9e-7 at h = 0.9, 1.2, 1.6 and 2, D at most
+// 1.4 times as much).  Curved panels and uneven speeds add to the integrand's
+// degree: on the starfish with 32 panels (tol 1e-10, h = 0.86) D erred by 1e-8
+// without bisections.  The bound above, for the worst nodal values and panel, is
+// kept below tol/10, the size of the history part's error (tol/12 on the bench's
+// workloads); at that limit the errors were 4e-4 tol at most on starfish of 24 to
+// 96 panels, tol 1e-5 to 1e-10.  Half the nodes are half the work of a level: whole evaluations of S and D with 65536
 // boundary nodes (h = 0.15 after j bisections, tol 1e-8: j - 2 are taken) take 800
 // us against 1386 with j.
 static int level_bisections(const mhk_plan *P, const Host &H, int j)
 {
-    const double delta_j = P->delta / pow(4.0, j - 1), err = P->p.tol * 1e-2;
-    const double hmax = pow(err / 1.5e-11, 1.0 / 18.0) * sqrt(delta_j);
+    const double delta_j = P->delta / pow(4.0, j - 1), tol = P->p.tol;
+    const double hmax = pow(tol * 1e-2 / 1.5e-11, 1.0 / 18.0) * sqrt(delta_j);
     int m = j;
-    while (m > 0 && H.panel_half / (double)(1 << (m - 1)) <= hmax && rule_error(H, m - 1, delta_j) <= err) --m;
+    while (m > 0 && H.panel_half / (double)(1 << (m - 1)) <= hmax && rule_error_below(H, m - 1, delta_j, 0.1 * tol)) --m;
     return m;
 }
 
