@@ -1127,16 +1127,24 @@ template <int W, typename T>
 static hipError_t spread_w(mhk_plan *P, SpreadArgs<T> &A)
 {
     const History &G = P->hist;
-    // several densities share the window values of a workgroup: 8 accumulators
-    // of the volume or 6 of the boundary (4 doubles a lane each) stay in
-    // registers beside them
-    const bool one = A.B == 1;
+    const bool vol = A.f_vol, bnd = A.sigma || A.mu;
+    const int64_t blocks = (vol ? G.nvact : 0) + (bnd ? G.nbact : 0);
+    if (blocks == 0) return hipSuccess;
+    // Several densities share the window values of a workgroup (8 accumulators of
+    // the volume or 6 of the boundary, 4 doubles a lane each, stay in registers
+    // beside them) where single ones already fill the chip: beyond 1024 workgroups of
+    // one density each, or 4096 below 8 densities, as a workgroup's 8 of the volume
+    // take the matrix cores' time of 8 whatever their number.  History part, by
+    // eights against one each (4 wavefronts): FP64 V of 2 on 720 blocks 320 / 229 us,
+    // of 3 359 / 291, of 5 438 / 439 (3600 workgroups), of 8 548 / 628; of 16 on 122
+    // blocks 301 / 307 (1952 workgroups).  Without V the boundary's short lists gain
+    // nothing (S and D of 3 on 101 blocks 125 / 126).
+    const bool one = A.B == 1 || (vol && blocks * A.B <= (A.B < 8 ? 4096 : 1024));
     const int nv = one ? 1 : 8, nd = one ? 1 : 2;
     A.nvt = (A.B + nv - 1) / nv;
     A.nbt = (A.B + nd - 1) / nd;
-    A.nvw = A.f_vol ? G.nvact * A.nvt : 0;
-    const int64_t wg = A.nvw + (A.sigma || A.mu ? G.nbact * A.nbt : 0);
-    if (wg == 0) return hipSuccess;
+    A.nvw = vol ? G.nvact * A.nvt : 0;
+    const int64_t wg = A.nvw + (bnd ? G.nbact * A.nbt : 0);
     // wavefronts per block: few blocks leave the chip idle behind their long
     // lists, so they take 16 (up to two workgroups per CU) or 8; many blocks
     // fill it, and four shorter-lived wavefronts each finish more evenly.
@@ -1144,7 +1152,8 @@ static hipError_t spread_w(mhk_plan *P, SpreadArgs<T> &A)
     // workgroups (FP32) 26 / 18 / 14 us, 2236 workgroups 126 / 107 / 122 us,
     // 7149 workgroups (FP32) 219 / 234 / 287 us; 16 densities 750 / 843 us.  At
     // 2236 the gain alone is lost beside the level sums, which the larger LDS
-    // share keeps out (whole evaluation 1288 / 1315 us).
+    // share keeps out (whole evaluation 1288 / 1315 us).  8 FP32 densities of V on
+    // 14 blocks (history part): 87 us by eights with 4, 51 one each with 16.
     if (!one)
         hipLaunchKernelGGL((k_spread<W, T, 8, 2, 4>), dim3((unsigned)wg), dim3(256), 0, P->stream, A);
     else if (wg <= 512)
