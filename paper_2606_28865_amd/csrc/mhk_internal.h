@@ -51,7 +51,11 @@ constexpr int interp_edge(int W) { return W <= 8 ? 8 : W <= 12 ? 4 : 0; }
 // against 138 us by tiles; a block costs about as much for one target as for
 // 32, so that by tiles is the better below a dozen), and for any window where
 // the tiles are too few to fill the chip (104 thousand FP32 targets on 32
-// tiles: 25 against 64 us; with 1481 tiles, W = 8, FP32, 121 against 88 us);
+// tiles: 25 against 64 us; with 1481 tiles, W = 8, FP32, 121 against 88 us), there
+// from INTERP_MIN/4 per block on (5 tiles, 5.4 per block, W = 12: 8 against 23 us; 36
+// tiles, 6.7 per block: 9 against 27; FP32, 25 tiles, 4.8 per block: 7 against 12; four
+// densities 32 against 34 on 121 tiles with 4 per block, 30 against 25 with 2.3, and
+// FP32 22 against 19 on 25 tiles with 46, the one side on which tiles were faster);
 // straight from the grid up to INTERP_FEW targets per tile; by tiles else.
 constexpr int64_t INTERP_MIN = 16, INTERP_MIN_TILES = 512, INTERP_FEW = 8;
 constexpr int MAXJ = 8;          // maximum number of dyadic levels
