@@ -14,7 +14,7 @@ admissible when its relative max-norm difference to the reference is below
 the tolerance for S, D and V.  The fastest admissible candidate wins.
 Then, on that grid, the level-sum tile shapes (lv_block 256 or 512 targets
 per workgroup; lv_bch 2, 4 or 8 densities per pass when batch > 1; one persistent launch per level or one wavefront
-per work item) are timed the same way; they change only the order of the sums, so their results are
+per work item; those that launch the same sums once) are timed the same way; they change only the order of the sums, so their results are
 checked against the same reference and the fastest is kept.  Results are
 cached in a JSON file keyed by the problem's sizes and parameters.
 
@@ -54,6 +54,22 @@ def tile_candidates(batch):
     """(lv_block, lv_bch, lv_persist) triples tried on the chosen grid."""
     bchs = (1,) if batch == 1 else tuple(b for b in (2, 4, 8) if b <= max(2, batch))
     return [(nb, bc, ps) for ps in (0, 1) for nb in (256, 512) for bc in bchs]
+
+
+# from so many densities on, without lv_persist, the level sums take 16 at a time
+# on the matrix cores whatever lv_block and lv_bch say
+MATRIX_BATCH = 5
+
+
+def distinct_tiles(batch):
+    """tile_candidates without those that launch the same level sums as one before."""
+    out, seen = [], set()
+    for nb, bc, ps in tile_candidates(batch):
+        launch = (nb, bc, ps) if ps or batch < MATRIX_BATCH else None
+        if launch not in seen:
+            seen.add(launch)
+            out.append((nb, bc, ps))
+    return out
 
 
 def tune(geometry, alpha, tol, prec, densities, dx=0.0, delta=0.0, batch=1, candidates=None, reps=3,
@@ -123,7 +139,7 @@ def tune(geometry, alpha, tol, prec, densities, dx=0.0, delta=0.0, batch=1, cand
     best = min(ok, key=lambda c: c["ms"])
     tile_table = []
     if tiles:
-        tile_table = [trial(best["upsamp"], best["wspread"], nb, bc, ps) for nb, bc, ps in tile_candidates(batch)]
+        tile_table = [trial(best["upsamp"], best["wspread"], nb, bc, ps) for nb, bc, ps in distinct_tiles(batch)]
         ok2 = [c for c in tile_table if "ms" in c and c["err"] < tol]
         if ok2:
             best = min(ok2 + [best], key=lambda c: c["ms"])
