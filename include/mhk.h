@@ -305,9 +305,8 @@ typedef struct mhk_nystrom mhk_nystrom;
 typedef struct {
     int64_t n;            /* N_B                                                    */
     double alpha;
-    int64_t device_bytes; /* K (4 N_B^2 bytes: the triangle of its symmetric factor;
-                             up to 5632 nodes 8 N_B^2 more, K itself) plus GMRES and
-                             solve workspace                                        */
+    int64_t device_bytes; /* K (4 N_B^2 bytes: the triangle of its symmetric factor)
+                             plus GMRES and solve workspace                         */
     double ms_assemble;   /* time to build K on the device                         */
 } mhk_nys_info;
 
@@ -320,8 +319,7 @@ typedef struct {
 
 /* Assemble K on the device for the boundary (host arrays as for
  * mhk_plan_create; N_B <= 2^20).  K_ij = S_ij w_j (x_i - x_j).nu_j with S
- * symmetric, so S's lower triangle is kept: 4 N_B^2 bytes of device memory, and
- * for N_B <= 5632 K itself beside it.
+ * symmetric, so S's lower triangle is kept: 4 N_B^2 bytes of device memory.
  * Later calls run on the given stream (NULL: default stream).  *out is NULL
  * on error (MHK_ENOMEM when K does not fit). */
 mhk_status mhk_nystrom_create(double alpha, const mhk_boundary *boundary, void *hip_stream, mhk_nystrom **out);
@@ -342,9 +340,10 @@ mhk_status mhk_nystrom_solve(mhk_nystrom *nys, double shift, const double *rhs, 
 /* As mhk_nystrom_solve, for callers that cannot allocate memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * the GMRES workspace -- the Krylov basis, residual and product vectors,
- * partial sums of the dot products and the small Hessenberg data -- comes
- * from one fixed device array of 32 MiB in the library, not from
- * allocations, and the host side of the least-squares problem from the
+ * partial sums of the norms and the small Hessenberg data -- comes from one
+ * fixed device array of 32 MiB in the library, the partial sums of the products
+ * and of the Gram-Schmidt passes from buffers that the object holds for these
+ * calls from its creation, and the host side of the least-squares problem from the
  * stack.  The call allocates nothing: no hipMalloc, hipHostMalloc or
  * hipFree.  Limits: restart <= 64, and (restart + 3) N_B + (restart + 1)
  * min(256, N_B/256) + 3 restart doubles (each part rounded up to 256 bytes)

@@ -33,7 +33,6 @@ struct mhk_nystrom {
     hipStream_t stream = nullptr;
     double *S = nullptr;        // [tiles][64][128]
     double *geo = nullptr;      // [6][np]: x, y, nu_x, nu_y, w, diagonal of K
-    double *K = nullptr;        // [n][n], for products of few nodes only (n <= NYS_DENSE)
     int64_t nstrip = 0, ntile = 0, nitem = 0;
     int run = 1;                // tiles per work item
     int2 *item = nullptr;       // [nitem] strip and first tile column
@@ -59,7 +58,7 @@ struct mhk_nystrom {
     double ms_assemble = 0;
     int64_t bytes() const
     {
-        return (int64_t)sizeof(double) * (ntile * 64 * 128 + 6 * np + 3 * (ntile * 128 + nitem * 64) + np + (K ? n * n : 0) + 2 * work_n) +
+        return (int64_t)sizeof(double) * (ntile * 64 * 128 + 6 * np + 3 * (ntile * 128 + nitem * 64) + np + 2 * work_n) +
                nitem * 8 + (nstrip + 1) * 4 + ws_bytes;
     }
 };
@@ -83,10 +82,6 @@ namespace mhk {
 
 constexpr int BT = 256;         // threads per block of the vector kernels
 constexpr int TR = 64, TC = 128;   // rows and columns of a tile
-// nodes up to which K itself is kept beside its triangle, for products that keep
-// no partial sums (recorded ones, and those of the per-thread stream), and up to
-// which every product takes it
-constexpr int64_t NYS_DENSE = 5632, NYS_DENSE_ALL = 3072;
 enum { NYS_APPLY, NYS_SOLVE, NYS_NOALLOC };
 
 // tiles of the strips before strip I (strip k holds k/2 + 1 tile columns)
@@ -210,62 +205,11 @@ __global__ void __launch_bounds__(BT) k_nys_assemble(int64_t n, int64_t np, doub
     }
 }
 
-// K itself from the triangle of S, for the products of few nodes
-__global__ void __launch_bounds__(BT) k_nys_dense(int64_t n, int64_t np, const double *__restrict__ S,
-                                                  const double *__restrict__ geo, double *__restrict__ K)
-{
-    const int64_t i = blockIdx.x, j = (int64_t)blockIdx.y * BT + threadIdx.x;
-    if (j >= n) return;
-    const int64_t hi = max(i, j), lo = min(i, j);
-    const double s = S[(tile_ofs(hi / TR) + lo / TC) * (TR * TC) + hi % TR * TC + lo % TC];
-    const double *x = geo, *y = geo + np, *nx = geo + 2 * np, *ny = geo + 3 * np, *w = geo + 4 * np;
-    K[i * n + j] = i == j ? geo[5 * np + i] : w[j] * s * fma(x[i] - x[j], nx[j], (y[i] - y[j]) * ny[j]);
-}
-
 __device__ inline double wave_sum(double v)
 {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
-}
-
-// y = shift x + K x with K itself: GV_ROWS rows per workgroup, column pairs
-// along the threads (n is even); fixed reduction order.  One launch and no
-// partial sums, against the two of the triangle's product: 128, 2048, 3072 and
-// 3584 nodes 4.1, 5.4, 13.5 and 17.0 us against 7.6, 10.2, 13.9 and 17.6, and 27.8
-// against 21.0 at 4096, where the bytes decide; recorded, against k_nys_rows, 5.9 to
-// 11.9 us at 2048, 17.5 to 21.5 at 3584, 36 (at 5.7 TB/s) to 42 at 5632.
-constexpr int GV_ROWS = 8;
-__global__ void __launch_bounds__(BT) k_gemv(int64_t n, const double *__restrict__ K, double shift,
-                                             const double *__restrict__ x, double *__restrict__ y)
-{
-    const int64_t r0 = (int64_t)blockIdx.x * GV_ROWS;
-    const int tid = threadIdx.x;
-    double acc[GV_ROWS];
-#pragma unroll
-    for (int r = 0; r < GV_ROWS; ++r) acc[r] = 0.0;
-    for (int64_t c = 2 * (int64_t)tid; c < n; c += 2 * BT) {
-        const double x0 = x[c], x1 = x[c + 1];
-#pragma unroll
-        for (int r = 0; r < GV_ROWS; ++r) {
-            const double2 k = *reinterpret_cast<const double2 *>(K + (r0 + r) * n + c);
-            acc[r] = fma(k.x, x0, acc[r]);
-            acc[r] = fma(k.y, x1, acc[r]);
-        }
-    }
-    __shared__ double red[GV_ROWS][BT / 64];
-#pragma unroll
-    for (int r = 0; r < GV_ROWS; ++r) {
-        const double s = wave_sum(acc[r]);
-        if ((tid & 63) == 0) red[r][tid >> 6] = s;
-    }
-    __syncthreads();
-    if (tid < GV_ROWS) {
-        double s = 0.0;
-#pragma unroll
-        for (int q = 0; q < BT / 64; ++q) s += red[tid][q];
-        y[r0 + tid] = fma(shift, x[r0 + tid], s);
-    }
 }
 
 // Products of the tiles of one work item (a run of tile columns of one strip)
@@ -446,17 +390,19 @@ __global__ void __launch_bounds__(TC * SG) k_symv_sum(int64_t n, int64_t np, int
     }
 }
 
-// y = shift x + K x with nothing kept between launches, for products of more
-// than NYS_DENSE nodes recorded into a graph: its replays may run beside the
-// object's other products, whose partial sums k_symv keeps in the object.  One
-// workgroup per 8 QW rows i forms their whole sums: of the triangle's rows for j <
-// i and of its columns for j > i, so every element is read twice, by the
-// workgroups of its row and of its column.  At step t workgroups of the 128 rows
-// R take the elements of columns K = t - R (modulo the number of such groups), so
-// both read a tile at the same time and one of the reads can come from the
-// memory-side cache.  QW wavefronts a step (8 rows, or 128/QW rows of the columns,
-// each), G steps at a time.  Against the dense matrix (twice the bytes): 8192 nodes
-// 80 us (97), 10240 136 (140), 16384 318 (353), 32768 1375 (1439).
+// y = shift x + K x with nothing kept between launches, for products recorded
+// into a graph: its replays may run beside the object's other products, whose
+// partial sums k_symv keeps in the object; and one launch instead of two for
+// products of few nodes.  One workgroup per 8 QW rows i forms their whole sums: of
+// the triangle's rows for j < i and of its columns for j > i, so every element is
+// read twice, by the workgroups of its row and of its column.  At step t
+// workgroups of the 128 rows R take the elements of columns K = t - R (modulo the
+// number of such groups), so both read a tile at the same time and one of the
+// reads can come from the memory-side cache.  QW wavefronts a step (8 rows, or
+// 128/QW rows of the columns, each), G steps at a time.  Bound by load latency
+// (up to some 4096 nodes), then HBM.  Against the dense matrix, which has the same
+// bytes in one pass: 512 nodes 4.9 us (4.9), 2048 10.2 (9.3), 4096 24 (26), 5632
+// 42 (39), 8192 79 (97), 10240 131 (141), 16384 327 (354).
 template <int QW, int G>
 __global__ void __launch_bounds__(64 * QW * G) k_nys_rows(int64_t n, int64_t np, int64_t nstrip,
                                                       const double *__restrict__ S, const double *__restrict__ geo,
@@ -464,6 +410,7 @@ __global__ void __launch_bounds__(64 * QW * G) k_nys_rows(int64_t n, int64_t np,
                                                       double *__restrict__ y)
 {
     constexpr int RW = 8, NR = RW * QW, JW = TC / QW, LR = NR / 2, JL = 64 / LR;
+    static_assert(JW <= TR && JW == RW * JL, "a wavefront's rows j lie in one strip");
     const int64_t i0 = (int64_t)blockIdx.x * NR;
     const int R = (int)(i0 / TC), NK = (int)(np / TC);
     const double *__restrict__ gx = geo, *__restrict__ gy = geo + np, *__restrict__ gnx = geo + 2 * np,
@@ -471,9 +418,30 @@ __global__ void __launch_bounds__(64 * QW * G) k_nys_rows(int64_t n, int64_t np,
     __shared__ __align__(16) double jd[QW * G][JW][6];     // x, y, nu, w x of a wavefront's rows j
     __shared__ double rs[QW * G][RW], cs[QW * G][NR];
     const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64), qw = wave % QW;
-    // rows j < i: this wavefront's 8 rows, two columns per lane
+    // rows j < i: this wavefront's 8 rows, two columns per lane; columns i of the
+    // rows j > i: two columns per lane, JL rows per load
     const int64_t ir = i0 + RW * qw;
+    const int c = 2 * (lane % LR), jr = lane / LR;
     const double *rowp = S + tile_ofs(i0 / TR) * (TR * TC) + (ir % TR) * TC + 2 * lane;
+    // step t < NK: columns K = t - R; step NK: the columns of the tiles that hold the
+    // diagonal, whose rows step 2R (modulo NK) took
+    auto col_of = [&](int t) { return t == NK ? R : t >= R ? t - R : t - R + NK; };
+    auto fetch = [&](int t, double2 *s) {
+        const int K = col_of(t);
+        const double *p = rowp + (int64_t)K * (TR * TC);
+        int64_t step = TC;
+        if (t == NK || K > R) {
+            // (the last tile column's second strip may be missing: not summed below)
+            const int64_t j0 = (int64_t)K * TC + JW * qw, strip = min(j0 / TR, nstrip - 1);
+            p = S + (tile_ofs(strip) + R) * (TR * TC) + (j0 % TR + jr) * TC + i0 % TC + c;
+            step = JL * TC;
+        }
+#pragma unroll
+        for (int r = 0; r < RW; ++r) s[r] = *reinterpret_cast<const double2 *>(p + r * step);
+    };
+    int t = wave / QW;
+    double2 s[RW], ahead[RW];
+    if (t <= NK) fetch(t, s);
     double xr[RW], yr[RW], acc[RW];
 #pragma unroll
     for (int r = 0; r < RW; ++r) {
@@ -481,18 +449,12 @@ __global__ void __launch_bounds__(64 * QW * G) k_nys_rows(int64_t n, int64_t np,
         yr[r] = gy[ir + r];
         acc[r] = 0.0;
     }
-    // columns i of the rows j > i: two columns per lane, JL rows per load
-    const int c = 2 * (lane % LR), jr = lane / LR;
     const double2 xc = *reinterpret_cast<const double2 *>(gx + i0 + c), yc = *reinterpret_cast<const double2 *>(gy + i0 + c);
     double a0 = 0.0, a1 = 0.0;
     // diag: the tile holds the diagonal; its other elements are no part of the
     // sums (nor is zero times an infinite x)
     auto rows = [&](auto diag, int K) {
         const int64_t j = (int64_t)K * TC + 2 * lane;
-        const double *p = rowp + (int64_t)K * (TR * TC);
-        double2 s[RW];
-#pragma unroll
-        for (int r = 0; r < RW; ++r) s[r] = *reinterpret_cast<const double2 *>(p + r * TC);
         auto two = [&](const double *g) { return *reinterpret_cast<const double2 *>(g + j); };
         const double2 xj = two(gx), yj = two(gy), nx = two(gnx), ny = two(gny);
         double2 w = two(gw);
@@ -508,18 +470,9 @@ __global__ void __launch_bounds__(64 * QW * G) k_nys_rows(int64_t n, int64_t np,
     auto cols = [&](auto diag, int K) {
         const int64_t j0 = (int64_t)K * TC + JW * qw;
         if (j0 / TR >= nstrip) return;
-        double2 s[JW / JL];
-#pragma unroll
-        for (int q = 0; q < JW / JL; ++q) {
-            // (a tile column's last strip may be missing)
-            const int64_t j = j0 + JL * q + jr, strip = j / TR;
-            s[q] = make_double2(0.0, 0.0);
-            if (JW <= TR || strip < nstrip)
-                s[q] = *reinterpret_cast<const double2 *>(S + (tile_ofs(strip) + R) * (TR * TC) + j % TR * TC + i0 % TC + c);
-        }
-        for (int k = lane; k < JW; k += 64) {
-            const int64_t j = j0 + k;
-            double *d = jd[wave][k];
+        if (lane < JW) {
+            const int64_t j = j0 + lane;
+            double *d = jd[wave][lane];
             d[0] = gx[j];
             d[1] = gy[j];
             d[2] = gnx[j];
@@ -532,7 +485,7 @@ __global__ void __launch_bounds__(64 * QW * G) k_nys_rows(int64_t n, int64_t np,
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-        for (int q = 0; q < JW / JL; ++q) {
+        for (int q = 0; q < RW; ++q) {
             const double *d = jd[wave][JL * q + jr];
             const double2 g = *reinterpret_cast<const double2 *>(d), nu = *reinterpret_cast<const double2 *>(d + 2);
             const double w = d[4];
@@ -544,22 +497,36 @@ __global__ void __launch_bounds__(64 * QW * G) k_nys_rows(int64_t n, int64_t np,
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
-    for (int t = wave / QW; t < NK; t += G) {
-        const int K = t >= R ? t - R : t - R + NK;
-        if (K < R) {
-            rows(std::false_type(), K);
-        } else if (K > R) {
-            cols(std::false_type(), K);
-        } else {
-            rows(std::true_type(), K);
+    // the next step's elements are loaded while this one's are summed
+    for (; t <= NK; t += G) {
+        if (t + G <= NK) fetch(t + G, ahead);
+        const int K = col_of(t);
+        if (t == NK)
             cols(std::true_type(), K);
+        else if (K > R)
+            cols(std::false_type(), K);
+        else if (K < R)
+            rows(std::false_type(), K);
+        else
+            rows(std::true_type(), K);
+#pragma unroll
+        for (int r = 0; r < RW; ++r) s[r] = ahead[r];
+    }
+    // the rows' sums over the lanes, halving the rows a lane holds at each step;
+    // the row is bits 5..3 of the lane
+#pragma unroll
+    for (int h = RW / 2, m = 32; h >= 1; h /= 2, m /= 2) {
+        const bool up = (lane & m) != 0;
+#pragma unroll
+        for (int r = 0; r < h; ++r) {
+            const double keep = up ? acc[r + h] : acc[r], give = up ? acc[r] : acc[r + h];
+            acc[r] = keep + __shfl_xor(give, m, 64);
         }
     }
+    double v = acc[0];
 #pragma unroll
-    for (int r = 0; r < RW; ++r) {
-        const double v = wave_sum(acc[r]);
-        if (lane == 0) rs[wave][r] = v;
-    }
+    for (int m = 4; m >= 1; m /= 2) v += __shfl_xor(v, m, 64);
+    if (lane % 8 == 0) rs[wave][lane / 8] = v;
 #pragma unroll
     for (int m = LR; m < 64; m *= 2) {
         a0 += __shfl_xor(a0, m, 64);
@@ -571,7 +538,7 @@ __global__ void __launch_bounds__(64 * QW * G) k_nys_rows(int64_t n, int64_t np,
     }
     __syncthreads();
     if (tid < NR && i0 + tid < n) {
-        double v = 0.0;
+        v = 0.0;
 #pragma unroll
         for (int g = 0; g < G; ++g) v += rs[QW * g + tid / RW][tid % RW];
 #pragma unroll
@@ -1129,7 +1096,6 @@ mhk_status mhk_nystrom_create(double alpha, const mhk_boundary *b, void *hip_str
     mhk_status st = nys_alloc(N, &N->S, N->ntile * TR * TC);
     if (st == MHK_OK) st = nys_alloc(N, &N->geo, 6 * N->np);
     if (st == MHK_OK) st = nys_alloc(N, &N->na_part, 2 * (int64_t)(NOALLOC_MAX_RESTART + 1) * (N->np / TC));
-    if (st == MHK_OK && n <= NYS_DENSE) st = nys_alloc(N, &N->K, n * n);
     if (st == MHK_OK) st = nys_alloc(N, &tab, (int64_t)k1.size());
     if (st == MHK_OK) st = nys_alloc(N, &ia, N->nitem);
     N->item = reinterpret_cast<int2 *>(ia);
@@ -1162,11 +1128,6 @@ mhk_status mhk_nystrom_create(double alpha, const mhk_boundary *b, void *hip_str
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_nys_assemble, dim3((unsigned)N->nitem), dim3(BT), 0, N->stream, n, N->np, alpha,
                            (const double *)N->geo, (const double *)tab, (const int2 *)N->item, N->run, N->S);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess && N->K) {
-        hipLaunchKernelGGL(k_nys_dense, dim3((unsigned)n, (unsigned)((n + BT - 1) / BT)), dim3(BT), 0, N->stream, n,
-                           N->np, (const double *)N->S, (const double *)N->geo, N->K);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipEventRecord(e1, N->stream);
@@ -1205,19 +1166,16 @@ mhk_status mhk_nystrom_apply(mhk_nystrom *N, double shift, const double *x, doub
         set_error("null Nystrom matrix or vector, or x aliases y");
         return MHK_EINVAL;
     }
-    auto dense = [&]() -> mhk_status {
-        hipLaunchKernelGGL(k_gemv, dim3((unsigned)(N->n / GV_ROWS)), dim3(BT), 0, N->stream, N->n, (const double *)N->K,
-                           shift, x, y);
-        BIE_HIP(hipGetLastError());
-        return MHK_OK;
-    };
-    if (N->n <= NYS_DENSE_ALL) return dense();
     // products that must keep no partial sums in the object: recorded ones, and
-    // those of threads that each have a stream of their own under this handle
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (N->stream) BIE_HIP(hipStreamIsCapturing(N->stream, &cap));
-    const bool alone = cap == hipStreamCaptureStatusActive || N->stream == hipStreamPerThread;
-    if (alone && N->K) return dense();
+    // those of threads that each have a stream of their own under this handle; and
+    // those of few nodes, where the triangle's two launches take longer (128 nodes
+    // 7.9 us against 3.9, 1536 9.1 against 7.6, 2048 10.3 against 10.2)
+    bool alone = N->n <= 2048 || N->stream == hipStreamPerThread;
+    if (!alone && N->stream) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        BIE_HIP(hipStreamIsCapturing(N->stream, &cap));
+        alone = cap == hipStreamCaptureStatusActive;
+    }
     if (alone) {
         auto rows = [&](auto qw, auto g) {
             constexpr int QW = decltype(qw)::value, G = decltype(g)::value;
@@ -1225,17 +1183,18 @@ mhk_status mhk_nystrom_apply(mhk_nystrom *N, double shift, const double *x, doub
                                0, N->stream, N->n, N->np, N->nstrip, (const double *)N->S, (const double *)N->geo,
                                shift, x, y);
         };
-        // a workgroup per CU of as many wavefronts as fit (8192 nodes: 80 us, 81
-        // with <2, 2>); beyond 256 of them several small ones, which leave the CUs
-        // evenly loaded (10240: 136 against 170 us); and of 32 rows again once
-        // those are many too (14336: 249, 261 with <4, 3> and 280 with <2, 2>;
-        // 16384: 318, 324 and 353)
-        if (N->n <= 8192)
-            rows(std::integral_constant<int, 4>(), std::integral_constant<int, 3>());
-        else if (N->n <= 12288)
+        // few rows a workgroup while the chip has room for all (2048 nodes 10.2 us, 14
+        // with <4, 3>, as 4096 24 and 28); 32 of them with as many wavefronts as fit a
+        // CU (8192: 79, 81 with <2, 6>); beyond 256 such workgroups several small ones
+        // on a CU, which leave the CUs evenly loaded (10240: 131 against 169); and
+        // large ones again once those are many too (14336: 262 against 298; 16384:
+        // 327 against 377)
+        if (N->n <= 4096)
+            rows(std::integral_constant<int, 2>(), std::integral_constant<int, 6>());
+        else if (N->n > 8192 && N->n <= 12288)
             rows(std::integral_constant<int, 2>(), std::integral_constant<int, 2>());
         else
-            rows(std::integral_constant<int, 4>(), std::integral_constant<int, 2>());
+            rows(std::integral_constant<int, 4>(), std::integral_constant<int, 3>());
         BIE_HIP(hipGetLastError());
         return MHK_OK;
     }
@@ -1453,7 +1412,7 @@ void mhk_nystrom_destroy(mhk_nystrom *N)
     if (!N) return;
     (void)hipStreamSynchronize(N->stream);
     nys_free_ws(N);
-    for (double **p : {&N->S, &N->geo, &N->K, &N->na_part, &N->work}) nys_free(N, p);
+    for (double **p : {&N->S, &N->geo, &N->na_part, &N->work}) nys_free(N, p);
     for (NysPart &p : N->prod) {
         nys_free(N, &p.cp);
         nys_free(N, &p.rp);

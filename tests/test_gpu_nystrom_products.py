@@ -1,9 +1,9 @@
-"""Nystrom products that keep no partial sums in their object: recorded into a
-graph at sizes around the edges of its kernels (the dense matrix kept up to 5632
-nodes; then whole rows from the triangle, with remainders of 16 to 112 nodes in
-the last tile column), and of two threads that share the per-thread stream's
-handle.  Compared with the eager products of the triangle, which other tests
-compare with the dense matrix of the oracle."""
+"""Nystrom products that keep no partial sums in their object (whole rows from
+the triangle, two launches otherwise): recorded into a graph at sizes around the
+edges of their launch shapes, with remainders of 16 to 112 nodes in the last tile
+column; of few nodes; and of two threads that share the per-thread stream's
+handle.  Compared with eager products of the triangle, which other tests
+compare with the dense matrix of the oracle, and of few nodes with that."""
 import threading
 
 import numpy as np
@@ -11,6 +11,7 @@ import pytest
 
 import synth
 from helpers import rel_err
+from oracle import bie
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -24,7 +25,7 @@ def _boundary(panels):
     return synth.discretize([synth.Curve(r0=1.0, a=0.3, l1=5)], panels)
 
 
-@pytest.mark.parametrize("panels", [192, 193, 352, 353, 356, 359, 512, 513, 768, 772])
+@pytest.mark.parametrize("panels", [129, 192, 193, 256, 257, 260, 263, 512, 513, 768, 772])
 def test_captured(panels):
     import paper_2606_28865_amd as M
     n = 16 * panels
@@ -53,6 +54,21 @@ def test_captured(panels):
             else:
                 np.testing.assert_array_equal(a, b)
                 assert np.isinf(np.delete(a, k)).all()
+    nys.close()
+
+
+@pytest.mark.parametrize("panels", [1, 4, 5, 8, 9, 127, 128, 129])
+def test_few_nodes(panels):
+    import paper_2606_28865_amd as M
+    n = 16 * panels
+    print(f"case product n={n}", flush=True)
+    bnd = _boundary(panels)
+    K = bie.nystrom_matrix(bnd, 3.0)
+    nys = M.Nystrom(3.0, bnd)
+    x = np.random.default_rng(panels).standard_normal(n)
+    y = nys.apply(torch.as_tensor(x, device="cuda"), shift=-0.5).cpu().numpy()
+    # n sums of at most n terms, elements to a few eps
+    assert np.abs(y - (K @ x - 0.5 * x)).max() < 4 * n * 2.2e-16 * (np.abs(K) @ np.abs(x) + np.abs(x)).max()
     nys.close()
 
 
