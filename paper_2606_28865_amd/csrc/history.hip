@@ -1133,13 +1133,15 @@ static hipError_t spread_w(mhk_plan *P, SpreadArgs<T> &A)
     // Several densities share the window values of a workgroup (8 accumulators of
     // the volume or 6 of the boundary, 4 doubles a lane each, stay in registers
     // beside them) where single ones already fill the chip: beyond 1024 workgroups of
-    // one density each, or 4096 below 8 densities, as a workgroup's 8 of the volume
-    // take the matrix cores' time of 8 whatever their number.  History part, by
-    // eights against one each (4 wavefronts): FP64 V of 2 on 720 blocks 320 / 229 us,
-    // of 3 359 / 291, of 5 438 / 439 (3600 workgroups), of 8 548 / 628; of 16 on 122
-    // blocks 301 / 307 (1952 workgroups).  Without V the boundary's short lists gain
-    // nothing (S and D of 3 on 101 blocks 125 / 126).
-    const bool one = A.B == 1 || (vol && blocks * A.B <= (A.B < 8 ? 4096 : 1024));
+    // one density each, or 4096 up to 3 densities, as a workgroup's 8 of the volume
+    // take the matrix cores' time of 8 whatever their number, while single ones form
+    // the window values once each, beside level sums that need the VALU too.  By
+    // eights against one each, history part: FP64 V of 2 on 720 blocks 320 / 229 us, of
+    // 8 548 / 628, of 16 on 122 blocks 301 / 307 (1952 workgroups); whole evaluations:
+    // FP64 of 2 (834 workgroups) 300 / 275 us, of 3 (1251) 355 / 334, of 5 (2085) 479 /
+    // 484, of 7 (2919) 593 / 615.  Without V the boundary's short lists gain nothing (S
+    // and D of 3 on 101 blocks 125 / 126).
+    const bool one = A.B == 1 || (vol && blocks * A.B <= (A.B <= 3 ? 4096 : 1024));
     const int nv = one ? 1 : 8, nd = one ? 1 : 2;
     A.nvt = (A.B + nv - 1) / nv;
     A.nbt = (A.B + nd - 1) / nd;
