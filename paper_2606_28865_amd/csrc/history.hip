@@ -281,9 +281,11 @@ __device__ inline void spread_block(const SpreadArgs<T> &A, int b0, int nf, int 
 
 // One workgroup per (active 16 x 16 block, group of densities): NV volume
 // densities or ND boundary densities (S, D_x and D_y each).  The accumulators
-// are FP64 at both precisions.  Bound by VALU issue: about 120 instructions of
-// window values and 90 of LDS addressing per batch of 32 sources (1000 cycles
-// a SIMD) beside 512 cycles of the matrix cores.  Measured alone, 1.04M volume
+// are FP64 at both precisions.  Bound by latency with the VALU a third and the
+// matrix cores a fifth busy (waves wait for memory or LDS 58% of their cycles):
+// per batch of 32 sources gathered loads and an LDS exchange around some 120
+// instructions of window values, 90 of LDS addressing and 512 cycles of the
+// matrix cores.  Measured alone, 1.04M volume
 // and 16384 boundary sources on 1920^2, W = 12: 126 us (LDS atomic adds over
 // 32 x 32 tiles: 312 us); 16 densities on 2880^2: 741 us (3013); 4.09M sources
 // on 3840^2, W = 8, FP32: 215 us (430).  Blocks that no window meets are not

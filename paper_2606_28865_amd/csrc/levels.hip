@@ -3,7 +3,7 @@
 // Level j sums, for every target x,
 //   S_j(x) = sum_q w_q sigma_q K_j^S(|x - x_q|),
 //   D_j(x) = sum_q w_q mu_q nu_q.(x - x_q) K_j^D(|x - x_q|),
-// over the child nodes q of the panels bisected j times.  The kernels come
+// over the child nodes q of the panels bisected up to j times.  The kernels come
 // from one piecewise-polynomial table of K_j^S in a = r^2/(4 delta_j) held in
 // LDS: Horner's rule gives the polynomial and its derivative together, and
 // K_j^D is a constant times dK_j^S/da, applied once per target at the end

@@ -412,8 +412,8 @@ static_assert(GEO_N == LOCAL_GEO_N1 && GEO_N2 == LOCAL_GEO_N2, "local geometry l
 
 // ORDER is the order of the local expansions (1 or 2); first-order plans
 // get a kernel without the second-order registers.  Bound by the latency of the
-// search's and the series' loads (62% of the wave cycles; the VALU is busy a
-// third of the time), so four wavefronts per SIMD with a few registers spilled
+// search's and the series' loads (62% of the wave cycles; the VALU is busy half
+// of the time), so four wavefronts per SIMD with a few registers spilled
 // beat three, the coefficients of x and y and the nodes come interleaved in
 // 16-byte loads, the next candidate is loaded ahead, and only what k_local reads
 // of a target is stored: 4.07M targets 816 -> 686 us alone and 1414 -> 1093 us
